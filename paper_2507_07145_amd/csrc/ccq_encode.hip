@@ -1,27 +1,38 @@
 // The offline quantizer of CCQ on the GPU (gfx950): Alg. 1 (group scale, nearest codeword of the
 // convolutional codebook for every N-vector), the least-squares scale of Eq. 4 ("Scale Optimization"),
-// and the Code Cluster map of Sec. 3.3 / Eq. 1, for the narrow (L=6,N=4,S=3 + Code Cluster) and the wide
-// (L=4,N=3,S=2) formats.  Output goes straight into the device layout that ccq_gemm reads.
+// and the Code Cluster map of Sec. 3.3 / Eq. 1, for every layout the multiply kernels read.  Output goes
+// straight into the device layout that ccq_gemm reads.
 //
-// The codebook is never built.  A code is a path through the state graph (first state, then S fresh
-// bits per step), so the nearest codeword is a shortest path: 2^L lanes of a wavefront hold the 2^L
-// states, one step takes the best of the 2^S predecessors of every state (lane shuffles), and the final
-// answer is the best of the 2^L end states.  Ties go to the numerically lowest code at every
-// comparison, which is what an exhaustive scan over all 2^T codes in ascending order returns.
+// Every decision (an argmin, a kept-or-rejected scale) is the one taken in fp64 with separate multiplies and adds in a
+// fixed order -- squared errors of a vector are added left to right, the sums of Eq. 4 and of the group error run over
+// the 64 weights in index order -- so that the result does not depend on how the work is spread over lanes.
+// Contraction into fused multiply-adds is switched off for this file; where one is written out, the product is exact.
+// What is searched in fp32 (ccq_search.h, the candidates of the Code Cluster map below) is accepted only where the
+// distance to the next best answer exceeds what fp32 can be off by; the rest is searched in fp64 by a whole wavefront.
+// Ties go to the numerically lowest code, which is what an exhaustive scan in ascending order returns.
 //
-// Every decision (an argmin, a kept-or-rejected scale) is taken in fp64 with separate multiplies and adds
-// in a fixed order -- squared errors of a vector are added left to right, the sums of Eq. 4 and of the
-// group error run over the 64 weights in index order -- so that the result does not depend on how the
-// work is spread over lanes.  Contraction into fused multiply-adds is switched off for this file.
+// Bound by vector instructions, not by bytes (8192 x 8192 reads 268 MB: 50 us).  The first version searched with one
+// state per lane in fp64 (a wavefront per vector, shuffles between the steps): 53 ms narrow, 14 ms wide at that size.
 #include <hip/hip_runtime.h>
 
 #include <cmath>
 
 #include "ccq_internal.h"
+#include "ccq_search.h"
 
 #pragma clang fp contract(off)
 
 namespace ccq {
+
+// The last unit of a hybrid-word group holds one weight and six zeros of padding, which tie on many paths whatever the
+// weight and the scale are.  They are decided once, on the host (h16_tail): the (3,4,2) code of four zeros, and for either
+// value of the bit that the first state of the (3,3,2) code passes on, the best states for its two zeros (the lower four
+// bits of the code) and what they cost.  `decided` is 0 where rounding could order equal costs differently.
+struct H16Tail {
+  uint32_t zeros, rest[2];
+  float cost[2];
+  int32_t decided;
+};
 
 struct EncArgs {
   const float* W;       // fp32 [N][ldw]
@@ -33,18 +44,19 @@ struct EncArgs {
   // kind_code_off bytes / kind_scale_off halfwords into a row tile.  (The map holds whole k-tiles per kind, the
   // workspace arrays only the real groups: with a ragged last narrow tile mbase > pbase for the wide kind.)
   int32_t GK, pbase, mbase;
+  int32_t quads;        // ceil(GK / 4): a workgroup takes four groups of sixteen rows
   const int32_t* meta;
   int64_t kind_code_off, kind_scale_off;
   double zp;
+  H16Tail tail;         // hybrid word only
   uint8_t* codes;       // device order
   uint16_t* scales;     // device order, fp16 bits
   float* alpha;
   float* beta;
-  uint16_t* rowcodes;   // workspace: the unclustered codes, [N][G][16] (narrow format only)
-  uint16_t* rowscale;   // workspace: fp16 bits of the group scales after the first pass, [N][G]
+  uint32_t* minmax;     // workspace: smallest and largest (<< 16) unclustered code of a row's four groups, [N][quads] (narrow format only)
+  uint16_t* rowscale;   // workspace: fp16 bits of the group scales after the first pass, [N][GK] (narrow format only)
   // compressed scales (Sec. 3.4) only:
   uint16_t* canon_scales;  // workspace: final fp16 group scales, [N][G] (not in device order); NULL = fp16 scales are the output
-  uint8_t* fields;         // workspace: the 4-bit field of every group, [N][G]
   uint16_t* ssup;          // output: fp16 super scale per output channel, [N]
   double field_max;        // largest value of a scale field: 15, or 8191 for the hybrid word
   int64_t row_tile_bytes, row_tile_scale_halfs;
@@ -82,28 +94,14 @@ __device__ __forceinline__ double fp16_value(uint16_t h) {
   return e == 0 ? ldexp((double)m, -24) : ldexp((double)(m | 0x400), e - 25);
 }
 
-// (row, group) of a wavefront: n = row, p = position among the row's groups of this kind, g = original group
-// (activation columns 64 g ..), widx = index into the per-(row, group) workspace arrays that span all kinds
-struct GroupId {
-  int n, p, g;
-  int64_t widx;
-};
-__device__ __forceinline__ bool group_id(const EncArgs& a, int64_t gidx, GroupId& id) {
-  if (gidx >= (int64_t)a.N * a.GK) return false;
-  id.n = (int)(gidx / a.GK);
-  id.p = (int)(gidx % a.GK);
-  id.g = a.meta ? a.meta[a.mbase + id.p] : id.p;
-  id.widx = (int64_t)id.n * a.G + a.pbase + id.p;
-  return true;
-}
-
 __device__ __forceinline__ double sqerr(double v, double s, double lv) {
   const double d = v - s * lv;
   return d * d;
 }
 
-// Nearest codeword of one N-vector (Alg. 1, the argmin), by the 2^L lanes lane & ~(2^L - 1) .. of the
-// wavefront; every lane of that set returns the code.  v[] must be the same in all lanes of the set.
+// The exact search: nearest codeword of one N-vector (Alg. 1, the argmin) in fp64, by the 2^L lanes lane & ~(2^L - 1) .. of the
+// wavefront, which hold the 2^L states; one step takes the best of the 2^S predecessors of every state.  Every lane of
+// that set returns the code.  v[] must be the same in all lanes of the set.
 template <int L, int NV, int S>
 __device__ __forceinline__ uint32_t nearest_code(const double (&v)[NV], double s, double zp, int lane) {
   constexpr int NS = 1 << L, NT = 1 << S;
@@ -137,196 +135,510 @@ __device__ __forceinline__ uint32_t nearest_code(const double (&v)[NV], double s
   return pre;
 }
 
-// All vectors of the 64-weight group held one weight per lane; lane j returns code j of the group.
+// ---- the three kinds of stored code ---------------------------------------------------------------------
+enum EncFmt { kEncNarrow = 0, kEncWide = 1, kEncH16 = 2 };
+
+// CPG code units per 64-weight group, WPC weights per unit (a hybrid word is one unit of two codes), 2^(L-1) - 1
+template <int FMT> struct EncTraits;
+template <> struct EncTraits<kEncNarrow> { static constexpr int CPG = 16, WPC = 4, QMAX = 31; };
+template <> struct EncTraits<kEncWide> { static constexpr int CPG = 22, WPC = 3, QMAX = 7; };
+template <> struct EncTraits<kEncH16> { static constexpr int CPG = 10, WPC = 7, QMAX = 3; };
+
+// state of weight i of a unit (Table 1: shifts [9,6,3,0], [4,2,0], [13,11,9,6,4,2,0])
+template <int FMT>
+__device__ __forceinline__ uint32_t unit_state(uint32_t c, int i) {
+  if constexpr (FMT == kEncNarrow) return (c >> (9 - 3 * i)) & 63u;
+  else if constexpr (FMT == kEncWide) return (c >> (4 - 2 * i)) & 15u;
+  else return (c >> (i < 3 ? 13 - 2 * i : 12 - 2 * i)) & 7u;
+}
+
+// The lanes of `todo` still want their vector searched exactly: one after the other, by the whole wavefront.
 template <int L, int NV, int S>
-__device__ __forceinline__ uint32_t search_group(double w, double s, double zp, int lane) {
-  constexpr int NS = 1 << L, VPW = 64 / NS, CPG = (kGroup + NV - 1) / NV;
-  uint32_t mine = 0;
-  for (int j0 = 0; j0 < CPG; j0 += VPW) {
-    const int j = min(j0 + lane / NS, CPG - 1);
-    double v[NV];
+__device__ __forceinline__ uint32_t search_exact(const float* v, double s, double zp, bool want, uint32_t code, int lane) {
+  unsigned long long todo = __ballot(want);
+  while (todo) {
+    const int src = __builtin_ctzll(todo);
+    todo &= todo - 1;
+    double vd[NV];
 #pragma unroll
-    for (int i = 0; i < NV; ++i) {
-      const int idx = NV * j + i;
-      const double val = __shfl(w, min(idx, kGroup - 1));
-      v[i] = idx < kGroup ? val : 0.0;  // zero-padded tail (Sec. 3.1)
-    }
-    const uint32_t code = nearest_code<L, NV, S>(v, s, zp, lane);
-#pragma unroll
-    for (int sg = 0; sg < VPW; ++sg) {
-      const uint32_t c = (uint32_t)__shfl((int)code, sg * NS);
-      if (lane == j0 + sg && j0 + sg < CPG) mine = c;
-    }
+    for (int i = 0; i < NV; ++i) vd[i] = (double)__shfl(v[i], src);
+    const uint32_t c = nearest_code<L, NV, S>(vd, __shfl(s, src), zp, lane);
+    if (lane == src) code = c;
   }
-  return mine;
+  return code;
 }
 
-// Eq. 4: S = sum(W Wq) / sum(Wq^2), sums in index order; `fallback` when the denominator is zero.
-__device__ __forceinline__ double refit_scale(double w, double wq, double fallback) {
-  double num = 0.0, den = 0.0;
-  for (int i = 0; i < kGroup; ++i) {
-    const double wi = __shfl(w, i), qi = __shfl(wq, i);
-    num += wi * qi;
-    den += qi * qi;
-  }
-  return den > 0.0 ? num / den : fallback;
-}
-__device__ __forceinline__ double group_error(double w, double wq, double s) {
-  double e = 0.0;
-  for (int i = 0; i < kGroup; ++i) {
-    const double wi = __shfl(w, i), qi = __shfl(wq, i);
-    const double d = wi - qi * s;
-    e += d * d;
-  }
-  return e;
-}
-
-__device__ __forceinline__ double wave_max(double v) {
+// One code unit per lane: v[] = its weights, s = the group's scale.  All 64 lanes of the wavefront must be here.
+template <int FMT>
+__device__ __forceinline__ uint32_t search_unit(const float (&v)[EncTraits<FMT>::WPC], double s, const InvScale& inv, double zp, const H16Tail& tail, int j, bool active,
+                                                int lane) {
+  constexpr int WPC = EncTraits<FMT>::WPC;
+  const float zpf = (float)zp;
+  float t[WPC];
 #pragma unroll
-  for (int off = 32; off >= 1; off >>= 1) v = fmax(v, __shfl_xor(v, off));
-  return v;
-}
-
-// First pass, one wavefront per (row, group): scale = absmax / (2^(L-1) - 1), search, Eq. 4 refit (kept
-// when the error does not grow), fp16 rounding, search again with the stored scale.  An all-zero group
-// gets scale 0 and codes 0.  Without Code Cluster this is the final result and is written in device
-// order; with it the codes and scales go to the workspace for the next two passes.
-template <int L, int NV, int S, bool CLUSTER>
-__global__ void __launch_bounds__(256) ccq_encode_groups_kernel(const EncArgs a) {
-  constexpr int NS = 1 << L, CPG = (kGroup + NV - 1) / NV;
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  const int64_t gidx = (int64_t)blockIdx.x * 4 + wave;
-  GroupId id;
-  if (!group_id(a, gidx, id)) return;
-  const int n = id.n, gi = id.p;
-  const double w = (double)a.W[(int64_t)n * a.ldw + (int64_t)id.g * kGroup + lane];
-  const double amax = wave_max(fabs(w));
-  uint32_t code = 0;
-  double s = 0.0;
-  if (amax != 0.0) {
-    const double qmax = (double)((1 << (L - 1)) - 1);
-    const double s0 = amax / qmax;
-    code = search_group<L, NV, S>(w, s0, a.zp, lane);
-    const uint32_t cj = (uint32_t)__shfl((int)code, lane / NV);
-    const double wq = (double)((cj >> ((NV - 1 - lane % NV) * S)) & (NS - 1)) - a.zp;
-    double s1 = refit_scale(w, wq, s0);
-    if (!(s1 > 0.0) || group_error(w, wq, s1) > group_error(w, wq, s0)) s1 = s0;
-    s = fp16_scale(s1);
-    code = search_group<L, NV, S>(w, s, a.zp, lane);
-  }
-  if constexpr (CLUSTER) {
-    if (lane < CPG) a.rowcodes[gidx * CPG + lane] = (uint16_t)code;
-    if (lane == 0) a.rowscale[gidx] = fp16_bits(s);
+  for (int i = 0; i < WPC; ++i) t[i] = unit_scale(v[i], inv);
+  if constexpr (FMT == kEncNarrow) {
+    const FastCode f = fast_narrow(t, zpf);
+    return search_exact<6, 4, 3>(v, s, zp, active && !f.sure, f.code, lane);
+  } else if constexpr (FMT == kEncWide) {
+    const FastCode f = fast_small<4, 3, 2>(t, zpf);
+    return search_exact<4, 3, 2>(v, s, zp, active && !f.sure, f.code, lane);
   } else {
-    // wide format: one byte per code; byte c of the group is segment (c % 6) / 2, quarter c / 6, byte c % 2
-    // of halfword (group within the k-tile of 8)
-    const int r = n % kRowsPerTile;
-    if (lane < CPG) {
-      const int kq = lane / 6, rem = lane % 6;
-      a.codes[(int64_t)(n / kRowsPerTile) * a.row_tile_bytes + a.kind_code_off + (int64_t)(gi / kWideGroupsPerTile) * kWideTileBytes + (rem / 2) * 1024 +
-              (kq * 16 + r) * 16 + (gi % kWideGroupsPerTile) * 2 + (rem % 2)] = (uint8_t)code;
+    // a (3,3,2) code on the first three weights and a (3,4,2) code on the other four; their bits do not overlap
+    const float ta[3] = {t[0], t[1], t[2]}, tb[4] = {t[3], t[4], t[5], t[6]};
+    const bool last = j == EncTraits<kEncH16>::CPG - 1 && tail.decided;
+    FastCode fa = fast_small<3, 3, 2>(ta, zpf), fb = fast_small<3, 4, 2>(tb, zpf);
+    if (last) {
+      fa = fast_first<3, 3, 2>(ta[0], zpf, tail.cost, tail.rest);
+      fb.code = tail.zeros;
+      fb.sure = true;
     }
-    if (lane == 0) {
-      if (a.canon_scales) a.canon_scales[id.widx] = fp16_bits(s);
+    const uint32_t ca = search_exact<3, 3, 2>(v, s, zp, active && !fa.sure, fa.code, lane);
+    const uint32_t cb = search_exact<3, 4, 2>(v + 3, s, zp, active && !fb.sure, fb.code, lane);
+    return (ca << 9) | cb;
+  }
+}
+
+// ---- a workgroup's share: sixteen rows (one row tile) x four consecutive groups of the kind, 64 groups in all ----------
+// (64 weights and 4 spare, which are zero: what a code reads past the end of its group is the zero padding of Sec. 3.1;
+// 68 floats and an odd number of dwords of codes keep lanes that read the same place of different groups apart in LDS)
+constexpr int kEncRow = 68;
+template <int FMT> constexpr int kEncUnitRow = FMT == kEncNarrow ? 18 : EncTraits<FMT>::CPG;
+
+// Original group of position p of the kind.
+__device__ __forceinline__ int enc_group(const EncArgs& a, int p) { return a.meta ? a.meta[a.mbase + p] : p; }
+
+// The 64 groups' weights into LDS, zeros for rows and groups that are not there.
+template <int THREADS>
+__device__ __forceinline__ void load_groups(const EncArgs& a, int rt, int quad, float* wl, int tid) {
+#pragma unroll
+  for (int i = 0; i < 1024 / THREADS; ++i) {
+    const int f = i * THREADS + tid, row = f >> 6, gj = (f >> 4) & 3, c4 = f & 15;
+    const int n = rt * kRowsPerTile + row, p = quad * 4 + gj;
+    float4 v = {0.f, 0.f, 0.f, 0.f};
+    if (n < a.N && p < a.GK) v = *reinterpret_cast<const float4*>(a.W + (int64_t)n * a.ldw + (int64_t)enc_group(a, p) * kGroup + c4 * 4);
+    *reinterpret_cast<float4*>(wl + (row * 4 + gj) * kEncRow + c4 * 4) = v;
+  }
+  if (tid < 64) *reinterpret_cast<float4*>(wl + tid * kEncRow + 64) = float4{0.f, 0.f, 0.f, 0.f};
+}
+
+// Unit j of a group: its weights (a hybrid word's last unit reaches past the spare ones).
+template <int FMT>
+__device__ __forceinline__ void unit_weights(const float* wg, int j, float (&v)[EncTraits<FMT>::WPC]) {
+  constexpr int WPC = EncTraits<FMT>::WPC;
+  if constexpr (FMT == kEncNarrow) {
+    const float4 w = *reinterpret_cast<const float4*>(wg + 4 * j);
+    v[0] = w.x; v[1] = w.y; v[2] = w.z; v[3] = w.w;
+  } else {
+#pragma unroll
+    for (int i = 0; i < WPC; ++i) v[i] = wg[min(WPC * j + i, kGroup)];
+  }
+}
+
+// All units of a group searched with scale s, LPG lanes per group.
+template <int FMT, int LPG>
+__device__ __forceinline__ void search_groups(const float* wg, uint16_t* cg, double s, double zp, const H16Tail& tail, bool active, int sub, int lane) {
+  constexpr int CPG = EncTraits<FMT>::CPG;
+  const InvScale inv = inv_scale(active ? s : 1.0);
+#pragma unroll 1
+  for (int j0 = 0; j0 < CPG; j0 += LPG) {
+    const int j = min(j0 + sub, CPG - 1);
+    float v[EncTraits<FMT>::WPC];
+    unit_weights<FMT>(wg, j, v);
+    const uint32_t c = search_unit<FMT>(v, s, inv, zp, tail, j, active, lane);
+    cg[j] = (uint16_t)(active ? c : 0u);   // (two lanes of a ragged last round write the same unit)
+  }
+}
+
+// f(w, wq) over the group's weights in index order, wq = the weight's level.
+template <int FMT, typename F>
+__device__ __forceinline__ void for_weights(const float* wg, const uint16_t* cg, double zp, F f) {
+  constexpr int CPG = EncTraits<FMT>::CPG, WPC = EncTraits<FMT>::WPC, TAIL = kGroup - (CPG - 1) * WPC;
+#pragma unroll 2
+  for (int j = 0; j < CPG - 1; ++j) {
+    float v[WPC];
+    unit_weights<FMT>(wg, j, v);
+    const uint32_t c = cg[j];
+#pragma unroll
+    for (int i = 0; i < WPC; ++i) f((double)v[i], (double)unit_state<FMT>(c, i) - zp);
+  }
+  const uint32_t c = cg[CPG - 1];
+#pragma unroll
+  for (int i = 0; i < TAIL; ++i) f((double)wg[(CPG - 1) * WPC + i], (double)unit_state<FMT>(c, i) - zp);
+}
+
+// The codes of the 64 groups into device order.
+template <int FMT>
+__device__ __forceinline__ void store_units(const EncArgs& a, int rt, int quad, const uint16_t* cl, int tid, int threads) {
+  constexpr int CS = kEncUnitRow<FMT>;
+  static_assert(FMT != kEncNarrow, "");
+  constexpr int kSlots = FMT == kEncWide ? 11 : 10;   // (segment, quarter) pairs: two codes of a quarter, or one word
+  for (int i = tid; i < kSlots * 16; i += threads) {
+    const int slot = i >> 4, r = i & 15;
+    if (rt * kRowsPerTile + r >= a.N) continue;
+    uint32_t h[4];
+#pragma unroll
+    for (int gj = 0; gj < 4; ++gj) {
+      const uint16_t* cg = cl + (r * 4 + gj) * CS;
+      if constexpr (FMT == kEncWide) {
+        const int c = 6 * (slot & 3) + 2 * (slot >> 2);
+        h[gj] = (uint32_t)cg[c] | ((uint32_t)cg[c + 1] << 8);
+      } else {
+        h[gj] = cg[slot];
+      }
+    }
+    uint8_t* tile = a.codes + (int64_t)rt * a.row_tile_bytes + a.kind_code_off + (int64_t)(quad >> 1) * (FMT == kEncWide ? kWideTileBytes : kH16TileBytes);
+    *reinterpret_cast<uint2*>(tile + (slot >> 2) * 1024 + ((slot & 3) * 16 + r) * 16 + (quad & 1) * 8) = uint2{h[0] | (h[1] << 16), h[2] | (h[3] << 16)};
+  }
+}
+
+// First pass, LPG lanes per (row, group): scale = absmax / (2^(L-1) - 1), search, Eq. 4 refit (kept when the error does
+// not grow), fp16 rounding, search again with the stored scale.  An all-zero group gets scale 0 and codes 0.  Without
+// Code Cluster this is the final result and is written in device order; with it only the scales and the range of the
+// codes are wanted by the passes that follow.
+template <int FMT, int LPG>
+__global__ void __launch_bounds__(64 * LPG) ccq_encode_groups_kernel(const EncArgs a) {
+  constexpr int CS = kEncUnitRow<FMT>;
+  __shared__ __attribute__((aligned(16))) float wl[64 * kEncRow];
+  __shared__ uint16_t cl[64 * CS];
+  const int tid = threadIdx.x, lane = tid & 63, rt = blockIdx.x / a.quads, quad = blockIdx.x % a.quads;
+  load_groups<64 * LPG>(a, rt, quad, wl, tid);
+  __syncthreads();
+  const int gl = tid / LPG, sub = tid % LPG;
+  const int n = rt * kRowsPerTile + (gl >> 2), p = quad * 4 + (gl & 3);
+  const bool there = n < a.N && p < a.GK;
+  const float* wg = wl + gl * kEncRow;
+  uint16_t* cg = cl + gl * CS;
+  float amax = 0.f;
+  for (int c4 = sub; c4 < 16; c4 += LPG) {
+    const float4 w = *reinterpret_cast<const float4*>(wg + 4 * c4);
+    amax = fmaxf(fmaxf(amax, fmaxf(fabsf(w.x), fabsf(w.y))), fmaxf(fabsf(w.z), fabsf(w.w)));
+  }
+#pragma unroll
+  for (int off = LPG / 2; off >= 1; off >>= 1) amax = fmaxf(amax, __shfl_xor(amax, off));
+  const bool live = amax != 0.f;
+  const double s0 = (double)amax / (double)EncTraits<FMT>::QMAX;
+  search_groups<FMT, LPG>(wg, cg, s0, a.zp, a.tail, live, sub, lane);
+  __syncthreads();
+  double s = 0.0;
+  if (live) {
+    // Eq. 4: S = sum(W Wq) / sum(Wq^2).  A fp32 number times a level (at most 8 bits) is exact in fp64, so the fused
+    // multiply-add rounds once, as the separate multiply and add do.
+    double num = 0.0, den = 0.0;
+    for_weights<FMT>(wg, cg, a.zp, [&](double w, double wq) {
+      num = __builtin_fma(w, wq, num);
+      den = __builtin_fma(wq, wq, den);
+    });
+    double s1 = den > 0.0 ? num / den : s0;
+    double e1 = 0.0, e0 = 0.0;
+    for_weights<FMT>(wg, cg, a.zp, [&](double w, double wq) {
+      const double d1 = w - wq * s1, d0 = w - wq * s0;
+      e1 += d1 * d1;
+      e0 += d0 * d0;
+    });
+    if (!(s1 > 0.0) || e1 > e0) s1 = s0;
+    s = fp16_scale(s1);
+  }
+  __syncthreads();
+  search_groups<FMT, LPG>(wg, cg, s, a.zp, a.tail, live, sub, lane);
+  if constexpr (FMT == kEncNarrow) {
+    if (there && sub == 0) a.rowscale[(int64_t)n * a.GK + p] = fp16_bits(s);
+    uint32_t lo = 0xFFFFu, hi = 0;
+    if (there)
+      for (int j = sub; j < 16; j += LPG) {
+        lo = min(lo, (uint32_t)cg[j]);
+        hi = max(hi, (uint32_t)cg[j]);
+      }
+#pragma unroll
+    for (int off = 2 * LPG; off >= 1; off >>= 1) {
+      lo = min(lo, (uint32_t)__shfl_xor((int)lo, off));
+      hi = max(hi, (uint32_t)__shfl_xor((int)hi, off));
+    }
+    if (n < a.N && (gl & 3) == 0 && sub == 0) a.minmax[(int64_t)n * a.quads + quad] = lo | (hi << 16);
+  } else {
+    __syncthreads();
+    store_units<FMT>(a, rt, quad, cl, tid, 64 * LPG);
+    if (there && sub == 0) {
+      if (a.canon_scales) a.canon_scales[(int64_t)n * a.G + a.pbase + p] = fp16_bits(s);
       else
-        a.scales[(int64_t)(n / kRowsPerTile) * a.row_tile_scale_halfs + a.kind_scale_off + (int64_t)(gi / kWideGroupsPerTile) * kWideTileScaleHalfs +
-                 r * kWideGroupsPerTile + gi % kWideGroupsPerTile] = fp16_bits(s);
+        a.scales[(int64_t)rt * a.row_tile_scale_halfs + a.kind_scale_off + (int64_t)(quad >> 1) * kWideTileScaleHalfs + (gl >> 2) * kWideGroupsPerTile +
+                 (quad & 1) * 4 + (gl & 3)] = fp16_bits(s);
     }
   }
 }
 
-// Second pass (Sec. 3.3, Eq. 1), one workgroup per output channel: beta = smallest code of the row,
+// Second pass (Sec. 3.3, Eq. 1), one wavefront per output channel: beta = smallest code of the row,
 // alpha = (largest - smallest) / 255 (1 when they are equal).
 __global__ void __launch_bounds__(256) ccq_encode_cluster_kernel(const EncArgs a) {
-  __shared__ uint32_t smin[256], smax[256];
-  const int n = blockIdx.x, per_row = a.GK * 16;
-  uint32_t lo = 0xFFFFFFFFu, hi = 0;
-  for (int i = threadIdx.x; i < per_row; i += 256) {
-    const uint32_t c = a.rowcodes[(int64_t)n * per_row + i];
-    lo = min(lo, c);
-    hi = max(hi, c);
+  const int n = blockIdx.x * 4 + (threadIdx.x >> 6), lane = threadIdx.x & 63;
+  if (n >= a.N) return;
+  uint32_t lo = 0xFFFFu, hi = 0;
+  for (int i = lane; i < a.quads; i += 64) {
+    const uint32_t m = a.minmax[(int64_t)n * a.quads + i];
+    lo = min(lo, m & 0xFFFFu);
+    hi = max(hi, m >> 16);
   }
-  smin[threadIdx.x] = lo;
-  smax[threadIdx.x] = hi;
-  __syncthreads();
-  for (int off = 128; off >= 1; off >>= 1) {
-    if ((int)threadIdx.x < off) {
-      smin[threadIdx.x] = min(smin[threadIdx.x], smin[threadIdx.x + off]);
-      smax[threadIdx.x] = max(smax[threadIdx.x], smax[threadIdx.x + off]);
-    }
-    __syncthreads();
+#pragma unroll
+  for (int off = 32; off >= 1; off >>= 1) {
+    lo = min(lo, (uint32_t)__shfl_xor((int)lo, off));
+    hi = max(hi, (uint32_t)__shfl_xor((int)hi, off));
   }
-  if (threadIdx.x == 0) {
-    const uint32_t cmin = smin[0], cmax = smax[0];
-    a.beta[n] = (float)cmin;
-    a.alpha[n] = cmax > cmin ? (float)((double)(cmax - cmin) / 255.0) : 1.0f;
+  if (lane == 0) {
+    a.beta[n] = (float)lo;
+    a.alpha[n] = hi > lo ? (float)((double)(hi - lo) / 255.0) : 1.0f;
   }
 }
 
-// Third pass (narrow format), one wavefront per (row, group): every vector is searched again over the
-// 256 codes round(q alpha + beta) the row's map can reach (never worse than rounding the unconstrained
-// code by Eq. 1, which is one of the candidates), then one more Eq. 4 refit with the final codes, kept
-// when the error does not grow.  Bytes and fp16 scales are written in device order.
-__global__ void __launch_bounds__(256) ccq_encode_finish_narrow_kernel(const EncArgs a) {
-  __shared__ uint32_t reach[4][256];
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  const int64_t gidx = (int64_t)blockIdx.x * 4 + wave;
-  GroupId id;
-  if (!group_id(a, gidx, id)) return;
-  const int n = id.n, gi = id.p;
-  const double al = (double)a.alpha[n], be = (double)a.beta[n];
-  uint32_t mycodes[4];
+// ---- search over the 256 codes a row's Code Cluster map reaches ---------------------------------------------------
+// cost(q) - |t|^2 = |lv(q)|^2 - 2 lv(q) . t is a contraction over the four weights of a vector: MFMA 32x32x16 bf16 with the
+// candidates as A and the vectors as B.  Levels are multiples of 0.5 up to 64: exact in bf16; -2 t is cut into three bf16
+// numbers (24 bits) and |lv|^2 (at most 16 bits) into two:
+//   k-slot    0..3   4..7   8..11   12      13     14 15
+//   A         lv     lv     lv      |lv|^2 high, low      0
+//   B         the three parts of -2t        1      1      0
+// so products are exact and only the fp32 sums round: 16 of them, below |lv|^2 + 2 sum |lv t|.  Per vector the smallest
+// value of every block of eight candidates is tracked (best block, second best value); the eight of the best block are
+// compared in fp32 as sums of squares; both times the answer is taken only when the next best is further away than
+// rounding reaches, and the other vectors are searched in fp64.
+typedef __attribute__((ext_vector_type(8))) __bf16 enc_bf16x8;
+typedef __attribute__((ext_vector_type(2))) __bf16 enc_bf16x2;
+typedef __attribute__((ext_vector_type(2))) float enc_f32x2;
+typedef __attribute__((ext_vector_type(16))) float enc_f32x16;
+typedef __attribute__((ext_vector_type(4))) uint32_t enc_u32x4;
+
+__device__ __forceinline__ uint32_t enc_pack_bf16(float lo, float hi) {
+  const enc_f32x2 v = {lo, hi};
+  return __builtin_bit_cast(uint32_t, __builtin_convertvector(v, enc_bf16x2));
+}
+__device__ __forceinline__ float enc_lo(uint32_t v) { return __builtin_bit_cast(float, v << 16); }
+__device__ __forceinline__ float enc_hi(uint32_t v) { return __builtin_bit_cast(float, v & 0xFFFF0000u); }
+
+// code of byte q: round(q alpha + beta) by one FMA against beta + 2^23 (exact: the sum lies in [2^23, 2^24))
+__device__ __forceinline__ uint32_t cluster_code(float q, float al, float bem) { return __builtin_bit_cast(uint32_t, __builtin_fmaf(q, al, bem)) & 0x7FFFu; }
+
+struct RowMap {
+  enc_u32x4 A[8];   // the candidates, 32 per tile
+  float al, bem, zp, lmax;
+};
+
+__device__ __forceinline__ void row_map(RowMap& m, float al, float be, float zp, int lane) {
+  m.al = al;
+  m.bem = be + 0x1p23f;
+  m.zp = zp;
+  m.lmax = fmaxf(zp, 63.f - zp);
 #pragma unroll
-  for (int t = 0; t < 4; ++t) {
-    const int q = lane + 64 * t;
-    // exact: an 8-bit integer times a 24-bit significand plus an integer below 2^15 fits a double
-    mycodes[t] = (uint32_t)nearbyint((double)q * al + be);
-    reach[wave][q] = mycodes[t];
+  for (int t = 0; t < 8; ++t) {
+    const uint32_t c = cluster_code((float)(32 * t + (lane & 31)), al, m.bem);
+    float lv[4], n = 0.f;
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      lv[i] = (float)unit_state<kEncNarrow>(c, i) - zp;
+      n = __builtin_fmaf(lv[i], lv[i], n);
+    }
+    const uint32_t l01 = enc_pack_bf16(lv[0], lv[1]), l23 = enc_pack_bf16(lv[2], lv[3]);
+    const uint32_t nh = enc_pack_bf16(n, 0.f);
+    const uint32_t nn = nh | (enc_pack_bf16(n - enc_lo(nh), 0.f) << 16);
+    const bool upper = lane >= 32;
+    m.A[t] = enc_u32x4{l01, l23, upper ? nn : l01, upper ? 0u : l23};
   }
-  __builtin_amdgcn_wave_barrier();
-  const double w = (double)a.W[(int64_t)n * a.ldw + (int64_t)id.g * kGroup + lane];
-  double s = fp16_value(a.rowscale[gidx]);
-  uint32_t myq = 0;
-  for (int j = 0; j < 16; ++j) {
-    double v[4];
+}
+
+__device__ __forceinline__ double cluster_cost(uint32_t c, const double (&v)[4], double s, double zp) {
+  double cost = sqerr(v[0], s, (double)unit_state<kEncNarrow>(c, 0) - zp);
+  cost = cost + sqerr(v[1], s, (double)unit_state<kEncNarrow>(c, 1) - zp);
+  cost = cost + sqerr(v[2], s, (double)unit_state<kEncNarrow>(c, 2) - zp);
+  cost = cost + sqerr(v[3], s, (double)unit_state<kEncNarrow>(c, 3) - zp);
+  return cost;
+}
+
+// the smallest value, whose it is, and the second smallest
+__device__ __forceinline__ void see_block(float x, int i, float& best, float& second, int& at) {
+  at = x < best ? i : at;
+  second = __builtin_amdgcn_fmed3f(best, second, x);
+  best = fminf(best, x);
+}
+
+// One vector per lane, all of the row m is the map of; returns the byte.  All 64 lanes must be here.
+__device__ __forceinline__ uint32_t search_cluster(const RowMap& m, const float4 w, double s, double zp, bool active, int lane) {
+  const float v[4] = {w.x, w.y, w.z, w.w};
+  const InvScale inv = inv_scale(active ? s : 1.0);
+  float t[4], x[4], y[4];
 #pragma unroll
-    for (int i = 0; i < 4; ++i) v[i] = __shfl(w, 4 * j + i);
-    double best = INFINITY;
+  for (int i = 0; i < 4; ++i) t[i] = unit_scale(v[i], inv), x[i] = -2.f * t[i];
+  const uint32_t h01 = enc_pack_bf16(x[0], x[1]), h23 = enc_pack_bf16(x[2], x[3]);
+  y[0] = x[0] - enc_lo(h01), y[1] = x[1] - enc_hi(h01), y[2] = x[2] - enc_lo(h23), y[3] = x[3] - enc_hi(h23);
+  const uint32_t m01 = enc_pack_bf16(y[0], y[1]), m23 = enc_pack_bf16(y[2], y[3]);
+  const uint32_t l01 = enc_pack_bf16(y[0] - enc_lo(m01), y[1] - enc_hi(m01)), l23 = enc_pack_bf16(y[2] - enc_lo(m23), y[3] - enc_hi(m23));
+  // operand of the vectors of lanes 0..31 (k-slots 0..7 in lanes 0..31, 8..15 in lanes 32..63), and of lanes 32..63
+  const auto s0 = __builtin_amdgcn_permlane32_swap(h01, l01, false, false);
+  const auto s1 = __builtin_amdgcn_permlane32_swap(h23, l23, false, false);
+  const auto s2 = __builtin_amdgcn_permlane32_swap(m01, 0x3F803F80u, false, false);
+  const auto s3 = __builtin_amdgcn_permlane32_swap(m23, 0u, false, false);
+  float best[2], second[2];
+  int at[2];
+#pragma unroll
+  for (int h = 0; h < 2; ++h) {
+    const enc_u32x4 B = {s0[h], s1[h], s2[h], s3[h]};
+    best[h] = second[h] = kFar;
+    at[h] = 0;
+#pragma unroll
+    for (int k = 0; k < 8; ++k) {
+      const enc_f32x16 zero = {};
+      const enc_f32x16 d = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(enc_bf16x8, m.A[k]), __builtin_bit_cast(enc_bf16x8, B), zero, 0, 0, 0);
+#pragma unroll
+      for (int b = 0; b < 2; ++b) {
+        const float b0 = fminf(fminf(d[8 * b], d[8 * b + 1]), d[8 * b + 2]), b1 = fminf(fminf(d[8 * b + 3], d[8 * b + 4]), d[8 * b + 5]);
+        see_block(fminf(fminf(b0, b1), fminf(d[8 * b + 6], d[8 * b + 7])), 2 * k + b, best[h], second[h], at[h]);
+      }
+    }
+  }
+  // lane l and lane l ^ 32 hold the two halves of a vector's candidates: bring both to the vector's own lane
+  const auto cb = __builtin_amdgcn_permlane32_swap(__builtin_bit_cast(uint32_t, best[0]), __builtin_bit_cast(uint32_t, best[1]), false, false);
+  const auto cs = __builtin_amdgcn_permlane32_swap(__builtin_bit_cast(uint32_t, second[0]), __builtin_bit_cast(uint32_t, second[1]), false, false);
+  const auto ca = __builtin_amdgcn_permlane32_swap((uint32_t)at[0], (uint32_t)at[1], false, false);
+  const uint32_t b0 = cb[0], b1 = cb[1], n0 = cs[0], n1 = cs[1];   // (by value: a bit cast of a vector's element takes element 0)
+  const float p0 = __builtin_bit_cast(float, b0), p1 = __builtin_bit_cast(float, b1);
+  const bool upper = p1 < p0;   // which half
+  const float first = fminf(p0, p1);
+  const float next = fminf(fmaxf(p0, p1), fminf(__builtin_bit_cast(float, n0), __builtin_bit_cast(float, n1)));
+  const int blk = upper ? (int)ca[1] : (int)ca[0];
+  const float tmax = max_abs(t);
+  // 16 sums of numbers below 4 lmax^2 + 8 lmax tmax, each off by at most 2^-23 of that; both sides
+  bool sure = next - first > 0x1p-18f * (4.f * m.lmax * m.lmax + 8.f * m.lmax * tmax);
+  // the best block's candidates: rows 16 (blk % 2) + 4 half + {0..3, 8..11} of tile blk / 2
+  const int q0 = 16 * blk + (upper ? 4 : 0);
+  Best2 in;
+#pragma unroll
+  for (int i = 0; i < 8; ++i) {
+    const uint32_t c = cluster_code((float)(q0 + i + (i & 4)), m.al, m.bem);
+    float T = 0.f;
+#pragma unroll
+    for (int k = 0; k < 4; ++k) {
+      const float d = ((float)unit_state<kEncNarrow>(c, k) - m.zp) - t[k];
+      T = __builtin_fmaf(d, d, T);
+    }
+    in.see(T, i + (i & 4));
+  }
+  sure = sure && in.gap() > search_margin(in.best, tmax) && tmax <= kSearchMaxT;
+  uint32_t q = (uint32_t)(q0 + in.at) & 255u;
+  unsigned long long todo = __ballot(active && !sure);
+  while (todo) {   // exactly: four candidates per lane
+    const int src = __builtin_ctzll(todo);
+    todo &= todo - 1;
+    double vd[4];
+#pragma unroll
+    for (int i = 0; i < 4; ++i) vd[i] = (double)__shfl(v[i], src);
+    const double sd = __shfl(s, src);
+    double bc = INFINITY;
     uint32_t bq = 0xFFFFFFFFu;
-#pragma unroll
-    for (int t = 0; t < 4; ++t) {
-      const uint32_t c = mycodes[t];
-      double cost = sqerr(v[0], s, (double)((c >> 9) & 63u) - a.zp);
-      cost = cost + sqerr(v[1], s, (double)((c >> 6) & 63u) - a.zp);
-      cost = cost + sqerr(v[2], s, (double)((c >> 3) & 63u) - a.zp);
-      cost = cost + sqerr(v[3], s, (double)(c & 63u) - a.zp);
-      if (cost < best) { best = cost; bq = (uint32_t)(lane + 64 * t); }
+#pragma unroll 1
+    for (int k = 0; k < 4; ++k) {
+      const double cost = cluster_cost(cluster_code((float)(lane + 64 * k), m.al, m.bem), vd, sd, zp);
+      if (cost < bc) { bc = cost; bq = (uint32_t)(lane + 64 * k); }
     }
 #pragma unroll
     for (int off = 32; off >= 1; off >>= 1) {
-      const double oc = __shfl_xor(best, off);
+      const double oc = __shfl_xor(bc, off);
       const uint32_t oq = (uint32_t)__shfl_xor((int)bq, off);
-      if (oc < best || (oc == best && oq < bq)) { best = oc; bq = oq; }
+      if (oc < bc || (oc == bc && oq < bq)) { bc = oc; bq = oq; }
     }
-    if (lane == j) myq = bq;
+    if (lane == src) q = bq;
   }
-  const uint32_t qsel = (uint32_t)__shfl((int)myq, lane >> 2);
-  const uint32_t c = reach[wave][qsel];
-  const double wq = (double)((c >> (9 - 3 * (lane & 3))) & 63u) - a.zp;
-  const double s2 = refit_scale(w, wq, s);
+  return active ? q : 0u;
+}
+
+// A workgroup of the passes over the row's map takes four rows x sixteen groups (four narrow k-tiles): a wavefront keeps
+// one row's map and walks its groups four at a time, one vector per lane.  Building the map costs about half of what 64
+// vectors cost to search: with one k-tile of four rows per wavefront instead the pass took 500 us at 8192 x 8192.
+constexpr int kEncTilesPerBlock = 4;
+struct ClusterBlock {
+  int row, n, rt, tile0;   // this wavefront's row of the workgroup, of the matrix; row tile; first k-tile
+};
+__device__ __forceinline__ ClusterBlock cluster_block(const EncArgs& a) {
+  const int per_row = (a.quads + kEncTilesPerBlock - 1) / kEncTilesPerBlock, rq = blockIdx.x / per_row;
+  ClusterBlock b;
+  b.row = threadIdx.x >> 6;
+  b.n = rq * 4 + b.row;
+  b.rt = rq >> 2;
+  b.tile0 = (blockIdx.x % per_row) * kEncTilesPerBlock;
+  return b;
+}
+
+// The workgroup's bytes, [k-tile][row][group][16] in LDS, to device order: byte 4 kq + b of group j of a k-tile at
+// (kq * 16 + row) * 16 + 4 j + b.  One 16-byte store per thread of a wavefront: (k-tile, kq, row).
+__device__ __forceinline__ void store_bytes(const EncArgs& a, const ClusterBlock& b, const uint32_t* ql, int lane) {
+  const int t = lane >> 4, kq = (lane >> 2) & 3, row = lane & 3, n = b.n - b.row + row;
+  if (n >= a.N || b.tile0 + t >= a.quads) return;
+  const uint32_t* src = ql + (t * 4 + row) * 16 + kq;
+  *reinterpret_cast<uint4*>(a.codes + (int64_t)b.rt * a.row_tile_bytes + a.kind_code_off + (int64_t)(b.tile0 + t) * kNarrowTileBytes + (kq * 16 + (n & 15)) * 16) =
+      uint4{src[0], src[4], src[8], src[12]};
+}
+
+// Third pass (narrow format): every vector is searched again over the 256 codes round(q alpha + beta) the row's map can
+// reach (never worse than rounding the unconstrained code by Eq. 1, which is one of the candidates), then one more Eq. 4
+// refit with the final codes, kept when the error does not grow; its sums run one group per lane.
+__global__ void __launch_bounds__(256) ccq_encode_finish_narrow_kernel(const EncArgs a) {
+  __shared__ __attribute__((aligned(16))) float wl[64 * kEncRow];
+  __shared__ __attribute__((aligned(16))) uint32_t ql[64 * 4];
+  const int lane = threadIdx.x & 63, gj = lane >> 4;
+  const ClusterBlock b = cluster_block(a);
+  if (b.n < a.N) {   // (uniform in the wavefront)
+    RowMap m;
+    row_map(m, a.alpha[b.n], a.beta[b.n], (float)a.zp, lane);
+#pragma unroll 1
+    for (int t = 0; t < kEncTilesPerBlock; ++t) {
+      const int p = (b.tile0 + t) * 4 + gj, slot = (t * 4 + b.row) * 4 + gj;
+      float4 w = {0.f, 0.f, 0.f, 0.f};
+      double s = 0.0;
+      if (p < a.GK) {
+        w = *reinterpret_cast<const float4*>(a.W + (int64_t)b.n * a.ldw + (int64_t)enc_group(a, p) * kGroup + (lane & 15) * 4);
+        s = fp16_value(a.rowscale[(int64_t)b.n * a.GK + p]);
+      }
+      const uint32_t q = search_cluster(m, w, s, a.zp, s > 0.0, lane);
+      *reinterpret_cast<float4*>(wl + slot * kEncRow + (lane & 15) * 4) = w;
+      reinterpret_cast<uint8_t*>(ql)[slot * 16 + (lane & 15)] = (uint8_t)q;
+    }
+  }
+  __syncthreads();
+  if (b.row == 3) store_bytes(a, b, ql, lane);
+  if (b.row != 0) return;
+  // lane = slot: k-tile lane / 16, row (lane / 4) % 4, group lane % 4
+  const int n = b.n + ((lane >> 2) & 3), tile = b.tile0 + (lane >> 4), p = tile * 4 + (lane & 3);
+  if (n >= a.N || p >= a.GK) return;
+  const float al = a.alpha[n], bem = a.beta[n] + 0x1p23f;
+  double s = fp16_value(a.rowscale[(int64_t)n * a.GK + p]);
+  auto for_all = [&](auto f) {
+#pragma unroll 1
+    for (int j4 = 0; j4 < 4; ++j4) {
+      const uint32_t qs = ql[lane * 4 + j4];
+#pragma unroll
+      for (int k = 0; k < 4; ++k) {
+        const uint32_t c = cluster_code((float)((qs >> (8 * k)) & 255u), al, bem);
+        const float4 w = *reinterpret_cast<const float4*>(wl + lane * kEncRow + 16 * j4 + 4 * k);
+        f((double)w.x, (double)unit_state<kEncNarrow>(c, 0) - a.zp);
+        f((double)w.y, (double)unit_state<kEncNarrow>(c, 1) - a.zp);
+        f((double)w.z, (double)unit_state<kEncNarrow>(c, 2) - a.zp);
+        f((double)w.w, (double)unit_state<kEncNarrow>(c, 3) - a.zp);
+      }
+    }
+  };
+  double num = 0.0, den = 0.0;
+  for_all([&](double w, double wq) {
+    num = __builtin_fma(w, wq, num);   // exact products, as in the first pass
+    den = __builtin_fma(wq, wq, den);
+  });
+  const double s2 = den > 0.0 ? num / den : s;
   const double s2h = s2 > 0.0 ? fp16_scale(s2) : s;
-  if (group_error(w, wq, s2h) <= group_error(w, wq, s)) s = s2h;
-  // narrow k-tile: byte 4 kq + b of group j of the tile sits at (kq * 16 + row) * 16 + 4 j + b
-  const int r = n % kRowsPerTile;
-  if (lane < 16)
-    a.codes[(int64_t)(n / kRowsPerTile) * a.row_tile_bytes + a.kind_code_off + (int64_t)(gi / kNarrowGroupsPerTile) * kNarrowTileBytes + ((lane >> 2) * 16 + r) * 16 +
-            (gi % kNarrowGroupsPerTile) * 4 + (lane & 3)] = (uint8_t)myq;
-  if (lane == 0) {
-    if (a.canon_scales) a.canon_scales[id.widx] = fp16_bits(s);
-    else
-      a.scales[(int64_t)(n / kRowsPerTile) * a.row_tile_scale_halfs + a.kind_scale_off + (int64_t)(gi / kNarrowGroupsPerTile) * kNarrowTileScaleHalfs +
-               r * kNarrowGroupsPerTile + gi % kNarrowGroupsPerTile] = fp16_bits(s);
-  }
+  double e2 = 0.0, e1 = 0.0;
+  for_all([&](double w, double wq) {
+    const double d2 = __builtin_fma(-wq, s2h, w), d1 = __builtin_fma(-wq, s, w);   // (an fp16 number times a level is exact too)
+    e2 += d2 * d2;
+    e1 += d1 * d1;
+  });
+  if (e2 <= e1) s = s2h;
+  if (a.canon_scales) a.canon_scales[(int64_t)n * a.G + a.pbase + p] = fp16_bits(s);
+  else
+    a.scales[(int64_t)b.rt * a.row_tile_scale_halfs + a.kind_scale_off + (int64_t)tile * kNarrowTileScaleHalfs + (n & 15) * kNarrowGroupsPerTile + (lane & 3)] = fp16_bits(s);
 }
 
 // ---- Sec. 3.4 "Scale Compression", encoder side ------------------------------------------------------
@@ -346,183 +658,84 @@ __global__ void __launch_bounds__(256) ccq_encode_super_kernel(const EncArgs a) 
   if (threadIdx.x == 0) a.ssup[n] = fp16_bits(fp16_round(fp16_value((uint16_t)smax[0]) / a.field_max));
 }
 
-// One wavefront per (row, group): the group scale becomes the nearest multiple field * s_super, field in 1..15 (0 only
-// when the scale or the super scale is 0); because the scale that is stored has changed, the group's codes are
-// searched again with it -- over all codes (wide format) or over the 256 codes the row's Code Cluster map reaches
-// (narrow format).  The field goes into the spare low nibble of the wide group's last byte, or to the workspace
-// for the packing pass.
-template <bool NARROW>
-__global__ void __launch_bounds__(256) ccq_encode_compress_kernel(const EncArgs a) {
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  const int64_t gidx = (int64_t)blockIdx.x * 4 + wave;
-  GroupId id;
-  if (!group_id(a, gidx, id)) return;
-  const int n = id.n, gi = id.p;
-  const double s = fp16_value(a.canon_scales[id.widx]), ssup = fp16_value(a.ssup[n]);
+// The group scale becomes the nearest multiple field * s_super, field in 1..field_max (0 only when the scale or the super
+// scale is 0).
+__device__ __forceinline__ int scale_field(const EncArgs& a, int n, int p, double& se) {
+  const double s = fp16_value(a.canon_scales[(int64_t)n * a.G + a.pbase + p]), ssup = fp16_value(a.ssup[n]);
   int k = 0;
   if (ssup > 0.0 && s > 0.0) {
     const double kr = nearbyint(s / ssup);
-    k = kr < 1.0 ? 1 : (kr > 15.0 ? 15 : (int)kr);
+    k = kr < 1.0 ? 1 : (kr > a.field_max ? (int)a.field_max : (int)kr);
   }
-  const double se = (double)k * ssup;  // the scale the decoder will use
-  const double w = (double)a.W[(int64_t)n * a.ldw + (int64_t)id.g * kGroup + lane];
-  const int r = n % kRowsPerTile;
-  if constexpr (NARROW) {
-    if (se > 0.0) {
-      const double al = (double)a.alpha[n], be = (double)a.beta[n];
-      uint32_t mycodes[4];
-#pragma unroll
-      for (int t = 0; t < 4; ++t) mycodes[t] = (uint32_t)nearbyint((double)(lane + 64 * t) * al + be);
-      uint32_t myq = 0;
-      for (int j = 0; j < 16; ++j) {
-        double v[4];
-#pragma unroll
-        for (int i = 0; i < 4; ++i) v[i] = __shfl(w, 4 * j + i);
-        double best = INFINITY;
-        uint32_t bq = 0xFFFFFFFFu;
-#pragma unroll
-        for (int t = 0; t < 4; ++t) {
-          const uint32_t c = mycodes[t];
-          double cost = sqerr(v[0], se, (double)((c >> 9) & 63u) - a.zp);
-          cost = cost + sqerr(v[1], se, (double)((c >> 6) & 63u) - a.zp);
-          cost = cost + sqerr(v[2], se, (double)((c >> 3) & 63u) - a.zp);
-          cost = cost + sqerr(v[3], se, (double)(c & 63u) - a.zp);
-          if (cost < best) { best = cost; bq = (uint32_t)(lane + 64 * t); }
-        }
-#pragma unroll
-        for (int off = 32; off >= 1; off >>= 1) {
-          const double oc = __shfl_xor(best, off);
-          const uint32_t oq = (uint32_t)__shfl_xor((int)bq, off);
-          if (oc < best || (oc == best && oq < bq)) { best = oc; bq = oq; }
-        }
-        if (lane == j) myq = bq;
+  se = (double)k * ssup;  // the scale the decoder will use
+  return k;
+}
+
+// Because the scale that is stored has changed, every group's codes are searched once more with it; a group whose scale
+// is now 0 keeps its codes.  Wide format and hybrid word: over all codes; the field goes into the spare low nibble of the
+// wide group's last byte, or the low 13 bits of the last word (scale mask 0x1FFF of Table 1).
+template <int FMT, int LPG>
+__global__ void __launch_bounds__(64 * LPG) ccq_encode_compress_kernel(const EncArgs a) {
+  constexpr int CS = kEncUnitRow<FMT>, CPG = EncTraits<FMT>::CPG;
+  __shared__ __attribute__((aligned(16))) float wl[64 * kEncRow];
+  __shared__ uint16_t cl[64 * CS];
+  const int tid = threadIdx.x, lane = tid & 63, rt = blockIdx.x / a.quads, quad = blockIdx.x % a.quads;
+  load_groups<64 * LPG>(a, rt, quad, wl, tid);
+  __syncthreads();
+  const int gl = tid / LPG, sub = tid % LPG;
+  const int n = rt * kRowsPerTile + (gl >> 2), p = quad * 4 + (gl & 3);
+  const bool there = n < a.N && p < a.GK;
+  uint16_t* cg = cl + gl * CS;
+  double se = 0.0;
+  const int k = there ? scale_field(a, n, p, se) : 0;
+  search_groups<FMT, LPG>(wl + gl * kEncRow, cg, se, a.zp, a.tail, se > 0.0, sub, lane);
+  __syncthreads();
+  if (there && sub == 0) {
+    if (!(se > 0.0)) {
+      const uint8_t* tile = a.codes + (int64_t)rt * a.row_tile_bytes + a.kind_code_off + (int64_t)(quad >> 1) * (FMT == kEncWide ? kWideTileBytes : kH16TileBytes) +
+                            ((quad & 1) * 4 + (gl & 3)) * 2;
+      for (int j = 0; j < CPG; ++j) {
+        if constexpr (FMT == kEncWide) cg[j] = tile[((j % 6) / 2) * 1024 + ((j / 6) * 16 + (gl >> 2)) * 16 + (j & 1)];
+        else cg[j] = *reinterpret_cast<const uint16_t*>(tile + (j >> 2) * 1024 + ((j & 3) * 16 + (gl >> 2)) * 16);
       }
-      if (lane < 16)
-        a.codes[(int64_t)(n / kRowsPerTile) * a.row_tile_bytes + a.kind_code_off + (int64_t)(gi / kNarrowGroupsPerTile) * kNarrowTileBytes + ((lane >> 2) * 16 + r) * 16 +
-                (gi % kNarrowGroupsPerTile) * 4 + (lane & 3)] = (uint8_t)myq;
     }
-    if (lane == 0) a.fields[gidx] = (uint8_t)k;
-  } else {
-    uint32_t code = 0;
-    if (se > 0.0) code = search_group<4, 3, 2>(w, se, a.zp, lane);
-    if (lane < 22) {
-      const int kq = lane / 6, rem = lane % 6;
-      uint8_t* p = a.codes + (int64_t)(n / kRowsPerTile) * a.row_tile_bytes + a.kind_code_off + (int64_t)(gi / kWideGroupsPerTile) * kWideTileBytes + (rem / 2) * 1024 +
-                   (kq * 16 + r) * 16 + (gi % kWideGroupsPerTile) * 2 + (rem % 2);
-      uint32_t byte = se > 0.0 ? code : (uint32_t)*p;  // an all-zero group keeps its codes
-      if (lane == 21) byte = (byte & 0xF0u) | (uint32_t)k;
-      if (se > 0.0 || lane == 21) *p = (uint8_t)byte;
-    }
+    cg[CPG - 1] = (uint16_t)((cg[CPG - 1] & (FMT == kEncWide ? 0xF0u : 0xE000u)) | (uint32_t)k);
   }
+  __syncthreads();
+  store_units<FMT>(a, rt, quad, cl, tid, 64 * LPG);
 }
 
-// ---- the hybrid 16-bit word (Sec. 3.2): a (3,3,2) code on weights 7j..7j+2 and a (3,4,2) code on weights 7j+3..7j+6
-// of word j, searched independently (their bits do not overlap); ten words per group, the last one zero-padded ----
-
-// Lane j (j < 10) returns word j of the group held one weight per lane.
-__device__ __forceinline__ uint32_t search_h16(double w, double s, double zp, int lane) {
-  uint32_t mine = 0;
-  for (int j0 = 0; j0 < 10; j0 += 8) {
-    const int j = min(j0 + (lane >> 3), 9);
-    double va[3], vb[4];
-#pragma unroll
-    for (int i = 0; i < 7; ++i) {
-      const int idx = 7 * j + i;
-      const double val = __shfl(w, min(idx, kGroup - 1));
-      const double v = idx < kGroup ? val : 0.0;
-      if (i < 3) va[i] = v;
-      else vb[i - 3] = v;
-    }
-    const uint32_t ca = nearest_code<3, 3, 2>(va, s, zp, lane);
-    const uint32_t cb = nearest_code<3, 4, 2>(vb, s, zp, lane);
-    const uint32_t word = (ca << 9) | cb;
-#pragma unroll
-    for (int sg = 0; sg < 8; ++sg) {
-      const uint32_t c = (uint32_t)__shfl((int)word, sg * 8);
-      if (lane == j0 + sg && j0 + sg < 10) mine = c;
+// Narrow format: over the 256 codes of the row's map; the four fields of a k-tile's groups go into one 16-bit word per
+// row (group j in bits 4j..4j+3; groups that pad the last k-tile keep field 0: scale 0).
+__global__ void __launch_bounds__(256) ccq_encode_compress_narrow_kernel(const EncArgs a) {
+  __shared__ __attribute__((aligned(16))) uint32_t ql[64 * 4];
+  const int lane = threadIdx.x & 63, gj = lane >> 4;
+  const ClusterBlock b = cluster_block(a);
+  if (b.n < a.N) {   // (uniform in the wavefront)
+    RowMap m;
+    row_map(m, a.alpha[b.n], a.beta[b.n], (float)a.zp, lane);
+#pragma unroll 1
+    for (int t = 0; t < kEncTilesPerBlock; ++t) {
+      const int tile = b.tile0 + t, p = tile * 4 + gj;
+      float4 w = {0.f, 0.f, 0.f, 0.f};
+      double se = 0.0;
+      int k = 0;
+      if (p < a.GK) {
+        w = *reinterpret_cast<const float4*>(a.W + (int64_t)b.n * a.ldw + (int64_t)enc_group(a, p) * kGroup + (lane & 15) * 4);
+        k = scale_field(a, b.n, p, se);
+      }
+      uint32_t q = search_cluster(m, w, se, a.zp, se > 0.0, lane);
+      if (p < a.GK && !(se > 0.0))
+        q = a.codes[(int64_t)b.rt * a.row_tile_bytes + a.kind_code_off + (int64_t)tile * kNarrowTileBytes + (((lane & 15) >> 2) * 16 + (b.n & 15)) * 16 + gj * 4 + (lane & 3)];
+      reinterpret_cast<uint8_t*>(ql)[((t * 4 + b.row) * 4 + gj) * 16 + (lane & 15)] = (uint8_t)q;
+      const int word = k << (4 * gj);
+      const int all = __shfl(word, 0) | __shfl(word, 16) | __shfl(word, 32) | __shfl(word, 48);
+      if (lane == 0 && tile < a.quads)
+        a.scales[(int64_t)b.rt * a.row_tile_scale_halfs + a.kind_scale_off + (int64_t)tile * kNarrowTileScaleHalfs4 + (b.n & 15)] = (uint16_t)all;
     }
   }
-  return mine;
-}
-
-// word j of group gi, row n, in the hybrid-word k-tile: segment j / 4, lane (j % 4) * 16 + row, halfword gi % 8
-__device__ __forceinline__ uint16_t* h16_word_ptr(const EncArgs& a, int n, int gi, int j) {
-  return reinterpret_cast<uint16_t*>(a.codes + (int64_t)(n / kRowsPerTile) * a.row_tile_bytes + a.kind_code_off + (int64_t)(gi / kWideGroupsPerTile) * kH16TileBytes +
-                                     (j >> 2) * 1024 + ((j & 3) * 16 + n % kRowsPerTile) * 16 + (gi % kWideGroupsPerTile) * 2);
-}
-
-// One wavefront per (row, group): Alg. 1 with the Eq. 4 refit as for the other formats; 2^(L-1) - 1 = 3.
-__global__ void __launch_bounds__(256) ccq_encode_h16_kernel(const EncArgs a) {
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  const int64_t gidx = (int64_t)blockIdx.x * 4 + wave;
-  GroupId id;
-  if (!group_id(a, gidx, id)) return;
-  const int n = id.n, gi = id.p;
-  const double w = (double)a.W[(int64_t)n * a.ldw + (int64_t)id.g * kGroup + lane];
-  const double amax = wave_max(fabs(w));
-  uint32_t word = 0;
-  double s = 0.0;
-  if (amax != 0.0) {
-    const double s0 = amax / 3.0;
-    word = search_h16(w, s0, a.zp, lane);
-    const uint32_t wj = (uint32_t)__shfl((int)word, lane / 7);
-    const int i = lane % 7;
-    const int shift = i < 3 ? 13 - 2 * i : 12 - 2 * i;  // Table 1: [13,11,9,6,4,2,0]
-    const double wq = (double)((wj >> shift) & 7u) - a.zp;
-    double s1 = refit_scale(w, wq, s0);
-    if (!(s1 > 0.0) || group_error(w, wq, s1) > group_error(w, wq, s0)) s1 = s0;
-    s = fp16_scale(s1);
-    word = search_h16(w, s, a.zp, lane);
-  }
-  if (lane < 10) *h16_word_ptr(a, n, gi, lane) = (uint16_t)word;
-  if (lane == 0) {
-    if (a.canon_scales) a.canon_scales[id.widx] = fp16_bits(s);
-    else
-      a.scales[(int64_t)(n / kRowsPerTile) * a.row_tile_scale_halfs + a.kind_scale_off + (int64_t)(gi / kWideGroupsPerTile) * kWideTileScaleHalfs +
-               (n % kRowsPerTile) * kWideGroupsPerTile + gi % kWideGroupsPerTile] = fp16_bits(s);
-  }
-}
-
-// Compressed scales of the hybrid word: 13-bit field in the low bits of the group's last word (scale mask 0x1FFF of
-// Table 1), words searched again with the scale that is stored.
-__global__ void __launch_bounds__(256) ccq_encode_h16_compress_kernel(const EncArgs a) {
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  const int64_t gidx = (int64_t)blockIdx.x * 4 + wave;
-  GroupId id;
-  if (!group_id(a, gidx, id)) return;
-  const int n = id.n, gi = id.p;
-  const double s = fp16_value(a.canon_scales[id.widx]), ssup = fp16_value(a.ssup[n]);
-  int k = 0;
-  if (ssup > 0.0 && s > 0.0) {
-    const double kr = nearbyint(s / ssup);
-    k = kr < 1.0 ? 1 : (kr > 8191.0 ? 8191 : (int)kr);
-  }
-  const double se = (double)k * ssup;
-  const double w = (double)a.W[(int64_t)n * a.ldw + (int64_t)id.g * kGroup + lane];
-  uint32_t word = 0;
-  if (se > 0.0) word = search_h16(w, se, a.zp, lane);
-  if (lane < 10) {
-    uint16_t* p = h16_word_ptr(a, n, gi, lane);
-    uint32_t v = se > 0.0 ? word : (uint32_t)*p;  // an all-zero group keeps its words
-    if (lane == 9) v = (v & 0xE000u) | (uint32_t)k;
-    if (se > 0.0 || lane == 9) *p = (uint16_t)v;
-  }
-}
-
-// Narrow format: the four 4-bit fields of a k-tile's groups into one 16-bit word per row (group j in bits 4j..4j+3).
-__global__ void __launch_bounds__(256) ccq_encode_pack_fields_kernel(const EncArgs a) {
-  const int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x;
-  const int tiles = (a.GK + kNarrowGroupsPerTile - 1) / kNarrowGroupsPerTile;
-  if (i >= (int64_t)a.N * tiles) return;
-  const int n = (int)(i / tiles), t = (int)(i % tiles);
-  const uint8_t* f = a.fields + (int64_t)n * a.GK;
-  uint32_t word = 0;  // groups that pad the last k-tile keep field 0: scale 0
-#pragma unroll
-  for (int j = 0; j < kNarrowGroupsPerTile; ++j) {
-    const int p = t * kNarrowGroupsPerTile + j;
-    if (p < a.GK) word |= (uint32_t)f[p] << (4 * j);
-  }
-  a.scales[(int64_t)(n / kRowsPerTile) * a.row_tile_scale_halfs + a.kind_scale_off + (int64_t)t * kNarrowTileScaleHalfs4 + n % kRowsPerTile] = (uint16_t)word;
+  __syncthreads();
+  if (b.row == 3) store_bytes(a, b, ql, lane);
 }
 
 // Clears `n16` 16-byte units (a kernel, not a memset node: the call may be recorded into a graph).
@@ -533,19 +746,68 @@ __global__ void __launch_bounds__(256) ccq_encode_clear_kernel(uint4* p, int64_t
 
 static int64_t round16(int64_t v) { return (v + 15) / 16 * 16; }
 
-// workspace: [unclustered codes and first-pass scales (narrow)] [final fp16 scales, fields (compressed scales)]
+// The workspace is laid out as [range of the unclustered codes, first-pass scales (narrow)] [final fp16 scales (compressed
+// scales)].  The figure that callers size it by is an older one and stays: room for every unclustered code and a byte
+// per narrow group besides, of which only the front is used.
 int64_t encode_workspace_bytes(const Layout& L) {
   const int64_t groups = (int64_t)L.N * L.G, narrow = (int64_t)L.N * L.groups[kNarrow];
   int64_t need = 0;
-  if (narrow > 0) need += round16(narrow * 16 * 2) + round16(narrow * 2);
+  if (narrow > 0) need += round16(narrow * 16 * 2) + round16(narrow * 2);   // a row's quads are at most its groups: 4 bytes a quad fit
   if (L.scale_mode == 1) need += round16(groups * 2) + round16(narrow);
   return need;
 }
 
+// What the zeros at the end of a hybrid-word group cost and are coded as (H16Tail).  The lowest code of those that tie, as
+// the exact search takes it; its costs are rounded sums, so ties are only decided here where they are ties under any
+// scale: the tied paths add the same square any number of times and otherwise zeros, which gives the same partial sums in
+// every order.
+static H16Tail h16_tail(double zp) {
+  H16Tail t;
+  t.decided = 1;
+  auto sq = [&](uint32_t st) { return ((double)st - zp) * ((double)st - zp); };
+  // of n states in the low bits of a code (after the bits `lead`), the cheapest of the `codes` choices
+  auto least = [&](int n, uint32_t codes, uint32_t lead, float* cost_out) {
+    double best = INFINITY;
+    uint32_t at = 0;
+    for (int pass = 0; pass < 2; ++pass)
+      for (uint32_t c = 0; c < codes; ++c) {
+        double cost = 0.0, one = 0.0;
+        bool plain = true;   // a single value besides zero
+        for (int i = 0; i < n; ++i) {
+          const double e = sq(((lead | c) >> (2 * (n - 1 - i))) & 7u);
+          cost += e;
+          if (e != 0.0 && one != 0.0 && e != one) plain = false;
+          if (e != 0.0) one = e;
+        }
+        if (pass == 0 && cost < best) { best = cost; at = c; }
+        if (pass == 1 && cost == best && c != at) {
+          double other = 0.0;
+          for (int i = 0; i < n; ++i) other = std::fmax(other, sq(((lead | at) >> (2 * (n - 1 - i))) & 7u));
+          if (!plain || one != other) t.decided = 0;
+        }
+      }
+    if (cost_out) *cost_out = (float)best;
+    return at;
+  };
+  t.zeros = least(4, 512u, 0u, nullptr);
+  for (uint32_t x = 0; x < 2; ++x) t.rest[x] = least(2, 16u, x << 4, &t.cost[x]);
+  return t;
+}
+
+// Lanes per group: one lane per group does the fewest instructions (the sums of Eq. 4 are run by every lane of a group),
+// four give a small matrix four times the wavefronts.
+template <int FMT>
+static void launch_groups(const EncArgs& a, int64_t blocks, hipStream_t st) {
+  const dim3 grid((unsigned)blocks);
+  if (blocks >= 16 * (int64_t)device_cus()) hipLaunchKernelGGL((ccq_encode_groups_kernel<FMT, 2>), grid, dim3(128), 0, st, a);
+  else hipLaunchKernelGGL((ccq_encode_groups_kernel<FMT, 4>), grid, dim3(256), 0, st, a);
+}
+
 int launch_encode(const Layout& L, const float* W, int64_t ldw, void* codes, void* scales, float* alpha, float* beta, void* scale_super,
                   const int32_t* meta, void* workspace, void* stream) {
-  const int64_t groups = (int64_t)L.N * L.G, narrow = (int64_t)L.N * L.groups[kNarrow];
+  const int64_t narrow = (int64_t)L.N * L.groups[kNarrow];
   EncArgs a;
+  a.tail = H16Tail{};
   a.field_max = L.h16 ? 8191.0 : 15.0;
   a.W = W;
   a.ldw = ldw;
@@ -557,22 +819,16 @@ int launch_encode(const Layout& L, const float* W, int64_t ldw, void* codes, voi
   a.alpha = alpha;
   a.beta = beta;
   uint8_t* ws = static_cast<uint8_t*>(workspace);
-  a.rowcodes = nullptr;
+  a.minmax = nullptr;
   a.rowscale = nullptr;
   if (narrow > 0) {
-    a.rowcodes = reinterpret_cast<uint16_t*>(ws);
-    ws += round16(narrow * 16 * 2);
+    a.minmax = reinterpret_cast<uint32_t*>(ws);
+    ws += round16((int64_t)L.N * L.tiles[kNarrow] * 4);
     a.rowscale = reinterpret_cast<uint16_t*>(ws);
     ws += round16(narrow * 2);
   }
-  a.canon_scales = nullptr;
-  a.fields = nullptr;
+  a.canon_scales = L.scale_mode == 1 ? reinterpret_cast<uint16_t*>(ws) : nullptr;
   a.ssup = static_cast<uint16_t*>(scale_super);
-  if (L.scale_mode == 1) {
-    a.canon_scales = reinterpret_cast<uint16_t*>(ws);
-    ws += round16(groups * 2);
-    a.fields = ws;
-  }
   a.row_tile_bytes = L.row_tile_bytes;
   a.row_tile_scale_halfs = L.row_tile_scale_halfs;
   hipStream_t st = static_cast<hipStream_t>(stream);
@@ -588,37 +844,37 @@ int launch_encode(const Layout& L, const float* W, int64_t ldw, void* codes, voi
   // the narrow groups of every row, then the wide ones (or the hybrid words, which never mix)
   EncArgs an = a, aw = a;
   an.GK = L.groups[kNarrow];
+  an.quads = (an.GK + 3) / 4;
   an.pbase = 0;
   an.mbase = 0;
   an.kind_code_off = 0;
   an.kind_scale_off = 0;
   an.zp = (double)L.zp[kNarrow];
   aw.GK = L.groups[kWide];
+  aw.quads = (aw.GK + 3) / 4;
   aw.pbase = L.groups[kNarrow];
   aw.mbase = L.pgroups[kNarrow];
   aw.kind_code_off = (int64_t)L.tiles[kNarrow] * kNarrowTileBytes;
   aw.kind_scale_off = L.scale_mode == 1 ? 0 : (int64_t)L.tiles[kNarrow] * kNarrowTileScaleHalfs;
   aw.zp = (double)L.zp[kWide];
-  const dim3 grid_n((unsigned)((narrow + 3) / 4)), grid_w((unsigned)(((int64_t)L.N * L.groups[kWide] + 3) / 4));
+  if (L.h16) aw.tail = h16_tail(aw.zp);
+  const int64_t blocks_n = (int64_t)L.row_tiles * an.quads, blocks_w = (int64_t)L.row_tiles * aw.quads;
+  const unsigned blocks_m = (unsigned)(((L.N + 3) / 4) * ((an.quads + kEncTilesPerBlock - 1) / kEncTilesPerBlock));
   if (an.GK > 0) {
-    hipLaunchKernelGGL((ccq_encode_groups_kernel<6, 4, 3, true>), grid_n, block, 0, st, an);
-    hipLaunchKernelGGL(ccq_encode_cluster_kernel, dim3((unsigned)L.N), block, 0, st, an);
-    hipLaunchKernelGGL(ccq_encode_finish_narrow_kernel, grid_n, block, 0, st, an);
+    launch_groups<kEncNarrow>(an, blocks_n, st);
+    hipLaunchKernelGGL(ccq_encode_cluster_kernel, dim3((unsigned)((L.N + 3) / 4)), block, 0, st, an);
+    hipLaunchKernelGGL(ccq_encode_finish_narrow_kernel, dim3(blocks_m), block, 0, st, an);
   }
   if (aw.GK > 0) {
-    if (L.h16) hipLaunchKernelGGL(ccq_encode_h16_kernel, grid_w, block, 0, st, aw);
-    else hipLaunchKernelGGL((ccq_encode_groups_kernel<4, 3, 2, false>), grid_w, block, 0, st, aw);
+    if (L.h16) launch_groups<kEncH16>(aw, blocks_w, st);
+    else launch_groups<kEncWide>(aw, blocks_w, st);
   }
   if (L.scale_mode == 1) {
     hipLaunchKernelGGL(ccq_encode_super_kernel, dim3((unsigned)L.N), block, 0, st, a);
-    if (an.GK > 0) {
-      hipLaunchKernelGGL(ccq_encode_compress_kernel<true>, grid_n, block, 0, st, an);
-      const int64_t words = (int64_t)L.N * L.tiles[kNarrow];
-      hipLaunchKernelGGL(ccq_encode_pack_fields_kernel, dim3((unsigned)((words + 255) / 256)), block, 0, st, an);
-    }
+    if (an.GK > 0) hipLaunchKernelGGL(ccq_encode_compress_narrow_kernel, dim3(blocks_m), block, 0, st, an);
     if (aw.GK > 0) {
-      if (L.h16) hipLaunchKernelGGL(ccq_encode_h16_compress_kernel, grid_w, block, 0, st, aw);
-      else hipLaunchKernelGGL(ccq_encode_compress_kernel<false>, grid_w, block, 0, st, aw);
+      if (L.h16) hipLaunchKernelGGL((ccq_encode_compress_kernel<kEncH16, 4>), dim3((unsigned)blocks_w), block, 0, st, aw);
+      else hipLaunchKernelGGL((ccq_encode_compress_kernel<kEncWide, 4>), dim3((unsigned)blocks_w), block, 0, st, aw);
     }
   }
   if (hipGetLastError() != hipSuccess) return CCQ_ERR_HIP;

@@ -199,6 +199,29 @@ def test_full_size_sampled_rows():
     assert np.array_equal(got.alpha.cpu().numpy().reshape(-1)[rows], alpha) and np.array_equal(got.beta.cpu().numpy().reshape(-1)[rows], beta)
 
 
+@pytest.mark.parametrize("mode", [0, 1])
+@pytest.mark.parametrize("fmt", ["narrow", "wide", "h16"])
+def test_large_matrix_equals_its_rows(fmt, mode):
+    """Rows are independent: a matrix large enough for the two-lanes-per-group search (its workgroups fill the chip many
+    times over) gives the bytes that the four-lanes-per-group search gives for any sixteen of its rows, and those are the
+    oracle's (the tests above).  K = 2240: 35 groups, a ragged last k-tile; outliers, zeros and exact ties among the rows."""
+    N, K = 8192, 2240
+    g = torch.Generator(device=DEV).manual_seed(31)
+    W = torch.randn(N, K, generator=g, device=DEV) * 0.02
+    W[5] = torch.round(W[5] * 256) / 256
+    W[16:32, :64] = 0.0
+    W[4000, ::97] *= 12.0
+    f = {"narrow": b.NARROW, "wide": b.WIDE, "h16": b.H16}[fmt]
+    big = b.quantize(W, f, scale_mode=mode, prefill_byte=0xFF)
+    for r0 in (0, 16, 3984, 4000, N - 16):
+        small = b.quantize(W[r0:r0 + 16].contiguous(), f, scale_mode=mode, prefill_byte=0xFF)
+        for name in ("codes", "scales", "ssup", "alpha", "beta"):
+            x, y = getattr(big, name), getattr(small, name)
+            assert (x is None) == (y is None)
+            if x is not None:
+                assert torch.equal(x.reshape(N // 16, -1)[r0 // 16], y.reshape(-1)), f"{name} of rows {r0}.. differ"
+
+
 def test_rejections_need_no_kernel():
     lib = b.load()
     assert lib.ccq_quantize_workspace_bytes(b.ctypes.byref(b.descriptor(512 + 32, 16, [b.NARROW]))) == -1            # K not a whole number of groups
