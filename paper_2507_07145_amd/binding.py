@@ -1,4 +1,5 @@
-"""Thin ctypes binding of libccq.so (include/ccq.h): argument marshalling only.
+"""Thin binding of libccq.so (include/ccq.h): argument marshalling only, through ctypes; the multiply calls of a decode
+loop go through a small native module (csrc/python/ccq_call.cpp) that does the same with less host time.
 
 Every step of the fused dequantize-and-multiply runs inside the HIP library;
 PyTorch is used for device memory and streams.  The functions carry the names
@@ -114,6 +115,24 @@ def load() -> ctypes.CDLL:
     L.ccq_status_string.argtypes = [ctypes.c_int]
     _lib = L
     return L
+
+
+_call = None
+
+
+def _calls():
+    """The native module of the multiply calls, given the library's entry points; raises if it has not been built."""
+    global _call
+    if _call is None:
+        L = load()
+        try:
+            from . import _ccq_call as m
+        except ImportError as e:
+            raise RuntimeError("_ccq_call.so is missing or does not load: build it with `python -m paper_2507_07145_amd.build`") from e
+        m.bind(*(ctypes.cast(getattr(L, name), ctypes.c_void_p).value for name in
+                 ("ccq_gemm", "ccq_gemm_workspace_bytes", "ccq_gemm_static", "ccq_grouped_gemm", "ccq_grouped_workspace_bytes")))
+        _call = m
+    return _call
 
 
 def _check(status: int, where: str) -> None:
@@ -355,6 +374,12 @@ def _new_output(rows: int, N: int, device) -> torch.Tensor:
 def gemm(w: Weight, x: torch.Tensor, out: torch.Tensor | None = None, workspace: torch.Tensor | None = None, stream=None,
          launch: ccq_launch | None = None) -> torch.Tensor:
     """y = x W_dq^T through ccq_gemm (or ccq_gemm_ex when `launch` is given).  x: bf16 [M][K] on the GPU."""
+    if launch is None and stream is None:
+        y = (_call or _calls()).gemm(w, x, out, workspace)
+        if type(y) is int:
+            _check(y, "ccq_gemm")
+        elif y is not None:
+            return y
     assert x.dtype == torch.bfloat16 and x.dim() == 2 and x.stride(1) == 1 and x.is_cuda
     M = x.shape[0]
     y = out if out is not None else _new_output(M, w.N, x.device)
@@ -376,6 +401,12 @@ def gemm(w: Weight, x: torch.Tensor, out: torch.Tensor | None = None, workspace:
 
 def gemm_static(w: Weight, x: torch.Tensor, out: torch.Tensor, stream=None) -> torch.Tensor:
     """y = x W_dq^T through ccq_gemm_static: no workspace, nothing allocated (the caller passes `out`)."""
+    if stream is None:
+        y = (_call or _calls()).gemm_static(w, x, out)
+        if type(y) is int:
+            _check(y, "ccq_gemm_static")
+        elif y is not None:
+            return y
     assert x.dtype == torch.bfloat16 and x.dim() == 2 and x.stride(1) == 1 and x.is_cuda
     assert out.dtype == torch.bfloat16 and out.shape == (x.shape[0], w.N) and out.stride(1) == 1
     _check(load().ccq_gemm_static(ctypes.byref(w.desc), _t_ptr(x), x.shape[0], x.stride(0), _t_ptr(out), out.stride(0), _stream_ptr(stream)),
@@ -398,6 +429,12 @@ def grouped_gemm(w: Weight, x: torch.Tensor, sorted_rows: torch.Tensor, expert_o
                  expert_offsets_host: np.ndarray | None = None, out: torch.Tensor | None = None, workspace: torch.Tensor | None = None,
                  stream=None) -> torch.Tensor:
     """y[p] = x[sorted_rows[p]] W_dq(e)^T for p in expert e's range, through ccq_grouped_gemm."""
+    if stream is None:
+        y = (_call or _calls()).grouped_gemm(w, x, sorted_rows, expert_offsets, expert_offsets_host, out, workspace)
+        if type(y) is int:
+            _check(y, "ccq_grouped_gemm")
+        elif y is not None:
+            return y
     assert x.dtype == torch.bfloat16 and x.dim() == 2 and x.stride(1) == 1 and x.is_cuda
     assert sorted_rows.dtype == torch.int32 and expert_offsets.dtype == torch.int32
     P = sorted_rows.numel()

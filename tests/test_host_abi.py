@@ -266,3 +266,23 @@ def test_padded_layouts(kinds, K, N, n_wide):
         assert meta.size == tn * 4 + tw * 8
         assert meta[:gn].tolist() == np.flatnonzero(gf == 0).tolist() and meta[tn * 4:tn * 4 + gw].tolist() == np.flatnonzero(gf == 1).tolist()
         assert np.all(meta[gn:tn * 4] == G - 1) and np.all(meta[tn * 4 + gw:] == G - 1)
+
+
+def test_native_call_module_leaves_odd_arguments_to_the_checks():
+    """The native host path answers None for arguments it does not handle (here: tensors that are not on the GPU, a weight
+    without a descriptor), and the general path then refuses them as before."""
+    import torch
+    w = b.Weight()
+    w.desc = b.descriptor(256, 16, [b.NARROW])
+    x = torch.zeros((1, 256), dtype=torch.bfloat16)
+    offs = torch.zeros(2, dtype=torch.int32)
+    m = b._calls()
+    assert m.gemm(w, x, None, None) is None and m.gemm_static(w, x, x) is None
+    assert m.gemm(b.Weight(), x, None, None) is None and m.gemm(None, None, None, None) is None
+    assert m.grouped_gemm(w, x, offs, offs, None, None, None) is None
+    with pytest.raises(AssertionError):
+        b.gemm(w, x)
+    with pytest.raises(AssertionError):
+        b.gemm_static(w, x, x)
+    with pytest.raises(AssertionError):
+        b.grouped_gemm(w, x, offs, offs)
