@@ -146,6 +146,15 @@ int ccq_pack_meta(const ccq_weight *w, void *out);
  * in k order, in byte p/2 at s_shift = 4*(p%2), Alg. 3) -> out HOST [scale_bytes]. */
 int ccq_pack_scales4(const ccq_weight *w, const uint8_t *canonical_sq, void *out);
 
+/* The same permutations on the GPU, for E matrices of one shape and format at once: canonical codes and scales
+ * (scale_mode 0: fp16 [N][K/64]; scale_mode 1: the packed fields [N][ceil(narrow groups / 2)], NULL when there are no
+ * narrow-format groups), DEVICE, 16-byte aligned, expert after expert without gaps -> codes_out [E][code_bytes],
+ * scales_out [E][scale_bytes], DEVICE, padding written as zeros: byte for byte what ccq_pack_codes, ccq_pack_scales and
+ * ccq_pack_scales4 give.  Of w's DEVICE pointers only `meta` is read, and only with a group map.  Enqueues on hip_stream
+ * and returns. */
+int ccq_pack_device(const ccq_weight *w, int32_t E, const void *canonical_codes, const void *canonical_scales, void *codes_out,
+                    void *scales_out, void *hip_stream);
+
 /* y[m][n] = sum_k x[m][k] * W_dq[n][k]   (the W2A16 GEMV / GEMM of the
  * "Inference Performance" section; Alg. 2/3 fused into the contraction).
  *   x DEVICE bf16 [M][ldx], y DEVICE bf16 [M][ldy] (round to nearest even),

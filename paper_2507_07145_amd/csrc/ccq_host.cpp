@@ -417,6 +417,20 @@ extern "C" int ccq_pack_meta(const ccq_weight* w, void* out_v) {
 
 static bool aligned16(const void* p) { return (reinterpret_cast<uintptr_t>(p) & 15u) == 0; }
 
+extern "C" int ccq_pack_device(const ccq_weight* w, int32_t E, const void* canonical_codes, const void* canonical_scales, void* codes_out,
+                               void* scales_out, void* hip_stream) {
+  if (!w || !canonical_codes || !codes_out) return CCQ_ERR_NULL;
+  Layout L;
+  int rc = make_layout(w, &L);
+  if (rc != CCQ_OK) return rc;
+  if (E <= 0) return CCQ_ERR_BAD_PARAM;
+  if (L.row_tile_scale_halfs > 0 && (!canonical_scales || !scales_out)) return CCQ_ERR_NULL;
+  if (L.has_map && !w->meta) return CCQ_ERR_NULL;
+  if (!aligned16(canonical_codes) || !aligned16(canonical_scales) || !aligned16(codes_out) || !aligned16(scales_out) || !aligned16(w->meta))
+    return CCQ_ERR_ALIGN;
+  return launch_pack(L, E, canonical_codes, canonical_scales, static_cast<const int32_t*>(w->meta), codes_out, scales_out, hip_stream);
+}
+
 static int check_weight_ptrs(const ccq_weight* w, const Layout& L) {
   if (!w->codes) return CCQ_ERR_NULL;
   if (!w->scales && (L.scale_mode == 0 || L.groups[kNarrow] > 0)) return CCQ_ERR_NULL;

@@ -169,6 +169,9 @@ int64_t gemm_workspace_need(const ccq_weight* w, int32_t M);
 int prefill_block_cols(const Layout& L, int M);  // column-block width launch_prefill uses: 128, 192 or 256
 int launch_prefill(const ccq_weight* w, const Layout& L, const void* x, int M, int64_t ldx, void* y, int64_t ldy, void* stream);
 
+// Canonical order to device order on the GPU (ccq_pack.hip), E experts stacked without gaps on both sides.
+int launch_pack(const Layout& L, int E, const void* codes, const void* scales, const int32_t* meta, void* codes_out, void* scales_out, void* stream);
+
 // The quantizer (ccq_encode.hip): every layout the multiply kernels read, fp16 or compressed group scales.
 int64_t encode_workspace_bytes(const Layout& L);
 int launch_encode(const Layout& L, const float* W, int64_t ldw, void* codes, void* scales, float* alpha, float* beta, void* scale_super,
