@@ -246,7 +246,10 @@ __device__ __forceinline__ void search_groups(const float* wg, uint16_t* cg, dou
     float v[EncTraits<FMT>::WPC];
     unit_weights<FMT>(wg, j, v);
     const uint32_t c = search_unit<FMT>(v, s, inv, zp, tail, j, active, lane);
-    cg[j] = (uint16_t)(active ? c : 0u);   // (two lanes of a ragged last round write the same unit)
+    // (two lanes of a ragged last round write the same unit.)  A vector with a NaN has no nearest code: the exact search
+    // returns all ones, which must not reach past the unit's own bits, where the next code lies
+    constexpr uint32_t kBits = FMT == kEncWide ? 0xFFu : 0xFFFFu;
+    cg[j] = (uint16_t)(active ? c & kBits : 0u);
   }
 }
 

@@ -222,6 +222,56 @@ def test_large_matrix_equals_its_rows(fmt, mode):
                 assert torch.equal(x.reshape(N // 16, -1)[r0 // 16], y.reshape(-1)), f"{name} of rows {r0}.. differ"
 
 
+def _nearest_wide(w: np.ndarray, s: np.ndarray) -> np.ndarray:
+    """Wide-format bytes [R][22] of groups w [R][64] at scales s [R]: the lowest of the codes with the smallest fp64 error."""
+    c = np.arange(256)
+    lv = np.stack([(c >> 4) & 15, (c >> 2) & 15, c & 15], 1).astype(np.float64) - 8.0
+    v = np.concatenate([w.astype(np.float64), np.zeros((w.shape[0], 2))], 1).reshape(-1, 22, 1, 3)
+    d = v - s.reshape(-1, 1, 1, 1) * lv
+    return np.argmin(d[..., 0] ** 2 + d[..., 1] ** 2 + d[..., 2] ** 2, axis=2).astype(np.uint8)
+
+
+@pytest.mark.parametrize("mode", [0, 1])
+def test_a_weight_that_is_not_a_number_stays_in_its_code(mode):
+    """Wide format: a NaN makes its own three-weight code meaningless and nothing else.  The other codes of its group are
+    the nearest ones at the scale of the remaining weights (absmax / 7, as the refit sum is not a number), all other groups
+    are those of the matrix without NaN."""
+    N, K = 16, 704                                          # eleven groups: a ragged last k-tile
+    W = synth.weights_normal(N, K, synth.rng(30, 77))
+    hurt = W.copy()
+    for n, k in ((0, 0), (1, 62), (2, 63), (3, 64 + 5), (3, 128 + 59), (4, 3 * 64 + 30), (5, 10 * 64 + 33), (6, 7 * 64 + 60)):
+        hurt[n, k] = np.nan
+    groups = hurt.reshape(-1, 64)
+    nan = np.isnan(groups)
+    with np.errstate(over="ignore"):
+        codes, scales, _, _ = o.quantize(W, o.F275)
+    codes = codes.reshape(-1, 22).copy()
+    s = o.fp16_bits_to_f64(scales).reshape(-1)
+    s[nan.any(1)] = np.float16(np.nanmax(np.abs(groups), axis=1).astype(np.float64) / 7.0)[nan.any(1)]
+    ssup = None
+    if mode == 1:
+        ssup = np.float16(s.reshape(N, -1).max(1) / 15.0)
+        k = np.clip(np.rint(s.reshape(N, -1) / ssup.astype(np.float64)[:, None]), 1, 15).reshape(-1)
+        codes = _nearest_wide(np.where(nan, 0.0, groups), k * np.repeat(ssup.astype(np.float64), K // 64))
+        codes[:, 21] = (codes[:, 21] & 0xF0) | k.astype(np.uint8)
+    else:
+        codes[nan.any(1)] = _nearest_wide(np.where(nan, 0.0, groups), s)[nan.any(1)]
+    own = np.concatenate([nan, np.zeros((nan.shape[0], 2), bool)], 1).reshape(-1, 22, 3).any(2)   # codes that hold a NaN
+    care = np.where(own, 0, 0xFF).astype(np.uint8)
+    if mode == 1:
+        care[:, 21] |= 0x0F
+    d = b.descriptor(K, N, [b.WIDE], scale_mode=mode)
+    got = b.quantize(torch.from_numpy(hurt).to(DEV), b.WIDE, scale_mode=mode, prefill_byte=0xFF)
+    g_codes = got.codes.cpu().numpy().reshape(-1)
+    bad = np.flatnonzero((g_codes ^ b.pack_codes(d, codes)) & b.pack_codes(d, care))
+    assert bad.size == 0, f"{bad.size} code bytes differ, first at {bad[:5]}"
+    if mode == 0:
+        want = s.astype(np.float16).view(np.uint16).reshape(N, -1)
+        assert np.array_equal(got.scales.cpu().numpy().view(np.uint16).reshape(-1), b.pack_scales(d, want))
+    else:
+        assert np.array_equal(got.ssup.cpu().numpy().view(np.uint16).reshape(-1), ssup.view(np.uint16))
+
+
 def test_rejections_need_no_kernel():
     lib = b.load()
     assert lib.ccq_quantize_workspace_bytes(b.ctypes.byref(b.descriptor(512 + 32, 16, [b.NARROW]))) == -1            # K not a whole number of groups
