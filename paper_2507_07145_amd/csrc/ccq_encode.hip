@@ -152,18 +152,33 @@ __device__ __forceinline__ uint32_t unit_state(uint32_t c, int i) {
   else return (c >> (i < 3 ? 13 - 2 * i : 12 - 2 * i)) & 7u;
 }
 
-// The lanes of `todo` still want their vector searched exactly: one after the other, by the whole wavefront.
+// The lanes that `want` it have their vector searched exactly, as many at a time as the wavefront has sets of 2^L lanes: one
+// (narrow), four (wide) or eight (either half of the hybrid word).  Weights with many zeros or few distinct values send a
+// large share of their vectors here (half zeros: 14 % of the wide ones, 21 % and 35 % of the halves of the hybrid word).
+// 8192 x 8192 with 9 in 10 weights zero, one vector at a time against sets: wide 1.32 -> 0.68 ms, hybrid word 8.98 ->
+// 1.48 ms (13.4 -> 2.15 ms with compressed scales); half zeros 2.68 -> 1.00 ms and 5.19 -> 1.00 ms.
 template <int L, int NV, int S>
 __device__ __forceinline__ uint32_t search_exact(const float* v, double s, double zp, bool want, uint32_t code, int lane) {
+  constexpr int kSets = 64 >> L;
+  const int set = lane >> L;
   unsigned long long todo = __ballot(want);
   while (todo) {
-    const int src = __builtin_ctzll(todo);
-    todo &= todo - 1;
+    const int rank = __builtin_amdgcn_mbcnt_hi((uint32_t)(todo >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)todo, 0));   // of this lane's vector in todo
+    const bool mine = ((todo >> lane) & 1) && rank < kSets;
+    int src = 0;   // whose vector this lane's set takes (sets left over repeat the last one)
+#pragma unroll
+    for (int k = 0; k < kSets; ++k) {
+      const int next = __builtin_ctzll(todo);
+      if (set >= k) src = next;
+      const unsigned long long rest = todo & (todo - 1);
+      todo = rest || k == kSets - 1 ? rest : todo;
+    }
     double vd[NV];
 #pragma unroll
     for (int i = 0; i < NV; ++i) vd[i] = (double)__shfl(v[i], src);
     const uint32_t c = nearest_code<L, NV, S>(vd, __shfl(s, src), zp, lane);
-    if (lane == src) code = c;
+    const uint32_t answer = (uint32_t)__shfl((int)c, (rank << L) & 63);
+    if (mine) code = answer;
   }
   return code;
 }

@@ -222,6 +222,69 @@ def test_large_matrix_equals_its_rows(fmt, mode):
                 assert torch.equal(x.reshape(N // 16, -1)[r0 // 16], y.reshape(-1)), f"{name} of rows {r0}.. differ"
 
 
+def _sparse(kind: str, N: int, K: int, seed: int = 0) -> torch.Tensor:
+    g = torch.Generator(device=DEV).manual_seed(seed)
+    W = torch.randn(N, K, generator=g, device=DEV) * 0.02
+    if kind == "half zeros":
+        W[torch.rand(N, K, generator=g, device=DEV) < 0.5] = 0.0
+    elif kind == "mostly zeros":
+        W[torch.rand(N, K, generator=g, device=DEV) < 0.9] = 0.0
+    elif kind == "ternary":
+        W = torch.sign(W) * (W.abs() > 0.012) * 0.02
+    return W
+
+
+@pytest.mark.parametrize("mode", [0, 1])
+@pytest.mark.parametrize("kind", ["half zeros", "mostly zeros", "ternary"])
+def test_weights_with_many_ties(kind, mode):
+    """Zeros and repeated values tie on many codes: up to half of the vectors take the exact search, any number of them per
+    wavefront.  Codes and scales against the oracle, every format."""
+    N, K = 33, 832
+    W = _sparse(kind, N, K, 5).cpu().numpy()
+    for name, bf, of in (("narrow", b.NARROW, o.F2), ("wide", b.WIDE, o.F275), ("h16", b.H16, None)):
+        fields = ssup = None
+        if of is None:
+            codes, scales = o.h16_quantize(W)
+            if mode == 1:
+                codes, ssup = o.h16_compress_scales(W, codes, scales)
+        else:
+            codes, scales, alpha, beta = o.quantize(W, of)
+            if mode == 1:
+                codes, fields, ssup = o.compress_scales(W, of, codes, scales, alpha, beta)
+        d = b.descriptor(K, N, bf if of is None else [bf], scale_mode=mode)
+        got = b.quantize(torch.from_numpy(W).to(DEV), bf, scale_mode=mode)
+        assert np.array_equal(got.codes.cpu().numpy().reshape(-1), b.pack_codes(d, codes)), f"{name}: codes differ"
+        if mode == 1:
+            assert np.array_equal(got.ssup.cpu().numpy().view(np.uint16).reshape(-1), ssup), f"{name}: super scales differ"
+        if got.scales is not None:
+            want = b.pack_scales(d, scales) if mode == 0 else b.pack_scales4(d, fields)
+            assert np.array_equal(got.scales.cpu().numpy().view(np.uint16).reshape(-1), want), f"{name}: scales differ"
+
+
+@pytest.mark.parametrize("fmt,limit", [("wide", 2.8), ("h16", 9.0)])
+def test_ties_do_not_cost_a_search_each(fmt, limit):
+    """The exact search takes as many vectors at once as a wavefront holds sets of states: a matrix that sends about a third
+    of its vectors there (9 in 10 zeros) costs a small multiple of a dense one: 1.8 (wide) and 4.5 times (hybrid word); one vector at a time
+    it was 3.9 and 26 times.  The limits lie half way, as ratios."""
+    f = {"wide": b.WIDE, "h16": b.H16}[fmt]
+
+    def best_us(W):
+        b.quantize(W, f)
+        out = []
+        for _ in range(5):
+            t0, t1 = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+            t0.record()
+            b.quantize(W, f)
+            t1.record()
+            torch.cuda.synchronize()
+            out.append(t0.elapsed_time(t1) * 1e3)
+        return min(out)
+
+    dense, sparse = best_us(_sparse("dense", 8192, 4096)), best_us(_sparse("mostly zeros", 8192, 4096))
+    print(f"{fmt}: dense {dense:.0f} us, mostly zeros {sparse:.0f} us")
+    assert sparse < limit * dense
+
+
 def _nearest_wide(w: np.ndarray, s: np.ndarray) -> np.ndarray:
     """Wide-format bytes [R][22] of groups w [R][64] at scales s [R]: the lowest of the codes with the smallest fp64 error."""
     c = np.arange(256)
