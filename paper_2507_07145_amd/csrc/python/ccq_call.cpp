@@ -8,14 +8,18 @@
 // kernel did.
 //
 // Every function returns the output tensor, a negative ccq_status as an int, or None when an argument is not of the plain
-// kind handled here; the Python code then goes through its general path, which checks and reports.
+// kind handled here; the Python code then goes through its general path, which checks and reports.  What PyTorch throws on
+// the way reaches Python as PyTorch's own exception (torch.OutOfMemoryError from an allocation, which a serving loop catches
+// to shrink its batch).
 #include <ATen/ATen.h>
 #include <ATen/hip/EmptyTensor.h>
 #include <Python.h>
 #include <c10/hip/HIPStream.h>
+#include <torch/csrc/Exceptions.h>
 #include <torch/csrc/autograd/python_variable.h>
 
 #include <cstdint>
+#include <optional>
 
 #include "ccq.h"
 
@@ -102,50 +106,44 @@ PyObject* general() { Py_RETURN_NONE; }
 
 // gemm(weight, x, out or None, workspace or None)
 PyObject* call_gemm(PyObject*, PyObject* const* a, Py_ssize_t n) {
+  HANDLE_TH_ERRORS
   if (n != 4 || !entry.gemm) return general();
-  try {
-    const at::Tensor* x = tensor(a[1]);
-    if (!plain_bf16(x)) return general();
-    Descriptor d(a[0]);
-    if (!d.w) return general();
-    const int64_t M = x->size(0);
-    if (M > INT32_MAX) return general();
-    at::Tensor made;
-    const at::Tensor* y = &made;
-    if (a[2] == Py_None) made = new_output(M, d.w->N, x->device());
-    else if (!(y = tensor(a[2])) || y->dim() != 2) return general();
-    Workspace ws;
-    if (a[3] == Py_None) {
-      const int64_t need = entry.gemm_workspace(d.w, (int32_t)M);
-      if (need < 0) return general();
-      ws.make(need, x->device());
-    } else if (!ws.of(a[3])) {
-      return general();
-    }
-    const int rc = entry.gemm(d.w, x->data_ptr(), (int32_t)M, x->stride(0), y->data_ptr(), y->stride(0), ws.ptr, ws.bytes, current_stream());
-    return answer(rc, a[2], std::move(made));
-  } catch (const std::exception& e) {
-    PyErr_SetString(PyExc_RuntimeError, e.what());
-    return nullptr;
+  const at::Tensor* x = tensor(a[1]);
+  if (!plain_bf16(x)) return general();
+  Descriptor d(a[0]);
+  if (!d.w) return general();
+  const int64_t M = x->size(0);
+  if (M > INT32_MAX) return general();
+  at::Tensor made;
+  const at::Tensor* y = &made;
+  if (a[2] == Py_None) made = new_output(M, d.w->N, x->device());
+  else if (!(y = tensor(a[2])) || y->dim() != 2) return general();
+  Workspace ws;
+  if (a[3] == Py_None) {
+    const int64_t need = entry.gemm_workspace(d.w, (int32_t)M);
+    if (need < 0) return general();
+    ws.make(need, x->device());
+  } else if (!ws.of(a[3])) {
+    return general();
   }
+  const int rc = entry.gemm(d.w, x->data_ptr(), (int32_t)M, x->stride(0), y->data_ptr(), y->stride(0), ws.ptr, ws.bytes, current_stream());
+  return answer(rc, a[2], std::move(made));
+  END_HANDLE_TH_ERRORS
 }
 
 // gemm_static(weight, x, out)
 PyObject* call_gemm_static(PyObject*, PyObject* const* a, Py_ssize_t n) {
+  HANDLE_TH_ERRORS
   if (n != 3 || !entry.gemm_static) return general();
-  try {
-    const at::Tensor *x = tensor(a[1]), *y = tensor(a[2]);
-    if (!plain_bf16(x) || !plain_bf16(y)) return general();
-    Descriptor d(a[0]);
-    if (!d.w) return general();
-    const int64_t M = x->size(0);
-    if (M > INT32_MAX || y->size(0) != M || y->size(1) != d.w->N) return general();
-    const int rc = entry.gemm_static(d.w, x->data_ptr(), (int32_t)M, x->stride(0), y->data_ptr(), y->stride(0), current_stream());
-    return answer(rc, a[2], at::Tensor());
-  } catch (const std::exception& e) {
-    PyErr_SetString(PyExc_RuntimeError, e.what());
-    return nullptr;
-  }
+  const at::Tensor *x = tensor(a[1]), *y = tensor(a[2]);
+  if (!plain_bf16(x) || !plain_bf16(y)) return general();
+  Descriptor d(a[0]);
+  if (!d.w) return general();
+  const int64_t M = x->size(0);
+  if (M > INT32_MAX || y->size(0) != M || y->size(1) != d.w->N) return general();
+  const int rc = entry.gemm_static(d.w, x->data_ptr(), (int32_t)M, x->stride(0), y->data_ptr(), y->stride(0), current_stream());
+  return answer(rc, a[2], at::Tensor());
+  END_HANDLE_TH_ERRORS
 }
 
 // Byte stride between the experts of one array of a stacked weight, 0 where there is none.
@@ -163,60 +161,63 @@ bool expert_stride(PyObject* weight, PyObject* name, int64_t* out, bool* there =
   return ok;
 }
 
+// The host copy of the expert offsets: a contiguous array of at least n int32.
+class HostOffsets {
+ public:
+  HostOffsets(PyObject* given, int64_t n) {
+    held_ = PyObject_GetBuffer(given, &view_, PyBUF_CONTIG_RO | PyBUF_FORMAT) == 0;
+    if (!held_) PyErr_Clear();
+    else if (view_.itemsize == 4 && view_.format && view_.format[0] == 'i' && view_.format[1] == 0 && view_.len >= (Py_ssize_t)(4 * n))
+      offsets = static_cast<const int32_t*>(view_.buf);
+  }
+  ~HostOffsets() {
+    if (held_) PyBuffer_Release(&view_);
+  }
+  const int32_t* offsets = nullptr;
+
+ private:
+  Py_buffer view_;
+  bool held_ = false;
+};
+
 // grouped_gemm(weight, x, sorted_rows, expert_offsets, host offsets (a contiguous int32 array) or None, out or None, workspace or None)
 PyObject* call_grouped(PyObject*, PyObject* const* a, Py_ssize_t n) {
+  HANDLE_TH_ERRORS
   if (n != 7 || !entry.grouped) return general();
-  Py_buffer host;
-  bool host_held = false;
-  PyObject* r = nullptr;
-  try {
-    do {
-      const at::Tensor *x = tensor(a[1]), *rows = tensor(a[2]), *offs = tensor(a[3]);
-      if (!plain_bf16(x) || !rows || !offs || rows->scalar_type() != at::kInt || offs->scalar_type() != at::kInt) break;
-      Descriptor d(a[0]);
-      if (!d.w) break;
-      PyObject* e = PyObject_GetAttr(a[0], names.E);
-      const long E = e ? PyLong_AsLong(e) : -1;
-      Py_XDECREF(e);
-      if (E <= 0 || E > INT32_MAX) break;
-      int64_t cs, ss, ab, sup;
-      bool has_alpha;
-      if (!expert_stride(a[0], names.codes, &cs) || !expert_stride(a[0], names.scales, &ss) || !expert_stride(a[0], names.alpha, &ab, &has_alpha) ||
-          !expert_stride(a[0], names.ssup, &sup))
-        break;
-      if (!has_alpha) ab = 2 * sup;   // (the super scales' stride is half of that of the fp32 arrays)
-      const int32_t* offs_host = nullptr;
-      if (a[4] != Py_None) {
-        if (PyObject_GetBuffer(a[4], &host, PyBUF_CONTIG_RO | PyBUF_FORMAT) != 0) break;
-        host_held = true;
-        if (host.itemsize != 4 || !host.format || host.format[0] != 'i' || host.format[1] != 0 || host.len < (Py_ssize_t)(4 * (E + 1))) break;
-        offs_host = static_cast<const int32_t*>(host.buf);
-      }
-      const int64_t P = rows->numel();
-      if (P > INT32_MAX || x->size(0) > INT32_MAX) break;
-      at::Tensor made;
-      const at::Tensor* y = &made;
-      if (a[5] == Py_None) made = new_output(P, d.w->N, x->device());
-      else if (!(y = tensor(a[5])) || y->dim() != 2) break;
-      Workspace ws;
-      if (a[6] == Py_None) ws.make(entry.grouped_workspace(d.w, (int32_t)E, (int32_t)P), x->device());
-      else if (!ws.of(a[6])) break;
-      const int rc = entry.grouped(d.w, (int32_t)E, cs, ss, ab, x->data_ptr(), (int32_t)x->size(0), x->stride(0), static_cast<const int32_t*>(rows->data_ptr()),
-                                   (int32_t)P, static_cast<const int32_t*>(offs->data_ptr()), offs_host, y->data_ptr(), y->stride(0), ws.ptr, ws.bytes,
-                                   current_stream());
-      r = answer(rc, a[5], std::move(made));
-    } while (false);
-  } catch (const std::exception& e) {
-    if (host_held) PyBuffer_Release(&host);
-    PyErr_SetString(PyExc_RuntimeError, e.what());
-    return nullptr;
-  }
-  if (host_held) PyBuffer_Release(&host);
-  if (!r) {
-    PyErr_Clear();
+  const at::Tensor *x = tensor(a[1]), *rows = tensor(a[2]), *offs = tensor(a[3]);
+  if (!plain_bf16(x) || !rows || !offs || rows->scalar_type() != at::kInt || offs->scalar_type() != at::kInt) return general();
+  Descriptor d(a[0]);
+  if (!d.w) return general();
+  PyObject* e = PyObject_GetAttr(a[0], names.E);
+  const long E = e ? PyLong_AsLong(e) : -1;
+  Py_XDECREF(e);
+  if (PyErr_Occurred()) PyErr_Clear();
+  if (E <= 0 || E > INT32_MAX) return general();
+  int64_t cs, ss, ab, sup;
+  bool has_alpha;
+  if (!expert_stride(a[0], names.codes, &cs) || !expert_stride(a[0], names.scales, &ss) || !expert_stride(a[0], names.alpha, &ab, &has_alpha) ||
+      !expert_stride(a[0], names.ssup, &sup))
     return general();
+  if (!has_alpha) ab = 2 * sup;   // (the super scales' stride is half of that of the fp32 arrays)
+  std::optional<HostOffsets> host;
+  if (a[4] != Py_None) {
+    host.emplace(a[4], E + 1);
+    if (!host->offsets) return general();
   }
-  return r;
+  const int64_t P = rows->numel();
+  if (P > INT32_MAX || x->size(0) > INT32_MAX) return general();
+  at::Tensor made;
+  const at::Tensor* y = &made;
+  if (a[5] == Py_None) made = new_output(P, d.w->N, x->device());
+  else if (!(y = tensor(a[5])) || y->dim() != 2) return general();
+  Workspace ws;
+  if (a[6] == Py_None) ws.make(entry.grouped_workspace(d.w, (int32_t)E, (int32_t)P), x->device());
+  else if (!ws.of(a[6])) return general();
+  const int rc = entry.grouped(d.w, (int32_t)E, cs, ss, ab, x->data_ptr(), (int32_t)x->size(0), x->stride(0), static_cast<const int32_t*>(rows->data_ptr()),
+                               (int32_t)P, static_cast<const int32_t*>(offs->data_ptr()), host ? host->offsets : nullptr, y->data_ptr(), y->stride(0), ws.ptr,
+                               ws.bytes, current_stream());
+  return answer(rc, a[5], std::move(made));
+  END_HANDLE_TH_ERRORS
 }
 
 // bind(addresses of ccq_gemm, ccq_gemm_workspace_bytes, ccq_gemm_static, ccq_grouped_gemm, ccq_grouped_workspace_bytes)
