@@ -76,6 +76,19 @@ at::Tensor new_output(int64_t rows, int64_t N, c10::Device device) {
   return y;
 }
 
+// Gives up the interpreter lock, as a foreign call through ctypes and torch.empty do: an allocation can wait for the device,
+// a launch for room in its queue, and other threads run meanwhile.  Nothing of Python is touched inside.
+class Unlocked {
+ public:
+  Unlocked() : state_(PyEval_SaveThread()) {}
+  ~Unlocked() { PyEval_RestoreThread(state_); }
+  Unlocked(const Unlocked&) = delete;
+  Unlocked& operator=(const Unlocked&) = delete;
+
+ private:
+  PyThreadState* state_;
+};
+
 struct Workspace {
   at::Tensor held;
   void* ptr = nullptr;
@@ -108,25 +121,24 @@ PyObject* general() { Py_RETURN_NONE; }
 PyObject* call_gemm(PyObject*, PyObject* const* a, Py_ssize_t n) {
   HANDLE_TH_ERRORS
   if (n != 4 || !entry.gemm) return general();
-  const at::Tensor* x = tensor(a[1]);
-  if (!plain_bf16(x)) return general();
+  const at::Tensor *x = tensor(a[1]), *y = tensor(a[2]);
+  if (!plain_bf16(x) || (a[2] != Py_None && (!y || y->dim() != 2))) return general();
   Descriptor d(a[0]);
   if (!d.w) return general();
   const int64_t M = x->size(0);
   if (M > INT32_MAX) return general();
-  at::Tensor made;
-  const at::Tensor* y = &made;
-  if (a[2] == Py_None) made = new_output(M, d.w->N, x->device());
-  else if (!(y = tensor(a[2])) || y->dim() != 2) return general();
   Workspace ws;
-  if (a[3] == Py_None) {
-    const int64_t need = entry.gemm_workspace(d.w, (int32_t)M);
-    if (need < 0) return general();
+  if (a[3] != Py_None && !ws.of(a[3])) return general();
+  const int64_t need = a[3] == Py_None ? entry.gemm_workspace(d.w, (int32_t)M) : 0;
+  if (need < 0) return general();
+  at::Tensor made;
+  int rc;
+  {
+    Unlocked u;
+    if (!y) y = &(made = new_output(M, d.w->N, x->device()));
     ws.make(need, x->device());
-  } else if (!ws.of(a[3])) {
-    return general();
+    rc = entry.gemm(d.w, x->data_ptr(), (int32_t)M, x->stride(0), y->data_ptr(), y->stride(0), ws.ptr, ws.bytes, current_stream());
   }
-  const int rc = entry.gemm(d.w, x->data_ptr(), (int32_t)M, x->stride(0), y->data_ptr(), y->stride(0), ws.ptr, ws.bytes, current_stream());
   return answer(rc, a[2], std::move(made));
   END_HANDLE_TH_ERRORS
 }
@@ -141,7 +153,11 @@ PyObject* call_gemm_static(PyObject*, PyObject* const* a, Py_ssize_t n) {
   if (!d.w) return general();
   const int64_t M = x->size(0);
   if (M > INT32_MAX || y->size(0) != M || y->size(1) != d.w->N) return general();
-  const int rc = entry.gemm_static(d.w, x->data_ptr(), (int32_t)M, x->stride(0), y->data_ptr(), y->stride(0), current_stream());
+  int rc;
+  {
+    Unlocked u;
+    rc = entry.gemm_static(d.w, x->data_ptr(), (int32_t)M, x->stride(0), y->data_ptr(), y->stride(0), current_stream());
+  }
   return answer(rc, a[2], at::Tensor());
   END_HANDLE_TH_ERRORS
 }
@@ -184,8 +200,9 @@ class HostOffsets {
 PyObject* call_grouped(PyObject*, PyObject* const* a, Py_ssize_t n) {
   HANDLE_TH_ERRORS
   if (n != 7 || !entry.grouped) return general();
-  const at::Tensor *x = tensor(a[1]), *rows = tensor(a[2]), *offs = tensor(a[3]);
+  const at::Tensor *x = tensor(a[1]), *rows = tensor(a[2]), *offs = tensor(a[3]), *y = tensor(a[5]);
   if (!plain_bf16(x) || !rows || !offs || rows->scalar_type() != at::kInt || offs->scalar_type() != at::kInt) return general();
+  if (a[5] != Py_None && (!y || y->dim() != 2)) return general();
   Descriptor d(a[0]);
   if (!d.w) return general();
   PyObject* e = PyObject_GetAttr(a[0], names.E);
@@ -206,16 +223,19 @@ PyObject* call_grouped(PyObject*, PyObject* const* a, Py_ssize_t n) {
   }
   const int64_t P = rows->numel();
   if (P > INT32_MAX || x->size(0) > INT32_MAX) return general();
-  at::Tensor made;
-  const at::Tensor* y = &made;
-  if (a[5] == Py_None) made = new_output(P, d.w->N, x->device());
-  else if (!(y = tensor(a[5])) || y->dim() != 2) return general();
   Workspace ws;
-  if (a[6] == Py_None) ws.make(entry.grouped_workspace(d.w, (int32_t)E, (int32_t)P), x->device());
-  else if (!ws.of(a[6])) return general();
-  const int rc = entry.grouped(d.w, (int32_t)E, cs, ss, ab, x->data_ptr(), (int32_t)x->size(0), x->stride(0), static_cast<const int32_t*>(rows->data_ptr()),
-                               (int32_t)P, static_cast<const int32_t*>(offs->data_ptr()), host ? host->offsets : nullptr, y->data_ptr(), y->stride(0), ws.ptr,
-                               ws.bytes, current_stream());
+  if (a[6] != Py_None && !ws.of(a[6])) return general();
+  const int64_t need = a[6] == Py_None ? entry.grouped_workspace(d.w, (int32_t)E, (int32_t)P) : 0;
+  at::Tensor made;
+  int rc;
+  {
+    Unlocked u;
+    if (!y) y = &(made = new_output(P, d.w->N, x->device()));
+    ws.make(need, x->device());
+    rc = entry.grouped(d.w, (int32_t)E, cs, ss, ab, x->data_ptr(), (int32_t)x->size(0), x->stride(0), static_cast<const int32_t*>(rows->data_ptr()), (int32_t)P,
+                       static_cast<const int32_t*>(offs->data_ptr()), host ? host->offsets : nullptr, y->data_ptr(), y->stride(0), ws.ptr, ws.bytes,
+                       current_stream());
+  }
   return answer(rc, a[5], std::move(made));
   END_HANDLE_TH_ERRORS
 }

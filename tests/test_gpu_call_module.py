@@ -1,4 +1,6 @@
 """The native host path of the multiply calls (_ccq_call.so) behaves as the general Python path does around the launch."""
+import ctypes
+
 import numpy as np
 import pytest
 import torch
@@ -39,3 +41,24 @@ def test_out_of_memory_is_the_allocators_exception():
     finally:
         torch.cuda.set_per_process_memory_fraction(1.0)
     assert b.gemm(w, x[:4]).shape == (4, N)
+
+
+def test_other_threads_run_during_a_call(monkeypatch):
+    """The entry points run without the interpreter lock.  CPython's own PyGILState_Check stands in for them (nothing is
+    launched): it returns 0, which is CCQ_OK, only where the calling thread does not hold the lock."""
+    w, we = _weight(64, 16), _weight(64, 16, experts=2)
+    x = torch.zeros((4, 64), dtype=torch.bfloat16, device=DEV)
+    out = torch.empty((4, 16), dtype=torch.bfloat16, device=DEV)
+    ws = torch.empty(1 << 16, dtype=torch.uint8, device=DEV)
+    rows = torch.zeros(4, dtype=torch.int32, device=DEV)
+    offs_host = np.array([0, 2, 4], dtype=np.int32)
+    offs = torch.from_numpy(offs_host).to(DEV)
+    check = ctypes.cast(ctypes.pythonapi.PyGILState_Check, ctypes.c_void_p).value
+    m = b._calls()
+    monkeypatch.setattr(b, "_call", None)                    # (the next call binds the library's entry points again)
+    m.bind(*[check] * 5)
+    try:
+        got = m.gemm(w, x, out, ws), m.gemm_static(w, x, out), m.grouped_gemm(we, x, rows, offs, offs_host, out, ws)
+    finally:
+        b._calls()
+    assert all(y is out for y in got), got
