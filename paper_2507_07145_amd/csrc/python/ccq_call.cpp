@@ -14,6 +14,8 @@
 #include <ATen/ATen.h>
 #include <ATen/hip/EmptyTensor.h>
 #include <Python.h>
+#include <c10/core/impl/LocalDispatchKeySet.h>
+#include <c10/core/impl/TorchDispatchModeTLS.h>
 #include <c10/hip/HIPStream.h>
 #include <torch/csrc/Exceptions.h>
 #include <torch/csrc/autograd/python_variable.h>
@@ -59,7 +61,12 @@ class Descriptor {
   bool held_ = false;
 };
 
-const at::Tensor* tensor(PyObject* o) { return THPVariable_Check(o) ? &THPVariable_Unpack(o) : nullptr; }
+// (A subclass may have an idea of its own of what its attributes are: the general path asks it.)
+const at::Tensor* tensor(PyObject* o) { return THPVariable_CheckExact(o) ? &THPVariable_Unpack(o) : nullptr; }
+
+// Outputs and workspaces are made past PyTorch's dispatcher.  Where someone looks on there (a TorchDispatchMode, a
+// functorch transform) the general path makes them, through it.
+bool looked_on() { return c10::impl::dispatch_mode_enabled() || c10::impl::tls_is_dispatch_key_included(c10::DispatchKey::FuncTorchDynamicLayerFrontMode); }
 
 bool plain_bf16(const at::Tensor* t) { return t && t->dim() == 2 && t->scalar_type() == at::kBFloat16 && t->is_cuda() && t->stride(1) == 1; }
 
@@ -120,7 +127,7 @@ PyObject* general() { Py_RETURN_NONE; }
 // gemm(weight, x, out or None, workspace or None)
 PyObject* call_gemm(PyObject*, PyObject* const* a, Py_ssize_t n) {
   HANDLE_TH_ERRORS
-  if (n != 4 || !entry.gemm) return general();
+  if (n != 4 || !entry.gemm || looked_on()) return general();
   const at::Tensor *x = tensor(a[1]), *y = tensor(a[2]);
   if (!plain_bf16(x) || (a[2] != Py_None && (!y || y->dim() != 2))) return general();
   Descriptor d(a[0]);
@@ -146,7 +153,7 @@ PyObject* call_gemm(PyObject*, PyObject* const* a, Py_ssize_t n) {
 // gemm_static(weight, x, out)
 PyObject* call_gemm_static(PyObject*, PyObject* const* a, Py_ssize_t n) {
   HANDLE_TH_ERRORS
-  if (n != 3 || !entry.gemm_static) return general();
+  if (n != 3 || !entry.gemm_static || looked_on()) return general();
   const at::Tensor *x = tensor(a[1]), *y = tensor(a[2]);
   if (!plain_bf16(x) || !plain_bf16(y)) return general();
   Descriptor d(a[0]);
@@ -199,7 +206,7 @@ class HostOffsets {
 // grouped_gemm(weight, x, sorted_rows, expert_offsets, host offsets (a contiguous int32 array) or None, out or None, workspace or None)
 PyObject* call_grouped(PyObject*, PyObject* const* a, Py_ssize_t n) {
   HANDLE_TH_ERRORS
-  if (n != 7 || !entry.grouped) return general();
+  if (n != 7 || !entry.grouped || looked_on()) return general();
   const at::Tensor *x = tensor(a[1]), *rows = tensor(a[2]), *offs = tensor(a[3]), *y = tensor(a[5]);
   if (!plain_bf16(x) || !rows || !offs || rows->scalar_type() != at::kInt || offs->scalar_type() != at::kInt) return general();
   if (a[5] != Py_None && (!y || y->dim() != 2)) return general();

@@ -4,6 +4,7 @@ import ctypes
 import numpy as np
 import pytest
 import torch
+from torch.utils._python_dispatch import TorchDispatchMode
 
 from paper_2507_07145_amd import binding as b
 from paper_2507_07145_amd import synth
@@ -62,3 +63,35 @@ def test_other_threads_run_during_a_call(monkeypatch):
     finally:
         b._calls()
     assert all(y is out for y in got), got
+
+
+class _Record(TorchDispatchMode):
+    def __init__(self):
+        super().__init__()
+        self.seen = []
+
+    def __torch_dispatch__(self, func, types, args=(), kwargs=None):
+        self.seen.append(str(func))
+        return func(*args, **(kwargs or {}))
+
+
+def test_a_dispatch_mode_sees_what_is_allocated():
+    """Memory trackers and tensor wrappers work by a TorchDispatchMode: outputs and workspaces come through it; and a tensor
+    subclass is not looked into past its own attributes."""
+    w, we = _weight(1024, 1003), _weight(64, 16, experts=2)
+    x = b.bf16_tensor(synth.activations_bf16(40, 1024, synth.rng(11, 1)), DEV)
+    rows = torch.zeros(4, dtype=torch.int32, device=DEV)
+    offs_host = np.array([0, 2, 4], dtype=np.int32)
+    offs = torch.from_numpy(offs_host).to(DEV)
+    assert b.gemm_workspace_bytes(w.desc, 40) > 0
+    want, want_e = b.gemm(w, x), b.grouped_gemm(we, x[:4, :64], rows, offs, offs_host)
+    with _Record() as r:
+        y = b.gemm(w, x)
+    assert sum(s.startswith("aten.empty") for s in r.seen) == 2, r.seen
+    with _Record() as r:
+        ye = b.grouped_gemm(we, x[:4, :64], rows, offs, offs_host)
+    assert sum(s.startswith("aten.empty") for s in r.seen) >= 1, r.seen
+    assert torch.equal(y, want) and torch.equal(ye, want_e)
+    sub = x.as_subclass(type("Sub", (torch.Tensor,), {}))
+    assert b._calls().gemm(w, sub, None, None) is None
+    assert torch.equal(b.gemm(w, sub), want)
