@@ -667,6 +667,7 @@ extern "C" int ccq_grouped_gemm(const ccq_weight* w0, int32_t E, int64_t codes_s
   c.L = L;
   c.m_tile_hint = grouped_tile_rows(E, P);
   int active = E, most_rows = P;
+  int64_t row_blocks = 0;   // of 64 rows
   if (expert_offsets_host) {
     active = 0;
     most_rows = 0;
@@ -674,6 +675,7 @@ extern "C" int ccq_grouped_gemm(const ccq_weight* w0, int32_t E, int64_t codes_s
       const int rows = expert_offsets_host[e + 1] - expert_offsets_host[e];
       active += rows > 0 ? 1 : 0;
       most_rows = std::max(most_rows, rows);
+      row_blocks += ceil_div(rows, 64);
     }
   }
   if (expert_offsets_host && active < E && active <= kMaxActiveList && E <= 65536) {
@@ -687,8 +689,8 @@ extern "C" int ccq_grouped_gemm(const ccq_weight* w0, int32_t E, int64_t codes_s
     // many rows per expert (a prefill-sized routing): the 64-row kernel, one grid over (row block, column block,
     // expert); on narrow-format weights measured 2.2-2.4 times faster than 64-row passes of the per-row-tile kernel
     // from 33 rows on, slower below
-    rc = launch_mid_grouped(w0, L, E, codes_stride, scales_stride, ab_stride, x, ldx, sorted_rows, P, expert_offsets_dev, most_rows, y, ldy,
-                            hip_stream);
+    rc = launch_mid_grouped(w0, L, E, codes_stride, scales_stride, ab_stride, x, ldx, sorted_rows, P, expert_offsets_dev, most_rows, row_blocks,
+                            y, ldy, hip_stream);
     if (rc != CCQ_ERR_UNSUPPORTED) return rc;
   }
   const int with_rows = expert_offsets_host ? active : std::min(E, P);   // experts that have rows (without the host copy: at most P)

@@ -575,10 +575,11 @@ int launch_mid(const ccq_weight* w, const Layout& L, const void* x, int M, int64
 
 // Grouped GEMM with many rows per expert: the same kernel over
 // (row block of the expert, column block, expert); blocks past an expert's rows return at once.  `most_rows` = the
-// largest row count of an expert (from the host copy of the offsets); K is not cut (no workspace).
+// largest row count of an expert, `row_blocks` = the 64-row blocks that hold rows, over all experts (from the host copy
+// of the offsets); K is not cut (no workspace).
 int launch_mid_grouped(const ccq_weight* w0, const Layout& L, int E, int64_t codes_stride, int64_t scales_stride, int64_t ab_stride, const void* x,
-                       int64_t ldx, const int32_t* sorted_rows, int P, const int32_t* expert_offsets, int most_rows, void* y, int64_t ldy,
-                       void* stream) {
+                       int64_t ldx, const int32_t* sorted_rows, int P, const int32_t* expert_offsets, int most_rows, int64_t row_blocks, void* y,
+                       int64_t ldy, void* stream) {
   if (E < 1 || E > 65535 || most_rows < 1) return CCQ_ERR_UNSUPPORTED;
   MidArgs a;
   a.codes = static_cast<const uint8_t*>(w0->codes);
@@ -613,9 +614,7 @@ int launch_mid_grouped(const ccq_weight* w0, const Layout& L, int E, int64_t cod
   a.ab_stride = ab_stride;
   const int n_blocks = (L.N + kMidBN - 1) / kMidBN;
   dim3 grid((unsigned)(a.m_blocks * n_blocks), 1u, (unsigned)E);
-  // at least the rows' share of the blocks have rows
-  const int64_t busy = (int64_t)n_blocks * ((P + bm - 1) / bm);
-  return mid_launch(L, a, true, bm, 1, grid, busy, stream);
+  return mid_launch(L, a, true, bm, 1, grid, n_blocks * row_blocks, stream);
 }
 
 }  // namespace ccq
