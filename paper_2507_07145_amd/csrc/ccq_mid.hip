@@ -95,8 +95,11 @@ __device__ __forceinline__ uint32_t dword_sel(const u32x4& v, int j) { return j 
 // 272 -> 246 us; mix 8192 x 28672, M = 128, 107 -> 97 us; hybrid word 7232 x 5001, M = 777, 204 -> 185 us.
 // WK: K shares inside the workgroup (two: another four wavefronts with an activation tile of their own take every block's
 // second share, and the sums meet in LDS).
+// Two wavefronts per SIMD, neither more nor less: told "at least two", the compiler kept the narrow instance with fp16
+// scales to 108 registers for the sake of four, and each MFMA then waited for an LDS read of its own (8192 x 8192, M = 128,
+// 42.7 us; 36.8 us with the reads of a step in flight together, 225 registers).  Few calls have more than two to give.
 template <int FM, int SM, bool GROUPED, int BM, int WK>
-__global__ void __launch_bounds__(256 * WK, FM == 1 && SM == 0 && BM == 64 ? 3 : 2) ccq_mid_kernel(const MidArgs a) {
+__global__ void __launch_bounds__(256 * WK) __attribute__((amdgpu_waves_per_eu(2, 2))) ccq_mid_kernel(const MidArgs a) {
   constexpr bool HAS_N = FM == 1 || FM == 3, HAS_W = FM >= 2, META = FM == 3, H16 = FM == 4;
   constexpr int ROW = H16 ? kMidRowH16 : kMidRow;
   constexpr int MT = BM / 32;          // 32-row accumulator tiles, and 16-byte activation chunks per thread and step (chunk i: rows of tile i)

@@ -63,3 +63,11 @@ def test_uneven_experts():
     rows each (192 blocks); taken for 168 blocks they ran two shares to a workgroup and in two rounds, 47 us."""
     w = _weight("wide", 2048, 1536, experts=16)
     assert _ratio(_grouped(w, [600] + [17] * 15), _grouped(w, [64] * 16)) < 1.9
+
+
+def test_scale_modes_alike():
+    """Narrow format, 128 rows: the two scale modes do the same work.  37 us each; with the compiler after four wavefronts
+    per SIMD, the one with fp16 scales waited for every LDS read by itself: 43 against 37 us."""
+    K = N = 8192
+    f, g = (_dense(_weight("narrow", K, N, mode), 128) for mode in (0, 1))
+    assert _ratio(f, g) < 1.08
