@@ -94,7 +94,8 @@ __device__ __forceinline__ uint32_t dword_sel(const u32x4& v, int j) { return j 
 // weights passed through LDS by eight wavefronts: wide 8192 x 28672, M = 64, 60.8 -> 56.4 us; 4096 x 11008, M = 2048,
 // 272 -> 246 us; mix 8192 x 28672, M = 128, 107 -> 97 us; hybrid word 7232 x 5001, M = 777, 204 -> 185 us.
 // WK: K shares inside the workgroup (two: another four wavefronts with an activation tile of their own take every block's
-// second share, and the sums meet in LDS).
+// second share, and the sums meet in LDS: shares s and S + s, so that a long one meets a short one; wide 11008 x 1000,
+// M = 64, 20.2 -> 17.9 us against shares 2 s and 2 s + 1).
 // Two wavefronts per SIMD, neither more nor less: told "at least two", the compiler kept the narrow instance with fp16
 // scales to 108 registers for the sake of four, and each MFMA then waited for an LDS read of its own (8192 x 8192, M = 128,
 // 42.7 us; 36.8 us with the reads of a step in flight together, 225 registers).  Few calls have more than two to give.
@@ -133,7 +134,7 @@ __global__ void __launch_bounds__(256 * WK) __attribute__((amdgpu_waves_per_eu(2
   const int ti = (lane >> 4) & 1, h = lane >> 5;  // the column this lane multiplies: row tile ti of the wavefront, row nl; k half h
 
   // this share's k-tiles of each kind, and its steps (one 64-weight group each): narrow first, then wide
-  const int share = split * WK + wk;
+  const int share = split + wk * gridDim.y;   // the longer shares come first: a workgroup of two has at most one of them
   int tA[2], tB[2];
 #pragma unroll
   for (int k = 0; k < 2; ++k) {
@@ -449,7 +450,7 @@ __global__ void __launch_bounds__(256 * WK) __attribute__((amdgpu_waves_per_eu(2
 
   if constexpr (WK == 2) {
     // the shorter share keeps up with the other one's barriers, then hands its sums over (or takes them)
-    const int other = share ^ 1;
+    const int other = split + (1 - wk) * gridDim.y;
     const int steps_other = (HAS_N ? (a.sq[kNarrow] + (other < a.sr[kNarrow] ? 1 : 0)) * kNarrowGroupsPerTile : 0) +
                             (HAS_W ? (a.sq[kWide] + (other < a.sr[kWide] ? 1 : 0)) * kWideGroupsPerTile : 0);
     for (int i = nsteps; i < steps_other; ++i) lds_barrier();
