@@ -561,10 +561,15 @@ int launch_mid(const ccq_weight* w, const Layout& L, const void* x, int M, int64
   a.g_last = L.G - 1;
   a.n_last = L.N - 1;
   a.row_tiles = L.row_tiles;
-  // 128-row blocks where K is not cut and they still give 13 of 16 CUs a workgroup: N = 28000, M = 96 (219 blocks of 256
-  // CUs) 77.7 -> 65.8 us, N = 28672, M = 100 (224) 91.2 -> 87.9 us; N = 24576, M = 128 (192) 45.8 -> 48.7 us
+  // 128-row blocks where K is not cut, they still give 13 of 16 CUs a workgroup (N = 28000, M = 96, 219 blocks of 256 CUs:
+  // 77.7 -> 65.8 us; N = 24576, M = 128, 192 blocks: 45.8 -> 48.7 us), and they need fewer rounds of workgroups over the
+  // chip than 64-row ones, as each lasts about half as long again (narrow 7168 x 18432: M = 200, two rounds against three,
+  // 109 us either way; M = 160, two against two, 105 against 78 us; 1024 x 20000, M = 300, two against four, 25 against 30 us)
+  const int64_t cus = device_cus();
   const int n_blocks = (L.N + kMidBN - 1) / kMidBN;
-  const int bm = mid_has_wide_block(L) && S == 1 && (int64_t)((M + 2 * kMidBM - 1) / (2 * kMidBM)) * n_blocks * 16 >= (int64_t)13 * device_cus() ? 2 * kMidBM : kMidBM;
+  const int64_t wg64 = (int64_t)((M + kMidBM - 1) / kMidBM) * n_blocks, wg128 = (int64_t)((M + 2 * kMidBM - 1) / (2 * kMidBM)) * n_blocks;
+  const bool fewer_rounds = (wg128 + cus - 1) / cus < (wg64 + cus - 1) / cus;
+  const int bm = mid_has_wide_block(L) && S == 1 && wg128 * 16 >= 13 * cus && fewer_rounds ? 2 * kMidBM : kMidBM;
   a.m_blocks = (M + bm - 1) / bm;
   a.tiles[0] = L.tiles[0];
   a.tiles[1] = L.tiles[1];

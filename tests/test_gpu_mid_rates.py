@@ -77,3 +77,10 @@ def test_uneven_shares():
     """22 k-tiles of the wide format in sixteen shares, two to a workgroup: a workgroup has two or three of them.  17.9 us
     against 14.7 us for 16 k-tiles; with the long shares side by side, four in a workgroup, 19.9 against 15.2 us."""
     assert _ratio(_dense(_weight("wide", 11008, 1000), 64), _dense(_weight("wide", 8192, 1000), 64)) < 1.26
+
+
+def test_a_few_rows_more_than_a_block():
+    """Narrow format, 160 rows against 128 at 144 column blocks: both are two rounds of 64-row blocks (81 and 76 us).  As
+    128-row blocks, also two rounds, the 160 rows took 106 us."""
+    w = _weight("narrow", 7168, 18432)
+    assert _ratio(_dense(w, 160), _dense(w, 128)) < 1.2
