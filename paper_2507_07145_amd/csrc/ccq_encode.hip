@@ -201,7 +201,7 @@ __device__ __forceinline__ uint32_t search_unit(const float (&v)[EncTraits<FMT>:
   } else {
     // a (3,3,2) code on the first three weights and a (3,4,2) code on the other four; their bits do not overlap
     const float ta[3] = {t[0], t[1], t[2]}, tb[4] = {t[3], t[4], t[5], t[6]};
-    const bool last = j == EncTraits<kEncH16>::CPG - 1 && tail.decided;
+    const bool last = j == EncTraits<kEncH16>::CPG - 1 && tail.decided && s == s;
     FastCode fa = fast_small<3, 3, 2>(ta, zpf), fb = fast_small<3, 4, 2>(tb, zpf);
     if (last) {
       fa = fast_first<3, 3, 2>(ta[0], zpf, tail.cost, tail.rest);
@@ -327,7 +327,7 @@ __global__ void __launch_bounds__(64 * LPG) ccq_encode_groups_kernel(const EncAr
   const bool there = n < a.N && p < a.GK;
   const float* wg = wl + gl * kEncRow;
   uint16_t* cg = cl + gl * CS;
-  float amax = 0.f;
+  float amax = __builtin_nanf("");   // stays one in a group of nothing else, which then has codes of all ones and the smallest scale
   for (int c4 = sub; c4 < 16; c4 += LPG) {
     const float4 w = *reinterpret_cast<const float4*>(wg + 4 * c4);
     amax = fmaxf(fmaxf(amax, fmaxf(fabsf(w.x), fabsf(w.y))), fmaxf(fabsf(w.z), fabsf(w.w)));

@@ -345,3 +345,36 @@ def test_rejections_need_no_kernel():
     d1 = b.descriptor(512, 16, [b.NARROW], scale_mode=1)
     assert lib.ccq_quantize_workspace_bytes(b.ctypes.byref(d1)) == (16 * 8 * 16 + 16 * 8) * 2 + 16 * 8 * 2 + 16 * 8
     assert lib.ccq_quantize(b.ctypes.byref(d), None, 512, None, None, None, None, None, None, 0, None) == -1
+
+@pytest.mark.parametrize("fmt", ["narrow", "wide", "h16"])
+def test_a_group_without_numbers(fmt):
+    """64 NaN are not 64 zeros: every whole code of the group is all ones (no code is nearest) and its scale the smallest normal
+    fp16 number, which a damaged checkpoint can be told by; in the narrow format the row's largest code is all ones too.
+    The other groups are those of the matrix with a copy of its neighbour in the group's place."""
+    N, K = 16, 704
+    W = synth.weights_normal(N, K, synth.rng(30, 78))
+    W[3, 64:128] = W[3, 128:192]
+    hurt = W.copy()
+    hurt[3, 64:128] = np.nan
+    if fmt == "h16":
+        codes, scales = o.h16_quantize(W)
+    else:
+        codes, scales, alpha, beta = o.quantize(W, o.F2 if fmt == "narrow" else o.F275)
+    codes, scales = codes.copy().reshape(N, K // 64, -1), scales.copy().reshape(N, -1)
+    codes[3, 1], scales[3, 1] = 0xFF, 0x0400
+    care = np.full_like(codes, 0xFF)
+    bf = {"narrow": b.NARROW, "wide": b.WIDE, "h16": b.H16}[fmt]
+    got = b.quantize(torch.from_numpy(hurt).to(DEV), bf)
+    g_scales = got.scales.cpu().numpy().view(np.uint16).reshape(-1)
+    d = b.descriptor(K, N, bf if fmt == "h16" else [bf])
+    want_scales = b.pack_scales(d, scales)
+    if fmt == "narrow":
+        care[3, :1] = care[3, 2:] = 0        # searched over the codes of another map
+        assert float(got.beta.reshape(-1)[3]) == float(beta[3]) and float(got.alpha.reshape(-1)[3]) == np.float32((65535.0 - float(beta[3])) / 255.0)
+        keep = b.pack_scales(d, np.where((np.arange(N) == 3)[:, None] & (np.arange(K // 64) != 1)[None], 0, 0xFFFF).astype(np.uint16))
+        assert np.array_equal(g_scales & keep, want_scales & keep)
+    else:
+        care[3, 1, -1 if fmt == "wide" else -2:] = 0   # the last code is padded with zeros, which are numbers
+        assert np.array_equal(g_scales, want_scales)
+    bad = np.flatnonzero((got.codes.cpu().numpy().reshape(-1) ^ b.pack_codes(d, codes)) & b.pack_codes(d, care))
+    assert bad.size == 0, f"{bad.size} code bytes differ, first at {bad[:5]}"
