@@ -258,13 +258,14 @@ __device__ __forceinline__ void search_groups(const float* wg, uint16_t* cg, dou
 #pragma unroll 1
   for (int j0 = 0; j0 < CPG; j0 += LPG) {
     const int j = min(j0 + sub, CPG - 1);
+    const bool mine = j0 + sub < CPG;   // (a ragged last round leaves lanes without a unit)
     float v[EncTraits<FMT>::WPC];
     unit_weights<FMT>(wg, j, v);
-    const uint32_t c = search_unit<FMT>(v, s, inv, zp, tail, j, active, lane);
-    // (two lanes of a ragged last round write the same unit.)  A vector with a NaN has no nearest code: the exact search
-    // returns all ones, which must not reach past the unit's own bits, where the next code lies
+    const uint32_t c = search_unit<FMT>(v, s, inv, zp, tail, j, active && mine, lane);
+    // A vector with a NaN has no nearest code: the exact search returns all ones, which must not reach past the unit's own
+    // bits, where the next code lies
     constexpr uint32_t kBits = FMT == kEncWide ? 0xFFu : 0xFFFFu;
-    cg[j] = (uint16_t)(active ? c & kBits : 0u);
+    if (mine) cg[j] = (uint16_t)(active ? c & kBits : 0u);
   }
 }
 
@@ -310,6 +311,26 @@ __device__ __forceinline__ void store_units(const EncArgs& a, int rt, int quad, 
   }
 }
 
+// Eq. 4: S = sum(W Wq) / sum(Wq^2), s0 where that is no better, rounded to the scale that is stored.  A fp32 number times a
+// level (at most 8 bits) is exact in fp64, so the fused multiply-add rounds once, as the separate multiply and add do.
+template <int FMT>
+__device__ __forceinline__ double refit_scale(const float* wg, const uint16_t* cg, double s0, double zp) {
+  double num = 0.0, den = 0.0;
+  for_weights<FMT>(wg, cg, zp, [&](double w, double wq) {
+    num = __builtin_fma(w, wq, num);
+    den = __builtin_fma(wq, wq, den);
+  });
+  double s1 = den > 0.0 ? num / den : s0;
+  double e1 = 0.0, e0 = 0.0;
+  for_weights<FMT>(wg, cg, zp, [&](double w, double wq) {
+    const double d1 = w - wq * s1, d0 = w - wq * s0;
+    e1 += d1 * d1;
+    e0 += d0 * d0;
+  });
+  if (!(s1 > 0.0) || e1 > e0) s1 = s0;
+  return fp16_scale(s1);
+}
+
 // First pass, LPG lanes per (row, group): scale = absmax / (2^(L-1) - 1), search, Eq. 4 refit (kept when the error does
 // not grow), fp16 rounding, search again with the stored scale.  An all-zero group gets scale 0 and codes 0.  Without
 // Code Cluster this is the final result and is written in device order; with it only the scales and the range of the
@@ -319,6 +340,7 @@ __global__ void __launch_bounds__(64 * LPG) ccq_encode_groups_kernel(const EncAr
   constexpr int CS = kEncUnitRow<FMT>;
   __shared__ __attribute__((aligned(16))) float wl[64 * kEncRow];
   __shared__ uint16_t cl[64 * CS];
+  __shared__ double sl[LPG > 4 ? 64 : 1];
   const int tid = threadIdx.x, lane = tid & 63, rt = blockIdx.x / a.quads, quad = blockIdx.x % a.quads;
   load_groups<64 * LPG>(a, rt, quad, wl, tid);
   __syncthreads();
@@ -337,27 +359,22 @@ __global__ void __launch_bounds__(64 * LPG) ccq_encode_groups_kernel(const EncAr
   const bool live = amax != 0.f;
   const double s0 = (double)amax / (double)EncTraits<FMT>::QMAX;
   search_groups<FMT, LPG>(wg, cg, s0, a.zp, a.tail, live, sub, lane);
-  __syncthreads();
-  double s = 0.0;
-  if (live) {
-    // Eq. 4: S = sum(W Wq) / sum(Wq^2).  A fp32 number times a level (at most 8 bits) is exact in fp64, so the fused
-    // multiply-add rounds once, as the separate multiply and add do.
-    double num = 0.0, den = 0.0;
-    for_weights<FMT>(wg, cg, a.zp, [&](double w, double wq) {
-      num = __builtin_fma(w, wq, num);
-      den = __builtin_fma(wq, wq, den);
-    });
-    double s1 = den > 0.0 ? num / den : s0;
-    double e1 = 0.0, e0 = 0.0;
-    for_weights<FMT>(wg, cg, a.zp, [&](double w, double wq) {
-      const double d1 = w - wq * s1, d0 = w - wq * s0;
-      e1 += d1 * d1;
-      e0 += d0 * d0;
-    });
-    if (!(s1 > 0.0) || e1 > e0) s1 = s0;
-    s = fp16_scale(s1);
+  if constexpr (LPG > 4) {
+    if (sub == 0) sl[gl] = s0;
   }
   __syncthreads();
+  double s = 0.0;
+  if constexpr (LPG <= 4) {   // every lane of a group runs its sums
+    if (live) s = refit_scale<FMT>(wg, cg, s0, a.zp);
+    __syncthreads();
+  } else {                    // one lane per group, all in the first wavefront: sixteen copies would share the CU's fp64 units
+    if (tid < 64) {
+      const double st = sl[tid];
+      if (st != 0.0) sl[tid] = refit_scale<FMT>(wl + tid * kEncRow, cl + tid * CS, st, a.zp);
+    }
+    __syncthreads();
+    s = sl[gl];
+  }
   search_groups<FMT, LPG>(wg, cg, s, a.zp, a.tail, live, sub, lane);
   if constexpr (FMT == kEncNarrow) {
     if (there && sub == 0) a.rowscale[(int64_t)n * a.GK + p] = fp16_bits(s);
@@ -568,25 +585,26 @@ __device__ __forceinline__ uint32_t search_cluster(const RowMap& m, const float4
 // A workgroup of the passes over the row's map takes four rows x sixteen groups (four narrow k-tiles): a wavefront keeps
 // one row's map and walks its groups four at a time, one vector per lane.  Building the map costs about half of what 64
 // vectors cost to search: with one k-tile of four rows per wavefront instead the pass took 500 us at 8192 x 8192.
-constexpr int kEncTilesPerBlock = 4;
 struct ClusterBlock {
   int row, n, rt, tile0;   // this wavefront's row of the workgroup, of the matrix; row tile; first k-tile
 };
+template <int TILES>
 __device__ __forceinline__ ClusterBlock cluster_block(const EncArgs& a) {
-  const int per_row = (a.quads + kEncTilesPerBlock - 1) / kEncTilesPerBlock, rq = blockIdx.x / per_row;
+  const int per_row = (a.quads + TILES - 1) / TILES, rq = blockIdx.x / per_row;
   ClusterBlock b;
   b.row = threadIdx.x >> 6;
   b.n = rq * 4 + b.row;
   b.rt = rq >> 2;
-  b.tile0 = (blockIdx.x % per_row) * kEncTilesPerBlock;
+  b.tile0 = (blockIdx.x % per_row) * TILES;
   return b;
 }
 
 // The workgroup's bytes, [k-tile][row][group][16] in LDS, to device order: byte 4 kq + b of group j of a k-tile at
 // (kq * 16 + row) * 16 + 4 j + b.  One 16-byte store per thread of a wavefront: (k-tile, kq, row).
+template <int TILES>
 __device__ __forceinline__ void store_bytes(const EncArgs& a, const ClusterBlock& b, const uint32_t* ql, int lane) {
   const int t = lane >> 4, kq = (lane >> 2) & 3, row = lane & 3, n = b.n - b.row + row;
-  if (n >= a.N || b.tile0 + t >= a.quads) return;
+  if (t >= TILES || n >= a.N || b.tile0 + t >= a.quads) return;
   const uint32_t* src = ql + (t * 4 + row) * 16 + kq;
   *reinterpret_cast<uint4*>(a.codes + (int64_t)b.rt * a.row_tile_bytes + a.kind_code_off + (int64_t)(b.tile0 + t) * kNarrowTileBytes + (kq * 16 + (n & 15)) * 16) =
       uint4{src[0], src[4], src[8], src[12]};
@@ -595,16 +613,17 @@ __device__ __forceinline__ void store_bytes(const EncArgs& a, const ClusterBlock
 // Third pass (narrow format): every vector is searched again over the 256 codes round(q alpha + beta) the row's map can
 // reach (never worse than rounding the unconstrained code by Eq. 1, which is one of the candidates), then one more Eq. 4
 // refit with the final codes, kept when the error does not grow; its sums run one group per lane.
+template <int TILES>
 __global__ void __launch_bounds__(256) ccq_encode_finish_narrow_kernel(const EncArgs a) {
-  __shared__ __attribute__((aligned(16))) float wl[64 * kEncRow];
-  __shared__ __attribute__((aligned(16))) uint32_t ql[64 * 4];
+  __shared__ __attribute__((aligned(16))) float wl[16 * TILES * kEncRow];
+  __shared__ __attribute__((aligned(16))) uint32_t ql[16 * TILES * 4];
   const int lane = threadIdx.x & 63, gj = lane >> 4;
-  const ClusterBlock b = cluster_block(a);
+  const ClusterBlock b = cluster_block<TILES>(a);
   if (b.n < a.N) {   // (uniform in the wavefront)
     RowMap m;
     row_map(m, a.alpha[b.n], a.beta[b.n], (float)a.zp, lane);
 #pragma unroll 1
-    for (int t = 0; t < kEncTilesPerBlock; ++t) {
+    for (int t = 0; t < TILES; ++t) {
       const int p = (b.tile0 + t) * 4 + gj, slot = (t * 4 + b.row) * 4 + gj;
       float4 w = {0.f, 0.f, 0.f, 0.f};
       double s = 0.0;
@@ -618,11 +637,11 @@ __global__ void __launch_bounds__(256) ccq_encode_finish_narrow_kernel(const Enc
     }
   }
   __syncthreads();
-  if (b.row == 3) store_bytes(a, b, ql, lane);
+  if (b.row == 3) store_bytes<TILES>(a, b, ql, lane);
   if (b.row != 0) return;
   // lane = slot: k-tile lane / 16, row (lane / 4) % 4, group lane % 4
   const int n = b.n + ((lane >> 2) & 3), tile = b.tile0 + (lane >> 4), p = tile * 4 + (lane & 3);
-  if (n >= a.N || p >= a.GK) return;
+  if (lane >= 16 * TILES || n >= a.N || p >= a.GK) return;
   const float al = a.alpha[n], bem = a.beta[n] + 0x1p23f;
   double s = fp16_value(a.rowscale[(int64_t)n * a.GK + p]);
   auto for_all = [&](auto f) {
@@ -725,15 +744,16 @@ __global__ void __launch_bounds__(64 * LPG) ccq_encode_compress_kernel(const Enc
 
 // Narrow format: over the 256 codes of the row's map; the four fields of a k-tile's groups go into one 16-bit word per
 // row (group j in bits 4j..4j+3; groups that pad the last k-tile keep field 0: scale 0).
+template <int TILES>
 __global__ void __launch_bounds__(256) ccq_encode_compress_narrow_kernel(const EncArgs a) {
-  __shared__ __attribute__((aligned(16))) uint32_t ql[64 * 4];
+  __shared__ __attribute__((aligned(16))) uint32_t ql[16 * TILES * 4];
   const int lane = threadIdx.x & 63, gj = lane >> 4;
-  const ClusterBlock b = cluster_block(a);
+  const ClusterBlock b = cluster_block<TILES>(a);
   if (b.n < a.N) {   // (uniform in the wavefront)
     RowMap m;
     row_map(m, a.alpha[b.n], a.beta[b.n], (float)a.zp, lane);
 #pragma unroll 1
-    for (int t = 0; t < kEncTilesPerBlock; ++t) {
+    for (int t = 0; t < TILES; ++t) {
       const int tile = b.tile0 + t, p = tile * 4 + gj;
       float4 w = {0.f, 0.f, 0.f, 0.f};
       double se = 0.0;
@@ -753,7 +773,7 @@ __global__ void __launch_bounds__(256) ccq_encode_compress_narrow_kernel(const E
     }
   }
   __syncthreads();
-  if (b.row == 3) store_bytes(a, b, ql, lane);
+  if (b.row == 3) store_bytes<TILES>(a, b, ql, lane);
 }
 
 // Clears `n16` 16-byte units (a kernel, not a memset node: the call may be recorded into a graph).
@@ -812,13 +832,27 @@ static H16Tail h16_tail(double zp) {
   return t;
 }
 
-// Lanes per group: one lane per group does the fewest instructions (the sums of Eq. 4 are run by every lane of a group),
-// four give a small matrix four times the wavefronts.
+// A matrix whose groups, 64 to a workgroup, are at most one workgroup per CU: there the time is one wavefront's, and sixteen
+// lanes per group, or one narrow k-tile of the map's passes, leave it a quarter of the vectors.  Against four lanes and
+// k-tiles: 256 x 4096 (256 workgroups) half zeros 400 -> 205 us (narrow), 84 -> 59 us (wide), dense 76 -> 69 and 46 -> 44 us;
+// 512 x 4096 dense 6 to 17 % slower.
+static bool few_blocks(int64_t blocks) { return blocks <= (int64_t)device_cus(); }
+
+// Lanes per group: few of them do the fewest instructions (the sums of Eq. 4 are run by every lane of a group), many give
+// a small matrix more wavefronts, each with fewer vectors that it searches exactly one after the other.
 template <int FMT>
 static void launch_groups(const EncArgs& a, int64_t blocks, hipStream_t st) {
   const dim3 grid((unsigned)blocks);
   if (blocks >= 16 * (int64_t)device_cus()) hipLaunchKernelGGL((ccq_encode_groups_kernel<FMT, 2>), grid, dim3(128), 0, st, a);
-  else hipLaunchKernelGGL((ccq_encode_groups_kernel<FMT, 4>), grid, dim3(256), 0, st, a);
+  else if (!few_blocks(blocks)) hipLaunchKernelGGL((ccq_encode_groups_kernel<FMT, 4>), grid, dim3(256), 0, st, a);
+  else hipLaunchKernelGGL((ccq_encode_groups_kernel<FMT, 16>), grid, dim3(1024), 0, st, a);
+}
+
+template <int FMT>
+static void launch_compress(const EncArgs& a, int64_t blocks, hipStream_t st) {
+  const dim3 grid((unsigned)blocks);
+  if (!few_blocks(blocks)) hipLaunchKernelGGL((ccq_encode_compress_kernel<FMT, 4>), grid, dim3(256), 0, st, a);
+  else hipLaunchKernelGGL((ccq_encode_compress_kernel<FMT, 16>), grid, dim3(1024), 0, st, a);
 }
 
 int launch_encode(const Layout& L, const float* W, int64_t ldw, void* codes, void* scales, float* alpha, float* beta, void* scale_super,
@@ -877,11 +911,13 @@ int launch_encode(const Layout& L, const float* W, int64_t ldw, void* codes, voi
   aw.zp = (double)L.zp[kWide];
   if (L.h16) aw.tail = h16_tail(aw.zp);
   const int64_t blocks_n = (int64_t)L.row_tiles * an.quads, blocks_w = (int64_t)L.row_tiles * aw.quads;
-  const unsigned blocks_m = (unsigned)(((L.N + 3) / 4) * ((an.quads + kEncTilesPerBlock - 1) / kEncTilesPerBlock));
+  const bool few_n = few_blocks(blocks_n);   // of the passes over the row's map: one narrow k-tile per wavefront, or four
+  const unsigned blocks_m = (unsigned)(((L.N + 3) / 4) * (few_n ? an.quads : (an.quads + 3) / 4));
   if (an.GK > 0) {
     launch_groups<kEncNarrow>(an, blocks_n, st);
     hipLaunchKernelGGL(ccq_encode_cluster_kernel, dim3((unsigned)((L.N + 3) / 4)), block, 0, st, an);
-    hipLaunchKernelGGL(ccq_encode_finish_narrow_kernel, dim3(blocks_m), block, 0, st, an);
+    if (few_n) hipLaunchKernelGGL(ccq_encode_finish_narrow_kernel<1>, dim3(blocks_m), block, 0, st, an);
+    else hipLaunchKernelGGL(ccq_encode_finish_narrow_kernel<4>, dim3(blocks_m), block, 0, st, an);
   }
   if (aw.GK > 0) {
     if (L.h16) launch_groups<kEncH16>(aw, blocks_w, st);
@@ -889,10 +925,11 @@ int launch_encode(const Layout& L, const float* W, int64_t ldw, void* codes, voi
   }
   if (L.scale_mode == 1) {
     hipLaunchKernelGGL(ccq_encode_super_kernel, dim3((unsigned)L.N), block, 0, st, a);
-    if (an.GK > 0) hipLaunchKernelGGL(ccq_encode_compress_narrow_kernel, dim3(blocks_m), block, 0, st, an);
+    if (an.GK > 0 && few_n) hipLaunchKernelGGL(ccq_encode_compress_narrow_kernel<1>, dim3(blocks_m), block, 0, st, an);
+    else if (an.GK > 0) hipLaunchKernelGGL(ccq_encode_compress_narrow_kernel<4>, dim3(blocks_m), block, 0, st, an);
     if (aw.GK > 0) {
-      if (L.h16) hipLaunchKernelGGL((ccq_encode_compress_kernel<kEncH16, 4>), dim3((unsigned)blocks_w), block, 0, st, aw);
-      else hipLaunchKernelGGL((ccq_encode_compress_kernel<kEncWide, 4>), dim3((unsigned)blocks_w), block, 0, st, aw);
+      if (L.h16) launch_compress<kEncH16>(aw, blocks_w, st);
+      else launch_compress<kEncWide>(aw, blocks_w, st);
     }
   }
   if (hipGetLastError() != hipSuccess) return CCQ_ERR_HIP;

@@ -201,11 +201,13 @@ def test_full_size_sampled_rows():
 
 @pytest.mark.parametrize("mode", [0, 1])
 @pytest.mark.parametrize("fmt", ["narrow", "wide", "h16"])
-def test_large_matrix_equals_its_rows(fmt, mode):
-    """Rows are independent: a matrix large enough for the two-lanes-per-group search (its workgroups fill the chip many
-    times over) gives the bytes that the four-lanes-per-group search gives for any sixteen of its rows, and those are the
-    oracle's (the tests above).  K = 2240: 35 groups, a ragged last k-tile; outliers, zeros and exact ties among the rows."""
-    N, K = 8192, 2240
+@pytest.mark.parametrize("N", [8192, 4112])
+def test_large_matrix_equals_its_rows(fmt, mode, N):
+    """Rows are independent: a matrix large enough for the search with two lanes per group (its workgroups fill the chip many
+    times over), or with four (more than one workgroup per CU), gives the bytes that the one with sixteen lanes gives for any
+    sixteen of its rows, and those are the oracle's (the tests above).  K = 2240: 35 groups, a ragged last k-tile; outliers,
+    zeros and exact ties among the rows."""
+    K = 2240
     g = torch.Generator(device=DEV).manual_seed(31)
     W = torch.randn(N, K, generator=g, device=DEV) * 0.02
     W[5] = torch.round(W[5] * 256) / 256
@@ -261,6 +263,19 @@ def test_weights_with_many_ties(kind, mode):
             assert np.array_equal(got.scales.cpu().numpy().view(np.uint16).reshape(-1), want), f"{name}: scales differ"
 
 
+def _best_us(W, f):
+    b.quantize(W, f)
+    out = []
+    for _ in range(5):
+        t0, t1 = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+        t0.record()
+        b.quantize(W, f)
+        t1.record()
+        torch.cuda.synchronize()
+        out.append(t0.elapsed_time(t1) * 1e3)
+    return min(out)
+
+
 @pytest.mark.parametrize("fmt,limit", [("wide", 2.8), ("h16", 9.0)])
 def test_ties_do_not_cost_a_search_each(fmt, limit):
     """The exact search takes as many vectors at once as a wavefront holds sets of states: a matrix that sends about a third
@@ -268,20 +283,18 @@ def test_ties_do_not_cost_a_search_each(fmt, limit):
     it was 3.9 and 26 times.  The limits lie half way, as ratios."""
     f = {"wide": b.WIDE, "h16": b.H16}[fmt]
 
-    def best_us(W):
-        b.quantize(W, f)
-        out = []
-        for _ in range(5):
-            t0, t1 = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
-            t0.record()
-            b.quantize(W, f)
-            t1.record()
-            torch.cuda.synchronize()
-            out.append(t0.elapsed_time(t1) * 1e3)
-        return min(out)
-
-    dense, sparse = best_us(_sparse("dense", 8192, 4096)), best_us(_sparse("mostly zeros", 8192, 4096))
+    dense, sparse = _best_us(_sparse("dense", 8192, 4096), f), _best_us(_sparse("mostly zeros", 8192, 4096), f)
     print(f"{fmt}: dense {dense:.0f} us, mostly zeros {sparse:.0f} us")
+    assert sparse < limit * dense
+
+
+@pytest.mark.parametrize("fmt,limit", [("narrow", 4.0), ("wide", 1.6)])
+def test_ties_in_a_small_matrix(fmt, limit):
+    """Few groups are spread over many wavefronts, each with few vectors to search exactly one after the other.  256 x 4096,
+    half zeros, against the same matrix dense: 3.0 and 1.35 times; with sixteen groups to a wavefront 5.2 and 1.8 times."""
+    f = {"narrow": b.NARROW, "wide": b.WIDE}[fmt]
+    dense, sparse = _best_us(_sparse("dense", 256, 4096), f), _best_us(_sparse("half zeros", 256, 4096), f)
+    print(f"{fmt}: dense {dense:.0f} us, half zeros {sparse:.0f} us: {sparse / dense:.2f}")
     assert sparse < limit * dense
 
 
