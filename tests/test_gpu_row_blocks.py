@@ -9,6 +9,7 @@ from cases import assert_gemm_close, canon_zero, grouped_rounded_weight_sigma, r
 from oracle import ccq_oracle as o
 from paper_2507_07145_amd import binding as b
 from paper_2507_07145_amd import synth
+from test_gpu_compressed_scales import _case as compressed_case
 
 pytestmark = pytest.mark.gpu
 DEV = "cuda:0"
@@ -43,18 +44,26 @@ def test_row_tile_edges(kinds, K, N, n_wide, counts):
             assert_gemm_close(got, ref, f"{kinds} {counts}", rounded=grouped_rounded_weight_sigma(x, rows, offs, lambda e: cases[e].W()))
 
 
+@pytest.mark.parametrize("mode", [0, 1])
 @pytest.mark.parametrize("M", [65, 97, 128])
-def test_dense_128_row_blocks(M):
+def test_dense_128_row_blocks(M, mode):
     """Enough columns (209 blocks of 128, the last one ragged) for the dense product to take 128-row blocks."""
-    case = random_case(320, 26700, ["narrow"], 24)
-    x = synth.activations_bf16(M, 320, synth.rng(24, M))
-    y = b.gemm(case.device_weight(DEV), b.bf16_tensor(x, DEV))
-    assert_gemm_close(b.bf16_bits(y), o.matmul(x, case.W()), f"M={M}", rounded=(x, case.W()))
+    K, N = 320, 26700
+    if mode == 0:
+        case = random_case(K, N, ["narrow"], 24)
+        W, w = case.W(), case.device_weight(DEV)
+    else:
+        W, w = compressed_case(["narrow"], K, N, 24)
+    x = synth.activations_bf16(M, K, synth.rng(24, M))
+    y = b.gemm(w, b.bf16_tensor(x, DEV))
+    assert_gemm_close(b.bf16_bits(y), o.matmul(x, W), f"M={M} mode {mode}", rounded=(x, W))
 
 
-@pytest.mark.parametrize("kinds,G,n_wide", [(["wide"], 25, None), (["wide"], 16, None), (["narrow", "wide"], 40, 17), (["narrow", "wide"], 12, 2)])
+@pytest.mark.parametrize("kinds,G,n_wide", [(["wide"], 25, None), (["wide"], 16, None), (["narrow", "wide"], 40, 17), (["narrow", "wide"], 12, 2),
+                                            (["wide"], 88, None), (["narrow", "wide"], 100, 44)])
 def test_two_shares_in_a_workgroup(kinds, G, n_wide):
-    """Few blocks on wide kinds: shares of unequal length side by side (or one, where a kind has a single k-tile)."""
+    """Few blocks on wide kinds: shares of unequal length side by side (or one, where a kind has a single k-tile); the last two
+    with K cut across the grid too, 11 k-tiles in ten shares, 14 + 6 in six."""
     case = random_case(64 * G, 200, kinds, 25, n_wide=n_wide)
     w = case.device_weight(DEV)
     for M in (17, 64, 70):
