@@ -99,8 +99,10 @@ __device__ __forceinline__ uint32_t dword_sel(const u32x4& v, int j) { return j 
 // Two wavefronts per SIMD, neither more nor less: told "at least two", the compiler kept the narrow instance with fp16
 // scales to 108 registers for the sake of four, and each MFMA then waited for an LDS read of its own (8192 x 8192, M = 128,
 // 42.7 us; 36.8 us with the reads of a step in flight together, 225 registers).  Few calls have more than two to give.
+// The hybrid word is left to the compiler, which takes 179 - 192 registers either way: 7232 x 5001, M = 777, 183.5 us; 188.4 us
+// with the upper bound of two.
 template <int FM, int SM, bool GROUPED, int BM, int WK>
-__global__ void __launch_bounds__(256 * WK) __attribute__((amdgpu_waves_per_eu(2, 2))) ccq_mid_kernel(const MidArgs a) {
+__global__ void __launch_bounds__(256 * WK) __attribute__((amdgpu_waves_per_eu(2, FM == 4 ? 8 : 2))) ccq_mid_kernel(const MidArgs a) {
   constexpr bool HAS_N = FM == 1 || FM == 3, HAS_W = FM >= 2, META = FM == 3, H16 = FM == 4;
   constexpr int ROW = H16 ? kMidRowH16 : kMidRow;
   constexpr int MT = BM / 32;          // 32-row accumulator tiles, and 16-byte activation chunks per thread and step (chunk i: rows of tile i)
