@@ -231,12 +231,17 @@ def _host_tensor(a: np.ndarray) -> torch.Tensor:
 
 # canonical bytes on the device at a time while a stack of experts is permuted there
 _PACK_CHUNK_BYTES = 256 << 20
+# canonical code bytes of a single matrix up to which the host permutes: the GPU's launch, copies and wait cost 7 - 17 us more
+# than they save there (512 x 128 narrow 106 -> 93 us, 64 x 16 98 -> 82 us; 1024 x 512 102 against 115 us).  A stack of experts
+# pays the host's fixed cost per expert (32 of 128 x 32: 300 against 97 us)
+_PACK_HOST_BYTES = 32 << 10
 
 
 def _pack_to_device(w: ccq_weight, info: ccq_info, E: int, codes: np.ndarray, scales: np.ndarray | None, device):
     """Canonical codes [E][bytes] and scales [E][entries] (host) -> device-order tensors on `device`.  On a GPU the canonical
     bytes are uploaded and permuted there (`w.meta` must be set if there is a group map): 4096 x 11008 with the
-    permutation on a host core took 3.3 - 4.0 ms, 0.54 ms this way, nearly all of it the upload."""
+    permutation on a host core took 3.3 - 4.0 ms, 0.54 ms this way, nearly all of it the upload.  Meanwhile the device holds up
+    to _PACK_CHUNK_BYTES of canonical bytes beside the result, or one expert's if those are more."""
     if codes.shape[1] != info.canonical_code_bytes:
         raise ValueError(f"canonical code stream has {codes.shape[1]} bytes, layout needs {info.canonical_code_bytes}")
     n_scales = 0
@@ -245,7 +250,7 @@ def _pack_to_device(w: ccq_weight, info: ccq_info, E: int, codes: np.ndarray, sc
         if scales.shape[1] != n_scales if w.scale_mode == 0 else scales.shape[1] < n_scales:
             raise ValueError("scale array size does not match the layout")
         scales = scales[:, :n_scales]
-    if torch.device(device).type != "cuda":
+    if torch.device(device).type != "cuda" or (E == 1 and codes.nbytes <= _PACK_HOST_BYTES):
         pack = pack_scales if w.scale_mode == 0 else pack_scales4
         pc = np.stack([pack_codes(w, codes[e]) for e in range(E)])
         ps = None if scales is None else np.stack([pack(w, scales[e]) for e in range(E)]).view(np.int16)
