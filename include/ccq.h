@@ -233,7 +233,8 @@ int64_t ccq_grouped_workspace_bytes(const ccq_weight *w0, int32_t E, int32_t P);
  * scale 0.  With scale_mode 1 the scales are then compressed (Sec. 3.4): per output channel s_super =
  * fp16(largest group scale / 15), every group scale becomes the nearest multiple field * s_super with the
  * field in 1..15 (0 for an all-zero group), and every group's codes are searched once more with the scale
- * that is stored.  All decisions are taken in fp64.
+ * that is stored.  Every decision is the one that fp64 arithmetic in a fixed order takes: codes are searched in
+ * fp32 where the result is provably the same, in fp64 otherwise; sums and scales are fp64.
  *   w: shape and format (any the multiply entry points accept: narrow, wide, a per-group mix, the hybrid
  *      word whose two codes are searched independently and whose field is 13 bits; either scale mode).  Of its
  *      DEVICE pointers only `meta` is read, and only for a per-group mix (ccq_pack_meta).

@@ -172,8 +172,10 @@ static DensePath dense_path(const Layout& L, int M) {
     // are compared in units of one output element per round of workgroups over the chip's CUs; the relative costs
     // per element are ratios measured between the kernels, not times: the 256-row kernel costs 1.0 with 192-column
     // blocks and 1.22 with 128 or 256 columns, up to 40 % more when more than half of the CUs are busy (the clock
-    // sinks under a full matrix load); the 64-row kernel, which decodes every weight tile four times as often,
-    // costs 2.4 and about 0.4 of a round in fixed set-up.
+    // sinks under a full matrix load); the 64-row kernel, whose blocks of 64 (or 128) rows decode every weight tile four
+    // (or two) times as often, costs 2.4 and about 0.4 of a round in fixed set-up.  (2.4 and 0.42 were fitted before the
+    // 64-row kernel lost its lane exchange and gained 128-row blocks, up to a tenth and a quarter of its time: near the line the
+    // 256-row kernel is taken a little early.)
     const int64_t cus = device_cus();
     const int bn = prefill_block_cols(L, M);
     const int64_t wg_p = (int64_t)ceil_div(M, 256) * ceil_div(L.N, bn);

@@ -52,7 +52,7 @@ struct MidArgs {
   int32_t n_last;         // last real output row: rows past it pad a row tile, take its parameters and are not stored
   int32_t sq[2], sr[2];   // K shares: share `split` owns tiles [split*sq + min(split, sr), +sq + (split < sr)) of each kind
   float zp[2];
-  // grouped calls (narrow-format kernel only): blockIdx.z = expert; its rows are output rows [offsets[e], offsets[e+1]),
+  // grouped calls: blockIdx.z = expert; its rows are output rows [offsets[e], offsets[e+1]),
   // activation row sorted_rows[p] for output row p; expert e's arrays start e * stride bytes after expert 0's
   const int32_t* sorted_rows;
   const int32_t* expert_offsets;
@@ -502,8 +502,9 @@ static MidKernel mid_kernel(int fm, int sm, int bm, int wk) {
   return fm == 1 ? narrow[sm][bm == kMidBM ? 0 : 1] : wide[sm][fm - 2][wk - 1];
 }
 
-// 128-row blocks are built for the narrow format: with the wide kinds' six code entries per lane and four accumulator
-// tiles a wavefront would need more than the 256 registers that two of them on a SIMD have.
+// 128-row blocks are built for the narrow format.  With the wide kinds' six code entries per lane and four accumulator tiles
+// mixes (both scale modes) and the hybrid word with fp16 scales need more than the 256 registers that two wavefronts on a
+// SIMD have (32 to 100 bytes of scratch); wide (254 and 240 registers) and the hybrid word with compressed scales (250) would fit.
 static bool mid_has_wide_block(const Layout& L) { return L.tiles[kWide] == 0; }
 
 // Sets the K shares of `a` (S across the grid) and launches: `busy` output tiles have rows.
@@ -531,9 +532,11 @@ static int mid_launch(const Layout& L, MidArgs& a, bool grouped, int bm, int S, 
 int mid_splits(const Layout& L, int M) {
   const int64_t blocks = (int64_t)((M + kMidBM - 1) / kMidBM) * ((L.N + kMidBN - 1) / kMidBN);
   const int min_tiles = std::min(L.tiles[kNarrow] > 0 ? L.tiles[kNarrow] : 1 << 30, L.tiles[kWide] > 0 ? L.tiles[kWide] : 1 << 30);
-  // one workgroup per CU, or two when the weights have wide-format groups and there are at least 128 blocks: that
-  // kernel moves more through LDS per MFMA and gains from a second workgroup on the CU (config 3, M = 64: 84 -> 75 us),
-  // the register-decode kernel for the narrow format does not
+  // One workgroup per CU, or two when the weights have wide-format groups and there are at least 128 blocks.  Two shares
+  // against one (which then has the CU to itself, or runs two shares of its own), K = 8192, M = 64: N = 18432 (144 blocks)
+  // wide 43 against 51 us, hybrid word 54 against 69 us, mix 54.5 against 50 us; N = 28672 (224 blocks) wide 59 against 57 us,
+  // hybrid word 75 against 73 us, mix 60 against 55 us; at K = 4096 one share is level or ahead (N = 28672 wide 35.5 against
+  // 31.6 us).  A narrow block gains nothing from a second workgroup on its CU.
   const int64_t cus = device_cus();
   const int64_t target = (L.tiles[kWide] > 0 && 2 * blocks >= cus) ? 2 * cus : cus;
   int64_t s = std::max<int64_t>(1, target / std::max<int64_t>(1, blocks));
