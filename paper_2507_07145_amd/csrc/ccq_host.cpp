@@ -190,6 +190,30 @@ static DensePath dense_path(const Layout& L, int M) {
   return kPathMid;
 }
 
+// Dense calls of 2 to 32 rows that take the one-launch kernel of ccq_few.hip instead of the path above (whose workspace is
+// asked for all the same).  That kernel cuts K inside a workgroup only: it wins where K is short, or N long enough for its
+// workgroups to fill the chip, and saves the pass over the partial tiles (new against old, us):
+//   narrow, 5 - 16 rows    K 1984 N 1152 6.0 / 7.9, K 3328 N 20940 13.0 / 19.5; K 4224 N 6612 9.7 / 9.3
+//   narrow, 17 - 32 rows   K 2496 N 4336 9.2 / 11.8, K 4288 N 23888 20 / 24; K 7680 N 1440 16 / 9.5
+//   wide, hybrid word, 2 - 16   K 832 N 7718 5.4 / 8.0, K 1984 N 3936 7.5 / 7.9; K 2560 N 4772 9.1 / 8.2
+//   wide kinds, 17 - 32    K 1152 N 7145 9.0 / 19, K 4864 N 3440 (mix) 23 / 33, K 8384 N 14224 29 / 38; K 10432 N 2330 31 / 17
+// (2 - 4 rows on the narrow format have a one-launch kernel already; so has a K that the old path does not cut.  Mixes of
+// 2 - 16 rows: 0.97 of the old time at K 640, 1.2 to 1.4 of it beyond 1600.)
+static bool dense_few(const Layout& L, int M) {
+  if (M < 2 || M > 32) return false;
+  const bool narrow = L.tiles[kWide] == 0, mix = L.tiles[kNarrow] > 0 && !narrow;
+  if (M > 16) {
+    if (narrow) return L.K <= 2560 || L.K <= 4 * L.row_tiles;
+    return L.K <= 4096 || L.K <= (mix ? 16 : 24) * L.row_tiles;
+  }
+  int a = 0, b = 0, sn = 0, sw = 0;
+  switch (dense_path(L, M)) {
+    case kPathGemv16: return (L.K <= 3072 || L.K <= 3 * L.row_tiles) && gemv16_shape(L, device_cus(), kMaxSplitsK, &a, &b) && L.tiles[kNarrow] > a;
+    case kPathGemv16NW: return !mix && L.K <= 2048 && gemv16_nw_shape(L, device_cus(), kMaxSplitsK, &a, &b, &sn, &sw) && sn + sw > 1;
+    default: return false;
+  }
+}
+
 // Workspace the per-row-tile kernel needs for M rows in the library's own decomposition: it walks the rows in
 // passes of kMaxSkinnyM and a last, shorter one.
 static int64_t skinny_need(const Layout& L, int M) {
@@ -492,6 +516,20 @@ int gemm_dispatch(const ccq_weight* w, const void* x, int32_t M, int64_t ldx, vo
   }
   if (!explicit_launch && dense_path(L, M) != kPathGemv16 && dense_path(L, M) != kPathGemv16NW && have < dense_need(L, M)) return CCQ_ERR_WORKSPACE;
 
+  if (!explicit_launch && dense_few(L, M)) {
+    SkinnyCall c;
+    c.w = w;
+    c.L = L;
+    c.x = x;
+    c.ldx = ldx;
+    c.y = y;
+    c.ldy = ldy;
+    c.M = M;
+    c.stream = stream;
+    rc = launch_few(c, M, M);
+    if (rc != CCQ_ERR_UNSUPPORTED) return rc;
+  }
+
   if (!explicit_launch) {
     const DensePath path = dense_path(L, M);
     // many rows, narrow format only: the 256-row LDS-tiled MFMA kernel
@@ -712,6 +750,21 @@ extern "C" int ccq_grouped_gemm(const ccq_weight* w0, int32_t E, int64_t codes_s
       if (rc != CCQ_ERR_UNSUPPORTED) return rc;
     }
   }
+  c.E = E;
+  c.codes_stride = codes_stride;
+  c.scales_stride = scales_stride;
+  c.ab_stride = ab_stride;
+  c.x = x;
+  c.ldx = ldx;
+  c.y = y;
+  c.ldy = ldy;
+  c.M = P;
+  c.sorted_rows = sorted_rows;
+  c.expert_offsets = expert_offsets_dev;
+  c.stream = hip_stream;
+  // up to 32 rows per expert, as far as is known (more are walked 32 at a time): the few-row kernel
+  rc = launch_few(c, T, expert_offsets_host ? most_rows : grouped_tile_rows(E, P));
+  if (rc != CCQ_ERR_UNSUPPORTED) return rc;
   if (most_rows == 1) {
     // no expert has more than one row (on formats or shapes the kernel above is not built for): the
     // one-held-row kernel (wavefront-private staging, no 16-row activation tile)
@@ -725,18 +778,6 @@ extern "C" int ccq_grouped_gemm(const ccq_weight* w0, int32_t E, int64_t codes_s
     c.d = grouped_decomp(L, E, P, active, workspace ? workspace_bytes : 0);
   }
   if (c.d.S > 1) c.partial = static_cast<float*>(workspace);
-  c.E = E;
-  c.codes_stride = codes_stride;
-  c.scales_stride = scales_stride;
-  c.ab_stride = ab_stride;
-  c.x = x;
-  c.ldx = ldx;
-  c.y = y;
-  c.ldy = ldy;
-  c.M = P;
-  c.sorted_rows = sorted_rows;
-  c.expert_offsets = expert_offsets_dev;
-  c.stream = hip_stream;
   return launch_skinny(c);
 }
 

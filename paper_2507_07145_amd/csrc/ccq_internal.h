@@ -110,6 +110,8 @@ struct SkinnyCall {
   uint16_t active_ids[kMaxActiveList] = {};
 };
 int launch_skinny(const SkinnyCall& c);
+// The same call with few rows per matrix, one launch without a workspace (ccq_few.hip; `d` and `partial` are not looked at).
+int launch_few(const SkinnyCall& c, int T, int most_rows);
 
 constexpr int kGemvMaxM = 4;       // rows of the four-row kernel
 
