@@ -63,7 +63,7 @@ struct Args {
   uint16_t active_ids[kMaxActiveList];
 };
 
-__device__ __forceinline__ uint32_t and_or(uint32_t a, uint32_t mask, uint32_t orv) { return (a & mask) | orv; }
+__device__ __forceinline__ uint32_t and_or(uint32_t a, uint32_t mask, uint32_t orv) { return __builtin_amdgcn_bitop3_b32(a, mask, orv, 0xEA); }
 __device__ __forceinline__ uint32_t dword_of(const u32x4& v, int j) { return j == 0 ? v.x : (j == 1 ? v.y : (j == 2 ? v.z : v.w)); }
 __device__ __forceinline__ f32x4 mfma(const u32x4 a, const u32x4 b, const f32x4 c) {
   return __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, a), __builtin_bit_cast(bf16x8, b), c, 0, 0, 0);
@@ -389,6 +389,7 @@ __global__ void __launch_bounds__(64 * max_waves(FM, MT, RT, WN)) __attribute__(
                   else sc = (float)(H16 ? hw & 0x1FFFu : (hw >> 8) & 0xFu);
                 }
                 if (lg > 0 || r > 0) add(acc[(r + RT - 1) % RT]);
+                asm volatile("" : "+v"(sc));   // converted once: v_fma_f32 issues at twice the rate of v_fma_mix_f32
                 psc = sc;
 #pragma unroll
                 for (int m = 0; m < LM; ++m) {

@@ -87,8 +87,8 @@ __device__ __forceinline__ float group_sum8(float s) {
 }
 
 // Plain C on purpose (no inline assembly: the compiler's hazard recognizer must see the instruction); mask and orv
-// are kept in registers by the caller so that a single v_and_or_b32 is selected.
-__device__ __forceinline__ uint32_t and_or(uint32_t a, uint32_t mask, uint32_t orv) { return (a & mask) | orv; }
+// are kept in registers by the caller so that a single v_bitop3_b32 is selected.
+__device__ __forceinline__ uint32_t and_or(uint32_t a, uint32_t mask, uint32_t orv) { return __builtin_amdgcn_bitop3_b32(a, mask, orv, 0xEA); }
 
 // The 16 weights of one lane for one group: dword d holds the clustered bytes of codes 4kq .. 4kq+3 of the group.
 // Returns, per k-step t (codes 2t, 2t+1), the four registers {state i of code 2t | state i of code 2t+1 << 16} + 128.
@@ -196,7 +196,7 @@ __device__ __forceinline__ void rows1_body(const Args& a, const uint32_t rtile0)
   __builtin_amdgcn_wave_barrier();
   uint32_t c4300 = 0x43004300u, mask = 0x003F003Fu;
   float magic = 8388608.f;
-  asm volatile("" : "+v"(c4300), "+s"(mask), "+v"(magic));   // register values, not literals: v_and_or_b32 gets selected
+  asm volatile("" : "+v"(c4300), "+s"(mask), "+v"(magic));   // register values, not literals: one v_bitop3_b32 without literals
   float be[RT];
 #pragma unroll
   for (int rt = 0; rt < RT; ++rt) be[rt] = be_raw[rt] + magic;   // + 2^23: exact, beta is an integer below 2^15
@@ -353,7 +353,7 @@ __device__ __forceinline__ void rows4_body(const Args& a, const int64_t ldx, con
   __builtin_amdgcn_wave_barrier();
   uint32_t c4300 = 0x43004300u, mask = 0x003F003Fu;
   float magic = 8388608.f;
-  asm volatile("" : "+v"(c4300), "+s"(mask), "+v"(magic));   // register values, not literals: v_and_or_b32 gets selected
+  asm volatile("" : "+v"(c4300), "+s"(mask), "+v"(magic));   // register values, not literals: one v_bitop3_b32 without literals
   const float be = be_raw + magic;   // + 2^23: exact, beta is an integer below 2^15
 
   // ---- contraction ------------------------------------------------------------------------------------------------
@@ -586,7 +586,7 @@ __device__ __forceinline__ void rows1_nw_body(const ArgsNW& a, const uint32_t rt
   const uint16_t* scale_row = a.scales + (size_t)rtile * (size_t)a.row_tile_scale_halfs;
   uint32_t c4300 = 0x43004300u, mask_n = 0x003F003Fu, mask_w = H16 ? 0x00070007u : 0x000F000Fu;
   float magic = 8388608.f;
-  asm volatile("" : "+v"(c4300), "+s"(mask_n), "+s"(mask_w), "+v"(magic));   // register values, not literals: v_and_or_b32 gets selected
+  asm volatile("" : "+v"(c4300), "+s"(mask_n), "+s"(mask_w), "+v"(magic));   // register values, not literals: one v_bitop3_b32 without literals
   uint32_t ssup = 0;
   float acc = 0.f;
 

@@ -64,7 +64,7 @@ constexpr int kMidBN = 128;
 constexpr int kMidRow = 64 + 8;     // bf16 elements per padded LDS row (144 bytes)
 constexpr int kMidRowH16 = 80 + 8;  // the same for the hybrid word: ten words of eight slots (176 bytes)
 
-__device__ __forceinline__ uint32_t and_or_m(uint32_t a, uint32_t mask, uint32_t orv) { return (a & mask) | orv; }
+__device__ __forceinline__ uint32_t and_or_m(uint32_t a, uint32_t mask, uint32_t orv) { return __builtin_amdgcn_bitop3_b32(a, mask, orv, 0xEA); }
 
 __device__ __forceinline__ uint32_t pack_bf16_m(float lo, float hi) {
   f32x2 v = {lo, hi};
@@ -170,7 +170,7 @@ __global__ void __launch_bounds__(256 * WK) __attribute__((amdgpu_waves_per_eu(2
   if constexpr (SM == 1)
     ssup = (float)__builtin_bit_cast(_Float16, reinterpret_cast<const uint16_t*>(reinterpret_cast<const uint8_t*>(a.scale_super) + e_ab / 2)[prow]);
   if constexpr (HAS_N) {
-    al = reinterpret_cast<const float*>(reinterpret_cast<const uint8_t*>(a.alpha) + e_ab)[prow];
+    al = reinterpret_cast<const float*>(reinterpret_cast<const uint8_t*>(a.alpha) + e_ab)[prow] * kAlphaScale;
     bem = reinterpret_cast<const float*>(reinterpret_cast<const uint8_t*>(a.beta) + e_ab)[prow] + 8388608.f;  // + 2^23: exact, beta is an integer below 2^15
   }
   const uint8_t* code_wide = code_row + (int64_t)a.tiles[kNarrow] * kNarrowTileBytes;

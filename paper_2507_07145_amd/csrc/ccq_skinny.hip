@@ -188,8 +188,8 @@ template <int KIND> struct TileRegs {
 // (a & mask) | orv.  Plain C on purpose: an instruction written as inline assembly is invisible to the
 // compiler's hazard recognizer, and a hand-written v_and_or_b32 whose result fed an MFMA one instruction
 // later gave wrong results on the device.  The callers keep mask and orv in registers (not literals) so
-// that the compiler can still select the single v_and_or_b32.
-__device__ __forceinline__ uint32_t and_or(uint32_t a, uint32_t mask, uint32_t orv) { return (a & mask) | orv; }
+// that the result is a single instruction (v_bitop3_b32).
+__device__ __forceinline__ uint32_t and_or(uint32_t a, uint32_t mask, uint32_t orv) { return __builtin_amdgcn_bitop3_b32(a, mask, orv, 0xEA); }
 
 __device__ __forceinline__ uint32_t dword_of(const u32x4& v, int j) {
   return j == 0 ? v.x : (j == 1 ? v.y : (j == 2 ? v.z : v.w));
@@ -850,7 +850,7 @@ __global__ void __launch_bounds__(skinny_max_threads(MT, MR, FM, SM)) ccq_skinny
   uint4* lds_x = reinterpret_cast<uint4*>(smem);
   const int frag_cap = a.frag_cap;
   float* lds_cneg = reinterpret_cast<float*>(smem + (size_t)frag_cap * 16);
-  // the compiler must see these as register values, not literals, to select v_and_or_b32
+  // the compiler must see these as register values, not literals, to select one v_bitop3_b32
   DecodeConsts dc = {0x43004300u, {0x003F003Fu, 0x000F000Fu, 0x00070007u}, {0.f, 0.f}};
   asm volatile("" : "+v"(dc.c4300), "+s"(dc.mask[0]), "+s"(dc.mask[1]), "+s"(dc.mask[2]));
   if constexpr (SM == 1) {
