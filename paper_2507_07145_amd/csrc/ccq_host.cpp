@@ -196,7 +196,7 @@ static DensePath dense_path(const Layout& L, int M) {
 //   narrow, 5 - 16 rows    K 1984 N 1152 6.0 / 7.9, K 3328 N 20940 13.0 / 19.5; K 4224 N 6612 9.7 / 9.3
 //   narrow, 17 - 32 rows   K 2496 N 4336 9.2 / 11.8, K 4288 N 23888 20 / 24; K 7680 N 1440 16 / 9.5
 //   wide, hybrid word, 2 - 16   K 832 N 7718 5.4 / 8.0, K 1984 N 3936 7.5 / 7.9; K 2560 N 4772 9.1 / 8.2
-//   wide kinds, 17 - 32    K 1152 N 7145 9.0 / 19, K 4864 N 3440 (mix) 23 / 33, K 8384 N 14224 29 / 38; K 10432 N 2330 31 / 17
+//   wide kinds, 17 - 32    K 1152 N 7145 9.0 / 19, K 8384 N 14224 29 / 38; K 8192 N 8192 26 / 21, K 10432 N 2330 31 / 17
 // (2 - 4 rows on the narrow format have a one-launch kernel already; so has a K that the old path does not cut.  Mixes of
 // 2 - 16 rows: 0.97 of the old time at K 640, 1.2 to 1.4 of it beyond 1600.)
 static bool dense_few(const Layout& L, int M) {
@@ -204,7 +204,7 @@ static bool dense_few(const Layout& L, int M) {
   const bool narrow = L.tiles[kWide] == 0, mix = L.tiles[kNarrow] > 0 && !narrow;
   if (M > 16) {
     if (narrow) return L.K <= 2560 || L.K <= 4 * L.row_tiles;
-    return L.K <= 4096 || L.K <= (mix ? 16 : 24) * L.row_tiles;
+    return L.K <= 4096 || L.K <= (mix ? 8 : 10) * L.row_tiles;
   }
   int a = 0, b = 0, sn = 0, sw = 0;
   switch (dense_path(L, M)) {
@@ -570,7 +570,7 @@ int gemm_dispatch(const ccq_weight* w, const void* x, int32_t M, int64_t ldx, vo
     }
     // a few dozen rows (or many rows on wide / mixed formats): the 64-row LDS-tiled kernel
     if (path == kPathMid || path == kPathPrefill) {
-      const int S = mid_splits(L, M);
+      const int S = mid_shares(L, M, mid_splits(L, M));
       float* partial = S > 1 ? static_cast<float*>(workspace) : nullptr;
       rc = launch_mid(w, L, x, M, ldx, y, ldy, partial, S, stream);
       if (rc == CCQ_OK && S > 1) rc = launch_reduce_splits(partial, y, ldy, M, L.N, L.Npad, S, stream);
@@ -707,7 +707,7 @@ extern "C" int ccq_grouped_gemm(const ccq_weight* w0, int32_t E, int64_t codes_s
   c.L = L;
   c.m_tile_hint = grouped_tile_rows(E, P);
   int active = E, most_rows = P;
-  int64_t row_blocks = 0;   // of 64 rows
+  int64_t row_blocks[2] = {0, 0};   // of 64 and of 128 rows
   if (expert_offsets_host) {
     active = 0;
     most_rows = 0;
@@ -715,7 +715,8 @@ extern "C" int ccq_grouped_gemm(const ccq_weight* w0, int32_t E, int64_t codes_s
       const int rows = expert_offsets_host[e + 1] - expert_offsets_host[e];
       active += rows > 0 ? 1 : 0;
       most_rows = std::max(most_rows, rows);
-      row_blocks += ceil_div(rows, 64);
+      row_blocks[0] += ceil_div(rows, 64);
+      row_blocks[1] += ceil_div(rows, 128);
     }
   }
   if (expert_offsets_host && active < E && active <= kMaxActiveList && E <= 65536) {
@@ -729,7 +730,7 @@ extern "C" int ccq_grouped_gemm(const ccq_weight* w0, int32_t E, int64_t codes_s
     // many rows per expert (a prefill-sized routing): the 64-row kernel, one grid over (row block, column block,
     // expert); on narrow-format weights measured 2.2-2.4 times faster than 64-row passes of the per-row-tile kernel
     // from 33 rows on, slower below
-    rc = launch_mid_grouped(w0, L, E, codes_stride, scales_stride, ab_stride, x, ldx, sorted_rows, P, expert_offsets_dev, most_rows, row_blocks,
+    rc = launch_mid_grouped(w0, L, E, codes_stride, scales_stride, ab_stride, x, ldx, sorted_rows, T, P, expert_offsets_dev, most_rows, row_blocks,
                             y, ldy, hip_stream);
     if (rc != CCQ_ERR_UNSUPPORTED) return rc;
   }

@@ -148,9 +148,10 @@ int launch_gemv16(const ccq_weight* w, const Layout& L, const void* x, int M, in
 // shares whose fp32 partial tiles go to `partial` ([S][M][N]) when S > 1 (then call launch_reduce_splits).
 constexpr int kMidMinM = 17;
 int launch_mid_grouped(const ccq_weight* w0, const Layout& L, int E, int64_t codes_stride, int64_t scales_stride, int64_t ab_stride, const void* x,
-                       int64_t ldx, const int32_t* sorted_rows, int P, const int32_t* expert_offsets, int most_rows, int64_t row_blocks, void* y,
+                       int64_t ldx, const int32_t* sorted_rows, int T, int P, const int32_t* expert_offsets, int most_rows, const int64_t (&row_blocks)[2], void* y,
                        int64_t ldy, void* stream);
-int mid_splits(const Layout& L, int M);
+int mid_splits(const Layout& L, int M);              // the most shares across the grid (what the workspace is asked for)
+int mid_shares(const Layout& L, int M, int most);    // those that a call takes
 int launch_mid(const ccq_weight* w, const Layout& L, const void* x, int M, int64_t ldx, void* y, int64_t ldy, float* partial, int S,
                void* stream);
 // y[m][n] = bf16(sum_s partial[s][m][n]), shares added in index order (ccq_skinny.hip).

@@ -3,7 +3,7 @@
 //
 // With that many rows the per-row-tile kernel re-stages the activations far too often, and the
 // 256-row kernel wastes three quarters of its tile.  Here a workgroup of four wavefronts owns a 64 x 128 (or, on the
-// narrow format, 128 x 128) tile of the output and a contiguous share of K (grid.y = S shares; fp32 partial tiles go to
+// narrow format, 128 x 128) tile of the output and a share of K (S shares across the grid, up to four in a workgroup; fp32 partial tiles go to
 // the workspace and are added in index order by the reduction kernel when S > 1).  K is walked one 64-weight group per
 // step; per step
 //   - the workgroup copies the activation tile of that group's columns to LDS,
@@ -15,8 +15,9 @@
 // The hybrid 16-bit word of Sec. 3.2 (a (3,3,2) and a (3,4,2) code side by side, seven weights per
 // word, ten words per group) takes the place of the wide format when it is used: eight k-slots per word (seven weights
 // and one unused slot, 80 slots per group), five MFMA k-steps instead of four.
-// The decode (about 3 vector instructions per weight, shared by the rows of the block) and the LDS reads of the
-// activation tile are the bound.
+// The decode (about 3 vector instructions per weight, shared by the rows of the block) and the way of the activations through LDS
+// (every wavefront reads the whole tile: 1 KB per MFMA) are the bound: of 206 us (wide 8192 x 8192, M = 1024) 75 go without the decode,
+// 38 without the LDS stores, 18 without the MFMAs.
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
@@ -45,11 +46,12 @@ struct MidArgs {
   float* partial;
   int64_t ldx, ldy;
   int64_t row_tile_bytes, row_tile_scale_halfs;
-  int32_t M, N, row_tiles, m_blocks;  // N: rows of the device layout (a multiple of 16), the row stride of `partial`
+  int32_t M, N, row_tiles;  // N: rows of the device layout (a multiple of 16), the row stride of `partial`
   int32_t tiles[2];       // k-tiles per kind
   int32_t groups_narrow;  // narrow entries of the group map (whole k-tiles), the offset of the wide ones
   int32_t g_last;         // last real group of K: groups past it pad a k-tile (zero scale) and read this group's activations
   int32_t n_last;         // last real output row: rows past it pad a row tile, take its parameters and are not stored
+  int32_t wk;             // K shares within a workgroup, 256 threads each (of S wk in all)
   int32_t sq[2], sr[2];   // K shares: share `split` owns tiles [split*sq + min(split, sr), +sq + (split < sr)) of each kind
   float zp[2];
   // grouped calls: blockIdx.z = expert; its rows are output rows [offsets[e], offsets[e+1]),
@@ -89,20 +91,18 @@ __device__ __forceinline__ uint32_t dword_sel(const u32x4& v, int j) { return j 
 // scales; 1 the compressed scales of Sec. 3.4: group scale = 4-bit field * per-row super scale, first line of
 // Alg. 2 / Alg. 3; the field of a narrow group comes from the packed scale array, that of a wide group from the
 // spare low nibble of the group's last code byte, the hybrid word's 13-bit field from its last word).
-// BM: rows of the block (64, or 128: a weight tile decoded once for twice the rows; narrow, 64 experts of 2048 x 7168 with
-// 48 - 85 rows each: 338 -> 216 us against the two 64-row blocks with bpermute exchange that came before).  Against decoded
-// weights passed through LDS by eight wavefronts: wide 8192 x 28672, M = 64, 60.8 -> 56.4 us; 4096 x 11008, M = 2048,
-// 272 -> 246 us; mix 8192 x 28672, M = 128, 107 -> 97 us; hybrid word 7232 x 5001, M = 777, 204 -> 185 us.
-// WK: K shares inside the workgroup (two: another four wavefronts with an activation tile of their own take every block's
-// second share, and the sums meet in LDS: shares s and S + s, so that a long one meets a short one; wide 11008 x 1000,
-// M = 64, 20.2 -> 17.9 us against shares 2 s and 2 s + 1).
-// Two wavefronts per SIMD, neither more nor less: told "at least two", the compiler kept the narrow instance with fp16
-// scales to 108 registers for the sake of four, and each MFMA then waited for an LDS read of its own (8192 x 8192, M = 128,
-// 42.7 us; 36.8 us with the reads of a step in flight together, 225 registers).  Few calls have more than two to give.
-// The hybrid word is left to the compiler, which takes 179 - 192 registers either way: 7232 x 5001, M = 777, 183.5 us; 188.4 us
-// with the upper bound of two.
-template <int FM, int SM, bool GROUPED, int BM, int WK>
-__global__ void __launch_bounds__(256 * WK) __attribute__((amdgpu_waves_per_eu(2, FM == 4 ? 8 : 2))) ccq_mid_kernel(const MidArgs a) {
+// BM: rows of the block (64, or 128 on the narrow format: a weight tile decoded once for twice the rows).
+// a.wk shares of K sit in one workgroup (256 threads and an activation tile each); share s of the workgroup works on k-tiles of
+// shares split + s S, so that a long one meets short ones, and the sums meet in LDS.
+// DEEP: two wavefronts per SIMD with four activation tiles on their way and the next step's fragments decoded during the current
+// one, for launches that have no more wavefronts than that to give; otherwise three (four on narrow 64-row blocks) that
+// cover each other's latencies (64 experts of 2048 x 7168, 48 - 85 rows: 209 -> 200 us; wide 1024 x 20000, M = 1500, 1.12 x; with up
+// to two workgroups per CU the lean variant is up to a fifth slower: 16 experts of 2048 x 1536, one with 600 rows, 28 against 35 us).
+// A priority for the wavefronts that multiply (or for those that decode), shares that alternate between the two, and a scheduling
+// barrier between the two all cost 3 to 8 %: the compiler's interleaving of one step's decode and products is what overlaps them.
+constexpr int mid_waves(int fm, int bm, bool deep) { return deep ? 2 : (fm == 1 && bm == kMidBM ? 4 : 3); }
+template <int FM, int SM, bool GROUPED, int BM, bool DEEP>
+__global__ void __launch_bounds__(256 * mid_waves(FM, BM, DEEP)) __attribute__((amdgpu_waves_per_eu(mid_waves(FM, BM, DEEP), DEEP && FM != 4 ? 2 : 8))) ccq_mid_kernel(const MidArgs a) {
   constexpr bool HAS_N = FM == 1 || FM == 3, HAS_W = FM >= 2, META = FM == 3, H16 = FM == 4;
   constexpr int ROW = H16 ? kMidRowH16 : kMidRow;
   constexpr int MT = BM / 32;          // 32-row accumulator tiles, and 16-byte activation chunks per thread and step (chunk i: rows of tile i)
@@ -112,13 +112,14 @@ __global__ void __launch_bounds__(256 * WK) __attribute__((amdgpu_waves_per_eu(2
   extern __shared__ __align__(16) unsigned char smem[];
   const int tid = threadIdx.x & 255, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-  const int wk = WK == 1 ? 0 : __builtin_amdgcn_readfirstlane(threadIdx.x >> 8);
+  const int wk = __builtin_amdgcn_readfirstlane(threadIdx.x >> 8);   // share of K within the workgroup
   uint16_t* As = reinterpret_cast<uint16_t*>(smem) + wk * 2 * BM * ROW;    // [2][BM][ROW] of this share
   // original group of each step of this share (META only); every share has room for the longest
-  int32_t* lds_meta = reinterpret_cast<int32_t*>(reinterpret_cast<uint16_t*>(smem) + WK * 2 * BM * ROW) + wk * ((a.sq[kNarrow] + 1) * kNarrowGroupsPerTile + (a.sq[kWide] + 1) * kWideGroupsPerTile);
+  int32_t* lds_meta = reinterpret_cast<int32_t*>(reinterpret_cast<uint16_t*>(smem) + a.wk * 2 * BM * ROW) + wk * ((a.sq[kNarrow] + 1) * kNarrowGroupsPerTile + (a.sq[kWide] + 1) * kWideGroupsPerTile);
 
-  const int m_block = blockIdx.x % a.m_blocks, n_block = blockIdx.x / a.m_blocks;
-  const int split = blockIdx.y;
+  // row blocks of a column block side by side: they share its codes
+  const int m_block = blockIdx.x, n_block = blockIdx.y;   // (from one index a division costs 0.4 us)
+  const int split = GROUPED ? 0 : blockIdx.z, splits = GROUPED ? 1 : gridDim.z;
   const int m0 = m_block * BM, n0 = n_block * kMidBN;
   // rows of this block's matrix: all M (dense), or the expert's (grouped; row_off = its first output row)
   int Me = a.M, row_off = 0;
@@ -136,7 +137,7 @@ __global__ void __launch_bounds__(256 * WK) __attribute__((amdgpu_waves_per_eu(2
   const int ti = (lane >> 4) & 1, h = lane >> 5;  // the column this lane multiplies: row tile ti of the wavefront, row nl; k half h
 
   // this share's k-tiles of each kind, and its steps (one 64-weight group each): narrow first, then wide
-  const int share = split + wk * gridDim.y;   // the longer shares come first: a workgroup of two has at most one of them
+  const int share = split + wk * splits;   // the longer shares come first: a workgroup of two has at most one of them
   int tA[2], tB[2];
 #pragma unroll
   for (int k = 0; k < 2; ++k) {
@@ -161,10 +162,14 @@ __global__ void __launch_bounds__(256 * WK) __attribute__((amdgpu_waves_per_eu(2
     return min((HAS_N ? tA[kNarrow] * kNarrowGroupsPerTile : tA[kWide] * kWideGroupsPerTile) + s, a.g_last);
   };
 
-  const int rtile = min(n0 / 16 + wave * 2 + ti, a.row_tiles - 1);  // ragged last block: re-decode the last tile, never stored
+  const int rtile0 = min(n0 / 16 + wave * 2, a.row_tiles - 1), rtile = min(n0 / 16 + wave * 2 + ti, a.row_tiles - 1);  // ragged last block: re-decode the last tile, never stored
   const int prow = min(rtile * 16 + nl, a.n_last);
-  const uint8_t* code_row = a.codes + e_codes + (int64_t)rtile * a.row_tile_bytes;
-  const uint16_t* scale_row = reinterpret_cast<const uint16_t*>(reinterpret_cast<const uint8_t*>(a.scales) + e_scales) + (int64_t)rtile * a.row_tile_scale_halfs;
+  // Uniform bases and 32-bit lane offsets: with three or four wavefronts on a SIMD no vector instruction is spent on the addresses
+  // of a request.  (With one or two, where a step waits for its latencies, 64-bit lane addresses are level or up to 4 % faster: a
+  // uniform one has to come back from the group map through a readfirstlane.)
+  const uint8_t* code_row = a.codes + e_codes + (int64_t)rtile0 * a.row_tile_bytes;
+  const uint16_t* scale_row = reinterpret_cast<const uint16_t*>(reinterpret_cast<const uint8_t*>(a.scales) + e_scales) + (int64_t)rtile0 * a.row_tile_scale_halfs;
+  const uint32_t code_lane = (uint32_t)(rtile - rtile0) * (uint32_t)a.row_tile_bytes, scale_lane = (uint32_t)(rtile - rtile0) * (uint32_t)a.row_tile_scale_halfs * 2u;
   float al = 0.f, bem = 0.f, ssup = 0.f;
   // expert e's super scales: half the byte stride of alpha / beta (fp16 against fp32)
   if constexpr (SM == 1)
@@ -183,31 +188,44 @@ __global__ void __launch_bounds__(256 * WK) __attribute__((amdgpu_waves_per_eu(2
   uint2 sn, sn_next;
   u32x4 cw[NQ], cw_next[NQ];
   uint4 sw, sw_next;
-  int woff[NQ];  // byte offset of entry i in a wide k-tile
+  uint32_t woff[NQ];  // byte offset of entry i in a wide k-tile
 #pragma unroll
   for (int i = 0; i < NQ; ++i) {
     const int e = H16 ? 2 * i + h : 5 * h + i;                 // word, or two-byte entry, of the group
     const int t = H16 ? e / 4 : e % 3, kq = H16 ? e % 4 : e / 3;
-    woff[i] = t * 1024 + (kq * 16 + nl) * 16;
+    woff[i] = code_lane + t * 1024 + (kq * 16 + nl) * 16;
   }
   auto load_narrow = [&](u32x4 (&c)[2], uint2& sc, int kt) {
     kt = min(kt, a.tiles[kNarrow] - 1);
+    const uint8_t* t = code_row + (int64_t)kt * kNarrowTileBytes;
+    uint32_t off = code_lane + (uint32_t)(nl + 32 * h) * 16u, soff = scale_lane + (uint32_t)nl * (SM == 0 ? 8u : 2u);
+    asm volatile("" : "+v"(off), "+v"(soff));
 #pragma unroll
-    for (int q = 0; q < 2; ++q)
-      c[q] = __builtin_nontemporal_load(reinterpret_cast<const u32x4*>(code_row + (int64_t)kt * kNarrowTileBytes + (nl + 16 * (2 * h + q)) * 16));
-    if constexpr (SM == 0) sc = *reinterpret_cast<const uint2*>(scale_row + (int64_t)kt * kNarrowTileScaleHalfs + nl * 4);
-    else sc = uint2{(uint32_t)scale_row[(int64_t)kt * kNarrowTileScaleHalfs4 + nl], 0u};  // the tile's four 4-bit fields
+    for (int q = 0; q < 2; ++q) c[q] = __builtin_nontemporal_load(reinterpret_cast<const u32x4*>(t + off + q * 256));
+    const char* sb = reinterpret_cast<const char*>(scale_row + (int64_t)kt * (SM == 0 ? kNarrowTileScaleHalfs : kNarrowTileScaleHalfs4)) + soff;
+    if constexpr (SM == 0) sc = *reinterpret_cast<const uint2*>(sb);
+    else sc = uint2{(uint32_t)*reinterpret_cast<const uint16_t*>(sb), 0u};  // the tile's four 4-bit fields
   };
   auto load_wide = [&](u32x4 (&c)[NQ], uint4& sc, int kt) {
     kt = min(kt, a.tiles[kWide] - 1);
     const uint8_t* t = code_wide + (int64_t)kt * WTILE;
 #pragma unroll
-    for (int i = 0; i < NQ; ++i) c[i] = __builtin_nontemporal_load(reinterpret_cast<const u32x4*>(t + woff[i]));
-    if constexpr (SM == 0) sc = *reinterpret_cast<const uint4*>(scale_wide + (int64_t)kt * kWideTileScaleHalfs + nl * 8);
-    else sc = uint4{0u, 0u, 0u, 0u};  // the fields sit in the code stream
+    for (int i = 0; i < NQ; ++i) {
+      uint32_t off = woff[i];
+      if constexpr (!DEEP) asm volatile("" : "+v"(off));
+      c[i] = __builtin_nontemporal_load(reinterpret_cast<const u32x4*>(t + off));
+    }
+    if constexpr (SM == 0) {
+      uint32_t soff = scale_lane + (uint32_t)nl * 16u;
+      asm volatile("" : "+v"(soff));
+      sc = *reinterpret_cast<const uint4*>(reinterpret_cast<const char*>(scale_wide + (int64_t)kt * kWideTileScaleHalfs) + soff);
+    } else {
+      sc = uint4{0u, 0u, 0u, 0u};  // the fields sit in the code stream
+    }
   };
 
-  const uint16_t* xrow[MT];
+  const uint16_t* xbase = a.x + (GROUPED ? 0 : (int64_t)m0 * a.ldx);
+  uint32_t xoff[MT];
   const int a_lds_off = (tid >> 3) * ROW + (H16 ? 0 : (tid & 7) * 8);  // of chunk 0; chunk i lies 32 rows further per i
 #pragma unroll
   for (int i = 0; i < MT; ++i) {
@@ -215,8 +233,10 @@ __global__ void __launch_bounds__(256 * WK) __attribute__((amdgpu_waves_per_eu(2
     int64_t xr = row_off + min(m0 + row, Me - 1);  // rows past the end re-read the last row; their products are never stored
     if constexpr (GROUPED) {
       if (a.sorted_rows) xr = a.sorted_rows[xr];
+    } else {
+      xr -= m0;
     }
-    xrow[i] = a.x + xr * a.ldx + col * 8;
+    xoff[i] = (uint32_t)((xr * a.ldx + col * 8) * 2);
   }
   // hybrid word: element e of a group sits in slot 8 (e / 7) + e % 7 (weight 63, alone in the last word, in
   // slot 72); the unused slots are cleared once and never written again
@@ -327,9 +347,19 @@ __global__ void __launch_bounds__(256 * WK) __attribute__((amdgpu_waves_per_eu(2
   auto run = [&](auto LC) {
     constexpr int LIVE = decltype(LC)::value;
     auto load_a = [&](u32x4 (&dst)[LIVE], int s) {
-      const int64_t off = (int64_t)group_of(s) * kGroup;
+      if constexpr (DEEP) {
+        const int64_t off = (int64_t)group_of(s) * (kGroup * 2);
 #pragma unroll
-      for (int i = 0; i < LIVE; ++i) dst[i] = *reinterpret_cast<const u32x4*>(xrow[i] + off);
+        for (int i = 0; i < LIVE; ++i) dst[i] = *reinterpret_cast<const u32x4*>(reinterpret_cast<const char*>(xbase) + xoff[i] + off);
+      } else {
+        const char* base = reinterpret_cast<const char*>(xbase + (int64_t)__builtin_amdgcn_readfirstlane(group_of(s)) * kGroup);
+#pragma unroll
+        for (int i = 0; i < LIVE; ++i) {
+          uint32_t off = xoff[i];
+          asm volatile("" : "+v"(off));
+          dst[i] = *reinterpret_cast<const u32x4*>(base + off);
+        }
+      }
     };
     auto store_a = [&](int buf, const u32x4 (&src)[LIVE]) {
       uint16_t* dst = As + buf * BM * ROW;
@@ -360,82 +390,109 @@ __global__ void __launch_bounds__(256 * WK) __attribute__((amdgpu_waves_per_eu(2
     };
     // activation chunks of step s live in register set s % D, requested D steps ahead of their use; three or four row
     // tiles leave registers for two sets only, and their steps are longer
-    constexpr int D = LIVE >= 3 ? 2 : 4;
+    constexpr int D = DEEP ? (LIVE >= 3 ? 2 : 4) : (LIVE >= 3 ? 1 : 2);
+    constexpr bool AHEAD = DEEP && LIVE <= 2;   // the fragments of the next step are decoded during this one
     u32x4 areg[D][LIVE];
-    u32x4 bcur[KK], bnext[KK];
+    u32x4 bf[KK], bnext[KK];
     int s = 0;
     if constexpr (HAS_N) load_narrow(cn, sn, tA[kNarrow]);
     if constexpr (HAS_W) load_wide(cw, sw, tA[kWide]);
-    load_a(areg[0], 0);
-    load_a(areg[1], 1);
-    if constexpr (D == 4) {
-      load_a(areg[2], 2);
-      load_a(areg[3], 3);
-    }
+#pragma unroll
+    for (int d = 0; d < D; ++d) load_a(areg[d], d);
     store_a(0, areg[0]);
-    if constexpr (HAS_N) decode_narrow(bcur, 0);
-    else decode_wide(bcur, 0);
+    if constexpr (AHEAD) {
+      if constexpr (HAS_N) decode_narrow(bf, 0);
+      else decode_wide(bf, 0);
+    }
     lds_barrier();
-    // one step (J = s & 3): the activation tile of step s is multiplied with the fragments decoded during the previous
-    // step, while the fragments of step s + 1 are decoded and its activation tile goes to the other LDS buffer
-    auto step = [&](auto JC, auto&& prepare_next) {
+    // one step (J = s & 3): the activation tile of step s is multiplied while that of step s + 1 goes to the other LDS buffer
+    auto step = [&](auto JC, auto&& decode) {
       constexpr int J = decltype(JC)::value;
       constexpr int P = J & 1;
       load_a(areg[J % D], s + D);
-      if constexpr (LIVE >= 3) {   // no registers for a second set of fragments in flight: the next ones are decoded afterwards
-        multiply(P, bcur);
+      if constexpr (AHEAD) {
+        decode(bnext);
+        multiply(P, bf);
         store_a(P ^ 1, areg[(J + 1) % D]);
-        __builtin_amdgcn_sched_barrier(0);
-        prepare_next();
+#pragma unroll
+        for (int k = 0; k < KK; ++k) bf[k] = bnext[k];
       } else {
-        prepare_next();
-        multiply(P, bcur);
+        __builtin_amdgcn_sched_barrier(0);
+        decode(bf);
+        multiply(P, bf);
         store_a(P ^ 1, areg[(J + 1) % D]);
       }
-#pragma unroll
-      for (int k = 0; k < KK; ++k) bcur[k] = bnext[k];
       lds_barrier();
       ++s;
+    };
+    // group `now` of the held k-tile, or the one after it where fragments are decoded a step ahead
+    auto narrow_step = [&](auto JC, auto NOW) {
+      constexpr int now = decltype(NOW)::value;
+      step(JC, [&](u32x4 (&f)[KK]) { decode_narrow(f, AHEAD ? now + 1 : now); });
+    };
+    auto wide_step = [&](auto JC, auto NOW) {
+      constexpr int now = decltype(NOW)::value;
+      step(JC, [&](u32x4 (&f)[KK]) { decode_wide(f, AHEAD ? now + 1 : now); });
+    };
+    auto next_narrow = [&]() {
+      cn[0] = cn_next[0];
+      cn[1] = cn_next[1];
+      sn = sn_next;
+    };
+    auto next_wide = [&]() {
+#pragma unroll
+      for (int i = 0; i < NQ; ++i) cw[i] = cw_next[i];
+      sw = sw_next;
     };
     using J0 = std::integral_constant<int, 0>;
     using J1 = std::integral_constant<int, 1>;
     using J2 = std::integral_constant<int, 2>;
     using J3 = std::integral_constant<int, 3>;
+    using J4 = std::integral_constant<int, 4>;
+    using J5 = std::integral_constant<int, 5>;
+    using J6 = std::integral_constant<int, 6>;
+    using J7 = std::integral_constant<int, 7>;
     if constexpr (HAS_N) {
       for (int t = tA[kNarrow]; t < tB[kNarrow]; ++t) {
         load_narrow(cn_next, sn_next, t + 1);
-        step(J0{}, [&]() { decode_narrow(bnext, 1); });
-        step(J1{}, [&]() { decode_narrow(bnext, 2); });
-        step(J2{}, [&]() { decode_narrow(bnext, 3); });
-        step(J3{}, [&]() {
-          cn[0] = cn_next[0];
-          cn[1] = cn_next[1];
-          sn = sn_next;
-          if constexpr (HAS_W) {
-            if (t + 1 < tB[kNarrow]) decode_narrow(bnext, 0);
-            else decode_wide(bnext, 0);
-          } else {
-            decode_narrow(bnext, 0);  // of the next k-tile (after the last one: a repeat, not used)
-          }
-        });
+        narrow_step(J0{}, J0{});
+        narrow_step(J1{}, J1{});
+        narrow_step(J2{}, J2{});
+        if constexpr (AHEAD) {
+          step(J3{}, [&](u32x4 (&f)[KK]) {
+            next_narrow();
+            if constexpr (HAS_W) {
+              if (t + 1 < tB[kNarrow]) decode_narrow(f, 0);
+              else decode_wide(f, 0);
+            } else {
+              decode_narrow(f, 0);  // of the next k-tile (after the last one: a repeat, not used)
+            }
+          });
+        } else {
+          narrow_step(J3{}, J3{});
+          next_narrow();
+        }
       }
     }
     if constexpr (HAS_W) {
       for (int t = tA[kWide]; t < tB[kWide]; ++t) {
         load_wide(cw_next, sw_next, t + 1);
-        step(J0{}, [&]() { decode_wide(bnext, 1); });
-        step(J1{}, [&]() { decode_wide(bnext, 2); });
-        step(J2{}, [&]() { decode_wide(bnext, 3); });
-        step(J3{}, [&]() { decode_wide(bnext, 4); });
-        step(J0{}, [&]() { decode_wide(bnext, 5); });
-        step(J1{}, [&]() { decode_wide(bnext, 6); });
-        step(J2{}, [&]() { decode_wide(bnext, 7); });
-        step(J3{}, [&]() {
-#pragma unroll
-          for (int i = 0; i < NQ; ++i) cw[i] = cw_next[i];
-          sw = sw_next;
-          decode_wide(bnext, 0);
-        });
+        wide_step(J0{}, J0{});
+        wide_step(J1{}, J1{});
+        wide_step(J2{}, J2{});
+        wide_step(J3{}, J3{});
+        wide_step(J0{}, J4{});
+        wide_step(J1{}, J5{});
+        wide_step(J2{}, J6{});
+        if constexpr (AHEAD) {
+          step(J3{}, [&](u32x4 (&f)[KK]) {
+            next_wide();
+            decode_wide(f, 0);
+          });
+        } else {
+          wide_step(J3{}, J7{});
+          next_wide();
+        }
       }
     }
   };
@@ -449,26 +506,33 @@ __global__ void __launch_bounds__(256 * WK) __attribute__((amdgpu_waves_per_eu(2
     else if (live == 3) run(std::integral_constant<int, 3>{});
     else run(std::integral_constant<int, 4>{});
   }
-
-  if constexpr (WK == 2) {
-    // the shorter share keeps up with the other one's barriers, then hands its sums over (or takes them)
-    const int other = split + (1 - wk) * gridDim.y;
-    const int steps_other = (HAS_N ? (a.sq[kNarrow] + (other < a.sr[kNarrow] ? 1 : 0)) * kNarrowGroupsPerTile : 0) +
-                            (HAS_W ? (a.sq[kWide] + (other < a.sr[kWide] ? 1 : 0)) * kWideGroupsPerTile : 0);
-    for (int i = nsteps; i < steps_other; ++i) lds_barrier();
-    float* red = reinterpret_cast<float*>(smem) + wave * (MT * 16 * 64) + lane;   // the activation tiles' place: all are done with them
-    if (wk == 1) {
+  if (a.wk > 1) {
+    // the shorter shares keep up with the barriers of the longest one (share 0 of every kind), then the sums meet in LDS, where the
+    // activation tiles were: the upper half of the shares hands its sums to the lower one until one is left
+    const int longest = split;
+    const int steps_most = (HAS_N ? (a.sq[kNarrow] + (longest < a.sr[kNarrow] ? 1 : 0)) * kNarrowGroupsPerTile : 0) +
+                           (HAS_W ? (a.sq[kWide] + (longest < a.sr[kWide] ? 1 : 0)) * kWideGroupsPerTile : 0);
+    for (int i = nsteps; i < steps_most; ++i) lds_barrier();
+    for (int left = a.wk; left > 1;) {
+      const int keep = (left + 1) / 2;
+      float* red = reinterpret_cast<float*>(smem) + ((wk >= keep ? wk - keep : wk) * 4 + wave) * (MT * 16 * 64) + lane;
+      if (wk >= keep && wk < left) {
 #pragma unroll
-      for (int i = 0; i < MT; ++i)
+        for (int i = 0; i < MT; ++i)
 #pragma unroll
-        for (int r = 0; r < 16; ++r) red[(i * 16 + r) * 64] = acc[i][r];
+          for (int r = 0; r < 16; ++r) red[(i * 16 + r) * 64] = acc[i][r];
+      }
+      lds_barrier();
+      if (wk + keep < left) {
+#pragma unroll
+        for (int i = 0; i < MT; ++i)
+#pragma unroll
+          for (int r = 0; r < 16; ++r) acc[i][r] += red[(i * 16 + r) * 64];
+      }
+      left = keep;
+      if (left > 1) lds_barrier();
     }
-    lds_barrier();
-    if (wk == 1) return;
-#pragma unroll
-    for (int i = 0; i < MT; ++i)
-#pragma unroll
-      for (int r = 0; r < 16; ++r) acc[i][r] += red[(i * 16 + r) * 64];
+    if (wk > 0) return;
   }
 
   // epilogue: D[row][col], row = 8*(r/4) + 4*(lane/32) + r%4, col = lane%32
@@ -480,7 +544,7 @@ __global__ void __launch_bounds__(256 * WK) __attribute__((amdgpu_waves_per_eu(2
       const int m = m0 + i * 32 + 8 * (r >> 2) + 4 * (lane >> 5) + (r & 3);
       const float val = acc[i][r];  // by value: bit-casting the element lvalue itself reads element 0
       if (m < Me && n <= a.n_last) {
-        if (gridDim.y > 1) __builtin_nontemporal_store(val, &a.partial[((int64_t)split * a.M + row_off + m) * a.N + n]);
+        if (splits > 1) __builtin_nontemporal_store(val, &a.partial[((int64_t)split * a.M + row_off + m) * a.N + n]);
         else a.y[(int64_t)(row_off + m) * a.ldy + n] = (uint16_t)(pack_bf16_m(val, 0.f) & 0xFFFFu);
       }
     }
@@ -488,41 +552,50 @@ __global__ void __launch_bounds__(256 * WK) __attribute__((amdgpu_waves_per_eu(2
 }
 
 typedef void (*MidKernel)(const MidArgs);
-template <bool GROUPED>
-static MidKernel mid_kernel(int fm, int sm, int bm, int wk) {
-  static const MidKernel narrow[2][2] = {{ccq_mid_kernel<1, 0, GROUPED, kMidBM, 1>, ccq_mid_kernel<1, 0, GROUPED, 2 * kMidBM, 1>},
-                                         {ccq_mid_kernel<1, 1, GROUPED, kMidBM, 1>, ccq_mid_kernel<1, 1, GROUPED, 2 * kMidBM, 1>}};
-  static const MidKernel wide[2][3][2] = {
-      {{ccq_mid_kernel<2, 0, GROUPED, kMidBM, 1>, ccq_mid_kernel<2, 0, GROUPED, kMidBM, 2>},
-       {ccq_mid_kernel<3, 0, GROUPED, kMidBM, 1>, ccq_mid_kernel<3, 0, GROUPED, kMidBM, 2>},
-       {ccq_mid_kernel<4, 0, GROUPED, kMidBM, 1>, ccq_mid_kernel<4, 0, GROUPED, kMidBM, 2>}},
-      {{ccq_mid_kernel<2, 1, GROUPED, kMidBM, 1>, ccq_mid_kernel<2, 1, GROUPED, kMidBM, 2>},
-       {ccq_mid_kernel<3, 1, GROUPED, kMidBM, 1>, ccq_mid_kernel<3, 1, GROUPED, kMidBM, 2>},
-       {ccq_mid_kernel<4, 1, GROUPED, kMidBM, 1>, ccq_mid_kernel<4, 1, GROUPED, kMidBM, 2>}}};
-  return fm == 1 ? narrow[sm][bm == kMidBM ? 0 : 1] : wide[sm][fm - 2][wk - 1];
+template <bool GROUPED, int SM>
+static MidKernel mid_kernel(int fm, int bm, bool deep) {
+  switch (fm) {
+    case 1: return bm == kMidBM ? ccq_mid_kernel<1, SM, GROUPED, kMidBM, false>
+                                : (deep ? ccq_mid_kernel<1, SM, GROUPED, 2 * kMidBM, true> : ccq_mid_kernel<1, SM, GROUPED, 2 * kMidBM, false>);
+    case 2: return deep ? ccq_mid_kernel<2, SM, GROUPED, kMidBM, true> : ccq_mid_kernel<2, SM, GROUPED, kMidBM, false>;
+    case 3: return deep ? ccq_mid_kernel<3, SM, GROUPED, kMidBM, true> : ccq_mid_kernel<3, SM, GROUPED, kMidBM, false>;
+    default: return deep ? ccq_mid_kernel<4, SM, GROUPED, kMidBM, true> : ccq_mid_kernel<4, SM, GROUPED, kMidBM, false>;
+  }
 }
 
 // 128-row blocks are built for the narrow format.  With the wide kinds' six code entries per lane and four accumulator tiles
 // mixes (both scale modes) and the hybrid word with fp16 scales need more than the 256 registers that two wavefronts on a
 // SIMD have (32 to 100 bytes of scratch); wide (254 and 240 registers) and the hybrid word with compressed scales (250) would fit.
-static bool mid_has_wide_block(const Layout& L) { return L.tiles[kWide] == 0; }
+static bool mid_has_tall_blocks(const Layout& L) { return L.tiles[kWide] == 0; }
 
-// Sets the K shares of `a` (S across the grid) and launches: `busy` output tiles have rows.
-// With wide kinds and at most one workgroup per CU a wavefront would be alone on its SIMD: there two shares run side by
-// side in one workgroup, where every kind has a k-tile for each.
+// Sets the K shares of `a` (S across the grid, wk in a workgroup) and launches: `busy` output tiles have rows.
+// A wavefront takes about twice as long for a step as the SIMD needs for its instructions, so two to four of them should share
+// one.  With at most one workgroup per CU they come from K shares inside the workgroup, as many as the registers allow (us with
+// one / two / three / four, 0.59 of the CUs: narrow 10624 x 19200, M = 38, 71 / 56 / 51 / 50; mix 5952 x 15072, M = 99, 48 / 40 / 39);
+// narrow 64-row blocks take two shares up to two workgroups per CU (15168 x 3520, M = 710, 158 / 140 / 151 / 149), the others
+// one (wide 1536 x 5968, M = 487, 22 / 28).  A share has at least one k-tile of every kind.
 static int mid_launch(const Layout& L, MidArgs& a, bool grouped, int bm, int S, dim3 grid, int64_t busy, void* stream) {
   const int fm = L.h16 ? 4 : (L.tiles[kNarrow] > 0 ? 1 : 0) | (L.tiles[kWide] > 0 ? 2 : 0);
-  int wk = fm != 1 && busy * S <= device_cus() ? 2 : 1;
+  const int64_t cus = device_cus();
+  const bool narrow64 = fm == 1 && bm == kMidBM, one_each = busy * S <= cus, two_each = busy * S <= 2 * cus;
+  const bool deep = !narrow64 && two_each;
+  int wk = one_each ? mid_waves(fm, bm, deep) : (narrow64 && two_each ? 2 : 1);
   for (int k = 0; k < 2; ++k)
-    if (L.tiles[k] > 0 && L.tiles[k] < S * wk) wk = 1;
+    while (wk > 1 && L.tiles[k] > 0 && L.tiles[k] < S * wk) --wk;
   for (int k = 0; k < 2; ++k) {
     a.sq[k] = L.tiles[k] / (S * wk);
     a.sr[k] = L.tiles[k] % (S * wk);
   }
+  a.wk = wk;
   const size_t max_steps = (size_t)(a.sq[kNarrow] + 1) * kNarrowGroupsPerTile + (size_t)(a.sq[kWide] + 1) * kWideGroupsPerTile;
-  const size_t lds = wk * ((size_t)2 * bm * (fm == 4 ? kMidRowH16 : kMidRow) * 2 + (fm == 3 ? max_steps * 4 : 0));
-  if (lds > 64 * 1024) return CCQ_ERR_UNSUPPORTED;
-  const MidKernel kern = grouped ? mid_kernel<true>(fm, L.scale_mode, bm, wk) : mid_kernel<false>(fm, L.scale_mode, bm, wk);
+  const size_t lds = std::max(wk * ((size_t)2 * bm * (fm == 4 ? kMidRowH16 : kMidRow) * 2 + (fm == 3 ? max_steps * 4 : 0)), (size_t)(wk / 2) * bm * kMidBN * 4);
+  if (lds > 150 * 1024) return CCQ_ERR_UNSUPPORTED;
+  const MidKernel kern = grouped ? (L.scale_mode == 0 ? mid_kernel<true, 0>(fm, bm, deep) : mid_kernel<true, 1>(fm, bm, deep))
+                                 : (L.scale_mode == 0 ? mid_kernel<false, 0>(fm, bm, deep) : mid_kernel<false, 1>(fm, bm, deep));
+  if (lds > 48 * 1024 && hipFuncSetAttribute(reinterpret_cast<const void*>(kern), hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds) != hipSuccess) {
+    (void)hipGetLastError();
+    return CCQ_ERR_HIP;
+  }
   hipLaunchKernelGGL(kern, grid, dim3(256 * wk), lds, static_cast<hipStream_t>(stream), a);
   return hipGetLastError() == hipSuccess ? CCQ_OK : CCQ_ERR_HIP;
 }
@@ -545,8 +618,18 @@ int mid_splits(const Layout& L, int M) {
   return (int)s;
 }
 
+// How many of the `most` shares that mid_splits allows (and the workspace holds) a call takes: with more than two thirds of the
+// CUs busy the shares inside a workgroup do without a pass over partial tiles (wide 4608 x 8160, M = 188, 192 blocks: two
+// across the grid 35, three inside 32 us; 6400 x 3856, M = 299, 155 blocks: three across 38, three inside 44).
+int mid_shares(const Layout& L, int M, int most) {
+  const int64_t blocks = (int64_t)((M + kMidBM - 1) / kMidBM) * ((L.N + kMidBN - 1) / kMidBN);
+  return blocks * 3 > 2 * (int64_t)device_cus() ? 1 : most;
+}
+
 int launch_mid(const ccq_weight* w, const Layout& L, const void* x, int M, int64_t ldx, void* y, int64_t ldy, float* partial, int S,
                void* stream) {
+  // activation offsets within a block are 32-bit, column blocks a grid dimension
+  if (ldx >= (int64_t)1 << 23 || L.N > 65535 * kMidBN) return CCQ_ERR_UNSUPPORTED;
   MidArgs a;
   a.codes = static_cast<const uint8_t*>(w->codes);
   a.scales = static_cast<const uint16_t*>(w->scales);
@@ -566,16 +649,14 @@ int launch_mid(const ccq_weight* w, const Layout& L, const void* x, int M, int64
   a.g_last = L.G - 1;
   a.n_last = L.N - 1;
   a.row_tiles = L.row_tiles;
-  // 128-row blocks where K is not cut, they still give 13 of 16 CUs a workgroup (N = 28000, M = 96, 219 blocks of 256 CUs:
-  // 77.7 -> 65.8 us; N = 24576, M = 128, 192 blocks: 45.8 -> 48.7 us), and they need fewer rounds of workgroups over the
-  // chip than 64-row ones, as each lasts about half as long again (narrow 7168 x 18432: M = 200, two rounds against three,
-  // 109 us either way; M = 160, two against two, 105 against 78 us; 1024 x 20000, M = 300, two against four, 25 against 30 us)
+  // 128-row blocks (narrow): where 64-row ones are more than one to a CU and 128-row ones are not, or where there are more than two
+  // 64-row ones (us with 64 / 128 rows: 4480 x 24294, M = 73, 48 / 35; 5120 x 6064, M = 361, 54 / 48; 2112 x 22144, M = 714, 107 / 98;
+  // 896 x 18642, M = 139, 1.7 and 1.1 to a CU, 17 / 24; 5120 x 1656, M = 784, 0.7 and 0.4 to a CU, 32 / 47).
   const int64_t cus = device_cus();
   const int n_blocks = (L.N + kMidBN - 1) / kMidBN;
   const int64_t wg64 = (int64_t)((M + kMidBM - 1) / kMidBM) * n_blocks, wg128 = (int64_t)((M + 2 * kMidBM - 1) / (2 * kMidBM)) * n_blocks;
-  const bool fewer_rounds = (wg128 + cus - 1) / cus < (wg64 + cus - 1) / cus;
-  const int bm = mid_has_wide_block(L) && S == 1 && wg128 * 16 >= 13 * cus && fewer_rounds ? 2 * kMidBM : kMidBM;
-  a.m_blocks = (M + bm - 1) / bm;
+  const int bm = mid_has_tall_blocks(L) && S == 1 && wg64 > cus && (wg128 <= cus || wg64 > 2 * cus) ? 2 * kMidBM : kMidBM;
+  const int m_blocks = (M + bm - 1) / bm;
   a.tiles[0] = L.tiles[0];
   a.tiles[1] = L.tiles[1];
   a.groups_narrow = L.pgroups[kNarrow];
@@ -583,18 +664,17 @@ int launch_mid(const ccq_weight* w, const Layout& L, const void* x, int M, int64
   a.expert_offsets = nullptr;
   a.codes_stride = a.scales_stride = a.ab_stride = 0;
   for (int k = 0; k < 2; ++k) a.zp[k] = L.zp[k];
-  dim3 grid((unsigned)(a.m_blocks * n_blocks), (unsigned)S);
-  return mid_launch(L, a, false, bm, S, grid, (int64_t)a.m_blocks * n_blocks, stream);
+  return mid_launch(L, a, false, bm, S, dim3((unsigned)m_blocks, (unsigned)n_blocks, (unsigned)S), (int64_t)m_blocks * n_blocks, stream);
 }
 
 // Grouped GEMM with many rows per expert: the same kernel over
 // (row block of the expert, column block, expert); blocks past an expert's rows return at once.  `most_rows` = the
-// largest row count of an expert, `row_blocks` = the 64-row blocks that hold rows, over all experts (from the host copy
+// largest row count of an expert, `row_blocks` = the blocks of 64 and of 128 rows that hold rows, over all experts (from the host copy
 // of the offsets); K is not cut (no workspace).
 int launch_mid_grouped(const ccq_weight* w0, const Layout& L, int E, int64_t codes_stride, int64_t scales_stride, int64_t ab_stride, const void* x,
-                       int64_t ldx, const int32_t* sorted_rows, int P, const int32_t* expert_offsets, int most_rows, int64_t row_blocks, void* y,
+                       int64_t ldx, const int32_t* sorted_rows, int T, int P, const int32_t* expert_offsets, int most_rows, const int64_t (&row_blocks)[2], void* y,
                        int64_t ldy, void* stream) {
-  if (E < 1 || E > 65535 || most_rows < 1) return CCQ_ERR_UNSUPPORTED;
+  if (E < 1 || E > 65535 || most_rows < 1 || (int64_t)T * ldx * 2 >= (int64_t)1 << 32 || L.N > 65535 * kMidBN) return CCQ_ERR_UNSUPPORTED;
   MidArgs a;
   a.codes = static_cast<const uint8_t*>(w0->codes);
   a.scales = static_cast<const uint16_t*>(w0->scales);
@@ -615,8 +695,8 @@ int launch_mid_grouped(const ccq_weight* w0, const Layout& L, int E, int64_t cod
   a.n_last = L.N - 1;
   a.row_tiles = L.row_tiles;
   // 128-row blocks as soon as an expert has more rows than a 64-row block holds
-  const int bm = mid_has_wide_block(L) && most_rows > kMidBM ? 2 * kMidBM : kMidBM;
-  a.m_blocks = (most_rows + bm - 1) / bm;
+  const int bm = mid_has_tall_blocks(L) && most_rows > kMidBM ? 2 * kMidBM : kMidBM;
+  const int m_blocks = (most_rows + bm - 1) / bm;
   a.tiles[0] = L.tiles[0];
   a.tiles[1] = L.tiles[1];
   a.groups_narrow = L.pgroups[kNarrow];
@@ -627,8 +707,7 @@ int launch_mid_grouped(const ccq_weight* w0, const Layout& L, int E, int64_t cod
   a.scales_stride = scales_stride;
   a.ab_stride = ab_stride;
   const int n_blocks = (L.N + kMidBN - 1) / kMidBN;
-  dim3 grid((unsigned)(a.m_blocks * n_blocks), 1u, (unsigned)E);
-  return mid_launch(L, a, true, bm, 1, grid, n_blocks * row_blocks, stream);
+  return mid_launch(L, a, true, bm, 1, dim3((unsigned)m_blocks, (unsigned)n_blocks, (unsigned)E), n_blocks * row_blocks[bm == kMidBM ? 0 : 1], stream);
 }
 
 }  // namespace ccq
