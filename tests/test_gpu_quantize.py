@@ -391,3 +391,17 @@ def test_a_group_without_numbers(fmt):
         assert np.array_equal(g_scales, want_scales)
     bad = np.flatnonzero((got.codes.cpu().numpy().reshape(-1) ^ b.pack_codes(d, codes)) & b.pack_codes(d, care))
     assert bad.size == 0, f"{bad.size} code bytes differ, first at {bad[:5]}"
+
+
+@pytest.mark.parametrize("fmt_name", ["narrow", "wide"])
+@pytest.mark.parametrize("step", [0.0, 2.0 ** -22, 2.0 ** -12, 2.0 ** -6])
+def test_scales_that_hardly_move(fmt_name, step):
+    """Groups on their own grid (the least-squares scale is the first one, both errors are zero), next to it, and far from it; the last
+    rows over the whole range of fp32 scales: which of two scales is the better is decided with and without the sums of errors."""
+    N, K, Q = 32, 256, 31 if fmt_name == "narrow" else 7
+    rng = synth.rng(31, 5)
+    level = rng.integers(-Q, Q + 1, size=(N, K // 64, 64)).astype(np.float64)
+    level[:, :, 0] = Q
+    W = level * (1.0 + step * rng.standard_normal(level.shape)) * 2.0 ** -6
+    W[N - 8:] *= 2.0 ** np.array([-140, -100, -30, -9, 9, 20, 60, 100])[:, None, None]
+    _compare(fmt_name, W.reshape(N, K).astype(np.float32))
