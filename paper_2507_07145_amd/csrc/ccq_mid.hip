@@ -33,6 +33,7 @@ typedef __attribute__((ext_vector_type(2))) __bf16 bf16x2;
 typedef __attribute__((ext_vector_type(2))) float f32x2;
 typedef __attribute__((ext_vector_type(16))) float f32x16;
 typedef __attribute__((ext_vector_type(4))) uint32_t u32x4;
+typedef u32x4 u32x4_dword __attribute__((aligned(4)));
 
 struct MidArgs {
   const uint8_t* codes;
@@ -86,7 +87,7 @@ __device__ __forceinline__ uint32_t dword_sel(const u32x4& v, int j) { return j 
 //           beside them (30, 31 or 32, 63) one by one, and one funnel shift per dword moves the row into place, by
 //           zero or by one weight.
 //   hybrid word (Sec. 3.2)  words h, 2 + h, 4 + h, 6 + h, 8 + h: seven weights and one unused slot are the eight k-slots
-//           of one MFMA, five of them per group; the activation tile is scattered into the same slot order.
+//           of one MFMA, five of them per group; the activation tile lies in the same slot order.
 // FM: formats present (1 narrow, 2 wide, 3 both, 4 the hybrid word; a group map exists only for 3).  SM: scale mode (0 fp16 group
 // scales; 1 the compressed scales of Sec. 3.4: group scale = 4-bit field * per-row super scale, first line of
 // Alg. 2 / Alg. 3; the field of a narrow group comes from the packed scale array, that of a wide group from the
@@ -225,31 +226,34 @@ __global__ void __launch_bounds__(256 * mid_waves(FM, BM, DEEP)) __attribute__((
   };
 
   const uint16_t* xbase = a.x + (GROUPED ? 0 : (int64_t)m0 * a.ldx);
-  uint32_t xoff[MT];
-  const int a_lds_off = (tid >> 3) * ROW + (H16 ? 0 : (tid & 7) * 8);  // of chunk 0; chunk i lies 32 rows further per i
+  // Activation chunks of a step per thread.  Chunk i is 16 bytes of a row of tile i, or, with the hybrid word, the eight slots of one
+  // word (element e of a group sits in slot 8 (e / 7) + e % 7, the eighth slot is zero): ten to a row, 640 to a tile, which 256
+  // threads take in three rounds (the last one repeats half).  A word's seven elements lie in 16 bytes that start on a dword: at an
+  // even word's first element, or one element before an odd word's; word 9 is the last element of the row's last 16 bytes.
+  // (777 rows of 7232 x 5001, compressed scales: 161 us; with eight 16-bit writes per 16 bytes into the slots 168 us.)
+  constexpr int CHUNKS = H16 ? 3 : MT;
+  static_assert(!H16 || BM == 64, "");
+  uint32_t xoff[CHUNKS];
+  int a_lds[H16 ? CHUNKS : 1];   // halfword of chunk i in the tile; of chunk 0: chunk i lies 32 rows further per i
+  bool last_word[CHUNKS];
+  if constexpr (!H16) a_lds[0] = (tid >> 3) * ROW + (tid & 7) * 8;
 #pragma unroll
-  for (int i = 0; i < MT; ++i) {
-    const int c = tid + 256 * i, row = c >> 3, col = c & 7;
+  for (int i = 0; i < CHUNKS; ++i) {
+    int c = tid + 256 * i;
+    if (H16 && c >= 640) c -= 640;
+    const int row = H16 ? c / 10 : c >> 3, u = H16 ? c % 10 : c & 7;
+    const int byte = H16 ? (u == 9 ? 112 : 14 * u - 2 * (u & 1)) : 16 * u;
     int64_t xr = row_off + min(m0 + row, Me - 1);  // rows past the end re-read the last row; their products are never stored
     if constexpr (GROUPED) {
       if (a.sorted_rows) xr = a.sorted_rows[xr];
     } else {
       xr -= m0;
     }
-    xoff[i] = (uint32_t)((xr * a.ldx + col * 8) * 2);
+    xoff[i] = (uint32_t)(xr * a.ldx * 2 + byte);
+    if constexpr (H16) a_lds[i] = row * ROW + 8 * u;
+    last_word[i] = H16 && u == 9;
   }
-  // hybrid word: element e of a group sits in slot 8 (e / 7) + e % 7 (weight 63, alone in the last word, in
-  // slot 72); the unused slots are cleared once and never written again
-  int a_slot[8];
-#pragma unroll
-  for (int j = 0; j < 8; ++j) {
-    const int e = (tid & 7) * 8 + j;
-    a_slot[j] = H16 ? (e == 63 ? 72 : 8 * (e / 7) + e % 7) : 0;
-  }
-  if constexpr (H16) {
-    for (int i = tid; i < 2 * BM * ROW / 8; i += 256) reinterpret_cast<u32x4*>(As)[i] = u32x4{0u, 0u, 0u, 0u};
-    __syncthreads();
-  }
+  const uint32_t odd_word = H16 && (tid & 1) ? 16u : 0u;   // 256 and 640 are even: so is every chunk's word, or none
 
   auto half_of = [](uint32_t d, int j) -> uint32_t { return (j & 1) ? (d >> 16) : (d & 0xFFFFu); };
   auto fp16_of = [&](uint32_t d, int j) -> float { return (float)__builtin_bit_cast(_Float16, (uint16_t)half_of(d, j)); };
@@ -346,34 +350,36 @@ __global__ void __launch_bounds__(256 * mid_waves(FM, BM, DEEP)) __attribute__((
   // condition makes the compiler wait for every outstanding load at the next use of any of them.
   auto run = [&](auto LC) {
     constexpr int LIVE = decltype(LC)::value;
-    auto load_a = [&](u32x4 (&dst)[LIVE], int s) {
+    constexpr int CH = H16 ? CHUNKS : LIVE;
+    using XVec = std::conditional_t<H16, u32x4_dword, u32x4>;
+    auto load_a = [&](u32x4 (&dst)[CH], int s) {
       if constexpr (DEEP) {
         const int64_t off = (int64_t)group_of(s) * (kGroup * 2);
 #pragma unroll
-        for (int i = 0; i < LIVE; ++i) dst[i] = *reinterpret_cast<const u32x4*>(reinterpret_cast<const char*>(xbase) + xoff[i] + off);
+        for (int i = 0; i < CH; ++i) dst[i] = *reinterpret_cast<const XVec*>(reinterpret_cast<const char*>(xbase) + xoff[i] + off);
       } else {
         const char* base = reinterpret_cast<const char*>(xbase + (int64_t)__builtin_amdgcn_readfirstlane(group_of(s)) * kGroup);
 #pragma unroll
-        for (int i = 0; i < LIVE; ++i) {
+        for (int i = 0; i < CH; ++i) {
           uint32_t off = xoff[i];
           asm volatile("" : "+v"(off));
-          dst[i] = *reinterpret_cast<const u32x4*>(base + off);
+          dst[i] = *reinterpret_cast<const XVec*>(base + off);
         }
       }
     };
-    auto store_a = [&](int buf, const u32x4 (&src)[LIVE]) {
+    auto store_a = [&](int buf, const u32x4 (&src)[CH]) {
       uint16_t* dst = As + buf * BM * ROW;
 #pragma unroll
-      for (int i = 0; i < LIVE; ++i) {
+      for (int i = 0; i < CH; ++i) {
         if constexpr (H16) {
+          u32x4 o;
 #pragma unroll
-          for (int q = 0; q < 4; ++q) {
-            const uint32_t d = src[i][q];
-            dst[a_lds_off + i * 32 * ROW + a_slot[2 * q]] = (uint16_t)(d & 0xFFFFu);
-            dst[a_lds_off + i * 32 * ROW + a_slot[2 * q + 1]] = (uint16_t)(d >> 16);
-          }
+          for (int q = 0; q < 3; ++q) o[q] = __builtin_amdgcn_alignbit(src[i][q + 1], src[i][q], odd_word);
+          o[3] = (src[i][3] >> odd_word) & 0xFFFFu;
+          if (last_word[i]) o = u32x4{o[3], 0u, 0u, 0u};
+          *reinterpret_cast<u32x4*>(dst + a_lds[i]) = o;
         } else {
-          *reinterpret_cast<u32x4*>(dst + a_lds_off + i * 32 * ROW) = src[i];
+          *reinterpret_cast<u32x4*>(dst + a_lds[0] + i * 32 * ROW) = src[i];
         }
       }
     };
@@ -392,7 +398,7 @@ __global__ void __launch_bounds__(256 * mid_waves(FM, BM, DEEP)) __attribute__((
     // tiles leave registers for two sets only, and their steps are longer
     constexpr int D = DEEP ? (LIVE >= 3 ? 2 : 4) : (LIVE >= 3 ? 1 : 2);
     constexpr bool AHEAD = DEEP && LIVE <= 2;   // the fragments of the next step are decoded during this one
-    u32x4 areg[D][LIVE];
+    u32x4 areg[D][CH];
     u32x4 bf[KK], bnext[KK];
     int s = 0;
     if constexpr (HAS_N) load_narrow(cn, sn, tA[kNarrow]);
