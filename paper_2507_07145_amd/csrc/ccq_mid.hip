@@ -64,6 +64,7 @@ struct MidArgs {
 
 constexpr int kMidBM = 64;
 constexpr int kMidBN = 128;
+constexpr int kMaxGridY = 65535;
 constexpr int kMidRow = 64 + 8;     // bf16 elements per padded LDS row (144 bytes)
 constexpr int kMidRowH16 = 80 + 8;  // the same for the hybrid word: ten words of eight slots (176 bytes)
 
@@ -101,9 +102,15 @@ __device__ __forceinline__ uint32_t dword_sel(const u32x4& v, int j) { return j 
 // to two workgroups per CU the lean variant is up to a fifth slower: 16 experts of 2048 x 1536, one with 600 rows, 28 against 35 us).
 // A priority for the wavefronts that multiply (or for those that decode), shares that alternate between the two, and a scheduling
 // barrier between the two all cost 3 to 8 %: the compiler's interleaving of one step's decode and products is what overlaps them.
+// FAR: the deep schedule with 64-bit offsets of the activation rows, for rows that lie further apart than 32 bits reach from the
+// first one of a block (dense) or of x (grouped).  In a dense call, whose offsets count from the block, it is level with 32-bit
+// ones and stands for both; grouped calls lose by it (narrow, 16 experts of 2048 x 1536, 80 rows each, 19.8 / 21.1 us).
+enum Schedule { kLean, kDeep, kFar };
 constexpr int mid_waves(int fm, int bm, bool deep) { return deep ? 2 : (fm == 1 && bm == kMidBM ? 4 : 3); }
-template <int FM, int SM, bool GROUPED, int BM, bool DEEP>
-__global__ void __launch_bounds__(256 * mid_waves(FM, BM, DEEP)) __attribute__((amdgpu_waves_per_eu(mid_waves(FM, BM, DEEP), DEEP && FM != 4 ? 2 : 8))) ccq_mid_kernel(const MidArgs a) {
+template <int FM, int SM, bool GROUPED, int BM, Schedule SCHEDULE>
+__global__ void __launch_bounds__(256 * mid_waves(FM, BM, SCHEDULE != kLean))
+    __attribute__((amdgpu_waves_per_eu(mid_waves(FM, BM, SCHEDULE != kLean), SCHEDULE != kLean && FM != 4 ? 2 : 8))) ccq_mid_kernel(const MidArgs a) {
+  constexpr bool DEEP = SCHEDULE != kLean;
   constexpr bool HAS_N = FM == 1 || FM == 3, HAS_W = FM >= 2, META = FM == 3, H16 = FM == 4;
   constexpr int ROW = H16 ? kMidRowH16 : kMidRow;
   constexpr int MT = BM / 32;          // 32-row accumulator tiles, and 16-byte activation chunks per thread and step (chunk i: rows of tile i)
@@ -233,7 +240,8 @@ __global__ void __launch_bounds__(256 * mid_waves(FM, BM, DEEP)) __attribute__((
   // (777 rows of 7232 x 5001, compressed scales: 161 us; with eight 16-bit writes per 16 bytes into the slots 168 us.)
   constexpr int CHUNKS = H16 ? 3 : MT;
   static_assert(!H16 || BM == 64, "");
-  uint32_t xoff[CHUNKS];
+  using RowOffset = std::conditional_t<SCHEDULE == kFar, int64_t, uint32_t>;
+  RowOffset xoff[CHUNKS];   // bytes from xbase
   int a_lds[H16 ? CHUNKS : 1];   // halfword of chunk i in the tile; of chunk 0: chunk i lies 32 rows further per i
   bool last_word[CHUNKS];
   if constexpr (!H16) a_lds[0] = (tid >> 3) * ROW + (tid & 7) * 8;
@@ -249,7 +257,7 @@ __global__ void __launch_bounds__(256 * mid_waves(FM, BM, DEEP)) __attribute__((
     } else {
       xr -= m0;
     }
-    xoff[i] = (uint32_t)(xr * a.ldx * 2 + byte);
+    xoff[i] = (RowOffset)(xr * a.ldx * 2 + byte);
     if constexpr (H16) a_lds[i] = row * ROW + 8 * u;
     last_word[i] = H16 && u == 9;
   }
@@ -558,14 +566,21 @@ __global__ void __launch_bounds__(256 * mid_waves(FM, BM, DEEP)) __attribute__((
 }
 
 typedef void (*MidKernel)(const MidArgs);
+template <int FM, int SM, bool GROUPED, int BM>
+static MidKernel mid_schedule(Schedule s) {
+  if (s == kLean) return ccq_mid_kernel<FM, SM, GROUPED, BM, kLean>;
+  if constexpr (GROUPED) {
+    if (s == kDeep) return ccq_mid_kernel<FM, SM, GROUPED, BM, kDeep>;
+  }
+  return ccq_mid_kernel<FM, SM, GROUPED, BM, kFar>;
+}
 template <bool GROUPED, int SM>
-static MidKernel mid_kernel(int fm, int bm, bool deep) {
+static MidKernel mid_kernel(int fm, int bm, Schedule s) {
   switch (fm) {
-    case 1: return bm == kMidBM ? ccq_mid_kernel<1, SM, GROUPED, kMidBM, false>
-                                : (deep ? ccq_mid_kernel<1, SM, GROUPED, 2 * kMidBM, true> : ccq_mid_kernel<1, SM, GROUPED, 2 * kMidBM, false>);
-    case 2: return deep ? ccq_mid_kernel<2, SM, GROUPED, kMidBM, true> : ccq_mid_kernel<2, SM, GROUPED, kMidBM, false>;
-    case 3: return deep ? ccq_mid_kernel<3, SM, GROUPED, kMidBM, true> : ccq_mid_kernel<3, SM, GROUPED, kMidBM, false>;
-    default: return deep ? ccq_mid_kernel<4, SM, GROUPED, kMidBM, true> : ccq_mid_kernel<4, SM, GROUPED, kMidBM, false>;
+    case 1: return bm == kMidBM ? ccq_mid_kernel<1, SM, GROUPED, kMidBM, kLean> : mid_schedule<1, SM, GROUPED, 2 * kMidBM>(s);
+    case 2: return mid_schedule<2, SM, GROUPED, kMidBM>(s);
+    case 3: return mid_schedule<3, SM, GROUPED, kMidBM>(s);
+    default: return mid_schedule<4, SM, GROUPED, kMidBM>(s);
   }
 }
 
@@ -580,11 +595,12 @@ static bool mid_has_tall_blocks(const Layout& L) { return L.tiles[kWide] == 0; }
 // one / two / three / four, 0.59 of the CUs: narrow 10624 x 19200, M = 38, 71 / 56 / 51 / 50; mix 5952 x 15072, M = 99, 48 / 40 / 39);
 // narrow 64-row blocks take two shares up to two workgroups per CU (15168 x 3520, M = 710, 158 / 140 / 151 / 149), the others
 // one (wide 1536 x 5968, M = 487, 22 / 28).  A share has at least one k-tile of every kind.
-static int mid_launch(const Layout& L, MidArgs& a, bool grouped, int bm, int S, dim3 grid, int64_t busy, void* stream) {
+// E: experts (0: a dense call).  `far`: the activation rows lie too far apart for 32-bit offsets.
+static int mid_launch(const Layout& L, MidArgs& a, int E, int bm, bool far, int S, int m_blocks, int64_t busy, void* stream) {
   const int fm = L.h16 ? 4 : (L.tiles[kNarrow] > 0 ? 1 : 0) | (L.tiles[kWide] > 0 ? 2 : 0);
   const int64_t cus = device_cus();
   const bool narrow64 = fm == 1 && bm == kMidBM, one_each = busy * S <= cus, two_each = busy * S <= 2 * cus;
-  const bool deep = !narrow64 && two_each;
+  const bool deep = !narrow64 && (two_each || far);
   int wk = one_each ? mid_waves(fm, bm, deep) : (narrow64 && two_each ? 2 : 1);
   for (int k = 0; k < 2; ++k)
     while (wk > 1 && L.tiles[k] > 0 && L.tiles[k] < S * wk) --wk;
@@ -596,14 +612,33 @@ static int mid_launch(const Layout& L, MidArgs& a, bool grouped, int bm, int S, 
   const size_t max_steps = (size_t)(a.sq[kNarrow] + 1) * kNarrowGroupsPerTile + (size_t)(a.sq[kWide] + 1) * kWideGroupsPerTile;
   const size_t lds = std::max(wk * ((size_t)2 * bm * (fm == 4 ? kMidRowH16 : kMidRow) * 2 + (fm == 3 ? max_steps * 4 : 0)), (size_t)(wk / 2) * bm * kMidBN * 4);
   if (lds > 150 * 1024) return CCQ_ERR_UNSUPPORTED;
-  const MidKernel kern = grouped ? (L.scale_mode == 0 ? mid_kernel<true, 0>(fm, bm, deep) : mid_kernel<true, 1>(fm, bm, deep))
-                                 : (L.scale_mode == 0 ? mid_kernel<false, 0>(fm, bm, deep) : mid_kernel<false, 1>(fm, bm, deep));
+  const Schedule schedule = far ? kFar : (deep ? kDeep : kLean);
+  const MidKernel kern = E > 0 ? (L.scale_mode == 0 ? mid_kernel<true, 0>(fm, bm, schedule) : mid_kernel<true, 1>(fm, bm, schedule))
+                               : (L.scale_mode == 0 ? mid_kernel<false, 0>(fm, bm, schedule) : mid_kernel<false, 1>(fm, bm, schedule));
   if (lds > 48 * 1024 && hipFuncSetAttribute(reinterpret_cast<const void*>(kern), hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds) != hipSuccess) {
     (void)hipGetLastError();
     return CCQ_ERR_HIP;
   }
-  hipLaunchKernelGGL(kern, grid, dim3(256 * wk), lds, static_cast<hipStream_t>(stream), a);
-  return hipGetLastError() == hipSuccess ? CCQ_OK : CCQ_ERR_HIP;
+  // column blocks are a grid dimension: more than it holds take several launches
+  const int n_blocks = (L.N + kMidBN - 1) / kMidBN;
+  for (int b0 = 0; b0 < n_blocks; b0 += kMaxGridY) {
+    const int64_t n0 = (int64_t)b0 * kMidBN, rt0 = n0 / kRowsPerTile;
+    MidArgs p = a;
+    auto advance = [](auto& ptr, int64_t by) { if (ptr) ptr += by; };
+    advance(p.codes, rt0 * a.row_tile_bytes);
+    advance(p.scales, rt0 * a.row_tile_scale_halfs);
+    advance(p.alpha, n0);
+    advance(p.beta, n0);
+    advance(p.scale_super, n0);
+    advance(p.y, n0);
+    advance(p.partial, n0);
+    p.row_tiles -= (int)rt0;
+    p.n_last -= (int)n0;
+    const dim3 grid((unsigned)m_blocks, (unsigned)std::min(kMaxGridY, n_blocks - b0), (unsigned)(E > 0 ? E : S));
+    hipLaunchKernelGGL(kern, grid, dim3(256 * wk), lds, static_cast<hipStream_t>(stream), p);
+    if (hipGetLastError() != hipSuccess) return CCQ_ERR_HIP;
+  }
+  return CCQ_OK;
 }
 
 // K shares for the mid-M kernel.  Every share costs a pass of fp32 partial tiles through memory (written, then
@@ -634,8 +669,6 @@ int mid_shares(const Layout& L, int M, int most) {
 
 int launch_mid(const ccq_weight* w, const Layout& L, const void* x, int M, int64_t ldx, void* y, int64_t ldy, float* partial, int S,
                void* stream) {
-  // activation offsets within a block are 32-bit, column blocks a grid dimension
-  if (ldx >= (int64_t)1 << 23 || L.N > 65535 * kMidBN) return CCQ_ERR_UNSUPPORTED;
   MidArgs a;
   a.codes = static_cast<const uint8_t*>(w->codes);
   a.scales = static_cast<const uint16_t*>(w->scales);
@@ -661,7 +694,8 @@ int launch_mid(const ccq_weight* w, const Layout& L, const void* x, int M, int64
   const int64_t cus = device_cus();
   const int n_blocks = (L.N + kMidBN - 1) / kMidBN;
   const int64_t wg64 = (int64_t)((M + kMidBM - 1) / kMidBM) * n_blocks, wg128 = (int64_t)((M + 2 * kMidBM - 1) / (2 * kMidBM)) * n_blocks;
-  const int bm = mid_has_tall_blocks(L) && S == 1 && wg64 > cus && (wg128 <= cus || wg64 > 2 * cus) ? 2 * kMidBM : kMidBM;
+  const bool far = (2 * kMidBM - 1) * ldx * 2 + 2 * kGroup > (int64_t)1 << 32;   // (a 64-row narrow block has the lean schedule only)
+  const int bm = mid_has_tall_blocks(L) && (far || (S == 1 && wg64 > cus && (wg128 <= cus || wg64 > 2 * cus))) ? 2 * kMidBM : kMidBM;
   const int m_blocks = (M + bm - 1) / bm;
   a.tiles[0] = L.tiles[0];
   a.tiles[1] = L.tiles[1];
@@ -670,7 +704,7 @@ int launch_mid(const ccq_weight* w, const Layout& L, const void* x, int M, int64
   a.expert_offsets = nullptr;
   a.codes_stride = a.scales_stride = a.ab_stride = 0;
   for (int k = 0; k < 2; ++k) a.zp[k] = L.zp[k];
-  return mid_launch(L, a, false, bm, S, dim3((unsigned)m_blocks, (unsigned)n_blocks, (unsigned)S), (int64_t)m_blocks * n_blocks, stream);
+  return mid_launch(L, a, 0, bm, far, S, m_blocks, (int64_t)m_blocks * n_blocks, stream);
 }
 
 // Grouped GEMM with many rows per expert: the same kernel over
@@ -680,7 +714,7 @@ int launch_mid(const ccq_weight* w, const Layout& L, const void* x, int M, int64
 int launch_mid_grouped(const ccq_weight* w0, const Layout& L, int E, int64_t codes_stride, int64_t scales_stride, int64_t ab_stride, const void* x,
                        int64_t ldx, const int32_t* sorted_rows, int T, int P, const int32_t* expert_offsets, int most_rows, const int64_t (&row_blocks)[2], void* y,
                        int64_t ldy, void* stream) {
-  if (E < 1 || E > 65535 || most_rows < 1 || (int64_t)T * ldx * 2 >= (int64_t)1 << 32 || L.N > 65535 * kMidBN) return CCQ_ERR_UNSUPPORTED;
+  if (E < 1 || E > 65535 || most_rows < 1) return CCQ_ERR_UNSUPPORTED;
   MidArgs a;
   a.codes = static_cast<const uint8_t*>(w0->codes);
   a.scales = static_cast<const uint16_t*>(w0->scales);
@@ -701,7 +735,8 @@ int launch_mid_grouped(const ccq_weight* w0, const Layout& L, int E, int64_t cod
   a.n_last = L.N - 1;
   a.row_tiles = L.row_tiles;
   // 128-row blocks as soon as an expert has more rows than a 64-row block holds
-  const int bm = mid_has_tall_blocks(L) && most_rows > kMidBM ? 2 * kMidBM : kMidBM;
+  const bool far = (int64_t)T * ldx * 2 > (int64_t)1 << 32;
+  const int bm = mid_has_tall_blocks(L) && (far || most_rows > kMidBM) ? 2 * kMidBM : kMidBM;
   const int m_blocks = (most_rows + bm - 1) / bm;
   a.tiles[0] = L.tiles[0];
   a.tiles[1] = L.tiles[1];
@@ -713,7 +748,7 @@ int launch_mid_grouped(const ccq_weight* w0, const Layout& L, int E, int64_t cod
   a.scales_stride = scales_stride;
   a.ab_stride = ab_stride;
   const int n_blocks = (L.N + kMidBN - 1) / kMidBN;
-  return mid_launch(L, a, true, bm, 1, dim3((unsigned)m_blocks, (unsigned)n_blocks, (unsigned)E), n_blocks * row_blocks[bm == kMidBM ? 0 : 1], stream);
+  return mid_launch(L, a, E, bm, far, 1, m_blocks, n_blocks * row_blocks[bm == kMidBM ? 0 : 1], stream);
 }
 
 }  // namespace ccq

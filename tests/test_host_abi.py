@@ -286,3 +286,19 @@ def test_native_call_module_leaves_odd_arguments_to_the_checks():
         b.gemm_static(w, x, x)
     with pytest.raises(AssertionError):
         b.grouped_gemm(w, x, offs, offs)
+
+
+@pytest.mark.skipif(bool(os.path.exists("/dev/kfd")), reason="the pointers are made up: only where nothing can be launched")
+@pytest.mark.parametrize("kinds", [["narrow"], ["wide"], ["narrow", "wide"], ["h16"]])
+@pytest.mark.parametrize("M,ldx", [(300, 1 << 23), (100, 1 << 25), (40, 1 << 29), (2000, 1 << 24)])
+def test_row_stride_does_not_change_the_workspace(kinds, M, ldx):
+    """A call that brings the workspace the library asks for gets as far as its launch, whatever the row stride."""
+    K = N = 8192
+    gf = synth.group_format_map(K // 64, 32, synth.rng(3, 9)) if len(kinds) == 2 else None
+    fmts = b.H16 if kinds == ["h16"] else [{"narrow": b.NARROW, "wide": b.WIDE}[k] for k in kinds]
+    w = b.descriptor(K, N, fmts, gf)
+    w.codes = w.scales = w.code_alpha = w.code_beta = w.meta = 4096
+    need = b.gemm_workspace_bytes(w, M)
+    vp = ctypes.c_void_p
+    rc = [b.load().ccq_gemm(ctypes.byref(w), vp(4096), M, ld, vp(4096), N, vp(4096), need, vp(0)) for ld in (K, ldx)]
+    assert rc == [-7, -7]
