@@ -160,6 +160,10 @@ int ccq_pack_device(const ccq_weight *w, int32_t E, const void *canonical_codes,
  *   x DEVICE bf16 [M][ldx], y DEVICE bf16 [M][ldy] (round to nearest even),
  *   fp32 accumulation.  ldx >= K, ldy >= N, in elements, multiples of 8; columns N.. of y are not written.
  *   The per-row arrays of the descriptor (code_alpha, code_beta, scale_super) hold N entries: no padding.
+ *   Infinite activations: where weights are multiplied as signed numbers (more than 32 rows; 17 to 32 rows on wide, mixed
+ *   and hybrid-word weights; in ccq_grouped_gemm experts with more than 32 rows, given the host offsets) an infinity gives an
+ *   infinity of the weight's sign, NaN with a zero weight, or with the padding where the last group of K shares its k-tile with
+ *   some.  Elsewhere the zero-point is taken off by a second sum and an infinity gives NaN in all outputs of its row.
  *   M = 0 is a no-op.  workspace DEVICE, workspace_bytes >= the value
  *   ccq_pack_info reports for M_max >= M (may be NULL if that value is 0). */
 int ccq_gemm(const ccq_weight *w, const void *x, int32_t M, int64_t ldx, void *y, int64_t ldy,

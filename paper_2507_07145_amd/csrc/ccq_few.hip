@@ -97,6 +97,15 @@ __device__ __forceinline__ float frag_sum(const u32x4 o, float s) {
   s = __builtin_amdgcn_fdot2_f32_bf16(__builtin_bit_cast(bf16x2, o3), ones, s, false);
   return s;
 }
+// Weights as bf16 integers 128 + state -> bf16((128 + state + cneg) s).
+__device__ __forceinline__ u32x4 signed_weights(const u32x4 w, float cneg, float s) {
+  auto pair = [&](uint32_t d) {
+    const f32x2 v = {(__builtin_bit_cast(float, d << 16) + cneg) * s, (__builtin_bit_cast(float, d & 0xFFFF0000u) + cneg) * s};
+    return __builtin_bit_cast(uint32_t, __builtin_convertvector(v, bf16x2));
+  };
+  const uint32_t w0 = w.x, w1 = w.y, w2 = w.z, w3 = w.w;
+  return u32x4{pair(w0), pair(w1), pair(w2), pair(w3)};
+}
 template <int CTRL>
 __device__ __forceinline__ float dpp_add(float s) {
   return s + __builtin_bit_cast(float, __builtin_amdgcn_mov_dpp(__builtin_bit_cast(int, s), CTRL, 0xF, 0xF, true));
@@ -111,9 +120,14 @@ constexpr int waves_per_simd(int fm, int mt, int rt, int wn) {
 constexpr uint32_t buffer_bytes(int fm, int mt) { return (fm == 1 ? 8192u + 256u : 12288u + 256u) * mt; }
 constexpr int max_waves(int fm, int mt, int rt, int wn) { return rt == 1 && mt == 1 && (fm == 1 || (fm != 3 && wn == 4)) ? 16 : 8; }
 
+// A wavefront's part of a k-tile: 16-byte code segments and scales of its RT row tiles.
+template <int RT, int NC>
+struct HeldTile { u32x4 c[RT][NC]; u32x4 s[RT]; };
+
 template <int FM, int SM, int MT, int RT, int WN>
 __global__ void __launch_bounds__(64 * max_waves(FM, MT, RT, WN)) __attribute__((amdgpu_waves_per_eu(waves_per_simd(FM, MT, RT, WN)))) ccq_few_kernel(const Args a) {
   extern __shared__ __align__(16) unsigned char smem[];
+  __shared__ int not_finite;   // of a dense call's only pass
   constexpr uint32_t kThreads = 64u * WN;
   constexpr uint32_t kFrags = (FM == 1 ? 8192u : 12288u) * MT, kBuf = buffer_bytes(FM, MT);   // one stage: four groups' fragments, then their start values
   const uint32_t lane = threadIdx.x & 63u, tid = threadIdx.x % kThreads;
@@ -156,14 +170,17 @@ __global__ void __launch_bounds__(64 * max_waves(FM, MT, RT, WN)) __attribute__(
   uint32_t c4300 = 0x43004300u, mask_n = 0x003F003Fu, mask_w = FM == 4 ? 0x00070007u : 0x000F000Fu;
   float magic = 8388608.f;
   asm volatile("" : "+v"(c4300), "+s"(mask_n), "+s"(mask_w), "+v"(magic));
+  if (threadIdx.x == 0) not_finite = 0;   // (barriers before the first sum)
   auto lds_barrier = [&]() {
     __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup", "local");
     __builtin_amdgcn_s_barrier();
     __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
   };
 
-  auto pass = [&](auto MC, int32_t m0) {
+  // SIGNED: weights are multiplied as bf16((128 + state - (128 + zp)) s), without start values (see below)
+  auto pass = [&](auto MC, auto SC, int32_t m0) -> bool {
     constexpr int LM = decltype(MC)::value;   // 16-row activation tiles of this pass
+    constexpr bool SIGNED = decltype(SC)::value;
     f32x4 acc[RT][LM];
 #pragma unroll
     for (int r = 0; r < RT; ++r)
@@ -189,7 +206,7 @@ __global__ void __launch_bounds__(64 * max_waves(FM, MT, RT, WN)) __attribute__(
       const size_t code_off = NARROW || FM != 3 ? 0 : (size_t)a.tiles[kNarrow] * kNarrowTileBytes;
       const size_t scale_off = NARROW || FM != 3 ? 0 : (size_t)a.tiles[kNarrow] * kNarrowTileScaleHalfs;
 
-      struct Tile { u32x4 c[RT][NC]; u32x4 s[RT]; };
+      using Tile = HeldTile<RT, NC>;
       auto load_tile = [&](Tile& v, int t) {
         t = max(min(t, tB - 1), 0);
 #pragma unroll
@@ -388,18 +405,28 @@ __global__ void __launch_bounds__(64 * max_waves(FM, MT, RT, WN)) __attribute__(
                   if constexpr (SM == 0) sc = (float)__builtin_bit_cast(_Float16, (uint16_t)hw);
                   else sc = (float)(H16 ? hw & 0x1FFFu : (hw >> 8) & 0xFu);
                 }
-                if (lg > 0 || r > 0) add(acc[(r + RT - 1) % RT]);
-                asm volatile("" : "+v"(sc));   // converted once: v_fma_f32 issues at twice the rate of v_fma_mix_f32
-                psc = sc;
+                if constexpr (SIGNED) {
+                  if constexpr (SM == 1) sc *= (float)__builtin_bit_cast(_Float16, (uint16_t)ssup[r]);
 #pragma unroll
-                for (int m = 0; m < LM; ++m) {
-                  p[m] = cin[m];
+                  for (int k = 0; k < T; ++k) {
+                    const u32x4 sw = signed_weights(w[k], cneg, sc);
 #pragma unroll
-                  for (int k = 0; k < T; ++k) p[m] = mfma(o[m][k], w[k], p[m]);
+                    for (int m = 0; m < LM; ++m) acc[r][m] = mfma(o[m][k], sw, acc[r][m]);
+                  }
+                } else {
+                  if (lg > 0 || r > 0) add(acc[(r + RT - 1) % RT]);
+                  asm volatile("" : "+v"(sc));   // converted once: v_fma_f32 issues at twice the rate of v_fma_mix_f32
+                  psc = sc;
+#pragma unroll
+                  for (int m = 0; m < LM; ++m) {
+                    p[m] = cin[m];
+#pragma unroll
+                    for (int k = 0; k < T; ++k) p[m] = mfma(o[m][k], w[k], p[m]);
+                  }
                 }
               }
             }
-            add(acc[RT - 1]);
+            if constexpr (!SIGNED) add(acc[RT - 1]);
           }
           if (h == SPT - 1) {
             __builtin_amdgcn_sched_barrier(0);
@@ -423,8 +450,26 @@ __global__ void __launch_bounds__(64 * max_waves(FM, MT, RT, WN)) __attribute__(
     if constexpr (FM == 2 || FM == 3) kind(std::integral_constant<int, kKW>{});
     if constexpr (FM == 4) kind(std::integral_constant<int, kKH>{});
 
+    // Infinite activations: the products with 128 + state and the start value are infinities of both signs, their sum is NaN.  Dense
+    // calls of 17 to 32 rows on the wide kinds, whose neighbours take kernels that multiply signed weights, are done again with
+    // those where a sum is not finite: an infinity then gives infinities (NaN with a zero weight), as there.
+    const bool again = !SIGNED && FM != 1 && MT == 2 && !a.expert_offsets && a.M > 16;
+    if (again) {
+      float f = 0.f;   // NaN if an addend is infinite or NaN
+#pragma unroll
+      for (int r = 0; r < RT; ++r)
+#pragma unroll
+        for (int m = 0; m < LM; ++m)
+#pragma unroll
+          for (int i = 0; i < 4; ++i) f = __builtin_fmaf(acc[r][m][i], 0.f, f);
+      if (f != f) not_finite = 1;
+    }
     if (a.wk > 1) {
       f32x4* red = reinterpret_cast<f32x4*>(smem);   // the activations' place: all are done with them
+      // the lane, asked for anew: addresses made of it are not held in registers over the loops above
+      uint32_t every = ~0u;
+      asm volatile("" : "+s"(every));
+      const uint32_t lane = __builtin_amdgcn_mbcnt_hi(every, __builtin_amdgcn_mbcnt_lo(every, 0u));
       if (wk > 0) {
 #pragma unroll
         for (int r = 0; r < RT; ++r)
@@ -439,27 +484,34 @@ __global__ void __launch_bounds__(64 * max_waves(FM, MT, RT, WN)) __attribute__(
 #pragma unroll
             for (int m = 0; m < LM; ++m) acc[r][m] += red[((((k - 1) * WN + wn) * RT + r) * LM + m) * 64u + lane];
       }
+    } else if (again) {
+      lds_barrier();
     }
+    if (again && __builtin_amdgcn_readfirstlane(not_finite)) return false;
     if (wk == 0) {
 #pragma unroll
       for (int r = 0; r < RT; ++r) {
         const uint32_t col = (rt0 + r) * 16u + n;
         if (rt0 + r < (uint32_t)a.row_tiles && col <= (uint32_t)a.n_last) {
-          const float mul = SM == 1 ? (float)__builtin_bit_cast(_Float16, (uint16_t)ssup[r]) : 1.f;
+          const float mul = SM == 1 && !SIGNED ? (float)__builtin_bit_cast(_Float16, (uint16_t)ssup[r]) : 1.f;
 #pragma unroll
           for (int m = 0; m < LM; ++m)
 #pragma unroll
             for (int i = 0; i < 4; ++i) {
               const int32_t row = m0 + 16 * m + 4 * (int32_t)kq + i;
-              if (row < rows) a.y[(size_t)(row0 + row) * (size_t)a.ldy + col] = to_bf16(SM == 1 ? acc[r][m][i] * mul : acc[r][m][i]);
+              if (row < rows) a.y[(size_t)(row0 + row) * (size_t)a.ldy + col] = to_bf16(SM == 1 && !SIGNED ? acc[r][m][i] * mul : acc[r][m][i]);
             }
         }
       }
     }
+    return true;
   };
   for (int32_t m0 = 0; m0 < rows; m0 += 16 * MT) {
-    if (MT == 1 || rows - m0 <= 16) pass(std::integral_constant<int, 1>{}, m0);
-    else pass(std::integral_constant<int, MT>{}, m0);
+    if (MT == 1 || rows - m0 <= 16) {
+      pass(std::integral_constant<int, 1>{}, std::false_type{}, m0);
+    } else if (!pass(std::integral_constant<int, MT>{}, std::false_type{}, m0)) {
+      if constexpr (FM != 1 && MT == 2) pass(std::integral_constant<int, MT>{}, std::true_type{}, m0);
+    }
   }
 }
 
