@@ -118,7 +118,7 @@ constexpr int waves_per_simd(int fm, int mt, int rt, int wn) {
   return fm == 3 || wn == 2 ? 3 : 4;
 }
 constexpr uint32_t buffer_bytes(int fm, int mt) { return (fm == 1 ? 8192u + 256u : 12288u + 256u) * mt; }
-constexpr int max_waves(int fm, int mt, int rt, int wn) { return rt == 1 && mt == 1 && (fm == 1 || (fm != 3 && wn == 4)) ? 16 : 8; }
+constexpr int max_waves(int fm, int mt, int rt, int wn) { return rt == 1 && mt == 1 && fm != 3 && wn == 4 ? 16 : 8; }
 
 // A wavefront's part of a k-tile: 16-byte code segments and scales of its RT row tiles.
 template <int RT, int NC>
@@ -254,14 +254,23 @@ __global__ void __launch_bounds__(64 * max_waves(FM, MT, RT, WN)) __attribute__(
         if constexpr (FM == 3) return a.meta[gbase + min(s * 4 + lg, last)];
         return min(gbase + lg + s * 4, a.g_last);
       };
+      // Mixes: the groups of a stage are asked for a stage before its activations.  (Asked for with them, every stage waits for the
+      // map, and with it for the codes requested before it: 8 experts of 7168 x 512 with one row each, 17.1 us.)
+      int groups[FM == 3 ? NUT : 1];
+      if constexpr (FM == 3)
+#pragma unroll
+        for (int i = 0; i < NUT; ++i) groups[i] = group_of(0, ulg[i]);
       u32x4 xr[NUT][NCH];
       auto load_x = [&](int s) {
 #pragma unroll
         for (int i = 0; i < NUT; ++i) {
-          const uint32_t g = (uint32_t)group_of(s, ulg[i]);
+          const uint32_t g = (uint32_t)(FM == 3 ? groups[FM == 3 ? i : 0] : group_of(s, ulg[i]));
 #pragma unroll
           for (int t = 0; t < NCH; ++t) xr[i][t] = load16(a.x, xoff[i][t] + g * (kGroup * 2));
         }
+        if constexpr (FM == 3)
+#pragma unroll
+          for (int i = 0; i < NUT; ++i) groups[i] = group_of(s + 1, ulg[i]);
       };
       const uint32_t frag_off[2] = {(kq * 16u + (n ^ (2u * kq))) * 16u, (kq * 16u + (n ^ (2u * kq + 1u))) * 16u};
       const float cneg = a.cneg[kt];
@@ -520,7 +529,11 @@ template <int FM, int SM>
 static Kernel pick(int mt, int rt, int wn) {
   if (rt == 1 && wn == 2) return mt == 1 ? ccq_few_kernel<FM, SM, 1, 1, 2> : ccq_few_kernel<FM, SM, 2, 1, 2>;
   if (rt == 1 && wn == 4) return mt == 1 ? ccq_few_kernel<FM, SM, 1, 1, 4> : ccq_few_kernel<FM, SM, 2, 1, 4>;
-  if (rt == 2 && wn == 8) return mt == 1 ? ccq_few_kernel<FM, SM, 1, 2, 8> : ccq_few_kernel<FM, SM, 2, 2, 8>;
+  if (rt == 2 && wn == 8) {
+    if (mt == 2) return ccq_few_kernel<FM, SM, 2, 2, 8>;
+    if constexpr (FM == 1) return ccq_few_kernel<FM, SM, 1, 2, 8>;
+    return nullptr;
+  }
   if (rt == 2 && wn == 4) {
     if (mt == 1) return ccq_few_kernel<FM, SM, 1, 2, 4>;
     if constexpr (FM != 3) return ccq_few_kernel<FM, SM, 2, 2, 4>;   // (a mix does not fit the registers)
@@ -544,34 +557,59 @@ struct Shape {
   int rt = 0, wn = 0, wk = 0;
   uint32_t lds = 0;
 };
-// The launch shape, by an estimate in cycles of a SIMD: instructions of a wavefront's stage (decode and products of RT x MT
-// tiles, its part of the staging, the rest) times the wavefronts that share the SIMD, or the latency of one wavefront
-// where few do, times the stages of the longest share of K, times the rounds of workgroups over the chip.  The constants are
-// fitted to 1500 timings of all shapes on 150 random calls (K 512 .. 28672, N 512 .. 28672, 1 .. 255 matrices); the shape taken was on
-// average 2.3 % slower than the best one.  Rows past the sixteenth are counted as if half of the matrices had them.
-static Shape choose_shape(const Layout& L, int fm, int mt, int64_t matrices) {
-  static const int kShapes[][3] = {{1, 2, 1}, {1, 2, 2}, {1, 2, 4}, {1, 2, 8}, {1, 4, 1}, {1, 4, 2}, {1, 4, 4}, {2, 4, 1}, {2, 4, 2}, {2, 8, 1}};
-  const double lm = mt == 1 ? 1.0 : 1.5;
+// Wavefronts that a SIMD holds of an instance, by the registers that the compiler gave it.
+static int waves_held(int fm, int mt, int rt, int wn) {
+  if (fm == 1) return mt == 2 ? 3 : (rt == 2 ? 4 : 5);
+  if (fm == 3) return mt == 1 && rt == 1 ? 3 : 2;
+  return mt == 2 ? 2 : (rt == 1 && wn == 4 ? 4 : 3);
+}
+
+// The launch shape, by an estimate in cycles.  A stage of a wavefront: its instructions (decode and products of RT x LM tiles, its part of
+// the staging, the rest) times the wavefronts that share the SIMD, or the latency of one wavefront where few do, and the wait at
+// the barrier, which other workgroups on the CU cover.  Times the stages of the longest share of K and the passes over the
+// rows, with what starting a pass takes; times the rounds of workgroups over the chip.  Where the grid has experts without
+// rows, their workgroups cost a dispatch each, and the others land unevenly on the CUs.  The constants are fitted to 33000 timings: all
+// shapes on 3404 random calls (K 512 .. 28672, N 512 .. 28672, 1 .. 256 matrices, 1 .. 512 tokens, with and without the host offsets).
+// The shape taken is on average 2 % slower than the best one (twentieth of the calls: 12 to 17 %); with the estimate of one pass over
+// the rows of all matrices that came before it was 7 to 18 % (us, before / now: 256 experts of 1024 x 2048, 16 tokens, hybrid word
+// 52 / 31; 64 of 7168 x 2048, 4 tokens without host offsets, mix 86 / 46).
+// Eight wavefronts of two row tiles each are not taken with experts without rows (the lone workgroup of a CU: 114 experts of 704 x
+// 1493, 16 tokens, hybrid word, 21 against 12 us) and not built for one 16-row tile on the wide kinds (best in 10 of 146 calls).
+static Shape choose_shape(const Layout& L, int fm, const FewRows& f) {
+  static const int kShapes[][3] = {{1, 2, 1}, {1, 2, 2}, {1, 2, 4}, {1, 4, 1}, {1, 4, 2}, {1, 4, 4}, {2, 4, 1}, {2, 4, 2}, {2, 8, 1}};
+  const int mt = f.most_rows <= 16 ? 1 : 2;
   const int64_t cus = device_cus();
+  const double empty = 1.0 - (double)f.with_rows / (double)f.matrices;
   Shape best;
   double least = 0.0;
   for (const auto& c : kShapes) {
     const int rt = c[0], wn = c[1], wk = c[2], waves = wn * wk;
     if (waves > max_waves(fm, mt, rt, wn) || (fm == 3 && mt == 2 && rt == 2 && wn == 4)) continue;
+    if (wn == 8 && (empty > 0.0 || (fm != 1 && mt == 1))) continue;
     const uint32_t lds = std::max<uint32_t>((uint32_t)(wk * 2) * buffer_bytes(fm, mt), (uint32_t)((wk - 1) * wn * rt * mt) * 1024u);
     if (lds > 150u * 1024u) continue;
-    const int64_t slots = std::max<int64_t>(1, std::min<int64_t>(4 * waves_per_simd(fm, mt, rt, wn) / waves, 160 * 1024 / lds));   // workgroups of a CU
-    const int64_t wgs = matrices * ((L.row_tiles + rt * wn - 1) / (rt * wn));
-    auto stage = [&](int kind, double per_simd) {
-      const double issue = kind == kNarrow ? rt * 4 * (25.0 + 4.2 * lm) + lm * 8 / wn * 15 + 32 : rt * 4 * (26.0 + 5.2 * lm) + lm * 4 / wn * 54 + 32;
-      return std::max(per_simd * issue * 4.6, issue * 9.5 + 450);
-    };
-    auto round = [&](double per_simd) {
-      return ((L.tiles[kNarrow] + wk - 1) / wk) * stage(kNarrow, per_simd) + 2 * ((L.tiles[kWide] + wk - 1) / wk) * stage(kWide, per_simd);
+    const int64_t slots = std::max<int64_t>(1, std::min<int64_t>(4 * waves_held(fm, mt, rt, wn) / waves, 160 * 1024 / lds));   // workgroups of a CU
+    const int64_t blocks = (L.row_tiles + rt * wn - 1) / (rt * wn), wgs = f.with_rows * blocks;
+    // all passes of a workgroup with `held` of them on its CU
+    auto workgroup = [&](double held) {
+      const double per_simd = held * waves / 4.0;
+      double t = 0.0;
+      for (int lm = 1; lm <= 2; ++lm) {
+        auto stage = [&](double tile, double unit, double rest) {
+          const double issue = rt * 4 * tile + unit * lm / wn + rest;
+          return std::max(per_simd * issue * 5.5, issue * 7.6 + 340.0) + 144.0 * waves / 4.0 / held;
+        };
+        t += f.passes[lm - 1] / (double)f.with_rows *
+             (((L.tiles[kNarrow] + wk - 1) / wk) * stage(21.6 + 4.2 * lm, 180.0, 32.0) + 2 * ((L.tiles[kWide] + wk - 1) / wk) * stage(21.6 + 8.8 * lm, 208.0, 23.0) + 6500.0 + 750.0 * wk);
+      }
+      return t;
     };
     const int64_t full = wgs / (cus * slots), rest = wgs % (cus * slots);
-    double t = full * round(slots * waves / 4.0) + 780.0 * wk;
-    if (rest) t += round((double)((rest + cus - 1) / cus) * waves / 4.0);
+    double t = (double)full * workgroup((double)slots) + 6.0 * (double)((f.matrices - f.with_rows) * blocks);
+    if (rest) {
+      const double even = (double)((rest + cus - 1) / cus), uneven = 1.0 + 1.72 * empty * (double)rest / (double)cus + (1.0 - empty) * (even - 1.0);
+      t += workgroup(empty > 0.0 ? std::min((double)slots, uneven) : even);
+    }
     if (best.rt == 0 || t < least) {
       least = t;
       best.rt = rt, best.wn = wn, best.wk = wk, best.lds = lds;
@@ -580,14 +618,20 @@ static Shape choose_shape(const Layout& L, int fm, int mt, int64_t matrices) {
   return best;
 }
 
+static int format_of(const Layout& L) { return L.h16 ? 4 : (L.tiles[kNarrow] > 0 ? 1 : 0) | (L.tiles[kWide] > 0 ? 2 : 0); }
+
 }  // namespace few
 
-// T: rows of x.  `most_rows`: the most rows that a matrix has, as far as the caller knows (more are walked in passes of 32).
-int launch_few(const SkinnyCall& c, int T, int most_rows) {
+void few_shape(const Layout& L, const FewRows& f, int (&shape)[4]) {
+  const few::Shape s = few::choose_shape(L, few::format_of(L), f);
+  shape[0] = f.most_rows <= 16 ? 1 : 2, shape[1] = s.rt, shape[2] = s.wn, shape[3] = s.wk;
+}
+
+// T: rows of x.
+int launch_few(const SkinnyCall& c, int T, const FewRows& f) {
   using namespace few;
   const Layout& L = c.L;
-  const int64_t matrices = c.expert_offsets ? (c.n_active > 0 ? c.n_active : c.E) : 1;
-  if ((int64_t)T * c.ldx * 2 >= (int64_t)1 << 32 || matrices > 65535) return CCQ_ERR_UNSUPPORTED;   // activation offsets are 32-bit
+  if ((int64_t)T * c.ldx * 2 >= (int64_t)1 << 32 || f.matrices > 65535) return CCQ_ERR_UNSUPPORTED;   // activation offsets are 32-bit
   Args a;
   a.codes = static_cast<const uint8_t*>(c.w->codes);
   a.scales = static_cast<const uint16_t*>(c.w->scales);
@@ -617,9 +661,8 @@ int launch_few(const SkinnyCall& c, int T, int most_rows) {
   }
   a.n_active = c.n_active;
   std::memcpy(a.active_ids, c.active_ids, sizeof(a.active_ids));
-  const int fm = L.h16 ? 4 : (L.tiles[kNarrow] > 0 ? 1 : 0) | (L.tiles[kWide] > 0 ? 2 : 0);
-  const int mt = most_rows <= 16 ? 1 : 2;
-  const Shape s = choose_shape(L, fm, mt, matrices);
+  const int fm = format_of(L), mt = f.most_rows <= 16 ? 1 : 2;
+  const Shape s = choose_shape(L, fm, f);
   const Kernel k = pick_kernel(fm, L.scale_mode, mt, s.rt, s.wn);
   if (!k) return CCQ_ERR_UNSUPPORTED;
   a.wk = s.wk;
@@ -627,7 +670,7 @@ int launch_few(const SkinnyCall& c, int T, int most_rows) {
     (void)hipGetLastError();
     return CCQ_ERR_HIP;
   }
-  const dim3 grid((unsigned)((L.row_tiles + s.wn * s.rt - 1) / (s.wn * s.rt)), (unsigned)matrices);
+  const dim3 grid((unsigned)((L.row_tiles + s.wn * s.rt - 1) / (s.wn * s.rt)), (unsigned)f.matrices);
   hipLaunchKernelGGL(k, grid, dim3((unsigned)(64 * s.wn * s.wk)), s.lds, static_cast<hipStream_t>(c.stream), a);
   return hipGetLastError() == hipSuccess ? CCQ_OK : CCQ_ERR_HIP;
 }

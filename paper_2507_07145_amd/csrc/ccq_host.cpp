@@ -214,6 +214,60 @@ static bool dense_few(const Layout& L, int M) {
   }
 }
 
+static FewRows few_rows_dense(int M) {
+  FewRows f;
+  f.most_rows = M;
+  f.passes[0] = M <= 16 ? 1.0 : 0.0;
+  f.passes[1] = M <= 16 ? 0.0 : 1.0;
+  return f;
+}
+
+static int grouped_tile_rows(int E, int P) {
+  // rows one pass holds: twice the mean rows per expert, rounded up to 16, at most 64
+  int64_t mean2 = E > 0 ? (2 * (int64_t)P + E - 1) / E : 0;
+  int rows = (int)std::min<int64_t>(kMaxSkinnyM, std::max<int64_t>(16, ((mean2 + 15) / 16) * 16));
+  return rows;
+}
+
+// Whether the grid of a grouped call has the experts with rows only, which travel in the kernel arguments.
+static bool experts_listed(int E, int active) { return active < E && active <= kMaxActiveList && E <= 65536; }
+
+// `listed`: the grid has the experts with rows only.
+static FewRows few_rows_grouped(int E, int P, const int32_t* offsets_host, bool listed) {
+  FewRows f;
+  f.matrices = E;
+  f.passes[0] = 0.0;
+  if (offsets_host) {
+    f.with_rows = 0;
+    for (int e = 0; e < E; ++e) {
+      const int rows = offsets_host[e + 1] - offsets_host[e];
+      f.with_rows += rows > 0 ? 1 : 0;
+      f.most_rows = std::max(f.most_rows, rows);
+    }
+    for (int e = 0; e < E; ++e) {
+      const int rows = offsets_host[e + 1] - offsets_host[e], rest = rows % 32;
+      if (f.most_rows <= 16) {
+        f.passes[0] += rows > 0 ? 1 : 0;
+      } else {
+        f.passes[0] += rest > 0 && rest <= 16 ? 1 : 0;
+        f.passes[1] += rows / 32 + (rest > 16 ? 1 : 0);
+      }
+    }
+    if (listed) f.matrices = f.with_rows;
+  } else {
+    f.with_rows = std::min(E, P);
+    f.most_rows = grouped_tile_rows(E, P);
+    const double mean = (double)P / (double)f.with_rows;
+    if (f.most_rows <= 16) {
+      f.passes[0] = (double)f.with_rows * std::max(1.0, mean / 16.0);
+    } else {
+      f.passes[0] = 0.5 * (double)f.with_rows;
+      f.passes[1] = (double)f.with_rows * std::max(0.5, mean / 32.0);
+    }
+  }
+  return f;
+}
+
 // Workspace the per-row-tile kernel needs for M rows in the library's own decomposition: it walks the rows in
 // passes of kMaxSkinnyM and a last, shorter one.
 static int64_t skinny_need(const Layout& L, int M) {
@@ -526,7 +580,7 @@ int gemm_dispatch(const ccq_weight* w, const void* x, int32_t M, int64_t ldx, vo
     c.ldy = ldy;
     c.M = M;
     c.stream = stream;
-    rc = launch_few(c, M, M);
+    rc = launch_few(c, M, few_rows_dense(M));
     if (rc != CCQ_ERR_UNSUPPORTED) return rc;
   }
 
@@ -643,13 +697,6 @@ extern "C" int ccq_gemm_ex(const ccq_weight* w, const void* x, int32_t M, int64_
   return gemm_dispatch(w, x, M, ldx, y, ldy, workspace, workspace_bytes, hip_stream, launch);
 }
 
-static int grouped_tile_rows(int E, int P) {
-  // rows one pass holds: twice the mean rows per expert, rounded up to 16, at most 64
-  int64_t mean2 = E > 0 ? (2 * (int64_t)P + E - 1) / E : 0;
-  int rows = (int)std::min<int64_t>(kMaxSkinnyM, std::max<int64_t>(16, ((mean2 + 15) / 16) * 16));
-  return rows;
-}
-
 // Launch shape of a grouped call.  `active` = experts that have rows (known only when the caller passes the
 // host copy of the offsets; otherwise all E are assumed busy).  With few active experts -- a decode step routes
 // a handful of tokens to 8 of 256 experts -- the row blocks alone cannot fill the chip, so K is cut into more
@@ -719,7 +766,7 @@ extern "C" int ccq_grouped_gemm(const ccq_weight* w0, int32_t E, int64_t codes_s
       row_blocks[1] += ceil_div(rows, 128);
     }
   }
-  if (expert_offsets_host && active < E && active <= kMaxActiveList && E <= 65536) {
+  if (expert_offsets_host && experts_listed(E, active)) {
     // launch over the experts that have rows only
     c.n_active = active;
     int k = 0;
@@ -763,12 +810,15 @@ extern "C" int ccq_grouped_gemm(const ccq_weight* w0, int32_t E, int64_t codes_s
   c.sorted_rows = sorted_rows;
   c.expert_offsets = expert_offsets_dev;
   c.stream = hip_stream;
-  // up to 32 rows per expert, as far as is known (more are walked 32 at a time): the few-row kernel
-  rc = launch_few(c, T, expert_offsets_host ? most_rows : grouped_tile_rows(E, P));
-  if (rc != CCQ_ERR_UNSUPPORTED) return rc;
+  if (most_rows > 1) {
+    // up to 32 rows per expert, as far as is known (more are walked 32 at a time): the few-row kernel
+    rc = launch_few(c, T, few_rows_grouped(E, P, expert_offsets_host, c.n_active > 0));
+    if (rc != CCQ_ERR_UNSUPPORTED) return rc;
+  }
   if (most_rows == 1) {
-    // no expert has more than one row (on formats or shapes the kernel above is not built for): the
-    // one-held-row kernel (wavefront-private staging, no 16-row activation tile)
+    // no expert has more than one row (on formats or shapes the kernels above are not built for): the
+    // one-held-row kernel (wavefront-private staging, no 16-row activation tile; few-row kernel against it, us: mix, 8 experts of
+    // 7168 x 512, 14.7 / 9.3, 7 of 4992 x 1903 16.4 / 12.4; narrow, 8 of 4864 x 1183, 11.7 / 9.2)
     c.m_tile_hint = 1;
     c.d = choose_decomp(L, 1, std::max(1, active), P);
     // the grid spans all E experts and most of them have no row: beyond about 64 workgroups per CU the dispatch of the
@@ -780,6 +830,22 @@ extern "C" int ccq_grouped_gemm(const ccq_weight* w0, int32_t E, int64_t codes_s
   }
   if (c.d.S > 1) c.partial = static_cast<float*>(workspace);
   return launch_skinny(c);
+}
+
+// For tests, no part of the interface: the launch shape of the few-row kernel for a dense call of `rows` rows (E = 0) or a grouped one:
+// 16-row tiles of a pass, row tiles of a wavefront, wavefronts side by side, shares of K; dense calls: whether the kernel is taken.
+extern "C" int ccq_few_launch_shape(const ccq_weight* w, int32_t E, int32_t rows, const int32_t* expert_offsets_host, int32_t* out) {
+  Layout L;
+  const int rc = make_layout(w, &L);
+  if (rc != CCQ_OK) return rc;
+  if (E < 0 || rows <= 0 || !out) return CCQ_ERR_BAD_PARAM;
+  int active = 0;
+  for (int e = 0; expert_offsets_host && e < E; ++e) active += expert_offsets_host[e + 1] > expert_offsets_host[e] ? 1 : 0;
+  int shape[4];
+  few_shape(L, E == 0 ? few_rows_dense(rows) : few_rows_grouped(E, rows, expert_offsets_host, expert_offsets_host && experts_listed(E, active)), shape);
+  for (int i = 0; i < 4; ++i) out[i] = shape[i];
+  out[4] = E == 0 && dense_few(L, rows);
+  return CCQ_OK;
 }
 
 // The GPU quantizer is built for every layout the multiply kernels read.

@@ -111,7 +111,15 @@ struct SkinnyCall {
 };
 int launch_skinny(const SkinnyCall& c);
 // The same call with few rows per matrix, one launch without a workspace (ccq_few.hip; `d` and `partial` are not looked at).
-int launch_few(const SkinnyCall& c, int T, int most_rows);
+// What is known of its rows: those are walked in passes of 16, or of 32 with a last one of 16 or 32.
+struct FewRows {
+  int64_t matrices = 1;           // of the grid
+  int64_t with_rows = 1;          // those that have rows (without the host offsets: the most that can have)
+  int most_rows = 0;              // of a matrix (without the host offsets: about twice the mean); passes of 32 from 17 on
+  double passes[2] = {1.0, 0.0};  // of 16 and of 32 rows, over all matrices
+};
+int launch_few(const SkinnyCall& c, int T, const FewRows& f);
+void few_shape(const Layout& L, const FewRows& f, int (&shape)[4]);   // 16-row tiles of a pass, row tiles and wavefronts side by side, shares of K
 
 constexpr int kGemvMaxM = 4;       // rows of the four-row kernel
 
