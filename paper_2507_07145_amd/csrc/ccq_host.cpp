@@ -192,23 +192,28 @@ static DensePath dense_path(const Layout& L, int M) {
 
 // Dense calls of 2 to 32 rows that take the one-launch kernel of ccq_few.hip instead of the path above (whose workspace is
 // asked for all the same).  That kernel cuts K inside a workgroup only: it wins where K is short, or N long enough for its
-// workgroups to fill the chip, and saves the pass over the partial tiles (new against old, us):
-//   narrow, 5 - 16 rows    K 1984 N 1152 6.0 / 7.9, K 3328 N 20940 13.0 / 19.5; K 4224 N 6612 9.7 / 9.3
-//   narrow, 17 - 32 rows   K 2496 N 4336 9.2 / 11.8, K 4288 N 23888 20 / 24; K 7680 N 1440 16 / 9.5
+// workgroups to fill the chip, and saves the pass over the partial tiles.  From 190 shapes of every format (K 512 .. 19200, N 512 ..
+// 28672) with 2 to 32 rows; new against old, us, on both sides of the lines:
+//   narrow, 5 - 16 rows     K 2752 N 1613 7.2 / 8.0, K 2624 N 16612 11.4 / 13.4; K 3392 N 17581 13.4 / 11.5
+//   narrow, 17 - 32         K 1216 N 559 7.7 / 8.1, K 1728 N 3769 8.1 / 8.9, K 4480 N 25064 22.3 / 28.1; K 1728 N 1024 7.3 / 6.4
 //   wide, hybrid word, 2 - 16   K 832 N 7718 5.4 / 8.0, K 1984 N 3936 7.5 / 7.9; K 2560 N 4772 9.1 / 8.2
-//   wide kinds, 17 - 32    K 1152 N 7145 9.0 / 19, K 8384 N 14224 29 / 38; K 8192 N 8192 26 / 21, K 10432 N 2330 31 / 17
-// (2 - 4 rows on the narrow format have a one-launch kernel already; so has a K that the old path does not cut.  Mixes of
-// 2 - 16 rows: 0.97 of the old time at K 640, 1.2 to 1.4 of it beyond 1600.)
+//   wide, 17 - 32           K 2560 N 975 10.7 / 15.7, K 6080 N 23789 28.6 / 39.4; K 3648 N 1109 14.3 / 13.1, K 7040 N 6605 22.4 / 19.9
+//   hybrid word, 17 - 32    K 3584 N 650 14.1 / 19.0, K 8768 N 12416 29.7 / 41.8; K 4800 N 814 1.15 of the old time
+//   mixes, 17 - 32          K 5248 N 516 19.8 / 33.3, K 8192 N 17423 43.9 / 49.4; K 10816 N 21124 1.2, K 11904 N 917 1.23 of the old time
+// Of the calls that take it, 25 of 3000 are more than 3 % slower than on the old path, none by more than 16 %.  (2 - 4 rows on the
+// narrow format have a one-launch kernel already; so has a K that the old path does not cut.  Mixes of 2 - 16 rows: up to 1.2 of the
+// old time from K 768 on.)
 static bool dense_few(const Layout& L, int M) {
   if (M < 2 || M > 32) return false;
   const bool narrow = L.tiles[kWide] == 0, mix = L.tiles[kNarrow] > 0 && !narrow;
   if (M > 16) {
-    if (narrow) return L.K <= 2560 || L.K <= 4 * L.row_tiles;
-    return L.K <= 4096 || L.K <= (mix ? 8 : 10) * L.row_tiles;
+    if (narrow) return L.K <= 1536 || (L.K <= 3072 && L.row_tiles >= 128) || L.K <= 4 * L.row_tiles;
+    if (mix) return L.K <= 10000;
+    return L.h16 ? L.K <= 4096 || L.K <= 12 * L.row_tiles : L.K <= 3584 || L.K <= 10 * L.row_tiles;
   }
   int a = 0, b = 0, sn = 0, sw = 0;
   switch (dense_path(L, M)) {
-    case kPathGemv16: return (L.K <= 3072 || L.K <= 3 * L.row_tiles) && gemv16_shape(L, device_cus(), kMaxSplitsK, &a, &b) && L.tiles[kNarrow] > a;
+    case kPathGemv16: return L.K <= 3072 && gemv16_shape(L, device_cus(), kMaxSplitsK, &a, &b) && L.tiles[kNarrow] > a;
     case kPathGemv16NW: return !mix && L.K <= 2048 && gemv16_nw_shape(L, device_cus(), kMaxSplitsK, &a, &b, &sn, &sw) && sn + sw > 1;
     default: return false;
   }
