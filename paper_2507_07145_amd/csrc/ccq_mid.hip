@@ -737,7 +737,11 @@ int launch_mid_grouped(const ccq_weight* w0, const Layout& L, int E, int64_t cod
   // 128-row blocks as soon as an expert has more rows than a 64-row block holds
   const bool far = (int64_t)T * ldx * 2 > (int64_t)1 << 32;
   const int bm = mid_has_tall_blocks(L) && (far || most_rows > kMidBM) ? 2 * kMidBM : kMidBM;
-  const int m_blocks = (most_rows + bm - 1) / bm;
+  // Where most blocks of the grid are past their expert's rows (one expert has most of them), the first blocks of the others, a
+  // row block count apart, would with an even count share a few of the chip's eight dies (narrow, 8 experts of 7168 x 512, one with
+  // 2000 rows, seven with 4: sixteen row blocks 93, seventeen 62 us).
+  int m_blocks = (most_rows + bm - 1) / bm;
+  if (m_blocks % 2 == 0 && 2 * row_blocks[bm == kMidBM ? 0 : 1] < (int64_t)m_blocks * E) ++m_blocks;
   a.tiles[0] = L.tiles[0];
   a.tiles[1] = L.tiles[1];
   a.groups_narrow = L.pgroups[kNarrow];
