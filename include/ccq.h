@@ -223,9 +223,8 @@ int ccq_grouped_gemm(const ccq_weight *w0, int32_t E, int64_t codes_stride, int6
                      const int32_t *expert_offsets_host, void *y, int64_t ldy, void *workspace,
                      int64_t workspace_bytes, void *hip_stream);
 
-/* Recommended workspace for P output rows (at most 64 MiB).  ccq_grouped_gemm works with any smaller
- * workspace, down to none: it only cuts K into fewer shares, which matters when few experts have rows
- * (pass expert_offsets_host so that the library can see that). */
+/* Workspace for P output rows: 0 (-1 for invalid arguments).  No kernel of ccq_grouped_gemm uses one; any that is
+ * brought is left alone. */
 int64_t ccq_grouped_workspace_bytes(const ccq_weight *w0, int32_t E, int32_t P);
 
 /* The offline quantizer on the GPU: Alg. 1 (group scale absmax / (2^(L-1) - 1), nearest codeword of the

@@ -97,8 +97,7 @@ bool decomp_ok(const Layout& L, const Decomp& d) {
 
 static int ceil_div(int a, int b) { return (a + b - 1) / b; }
 
-Decomp choose_decomp(const Layout& L, int M, int experts, int rows_total) {
-  (void)rows_total;
+Decomp choose_decomp(const Layout& L, int M, int experts) {
   Decomp d;
   const int64_t cus = device_cus();
   const int nt = L.tiles[kNarrow] + L.tiles[kWide];  // k-tiles per row tile
@@ -117,11 +116,8 @@ Decomp choose_decomp(const Layout& L, int M, int experts, int rows_total) {
     // wavefronts side by side that share one staged activation chunk: four, or eight for mixed formats with many
     // rows, whose staging (a gather through the group map, one row tile per wavefront) is the larger part of the
     // work (config 3, M = 16: 61 -> 42 us; 8192 x 8192 mixed: 21.8 -> 18.8 us; 4096 x 4096 is better off with four)
-    // -- and for grouped calls on long rows of narrow-format weights (config 4, K = 7168: 108 -> 96 us; with K = 2048
-    // four are better)
     const bool mixed_many_rows = L.tiles[kNarrow] > 0 && L.tiles[kWide] > 0 && L.row_tiles >= 2 * cus && M <= 16;
-    const bool grouped_long_k = experts > 1 && L.tiles[kWide] == 0 && L.tiles[kNarrow] >= 24 && M <= 32;
-    const int wr_max = (mixed_many_rows || grouped_long_k) ? 8 : 4;
+    const int wr_max = mixed_many_rows ? 8 : 4;
     d.WR = (int)std::min<int64_t>(wr_max, std::max(1, L.row_tiles / d.RT));
     d.WK = 1;
     int64_t row_blocks = (int64_t)ceil_div(L.row_tiles, d.RT * d.WR) * experts;
@@ -279,7 +275,7 @@ static int64_t skinny_need(const Layout& L, int M) {
   int64_t need = 0;
   for (int mc : {M >= kMaxSkinnyM ? kMaxSkinnyM : 0, M % kMaxSkinnyM}) {
     if (mc == 0) continue;
-    const Decomp d = choose_decomp(L, mc, 1, mc);
+    const Decomp d = choose_decomp(L, mc, 1);
     if (d.S > 1) need = std::max(need, (int64_t)d.S * mc * L.Npad * 4);
   }
   return need;
@@ -541,7 +537,7 @@ static int pass_decomp(const Layout& L, int mc, const ccq_launch* launch, Decomp
     d->S = launch->splits_k ? launch->splits_k : 1;
     if (!decomp_ok(L, *d)) return CCQ_ERR_BAD_PARAM;
   } else {
-    *d = choose_decomp(L, mc, 1, mc);
+    *d = choose_decomp(L, mc, 1);
   }
   return CCQ_OK;
 }
@@ -702,27 +698,11 @@ extern "C" int ccq_gemm_ex(const ccq_weight* w, const void* x, int32_t M, int64_
   return gemm_dispatch(w, x, M, ldx, y, ldy, workspace, workspace_bytes, hip_stream, launch);
 }
 
-// Launch shape of a grouped call.  `active` = experts that have rows (known only when the caller passes the
-// host copy of the offsets; otherwise all E are assumed busy).  With few active experts -- a decode step routes
-// a handful of tokens to 8 of 256 experts -- the row blocks alone cannot fill the chip, so K is cut into more
-// shares, as many as the workspace the caller brought allows.
-static Decomp grouped_decomp(const Layout& L, int E, int P, int active, int64_t workspace_bytes) {
-  Decomp d = choose_decomp(L, grouped_tile_rows(E, P), std::max(1, active), P);
-  const int64_t per_share = (int64_t)P * L.Npad * 4;
-  if (d.S > 1 && per_share > 0) d.S = (int)std::max<int64_t>(1, std::min<int64_t>(d.S, workspace_bytes / per_share));
-  return d;
-}
-
-// Recommended workspace: room for the K shares a call with few active experts would like (at most 64 MiB); a
-// smaller workspace, down to none, only means fewer shares.
+// No kernel that a grouped call takes uses a workspace.
 extern "C" int64_t ccq_grouped_workspace_bytes(const ccq_weight* w0, int32_t E, int32_t P) {
   Layout L;
   if (make_layout(w0, &L) != CCQ_OK || E <= 0 || P < 0) return -1;
-  if (P == 0) return 0;
-  const int active_min = std::max(1, std::min(E, (P + kMaxSkinnyM - 1) / kMaxSkinnyM));
-  Decomp d = choose_decomp(L, grouped_tile_rows(E, P), active_min, P);
-  const int64_t want = d.S > 1 ? (int64_t)d.S * P * L.Npad * 4 : 0;
-  return std::min<int64_t>(want, (int64_t)64 << 20);
+  return 0;
 }
 
 extern "C" int ccq_grouped_gemm(const ccq_weight* w0, int32_t E, int64_t codes_stride, int64_t scales_stride, int64_t ab_stride,
@@ -825,15 +805,16 @@ extern "C" int ccq_grouped_gemm(const ccq_weight* w0, int32_t E, int64_t codes_s
     // one-held-row kernel (wavefront-private staging, no 16-row activation tile; few-row kernel against it, us: mix, 8 experts of
     // 7168 x 512, 14.7 / 9.3, 7 of 4992 x 1903 16.4 / 12.4; narrow, 8 of 4864 x 1183, 11.7 / 9.2)
     c.m_tile_hint = 1;
-    c.d = choose_decomp(L, 1, std::max(1, active), P);
+    c.d = choose_decomp(L, 1, std::max(1, active));
     // the grid spans all E experts and most of them have no row: beyond about 64 workgroups per CU the dispatch of the
     // empty ones shows, and fewer, larger workgroups (several row tiles side by side, at most 512 threads) are faster
     const int wr_max = std::max(1, std::min(std::min(4, 8 / c.d.WK), L.row_tiles / c.d.RT));
     while (c.d.WR * 2 <= wr_max && (int64_t)ceil_div(L.row_tiles, c.d.RT * c.d.WR) * (c.n_active > 0 ? c.n_active : E) > 64 * (int64_t)device_cus()) c.d.WR *= 2;
   } else {
-    c.d = grouped_decomp(L, E, P, active, workspace ? workspace_bytes : 0);
+    // what the kernels above do not take (4 GiB of activations and more, over 65535 matrices)
+    c.d = choose_decomp(L, grouped_tile_rows(E, P), std::max(1, active));
+    c.d.S = 1;
   }
-  if (c.d.S > 1) c.partial = static_cast<float*>(workspace);
   return launch_skinny(c);
 }
 

@@ -82,7 +82,7 @@ struct Decomp {
   int WK = 1;  // wavefronts along K per workgroup
   int S = 1;   // workgroups along K
 };
-Decomp choose_decomp(const Layout& L, int M, int experts, int rows_total);
+Decomp choose_decomp(const Layout& L, int M, int experts);
 bool decomp_ok(const Layout& L, const Decomp& d);
 
 // Kernel launchers (ccq_skinny.hip).  All pointers DEVICE unless noted.

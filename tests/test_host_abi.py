@@ -302,3 +302,11 @@ def test_row_stride_does_not_change_the_workspace(kinds, M, ldx):
     vp = ctypes.c_void_p
     rc = [b.load().ccq_gemm(ctypes.byref(w), vp(4096), M, ld, vp(4096), N, vp(4096), need, vp(0)) for ld in (K, ldx)]
     assert rc == [-7, -7]
+
+
+def test_grouped_calls_ask_for_no_workspace():
+    lib = b.load()
+    for kinds in ([b.NARROW], [b.WIDE], b.H16):
+        w = b.descriptor(7168, 2048, kinds)
+        assert [lib.ccq_grouped_workspace_bytes(ctypes.byref(w), E, P) for E, P in ((64, 512), (8, 8), (256, 4096), (4, 0))] == [0] * 4
+        assert lib.ccq_grouped_workspace_bytes(ctypes.byref(w), 0, 4) == -1 and lib.ccq_grouped_workspace_bytes(ctypes.byref(w), 4, -1) == -1
