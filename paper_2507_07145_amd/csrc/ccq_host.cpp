@@ -166,21 +166,20 @@ static DensePath dense_path(const Layout& L, int M) {
     // 256-row tiles pay off once they fill enough of the chip.  Both kernels are bound by the same two things (matrix
     // core time, and the vector work of decoding a weight tile once per row block of the output), so their times
     // are compared in units of one output element per round of workgroups over the chip's CUs; the relative costs
-    // per element are ratios measured between the kernels, not times: the 256-row kernel costs 1.0 with 192-column
-    // blocks and 1.22 with 128 or 256 columns, up to 40 % more when more than half of the CUs are busy (the clock
-    // sinks under a full matrix load); the 64-row kernel, whose blocks of 64 (or 128) rows decode every weight tile four
-    // (or two) times as often, costs 2.4 and about 0.4 of a round in fixed set-up.  (2.4 and 0.42 were fitted before the
-    // 64-row kernel lost its lane exchange and gained 128-row blocks, up to a tenth and a quarter of its time: near the line the
-    // 256-row kernel is taken a little early.)
+    // per element are ratios between the kernels, not times: the 256-row kernel costs 1.0 with 192-column blocks, 1.3 with 128 and 1.2
+    // with 256 columns; the 64-row kernel, which decodes every weight tile four times as often (twice with 128-row blocks), costs
+    // 1.37 and 1.1 of a round in fixed set-up, and past two 64-row blocks per CU, where 128-row ones start a second round,
+    // at least four rounds.  Fitted to both kernels on 2325 calls of 144 to 2048 rows: 27 are more than 5 % slower than on the other
+    // one, by 12 % at most (with 2.4 and 0.42 for the 64-row kernel, from before its K shares and 128-row blocks: 219, up to 42 %;
+    // 11264 x 5020, 1500 rows, 277 against 195 us).
     const int64_t cus = device_cus();
     const int bn = prefill_block_cols(L, M);
     const int64_t wg_p = (int64_t)ceil_div(M, 256) * ceil_div(L.N, bn);
     const int64_t rounds_p = (wg_p + cus - 1) / cus;
-    const double fill = (double)wg_p / (double)(rounds_p * cus);
-    const double t_p = (double)rounds_p * 256.0 * bn * (bn == 192 ? 1.0 : 1.22) * (1.0 + 0.8 * std::max(0.0, fill - 0.5));
-    const int64_t wg_m = (int64_t)ceil_div(M, 64) * ceil_div(L.N, 128);
-    const double rounds_m = std::max(1.0, (double)wg_m / (double)cus);   // its workgroups are short: partial rounds overlap
-    const double t_m = (rounds_m + 0.42) * 64.0 * 128.0 * 2.4;
+    const double t_p = (double)rounds_p * 256.0 * bn * (bn == 192 ? 1.0 : (bn == 128 ? 1.3 : 1.2));
+    const double wg_m = (double)((int64_t)ceil_div(M, 64) * ceil_div(L.N, 128)) / (double)cus;
+    const double rounds_m = std::max(wg_m > 2.0 ? 4.0 : 1.0, wg_m);   // its workgroups are short: partial rounds overlap
+    const double t_m = (rounds_m + 1.1) * 64.0 * 128.0 * 1.37;
     return t_p <= t_m ? kPathPrefill : kPathMid;
   }
   return kPathMid;
@@ -771,9 +770,9 @@ extern "C" int ccq_grouped_gemm(const ccq_weight* w0, int32_t E, int64_t codes_s
       (c.n_active > 0 || (int64_t)(E - with_rows) * L.row_tiles <= std::max<int64_t>(64 * (int64_t)device_cus(), (int64_t)with_rows * L.row_tiles / 2))) {
     // one or a few tokens' decode step: every expert that has rows is a GEMV (or a four-row product) of its own.  (Not
     // when the grid would have to span many more experts without rows than with: dispatching their workgroups costs
-    // more than it saves.  Letting experts with more rows take one pass over their weights per four rows measured
-    // slower than the per-row-tile kernel once most experts need the four-row body: 181 against 150 us on 224 experts
-    // of 1024 x 7168 with 512 rows.)
+    // more than it saves.  Few-row kernel against it with two to four rows, 120 random calls, us: 10 experts of 1024 x 2968
+    // 7.5 / 6.1, 173 of 512 x 6520 78 / 52; nine are faster on the few-row kernel, K of 7, 11 or 13 k-tiles, the shares of one k-tile
+    // that these leave: 35 of 3328 x 4999 50 / 87.)
     rc = launch_gemv_grouped(w0, L, E, codes_stride, scales_stride, ab_stride, x, ldx, sorted_rows, expert_offsets_dev, y, ldy, most_rows,
                              c.n_active, c.active_ids, hip_stream);
     if (rc != CCQ_ERR_UNSUPPORTED) return rc;

@@ -647,8 +647,8 @@ int mid_splits(const Layout& L, int M) {
   const int64_t blocks = (int64_t)((M + kMidBM - 1) / kMidBM) * ((L.N + kMidBN - 1) / kMidBN);
   const int min_tiles = std::min(L.tiles[kNarrow] > 0 ? L.tiles[kNarrow] : 1 << 30, L.tiles[kWide] > 0 ? L.tiles[kWide] : 1 << 30);
   // One workgroup per CU, or two when the weights have wide-format groups and there are at least 128 blocks (K = 8192, M = 64, N = 18432,
-  // 144 blocks: two shares against one, which then runs two shares of its own: wide 43 against 51 us, hybrid word 54 against
-  // 69 us, mix 54.5 against 50 us).  Beyond two thirds of the CUs mid_shares takes one all the same.  A narrow block gains nothing from
+  // 144 blocks: two shares against one, which then runs two shares of its own: wide 40 against 50 us, hybrid word 50 against
+  // 64 us, mix 52 against 47 us; at K = 4096 28 / 28, 33 / 35 and 27 / 27).  Beyond two thirds of the CUs mid_shares takes one all the same.  A narrow block gains nothing from
   // a second workgroup on its CU.
   const int64_t cus = device_cus();
   const int64_t target = (L.tiles[kWide] > 0 && 2 * blocks >= cus) ? 2 * cus : cus;
