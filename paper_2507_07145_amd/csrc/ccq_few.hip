@@ -1,7 +1,9 @@
 // Products with few activation rows per matrix (about 2 to 32), every weight format and both scale modes, gfx950: the experts
 // of a grouped call, and dense calls small enough that a pass over partial tiles would cost more than it spreads.
 //
-// Bound: issue of vector instructions (decode), then HBM.  A workgroup is WN wavefronts side by side, each with RT row tiles
+// Bound: issue.  Narrow, 64 experts of 7168 x 2048 with 8 rows each, per SIMD: 29,600 vector instructions (118,000 cycles by
+// SQ_ACTIVE_INST_VALU) and 1,800 MFMAs (29,000) of 179,000 cycles; 31 % of the wavefronts' cycles are waits, no LDS bank conflict, 289 MB
+// read for 268.  A workgroup is WN wavefronts side by side, each with RT row tiles
 // of 16 output rows, times wk shares of K that meet in LDS at the end: one launch, no workspace.  The WN wavefronts of a
 // share walk K in stages of four 64-weight groups:
 //   - the activations of the stage after next are requested (lanes along a row: one request covers whole cache lines; read
@@ -15,9 +17,10 @@
 // One LDS-only barrier per stage.  The k-tiles a wavefront holds sit in slots that are refilled in place, two stages ahead
 // on the narrow format; moving them from slot to slot instead makes every move wait for its load.  The sums of a row tile
 // are added while the next one is decoded, so that no wavefront waits for its own matrix instruction.
-// Grouped, narrow, 64 experts of 7168 x 2048 with 8 rows each: 69 us against 92 us on the per-row-tile kernel (staging of
-// whole k-tiles between two barriers); wide 190 -> 81 us, hybrid word 204 -> 89 us; 243 experts of 7104 x 528 with up to 28
-// rows: 565 -> 118 us.
+// Grouped, narrow, 64 experts of 7168 x 2048 with 8 rows each: 72 us against 95 us on the per-row-tile kernel (staging of
+// whole k-tiles between two barriers); wide 200 -> 87 us, mix 168 -> 100 us, hybrid word 220 -> 96 us; 243 experts of 7104 x 528 with
+// up to 28 rows 565 -> 118 us.  Many rows without the host copy of the offsets, in passes of 32: 8 experts of 4096 x 4096 with 512
+// rows each 656 -> 286 us (147 us with the host copy, on the 64-row kernel).
 #include <hip/hip_runtime.h>
 
 #include <algorithm>

@@ -584,9 +584,9 @@ static MidKernel mid_kernel(int fm, int bm, Schedule s) {
   }
 }
 
-// 128-row blocks are built for the narrow format.  With the wide kinds' six code entries per lane and four accumulator tiles
-// mixes (both scale modes) and the hybrid word with fp16 scales need more than the 256 registers that two wavefronts on a
-// SIMD have (32 to 100 bytes of scratch); wide (254 and 240 registers) and the hybrid word with compressed scales (250) would fit.
+// 128-row blocks are built for the narrow format.  With the wide kinds' six code entries per lane and four accumulator tiles the lean
+// schedule does not fit the 168 registers of three wavefronts on a SIMD (68 to 120 bytes of scratch on wide weights and mixes); the
+// deep one would fit its 256 (234 to 253).
 static bool mid_has_tall_blocks(const Layout& L) { return L.tiles[kWide] == 0; }
 
 // Sets the K shares of `a` (S across the grid, wk in a workgroup) and launches: `busy` output tiles have rows.
