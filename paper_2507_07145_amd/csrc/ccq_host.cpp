@@ -833,6 +833,14 @@ extern "C" int ccq_few_launch_shape(const ccq_weight* w, int32_t E, int32_t rows
   return CCQ_OK;
 }
 
+// For tests, no part of the interface: the column block of the 256-row kernel where a dense call of M rows takes it, else 0.
+extern "C" int ccq_prompt_block_cols(const ccq_weight* w, int32_t M) {
+  Layout L;
+  const int rc = make_layout(w, &L);
+  if (rc != CCQ_OK) return rc;
+  return dense_path(L, M) == kPathPrefill ? prefill_block_cols(L, M) : 0;
+}
+
 // The GPU quantizer is built for every layout the multiply kernels read.
 static int encode_layout(const ccq_weight* w, Layout* L) { return make_layout(w, L); }
 

@@ -57,7 +57,8 @@ def test_compressed_scales_every_kernel(kinds, K, N, n_wide, M):
 
 @pytest.mark.parametrize("K,N,M", [(256, 1536, 2900), (256, 1024, 3400), (256, 2064, 4000)])
 def test_compressed_scales_256_row_kernel(K, N, M):
-    """Shapes the library sends to the 256-row kernel (column blocks of 192, 128 and 256)."""
+    """Thousands of rows, on both sides of the line between the 64-row and the 256-row kernel (the first shape; the other column
+    blocks of that kernel are in test_prompt_blocks.py)."""
     W, w = _case(["narrow"], K, N, 31 + N % 7, None)
     x = synth.activations_bf16(M, K, synth.rng(6, 600 + M))
     assert_gemm_close(_gemm_bits(w, x), o.matmul(x, W), f"compressed scales, 256-row kernel N={N} M={M}", rounded=(x, W))

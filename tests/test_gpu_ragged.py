@@ -76,7 +76,7 @@ def test_ragged_shapes_dense(ragged_cases, kinds, K, N, n_wide, M):
 
 @pytest.mark.parametrize("K,N,M", [(1088, 1000, 2900), (320, 1001, 3100), (1088, 2056, 4000)])
 def test_ragged_shapes_256_row_kernel(ragged_cases, K, N, M):
-    """Thousands of rows on narrow-format weights (the 256-row kernel where the library expects it to be faster)."""
+    """Thousands of rows on narrow-format weights (the 64-row kernel; ragged shapes of the 256-row one are in test_prompt_blocks.py)."""
     c, w = ragged_cases(["narrow"], K, N)
     _check(c, w, M, 200, f"ragged, many rows K={K} N={N}")
 
