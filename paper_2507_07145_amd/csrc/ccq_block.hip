@@ -1,0 +1,207 @@
+// Launches of the prompt kernel (ccq_block.h): which blocks and K shares a call takes, and whether it takes them at all.
+#include <algorithm>
+
+#include "ccq_block.h"
+
+namespace ccq {
+
+// Estimated times in microseconds, fitted to 17000 launches of 832 random calls (65 to 4096 rows, K 512 to 28672, N 1000 to 28672, all
+// formats; nine in ten within 8 %).  Per step of K (a 64-weight group) a block alone takes `alone` + `alone_row` mt, and with all CUs at work, where
+// the clock falls with the power, the chip takes `all` + `all_row` mt for a block on every CU; 128-row blocks run one or two to a CU.
+struct BlockRates {
+  double alone, alone_row, all, all_row, one128, two128, all128;
+};
+constexpr BlockRates kRatesNarrow = {0.08, 0.13, 0.12, 0.178, 0.66, 1.27, 1.74};
+constexpr BlockRates kRatesWide = {0.57, 0.08, 0.42, 0.151, 0.86, 1.54, 1.99};
+constexpr BlockRates kRatesH16 = {0.64, 0.08, 0.47, 0.151, 0.93, 1.70, 2.02};
+constexpr double kCallTime = 9.1, kSecondPart = 5.4;      // of the first and the second part of a call
+constexpr double kRoundTime = -3.0, kRoundTimeRow = 0.80; // more per round of blocks: start, and the outputs
+constexpr double kPartialRate = 9.9e6;                    // bytes of partial tiles, written and read, per microsecond
+// A plan's partial tiles: no more than this, and 32 rows of them fit the 8 MiB of ccq_gemm_static.
+constexpr int64_t kPartialMost = 100 << 20, kPartialRow = (8 << 20) / 32;
+
+static double part_time(const Layout& L, int M, const BlockPart& p) {
+  const double qn = L.tiles[kNarrow] ? 4.0 * ((L.tiles[kNarrow] + p.S - 1) / p.S) : 0.0, qw = L.tiles[kWide] ? 4.0 * ((2 * L.tiles[kWide] + p.S - 1) / p.S) : 0.0;
+  const BlockRates &n = kRatesNarrow, &w = L.h16 ? kRatesH16 : kRatesWide;
+  auto steps = [&](double BlockRates::*rate) { return qn * (n.*rate) + qw * (w.*rate); };   // all steps of a block
+  const int64_t cus = device_cus();
+  const int64_t blocks = (int64_t)((M + 32 * p.mt - 1) / (32 * p.mt)) * ((p.n_count + kBlockCols - 1) / kBlockCols) * p.S;
+  double t = 0.0;
+  if (p.mt > 4) {
+    const double alone = steps(&BlockRates::alone) + steps(&BlockRates::alone_row) * p.mt, all = steps(&BlockRates::all) + steps(&BlockRates::all_row) * p.mt;
+    const int64_t full = blocks / cus, rest = blocks % cus;
+    t = (double)full * std::max(alone, all) + (rest ? std::max(alone, all * (double)rest / (double)cus) : 0.0);
+    t += (double)(full + (rest ? 1 : 0)) * (kRoundTime + kRoundTimeRow * p.mt);
+  } else {
+    const double one = steps(&BlockRates::one128), two = steps(&BlockRates::two128), all = steps(&BlockRates::all128);
+    const int64_t full = blocks / (2 * cus), rest = blocks % (2 * cus);
+    t = (double)full * std::max(two, all) + (rest ? std::max(rest <= cus ? one : two, all * (double)rest / (double)(2 * cus)) : 0.0);
+    t += ((double)full + (rest == 0 ? 0.0 : (rest <= cus ? 0.5 : 1.0))) * (kRoundTime + kRoundTimeRow * p.mt);
+  }
+  if (p.S > 1) t += (double)p.S * M * p.n_count * 8.0 / kPartialRate;
+  return t;
+}
+
+static int64_t part_workspace(int M, const BlockPart& p) {
+  return p.S > 1 ? (int64_t)p.S * M * ((p.n_count + kRowsPerTile - 1) / kRowsPerTile * kRowsPerTile) * 4 : 0;
+}
+
+// The best blocks and shares for a range of columns.
+static double best_part(const Layout& L, int M, int n_first, int n_count, BlockPart* best) {
+  const int64_t cus = device_cus();
+  const int b = (M + 255) / 256;   // row blocks, and their heights without rows to spare
+  const int heights[4] = {4, std::max(5, (M + 32 * b - 1) / (32 * b)), std::max(5, (M + 32 * b + 31) / (32 * (b + 1))), 8};
+  double t_best = 1e30;
+  for (int h = 0; h < (M > 128 ? 4 : 1); ++h) {
+    for (int S : {1, 2, 3, 4, 5, 6, 8}) {
+      BlockPart p;
+      p.n_first = n_first;
+      p.n_count = n_count;
+      p.mt = heights[h];
+      p.S = S;
+      if (S > 1) {
+        const int64_t blocks = (int64_t)((M + 32 * p.mt - 1) / (32 * p.mt)) * ((n_count + kBlockCols - 1) / kBlockCols);
+        // more shares only while there are CUs for them (128-row blocks: two to a CU); every share has quads of every kind
+        if (blocks * S > (p.mt > 4 ? cus : 2 * cus) + 16) break;
+        if ((L.tiles[kNarrow] > 0 && L.tiles[kNarrow] < S) || (L.tiles[kWide] > 0 && 2 * L.tiles[kWide] < S)) break;
+        if (part_workspace(M, p) > kPartialMost || part_workspace(1, p) > kPartialRow) break;
+      }
+      const double t = part_time(L, M, p);
+      if (t < t_best) {
+        t_best = t;
+        *best = p;
+      }
+    }
+  }
+  return t_best;
+}
+
+// All columns alike, or as many as fill the CUs a whole number of times in tall blocks and the rest, which would leave CUs idle, in whatever
+// is best for them (narrow 7168 x 18432, M = 2048, 576 blocks of 256 x 256: 477 us, in three rounds; 512 of them and 128 blocks of
+// 128 x 256 in two shares: 424 us).
+static BlockPlan make_plan(const Layout& L, int M) {
+  BlockPlan plan;
+  plan.parts = 1;
+  plan.time = kCallTime + best_part(L, M, 0, L.N, &plan.part[0]);
+  const int64_t cus = device_cus();
+  const int b = (M + 255) / 256, mt = std::max(5, (M + 32 * b - 1) / (32 * b));
+  const int64_t row_blocks = (M + 32 * mt - 1) / (32 * mt), n_blocks = (L.N + kBlockCols - 1) / kBlockCols, rounds = row_blocks * n_blocks / cus;
+  const int64_t n_full = row_blocks > 0 ? cus * rounds / row_blocks : 0;
+  if (M > 128 && n_full > 0 && n_full < n_blocks) {
+    BlockPart p[2];
+    p[0].n_count = (int)n_full * kBlockCols;
+    p[0].mt = mt;
+    const double t = kCallTime + kSecondPart + part_time(L, M, p[0]) + best_part(L, M, p[0].n_count, L.N - p[0].n_count, &p[1]);
+    if (t < plan.time) {
+      plan.parts = 2;
+      plan.time = t;
+      plan.part[0] = p[0];
+      plan.part[1] = p[1];
+    }
+  }
+  // The 64-row kernel where it is as good: small products and short K.  (832 calls of 65 to 4096 rows against the kernels that served them before: 0.80
+  // of the time in the geometric mean, one more than 3 % slower, 75 rows of 1472 x 6080 by 9 %; with the 64-row kernel's time as it is, 25.)
+  if (plan.time > 0.95 * mid_time(L, M) - 1.5) plan.parts = 0;
+  return plan;
+}
+
+BlockPlan block_plan(const Layout& L, int M) {
+  if (M <= 64 || L.K < 512) return BlockPlan{};
+  // a call asks several times: the last answer of this thread, a function of these numbers
+  struct Key {
+    int tn, tw, h16, K, N, M, cus;
+    bool operator==(const Key& o) const { return tn == o.tn && tw == o.tw && h16 == o.h16 && K == o.K && N == o.N && M == o.M && cus == o.cus; }
+  };
+  static thread_local Key last{-1, -1, -1, -1, -1, -1, -1};
+  static thread_local BlockPlan plan;
+  const Key key{L.tiles[kNarrow], L.tiles[kWide], L.h16 ? 1 : 0, L.K, L.N, M, device_cus()};
+  if (!(key == last)) {
+    plan = make_plan(L, M);
+    last = key;
+  }
+  return plan;
+}
+
+int64_t block_workspace(int M, const BlockPlan& plan) {
+  int64_t need = 0;
+  for (int i = 0; i < plan.parts; ++i) need = std::max(need, part_workspace(M, plan.part[i]));
+  return need;
+}
+
+int64_t block_workspace_most(const Layout& L, int M_max) {
+  return M_max <= 64 || L.K < 512 ? 0 : std::min<int64_t>(kPartialMost, (int64_t)8 * M_max * L.Npad * 4);
+}
+
+static int launch_part(const ccq_weight* w, const Layout& L, const void* x, int M, int64_t ldx, void* y, int64_t ldy, float* partial, const BlockPart& p,
+                       void* stream) {
+  const int64_t rt0 = p.n_first / kRowsPerTile;
+  BlockArgs a;
+  a.codes = static_cast<const uint8_t*>(w->codes) + rt0 * L.row_tile_bytes;
+  a.scales = w->scales ? static_cast<const uint16_t*>(w->scales) + rt0 * L.row_tile_scale_halfs : nullptr;
+  a.alpha = w->code_alpha ? w->code_alpha + p.n_first : nullptr;
+  a.beta = w->code_beta ? w->code_beta + p.n_first : nullptr;
+  a.meta = static_cast<const int32_t*>(w->meta);
+  a.scale_super = w->scale_super ? static_cast<const uint16_t*>(w->scale_super) + p.n_first : nullptr;
+  a.x = static_cast<const uint16_t*>(x);
+  a.y = static_cast<uint16_t*>(y) + p.n_first;
+  a.partial = partial;
+  a.ldx = ldx;
+  a.ldy = ldy;
+  a.row_tile_bytes = L.row_tile_bytes;
+  a.row_tile_scale_halfs = L.row_tile_scale_halfs;
+  a.M = M;
+  a.N = p.n_count;
+  a.row_tiles = (p.n_count + kRowsPerTile - 1) / kRowsPerTile;
+  a.Npad = a.row_tiles * kRowsPerTile;
+  a.quads[kNarrow] = L.tiles[kNarrow];
+  a.quads[kWide] = 2 * L.tiles[kWide];
+  a.g_last = L.G - 1;
+  for (int k = 0; k < 2; ++k) {
+    a.sq[k] = a.quads[k] / p.S;
+    a.sr[k] = a.quads[k] % p.S;
+    a.zp[k] = L.zp[k];
+    for (int i = 0; i < 3; ++i) a.off[k][i] = -((k == kNarrow ? kNarrowBases[i] : kWideBases[i]) + L.zp[k]);
+  }
+  const int bm = 32 * p.mt;
+  const size_t lds = kBlockLds0 + (size_t)2 * bm * kGroup * 2;
+  const BlockKernel kern = L.h16 ? block_kernel_h16(L.scale_mode, p.mt)
+                                 : (L.tiles[kWide] == 0 ? block_kernel_narrow(L.scale_mode, p.mt)
+                                                        : (L.tiles[kNarrow] == 0 ? block_kernel_wide(L.scale_mode, p.mt) : block_kernel_mix(L.scale_mode, p.mt)));
+  if (lds > 48 * 1024 && hipFuncSetAttribute(reinterpret_cast<const void*>(kern), hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds) != hipSuccess) {
+    (void)hipGetLastError();
+    return CCQ_ERR_HIP;
+  }
+  const dim3 grid((unsigned)((M + bm - 1) / bm), (unsigned)((p.n_count + kBlockCols - 1) / kBlockCols), (unsigned)p.S);
+  hipLaunchKernelGGL(kern, grid, dim3(256), lds, static_cast<hipStream_t>(stream), a);
+  return hipGetLastError() == hipSuccess ? CCQ_OK : CCQ_ERR_HIP;
+}
+
+// With less of a workspace than the plan's, the rows go through it some at a time: the same sums in the same order for every output.
+int launch_block(const ccq_weight* w, const Layout& L, const void* x, int M, int64_t ldx, void* y, int64_t ldy, void* workspace, int64_t workspace_bytes,
+                 const BlockPlan& plan, void* stream) {
+  for (int i = 0; i < plan.parts; ++i) {
+    const BlockPart& p = plan.part[i];
+    // lane offsets have 32 bits; column blocks are a grid dimension
+    if ((int64_t)32 * p.mt * ldx * 2 >= (int64_t)1 << 32 || 4 * L.row_tile_bytes >= (int64_t)1 << 31 || (p.n_count + kBlockCols - 1) / kBlockCols > 65535)
+      return CCQ_ERR_UNSUPPORTED;
+    if (workspace_bytes < std::min(part_workspace(32, p), part_workspace(M, p))) return CCQ_ERR_UNSUPPORTED;
+  }
+  for (int i = 0; i < plan.parts; ++i) {
+    const BlockPart& p = plan.part[i];
+    int rows = M;
+    if (part_workspace(M, p) > workspace_bytes) rows = (int)(workspace_bytes / part_workspace(32, p)) * 32;
+    for (int m0 = 0; m0 < M; m0 += rows) {
+      const int m = std::min(rows, M - m0);
+      const uint16_t* xm = static_cast<const uint16_t*>(x) + m0 * ldx;
+      uint16_t* ym = static_cast<uint16_t*>(y) + m0 * ldy;
+      float* partial = p.S > 1 ? static_cast<float*>(workspace) : nullptr;
+      int rc = launch_part(w, L, xm, m, ldx, ym, ldy, partial, p, stream);
+      if (rc == CCQ_OK && p.S > 1)
+        rc = launch_reduce_splits(partial, ym + p.n_first, ldy, m, p.n_count, (p.n_count + kRowsPerTile - 1) / kRowsPerTile * kRowsPerTile, p.S, stream);
+      if (rc != CCQ_OK) return rc;
+    }
+  }
+  return CCQ_OK;
+}
+
+}  // namespace ccq

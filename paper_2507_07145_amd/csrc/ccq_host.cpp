@@ -137,7 +137,7 @@ Decomp choose_decomp(const Layout& L, int M, int experts) {
 using namespace ccq;
 
 // Which kernel a dense call of M rows uses when no launch shape is given.
-enum DensePath { kPathGemv, kPathGemv16, kPathGemv16NW, kPathSkinny, kPathRows, kPathMid, kPathPrefill };
+enum DensePath { kPathGemv, kPathGemv16, kPathGemv16NW, kPathSkinny, kPathRows, kPathMid, kPathPrefill, kPathBlock };
 static DensePath dense_path(const Layout& L, int M) {
   const bool narrow_only = L.tiles[kWide] == 0, wide_only = L.tiles[kNarrow] == 0;
   if (narrow_only && !L.has_map && M < kMidMinM) {
@@ -162,8 +162,12 @@ static DensePath dense_path(const Layout& L, int M) {
     if (!L.has_map && gemv16_shape(L, 256, kMaxSplitsK, &tpw, &nw)) return kPathGemv16;
     return kPathRows;
   }
-  if (narrow_only && M > 128) {
-    // 256-row tiles pay off once they fill enough of the chip.  Both kernels are bound by the same two things (matrix
+  // prompts: the block kernel, unless the 64-row one is as fast
+  if (block_plan(L, M).parts > 0) return kPathBlock;
+  if (narrow_only && M > 128 && L.K < 512) {
+    // Short K, which the block kernel leaves: 256-row tiles pay off once they fill enough of the chip (us on the 256-row, 64-row and
+    // block kernel: 320 x 1408, M = 5000, 12.6 / 17.4 / 15.9; 256 x 1024, M = 6000, 9.2 / 13.8 / 9.5; 256 x 1536, M = 2900, 11.1 / 13.0 / 9.4; from K = 512 on,
+    // on 208 random calls, never the fastest).  Both kernels are bound by the same two things (matrix
     // core time, and the vector work of decoding a weight tile once per row block of the output), so their times
     // are compared in units of one output element per round of workgroups over the chip's CUs; the relative costs
     // per element are ratios between the kernels, not times: the 256-row kernel costs 1.0 with 192-column blocks, 1.3 with 128 and 1.2
@@ -280,9 +284,9 @@ static int64_t skinny_need(const Layout& L, int M) {
   return need;
 }
 
-// Workspace one dense call of exactly M rows needs (fp32 partial tiles of the K shares) on the kernel the library
-// picks for it.
-static int64_t dense_need(const Layout& L, int M) {
+// The least workspace that a dense call of exactly M rows is served with (fp32 partial tiles of the K shares), on the kernel the library
+// picks for it; prompts are then, if need be, on the 64-row kernel.
+static int64_t dense_least(const Layout& L, int M) {
   if (M <= 0) return 0;
   switch (dense_path(L, M)) {
     case kPathGemv: {
@@ -307,7 +311,8 @@ static int64_t dense_need(const Layout& L, int M) {
       return S > 1 ? (int64_t)S * M * L.Npad * 4 : 0;
     }
     case kPathMid:
-    case kPathPrefill: {  // the 256-row kernel needs none; where it does not apply the 64-row kernel runs
+    case kPathBlock:
+    case kPathPrefill: {  // the 256-row kernel needs none; where it or the block kernel does not apply the 64-row kernel runs
       const int S = mid_splits(L, M);
       return S > 1 ? (int64_t)S * M * L.Npad * 4 : 0;
     }
@@ -316,18 +321,22 @@ static int64_t dense_need(const Layout& L, int M) {
   }
 }
 
+// The workspace that it is asked for: what the block kernel's shares take in one pass over the rows is more.
+static int64_t dense_need(const Layout& L, int M) { return std::max(dense_least(L, M), M <= 0 ? (int64_t)0 : block_workspace(M, block_plan(L, M))); }
+
 // The largest need over 1..M_max rows.  Between two multiples of 16 the kernel choice and the number of K shares
 // do not change (they depend on the row count through its 16-, 32-, 64- and 256-row blocks and the thresholds 1,
 // 4, 16, 32, 128), and with both fixed the need grows with the row count: only those row counts are looked at.
-// K is cut only while the row and column blocks do not fill the chip, which bounds the row counts that matter.
+// K is cut only while the row and column blocks do not fill the chip, which bounds the row counts that matter.  (The block kernel's
+// shares are not asked for row by row: a bound.)
 static int64_t dense_workspace_bytes(const Layout& L, int M_max) {
   int64_t need = 0;
   const int cap = std::min(M_max, 4096);
-  for (int m : {1, 2, 4}) if (m <= M_max) need = std::max(need, dense_need(L, m));
-  for (int m = 16; m <= cap; m += 16) need = std::max(need, dense_need(L, m));
-  need = std::max(need, dense_need(L, std::min(M_max, cap)));
-  if (M_max > cap) need = std::max(need, dense_need(L, M_max));
-  return need;
+  for (int m : {1, 2, 4}) if (m <= M_max) need = std::max(need, dense_least(L, m));
+  for (int m = 16; m <= cap; m += 16) need = std::max(need, dense_least(L, m));
+  need = std::max(need, dense_least(L, std::min(M_max, cap)));
+  if (M_max > cap) need = std::max(need, dense_least(L, M_max));
+  return std::max(need, block_workspace_most(L, M_max));
 }
 
 extern "C" int ccq_pack_info(const ccq_weight* w, int32_t M_max, ccq_info* out) {
@@ -568,7 +577,7 @@ int gemm_dispatch(const ccq_weight* w, const void* x, int32_t M, int64_t ldx, vo
     if (rc != CCQ_OK) return rc;
     if (d.S > 1) need_passes = std::max(need_passes, (int64_t)d.S * mc * L.Npad * 4);
   }
-  if (!explicit_launch && dense_path(L, M) != kPathGemv16 && dense_path(L, M) != kPathGemv16NW && have < dense_need(L, M)) return CCQ_ERR_WORKSPACE;
+  if (!explicit_launch && dense_path(L, M) != kPathGemv16 && dense_path(L, M) != kPathGemv16NW && have < dense_least(L, M)) return CCQ_ERR_WORKSPACE;
 
   if (!explicit_launch && dense_few(L, M)) {
     SkinnyCall c;
@@ -586,7 +595,11 @@ int gemm_dispatch(const ccq_weight* w, const void* x, int32_t M, int64_t ldx, vo
 
   if (!explicit_launch) {
     const DensePath path = dense_path(L, M);
-    // many rows, narrow format only: the 256-row LDS-tiled MFMA kernel
+    if (path == kPathBlock) {
+      rc = launch_block(w, L, x, M, ldx, y, ldy, workspace, have, block_plan(L, M), stream);
+      if (rc != CCQ_ERR_UNSUPPORTED) return rc;
+    }
+    // many rows and short K, narrow format only: the 256-row LDS-tiled MFMA kernel
     if (path == kPathPrefill) {
       rc = launch_prefill(w, L, x, M, ldx, y, ldy, stream);
       if (rc != CCQ_ERR_UNSUPPORTED) return rc;
@@ -623,7 +636,7 @@ int gemm_dispatch(const ccq_weight* w, const void* x, int32_t M, int64_t ldx, vo
       return rc;
     }
     // a few dozen rows (or many rows on wide / mixed formats): the 64-row LDS-tiled kernel
-    if (path == kPathMid || path == kPathPrefill) {
+    if (path == kPathMid || path == kPathBlock || path == kPathPrefill) {
       const int S = mid_shares(L, M, mid_splits(L, M));
       float* partial = S > 1 ? static_cast<float*>(workspace) : nullptr;
       rc = launch_mid(w, L, x, M, ldx, y, ldy, partial, S, stream);
@@ -681,6 +694,12 @@ int64_t gemm_workspace_need(const ccq_weight* w, int32_t M) {
   Layout L;
   if (!w || M < 0 || make_layout(w, &L) != CCQ_OK) return -1;
   return dense_need(L, M);
+}
+
+int64_t gemm_workspace_least(const ccq_weight* w, int32_t M) {
+  Layout L;
+  if (!w || M < 0 || make_layout(w, &L) != CCQ_OK) return -1;
+  return dense_least(L, M);
 }
 
 }  // namespace ccq
@@ -839,6 +858,23 @@ extern "C" int ccq_prompt_block_cols(const ccq_weight* w, int32_t M) {
   const int rc = make_layout(w, &L);
   if (rc != CCQ_OK) return rc;
   return dense_path(L, M) == kPathPrefill ? prefill_block_cols(L, M) : 0;
+}
+
+// For tests, no part of the interface: how a dense call of M rows goes to the block kernel (0: not at all): the number of ranges of columns, of
+// each the first column, the columns, 32-row tiles of a block and shares of K.
+extern "C" int ccq_prompt_plan(const ccq_weight* w, int32_t M, int32_t* out) {
+  Layout L;
+  const int rc = make_layout(w, &L);
+  if (rc != CCQ_OK) return rc;
+  if (!out) return CCQ_ERR_NULL;
+  if (dense_path(L, M) != kPathBlock) return 0;
+  const BlockPlan plan = block_plan(L, M);
+  for (int i = 0; i < plan.parts; ++i) {
+    const BlockPart& p = plan.part[i];
+    const int32_t v[4] = {p.n_first, p.n_count, p.mt, p.S};
+    std::memcpy(out + 4 * i, v, sizeof(v));
+  }
+  return plan.parts;
 }
 
 // The GPU quantizer is built for every layout the multiply kernels read.

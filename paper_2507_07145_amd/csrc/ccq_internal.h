@@ -160,6 +160,7 @@ int launch_mid_grouped(const ccq_weight* w0, const Layout& L, int E, int64_t cod
                        int64_t ldy, void* stream);
 int mid_splits(const Layout& L, int M);              // the most shares across the grid (what the workspace is asked for)
 int mid_shares(const Layout& L, int M, int most);    // those that a call takes
+double mid_time(const Layout& L, int M);             // estimate of a dense call, microseconds
 int launch_mid(const ccq_weight* w, const Layout& L, const void* x, int M, int64_t ldx, void* y, int64_t ldy, float* partial, int S,
                void* stream);
 // y[m][n] = bf16(sum_s partial[s][m][n]), shares added in index order (ccq_skinny.hip).
@@ -175,8 +176,27 @@ int launch_rows(const ccq_weight* w, const Layout& L, const void* x, int M, int6
 int gemm_dispatch(const ccq_weight* w, const void* x, int32_t M, int64_t ldx, void* y, int64_t ldy, void* workspace,
                   int64_t workspace_bytes, void* stream, const ccq_launch* launch);
 int64_t gemm_workspace_need(const ccq_weight* w, int32_t M);
+int64_t gemm_workspace_least(const ccq_weight* w, int32_t M);   // the least that a call is served with
 
-// Large-M kernel for narrow-format weights (ccq_prefill.hip).
+// Prompts, every format (ccq_block.h, ccq_block.hip): blocks of 32 mt x 256 outputs (mt = 4 .. 8) over one or two ranges of columns, K cut
+// into S shares whose fp32 partial tiles go through the workspace.
+struct BlockPart {
+  int n_first = 0, n_count = 0;   // columns; n_first a multiple of 256
+  int mt = 8, S = 1;
+};
+struct BlockPlan {
+  int parts = 0;                  // 0: the call is one for the other kernels
+  BlockPart part[2];
+  double time = 0.0;              // estimate, microseconds
+};
+BlockPlan block_plan(const Layout& L, int M);
+int64_t block_workspace(int M, const BlockPlan& plan);
+int64_t block_workspace_most(const Layout& L, int M_max);   // of any call of up to M_max rows, or more
+// CCQ_ERR_UNSUPPORTED, with nothing launched, where the rows lie too far apart or the workspace does not hold 32 rows.
+int launch_block(const ccq_weight* w, const Layout& L, const void* x, int M, int64_t ldx, void* y, int64_t ldy, void* workspace, int64_t workspace_bytes,
+                 const BlockPlan& plan, void* stream);
+
+// Large-M kernel for narrow-format weights and short K (ccq_prefill.hip).
 int prefill_block_cols(const Layout& L, int M);  // column-block width launch_prefill uses: 128, 192 or 256
 int launch_prefill(const ccq_weight* w, const Layout& L, const void* x, int M, int64_t ldx, void* y, int64_t ldy, void* stream);
 

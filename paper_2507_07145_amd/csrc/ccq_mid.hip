@@ -589,21 +589,29 @@ static MidKernel mid_kernel(int fm, int bm, Schedule s) {
 // deep one would fit its 256 (234 to 253).
 static bool mid_has_tall_blocks(const Layout& L) { return L.tiles[kWide] == 0; }
 
-// Sets the K shares of `a` (S across the grid, wk in a workgroup) and launches: `busy` output tiles have rows.
+// K shares in a workgroup, where S go across the grid and `busy` output tiles have rows.
 // A wavefront takes about twice as long for a step as the SIMD needs for its instructions, so two to four of them should share
 // one.  With at most one workgroup per CU they come from K shares inside the workgroup, as many as the registers allow (us with
 // one / two / three / four, 0.59 of the CUs: narrow 10624 x 19200, M = 38, 71 / 56 / 51 / 50; mix 5952 x 15072, M = 99, 48 / 40 / 39);
 // narrow 64-row blocks take two shares up to two workgroups per CU (15168 x 3520, M = 710, 158 / 140 / 151 / 149), the others
 // one (wide 1536 x 5968, M = 487, 22 / 28).  A share has at least one k-tile of every kind.
-// E: experts (0: a dense call).  `far`: the activation rows lie too far apart for 32-bit offsets.
-static int mid_launch(const Layout& L, MidArgs& a, int E, int bm, bool far, int S, int m_blocks, int64_t busy, void* stream) {
+// `far`: the activation rows lie too far apart for 32-bit offsets.
+static int mid_wk(const Layout& L, int bm, bool far, int S, int64_t busy, bool* deep) {
   const int fm = L.h16 ? 4 : (L.tiles[kNarrow] > 0 ? 1 : 0) | (L.tiles[kWide] > 0 ? 2 : 0);
   const int64_t cus = device_cus();
   const bool narrow64 = fm == 1 && bm == kMidBM, one_each = busy * S <= cus, two_each = busy * S <= 2 * cus;
-  const bool deep = !narrow64 && (two_each || far);
-  int wk = one_each ? mid_waves(fm, bm, deep) : (narrow64 && two_each ? 2 : 1);
+  *deep = !narrow64 && (two_each || far);
+  int wk = one_each ? mid_waves(fm, bm, *deep) : (narrow64 && two_each ? 2 : 1);
   for (int k = 0; k < 2; ++k)
     while (wk > 1 && L.tiles[k] > 0 && L.tiles[k] < S * wk) --wk;
+  return wk;
+}
+
+// E: experts (0: a dense call).
+static int mid_launch(const Layout& L, MidArgs& a, int E, int bm, bool far, int S, int m_blocks, int64_t busy, void* stream) {
+  const int fm = L.h16 ? 4 : (L.tiles[kNarrow] > 0 ? 1 : 0) | (L.tiles[kWide] > 0 ? 2 : 0);
+  bool deep = false;
+  const int wk = mid_wk(L, bm, far, S, busy, &deep);
   for (int k = 0; k < 2; ++k) {
     a.sq[k] = L.tiles[k] / (S * wk);
     a.sr[k] = L.tiles[k] % (S * wk);
@@ -666,6 +674,34 @@ int mid_shares(const Layout& L, int M, int most) {
   return blocks * 3 > 2 * (int64_t)device_cus() ? 1 : most;
 }
 
+// Rows of a block of a dense call.  128-row blocks (narrow): where 64-row ones are more than one to a CU and 128-row ones are not, or where
+// there are more than two 64-row ones (us with 64 / 128 rows: 4480 x 24294, M = 73, 48 / 35; 5120 x 6064, M = 361, 54 / 48; 2112 x 22144, M = 714,
+// 107 / 98; 896 x 18642, M = 139, 1.7 and 1.1 to a CU, 17 / 24; 5120 x 1656, M = 784, 0.7 and 0.4 to a CU, 32 / 47).
+static int mid_dense_rows(const Layout& L, int M, int S, bool far) {
+  const int64_t cus = device_cus(), n_blocks = (L.N + kMidBN - 1) / kMidBN;
+  const int64_t wg64 = (int64_t)((M + kMidBM - 1) / kMidBM) * n_blocks, wg128 = (int64_t)((M + 2 * kMidBM - 1) / (2 * kMidBM)) * n_blocks;
+  return mid_has_tall_blocks(L) && (far || (S == 1 && wg64 > cus && (wg128 <= cus || wg64 > 2 * cus))) ? 2 * kMidBM : kMidBM;
+}
+
+// What a dense call takes here, by a fit to 832 random calls of 65 to 4096 rows (nine in ten within 13 %): per step of K the longer of a wavefront's
+// own time and the time of those that share its SIMD, a start, and the pass over the partial tiles.
+double mid_time(const Layout& L, int M) {
+  struct Rates {
+    double alone, shared, start;
+  };
+  constexpr Rates narrow64 = {0.35, 0.28, 6.6}, narrow128 = {0.93, 0.50, 8.4}, wide = {0.41, 0.34, 6.3}, mix = {0.40, 0.34, 6.4}, h16 = {0.28, 0.46, 6.9};
+  const int S = mid_shares(L, M, mid_splits(L, M)), bm = mid_dense_rows(L, M, S, false);
+  const int64_t cus = device_cus(), blocks = (int64_t)((M + bm - 1) / bm) * ((L.N + kMidBN - 1) / kMidBN) * S;
+  bool deep = false;
+  const int wk = mid_wk(L, bm, false, S, blocks / S, &deep);
+  const Rates r = L.h16 ? h16 : (L.tiles[kWide] == 0 ? (bm == kMidBM ? narrow64 : narrow128) : (L.tiles[kNarrow] == 0 ? wide : mix));
+  auto steps = [&](int k, int groups) { return (L.tiles[k] + S * wk - 1) / (S * wk) * groups; };
+  const double waves = blocks <= 2 * cus ? (double)((blocks + cus - 1) / cus * wk) : ((double)blocks / (double)cus + 0.6) * wk;
+  double t = r.start + (steps(kNarrow, kNarrowGroupsPerTile) + steps(kWide, kWideGroupsPerTile)) * std::max(r.alone, r.shared * waves);
+  if (S > 1) t += 2.4 + (double)S * M * L.N * 8.0 / 9.0e6;
+  return t;
+}
+
 int launch_mid(const ccq_weight* w, const Layout& L, const void* x, int M, int64_t ldx, void* y, int64_t ldy, float* partial, int S,
                void* stream) {
   MidArgs a;
@@ -687,14 +723,9 @@ int launch_mid(const ccq_weight* w, const Layout& L, const void* x, int M, int64
   a.g_last = L.G - 1;
   a.n_last = L.N - 1;
   a.row_tiles = L.row_tiles;
-  // 128-row blocks (narrow): where 64-row ones are more than one to a CU and 128-row ones are not, or where there are more than two
-  // 64-row ones (us with 64 / 128 rows: 4480 x 24294, M = 73, 48 / 35; 5120 x 6064, M = 361, 54 / 48; 2112 x 22144, M = 714, 107 / 98;
-  // 896 x 18642, M = 139, 1.7 and 1.1 to a CU, 17 / 24; 5120 x 1656, M = 784, 0.7 and 0.4 to a CU, 32 / 47).
-  const int64_t cus = device_cus();
   const int n_blocks = (L.N + kMidBN - 1) / kMidBN;
-  const int64_t wg64 = (int64_t)((M + kMidBM - 1) / kMidBM) * n_blocks, wg128 = (int64_t)((M + 2 * kMidBM - 1) / (2 * kMidBM)) * n_blocks;
   const bool far = (2 * kMidBM - 1) * ldx * 2 + 2 * kGroup > (int64_t)1 << 32;   // (a 64-row narrow block has the lean schedule only)
-  const int bm = mid_has_tall_blocks(L) && (far || (S == 1 && wg64 > cus && (wg128 <= cus || wg64 > 2 * cus))) ? 2 * kMidBM : kMidBM;
+  const int bm = mid_dense_rows(L, M, S, far);
   const int m_blocks = (M + bm - 1) / bm;
   a.tiles[0] = L.tiles[0];
   a.tiles[1] = L.tiles[1];

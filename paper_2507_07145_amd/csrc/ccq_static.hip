@@ -46,8 +46,10 @@ using namespace ccq;
 extern "C" int64_t ccq_gemm_static_max_workspace(void) { return kStaticScratchBytes; }
 
 extern "C" int ccq_gemm_static(const ccq_weight* w, const void* x, int32_t M, int64_t ldx, void* y, int64_t ldy, void* hip_stream) {
+  // A prompt's K shares may ask for more than the array holds: its rows then go through the array some at a time.  Other calls
+  // that need more are refused; an invalid descriptor (-1) is reported by the dispatcher below.
   const int64_t need = gemm_workspace_need(w, M);
-  if (need > kStaticScratchBytes) return CCQ_ERR_WORKSPACE;  // an invalid descriptor (-1) is reported by the dispatcher below
+  if (need > kStaticScratchBytes && gemm_workspace_least(w, M) > kStaticScratchBytes) return CCQ_ERR_WORKSPACE;
   void* ws = nullptr;
   if (need > 0) {
     const int rc = scratch_of_current_device(&ws);
