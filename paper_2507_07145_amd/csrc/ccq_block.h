@@ -46,24 +46,35 @@ struct BlockArgs {
   int32_t sq[2], sr[2];         // K share s owns quads [s sq + min(s, sr), + sq + (s < sr)) of each kind that is present, at least one
   float zp[2];
   float off[2][3];              // -(kNarrowBases + zp), -(kWideBases + zp)
+  // grouped calls: blockIdx.z is the expert; its rows are output rows [offsets[e], offsets[e + 1]), activation row sorted_rows[p] for
+  // output row p; expert e's arrays start e * stride bytes after expert 0's
+  const int32_t* sorted_rows;
+  const int32_t* expert_offsets;
+  int64_t codes_stride, scales_stride, ab_stride;
 };
 
 constexpr int kBlockCols = 256;
-constexpr int kVectorCount(int kind, int sm, int mt) { return kind == 0 ? (sm == 0 ? 180 : 196) : (kind == 1 ? (sm == 0 ? (mt > 4 ? 180 : 196) : 196) : (sm == 0 ? 224 : 280)); }
+// Vector instructions that a step's two decodes are known to have, at least: what the order of a step asks for (kind: 0 narrow, 1 wide, 2 hybrid word).
+constexpr int decode_vectors(int kind, int sm, int mt) {
+  if (kind == 0) return sm == 0 ? 180 : 196;
+  if (kind == 1) return sm == 0 && mt != 4 ? 180 : 196;
+  return sm == 0 ? 224 : 280;
+}
 constexpr int kBlockLds0 = 256;   // activation tiles start here: global_load_lds takes LDS address 0 for no address
 
-// FM: formats present (1 narrow, 2 wide, 3 both, 4 the hybrid word; a group map exists only for 3).  SM: scale mode.
-template <int FM, int SM, int MT>
-__global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(MT > 4 ? 1 : 2, MT > 4 ? 1 : 2))) ccq_block_kernel(const BlockArgs a) {
+// One block: rows m0 .. of a's, columns n0 .., share `split`.  FM: formats present (1 narrow, 2 wide, 3 both, 4 the hybrid word; a group map exists
+// only for 3).  SM: scale mode.  GATHER: activation row sorted_rows[m] for row m.
+template <int FM, int SM, bool GATHER, int MT>
+__device__ __forceinline__ void block_tile(const BlockArgs& a, int wave, int m0, int n0, int split) {
   constexpr bool HAS_N = FM == 1 || FM == 3, HAS_W = FM >= 2, META = FM == 3, H16 = FM == 4;
   constexpr int BM = 32 * MT, kTile = BM * kGroup * 2;   // bytes of an activation tile
   constexpr int kWideTile = H16 ? kH16TileBytes : kWideTileBytes;
   extern __shared__ __align__(256) unsigned char smem[];
-  const int lane = threadIdx.x & 63;
-  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  // (the lane is asked for anew, not kept in a register for the other bodies of a grouped kernel)
+  int none = 0;
+  asm volatile("" : "+s"(none));
+  const int lane = __builtin_amdgcn_mbcnt_hi(~0u, __builtin_amdgcn_mbcnt_lo(~0u, none));
   const int nl = lane & 15, ti = (lane >> 4) & 1, h = lane >> 5;   // column of a 32-wide tile: row tile ti, row nl; k half h
-  const int m0 = blockIdx.x * BM, n0 = blockIdx.y * kBlockCols;
-  const int split = blockIdx.z;
 
   // this share's quads of a kind
   auto first_quad = [&](int k) { return split * a.sq[k] + min(split, a.sr[k]); };
@@ -92,13 +103,15 @@ __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(MT > 4
   // Activation rows to copy: one global_load_lds of a wavefront moves eight rows, lane l the chunk of row l / 8 that belongs at LDS
   // position l % 8.  Chunk c of row r lies at position c ^ swizzle(r), swizzle(r) = (r ^ r / 8 & 1) & 7.  The instruction's constant offset
   // counts in memory and in LDS: instruction i of four goes 1024 i bytes further in LDS, and xoff is as much less.
-  const char* xbase = reinterpret_cast<const char*>(a.x + (int64_t)m0 * a.ldx) - 3072;
+  const char* xbase = reinterpret_cast<const char*>(a.x + (GATHER ? 0 : (int64_t)m0 * a.ldx)) - 3072;
   asm volatile("" : "+s"(xbase));   // (the constant stays part of the base)
   uint32_t xoff[MT];
 #pragma unroll
   for (int i = 0; i < MT; ++i) {
     const int b = wave * MT + i, row = 8 * b + (lane >> 3), chunk = (lane & 7) ^ (lane >> 3) ^ (b & 1);
-    xoff[i] = (uint32_t)((int64_t)(min(m0 + row, a.M - 1) - m0) * a.ldx * 2 + chunk * 16 + (3072 - (i & 3) * 1024));  // rows past the end read the last row again; their products are never stored
+    const int m = min(m0 + row, a.M - 1);   // rows past the end read the last row again; their products are never stored
+    const int64_t xr = GATHER ? a.sorted_rows[m] : m - m0;
+    xoff[i] = (uint32_t)(xr * a.ldx * 2 + chunk * 16 + (3072 - (i & 3) * 1024));
   }
   // operand reads: half h of MFMA kk takes chunk 4h + kk (weights 32h + 8kk .. of the group) of row lane % 32
   uint32_t a_frag = kBlockLds0 + (lane & 31) * (kGroup * 2) + (((h * 4) ^ (lane & 7) ^ ((lane >> 3) & 1)) * 16);   // of kk = 0; the others differ in bits 4 and 5
@@ -118,7 +131,10 @@ __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(MT > 4
   auto copy_a = [&](int buf, int group) {
     const char* base = xbase + (int64_t)group * (kGroup * 2);
     // keeps the zero extensions next to the loads: uniform base + 32-bit lane offset
-    asm volatile("" : "+v"(xoff[0]), "+v"(xoff[1]), "+v"(xoff[2]), "+v"(xoff[3]));
+    if constexpr (MT == 1) asm volatile("" : "+v"(xoff[0]));
+    if constexpr (MT == 2) asm volatile("" : "+v"(xoff[0]), "+v"(xoff[MT > 1 ? 1 : 0]));
+    if constexpr (MT == 3) asm volatile("" : "+v"(xoff[0]), "+v"(xoff[MT > 1 ? 1 : 0]), "+v"(xoff[MT > 2 ? 2 : 0]));
+    if constexpr (MT > 3) asm volatile("" : "+v"(xoff[0]), "+v"(xoff[MT > 1 ? 1 : 0]), "+v"(xoff[MT > 2 ? 2 : 0]), "+v"(xoff[MT > 3 ? 3 : 0]));
     if constexpr (MT > 4) asm volatile("" : "+v"(xoff[4]), "+v"(xoff[MT > 5 ? 5 : 0]), "+v"(xoff[MT > 6 ? 6 : 1]), "+v"(xoff[MT > 7 ? 7 : 2]));
     auto one = [&](auto IC) {
       constexpr int i = decltype(IC)::value;
@@ -275,7 +291,7 @@ __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(MT > 4
     constexpr int held = 6 * MT + 2 * (MT / 2);   // MFMAs before the barrier
     // vector instructions that two decodes have at least: with more asked for, the order below comes out wrong
     constexpr bool wide = decltype(WIDE)::value;
-    constexpr int vector = kVectorCount(wide ? (H16 ? 2 : 1) : 0, SM, MT);
+    constexpr int vector = decode_vectors(wide ? (H16 ? 2 : 1) : 0, SM, MT);
     constexpr int asked = J & 1 ? 0 : (decltype(WIDE)::value ? 14 : 6) + (META && J == 0 ? 1 : 0);   // loads
     if constexpr (MT == 4) asm volatile("" : "+v"(a_frag));   // (the other three are formed in each step, not kept)
     load_frags(1, P, 1);
@@ -360,12 +376,12 @@ __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(MT > 4
   // Through the wavefront's own piece of LDS (32 rows of 128 bytes, 144 apart) they leave in whole lines: eight lanes to a row.
   unsigned char* own = smem + wave * (32 * 144);
   const int col = lane_now & 31, half = lane_now >> 5, row8 = lane_now >> 3, part = lane_now & 7;
-  unsigned char* put = own + col * 144 + half * (a.partial ? 16 : 8);
+  unsigned char* put = own + col * 144 + half * (!GATHER && a.partial ? 16 : 8);
   const u32x4* get = reinterpret_cast<const u32x4*>(own + row8 * 144 + part * 16);
 #pragma unroll
   for (int i = 0; i < MT; ++i) {
     if constexpr (MT > 4) asm volatile("" : "+a"(acc[i][0]), "+a"(acc[i][1]));   // read from the accumulator registers row tile by row tile
-    if (a.partial) {
+    if (!GATHER && a.partial) {
 #pragma unroll
       for (int c = 0; c < 2; ++c) {
 #pragma unroll
@@ -408,12 +424,46 @@ __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(MT > 4
   }
 }
 
+template <int FM, int SM, int MT>
+__global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(MT > 4 ? 1 : 2, MT > 4 ? 1 : 2))) ccq_block_kernel(const BlockArgs a) {
+  block_tile<FM, SM, false, MT>(a, __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), blockIdx.x * (32 * MT), blockIdx.y * kBlockCols, blockIdx.z);
+}
+
+// Grouped calls: blocks of up to 128 rows of an expert, as tall as its rows ask for: a body for each height, so that rows past an expert's end are
+// padded to 32, not to 128.  (64 experts of 2048 x 7168, 4096 rows, the fullest with 87: 64-row kernel 188, this 164 us; wide 302 / 216, mix
+// 292 / 197, hybrid word 356 / 215.)  Two blocks to a CU, as the dense kernel's 128-row blocks and bound as they are; the MFMAs of the padding are a
+// fifth of that time.
+template <int FM, int SM>
+__global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) ccq_block_grouped_kernel(const BlockArgs a) {
+  const int e = blockIdx.z, first = __builtin_amdgcn_readfirstlane(a.expert_offsets[e]), m0 = blockIdx.x * 128, n0 = blockIdx.y * kBlockCols;
+  BlockArgs p = a;
+  p.M = __builtin_amdgcn_readfirstlane(a.expert_offsets[e + 1]) - first;
+  if (m0 >= p.M) return;  // uniform: before any barrier
+  p.codes += e * a.codes_stride;
+  p.scales = reinterpret_cast<const uint16_t*>(reinterpret_cast<const uint8_t*>(a.scales) + e * a.scales_stride);
+  p.alpha = reinterpret_cast<const float*>(reinterpret_cast<const uint8_t*>(a.alpha) + e * a.ab_stride);
+  p.beta = reinterpret_cast<const float*>(reinterpret_cast<const uint8_t*>(a.beta) + e * a.ab_stride);
+  p.scale_super = reinterpret_cast<const uint16_t*>(reinterpret_cast<const uint8_t*>(a.scale_super) + e * a.ab_stride / 2);   // fp16 against fp32
+  p.sorted_rows += first;
+  p.y += (int64_t)first * a.ldy;
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int live = (min(p.M - m0, 128) + 31) / 32;
+  if (live == 1) block_tile<FM, SM, true, 1>(p, wave, m0, n0, 0);
+  else if (live == 2) block_tile<FM, SM, true, 2>(p, wave, m0, n0, 0);
+  else if (live == 3) block_tile<FM, SM, true, 3>(p, wave, m0, n0, 0);
+  else block_tile<FM, SM, true, 4>(p, wave, m0, n0, 0);
+}
+
 typedef void (*BlockKernel)(const BlockArgs);
 // The kernel of a format with blocks of 32 mt rows; each is built in a source file of its own.
 BlockKernel block_kernel_narrow(int scale_mode, int mt);
 BlockKernel block_kernel_wide(int scale_mode, int mt);
 BlockKernel block_kernel_mix(int scale_mode, int mt);
 BlockKernel block_kernel_h16(int scale_mode, int mt);
+BlockKernel block_grouped_narrow(int scale_mode);
+BlockKernel block_grouped_wide(int scale_mode);
+BlockKernel block_grouped_mix(int scale_mode);
+BlockKernel block_grouped_h16(int scale_mode);
 
 template <int FM, int SM>
 BlockKernel block_rows(int mt) {

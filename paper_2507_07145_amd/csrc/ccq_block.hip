@@ -5,7 +5,7 @@
 
 namespace ccq {
 
-// Estimated times in microseconds, fitted to 17000 launches of 832 random calls (65 to 4096 rows, K 512 to 28672, N 1000 to 28672, all
+// Estimated times in microseconds, fitted to 10800 launches of 832 random calls (65 to 4096 rows, K 512 to 28672, N 1000 to 28672, all
 // formats; nine in ten within 8 %).  Per step of K (a 64-weight group) a block alone takes `alone` + `alone_row` mt, and with all CUs at work, where
 // the clock falls with the power, the chip takes `all` + `all_row` mt for a block on every CU; 128-row blocks run one or two to a CU.
 struct BlockRates {
@@ -132,10 +132,11 @@ int64_t block_workspace_most(const Layout& L, int M_max) {
   return M_max <= 64 || L.K < 512 ? 0 : std::min<int64_t>(kPartialMost, (int64_t)8 * M_max * L.Npad * 4);
 }
 
-static int launch_part(const ccq_weight* w, const Layout& L, const void* x, int M, int64_t ldx, void* y, int64_t ldy, float* partial, const BlockPart& p,
-                       void* stream) {
+static BlockArgs block_args(const ccq_weight* w, const Layout& L, const void* x, int M, int64_t ldx, void* y, int64_t ldy, float* partial, const BlockPart& p) {
   const int64_t rt0 = p.n_first / kRowsPerTile;
   BlockArgs a;
+  a.sorted_rows = a.expert_offsets = nullptr;
+  a.codes_stride = a.scales_stride = a.ab_stride = 0;
   a.codes = static_cast<const uint8_t*>(w->codes) + rt0 * L.row_tile_bytes;
   a.scales = w->scales ? static_cast<const uint16_t*>(w->scales) + rt0 * L.row_tile_scale_halfs : nullptr;
   a.alpha = w->code_alpha ? w->code_alpha + p.n_first : nullptr;
@@ -162,6 +163,12 @@ static int launch_part(const ccq_weight* w, const Layout& L, const void* x, int 
     a.zp[k] = L.zp[k];
     for (int i = 0; i < 3; ++i) a.off[k][i] = -((k == kNarrow ? kNarrowBases[i] : kWideBases[i]) + L.zp[k]);
   }
+  return a;
+}
+
+static int launch_part(const ccq_weight* w, const Layout& L, const void* x, int M, int64_t ldx, void* y, int64_t ldy, float* partial, const BlockPart& p,
+                       void* stream) {
+  const BlockArgs a = block_args(w, L, x, M, ldx, y, ldy, partial, p);
   const int bm = 32 * p.mt;
   const size_t lds = kBlockLds0 + (size_t)2 * bm * kGroup * 2;
   const BlockKernel kern = L.h16 ? block_kernel_h16(L.scale_mode, p.mt)
@@ -202,6 +209,67 @@ int launch_block(const ccq_weight* w, const Layout& L, const void* x, int M, int
     }
   }
   return CCQ_OK;
+}
+
+// Grouped calls: blocks of up to 128 rows, and K is not cut.  Times by a fit to 565 random calls (4 to 160 experts, the fullest with 33 to 4000 rows; nine in
+// ten within 11 %): per step of K `alone` + `alone_row` times the 32-row tiles of the tallest block, and what the chip takes for all blocks, two to a CU;
+// the shorter of the two does not quite hide behind the longer.  Where blocks share CUs, which they do before each CU has one if the grid
+// has blocks without rows between them, a block takes 1.4 times as long.
+struct GroupedRates {
+  double alone, alone_row, all, all_row;
+};
+constexpr GroupedRates kGroupedNarrow = {0.30, 0.087, 0.47, 0.38}, kGroupedWide = {0.48, 0.088, 0.93, 0.32}, kGroupedH16 = {0.49, 0.105, 1.02, 0.30};
+
+static int grouped_row_blocks(int E, const GroupedRows& r) {
+  const int m = (r.most + 127) / 128;
+  // An even count of row blocks with many of them without rows leaves the others on a few of the chip's eight dies: an odd one spreads them.
+  return m % 2 == 0 && 8 * r.blocks128 < (int64_t)7 * m * E ? m + 1 : m;
+}
+
+double block_grouped_time(const Layout& L, int E, const GroupedRows& r) {
+  const double cus = device_cus(), n_blocks = (L.N + kBlockCols - 1) / kBlockCols;
+  const double blocks = n_blocks * (double)r.blocks128, tiles = n_blocks * (double)r.tiles32, grid = n_blocks * grouped_row_blocks(E, r) * E;
+  const double top = std::min(4, (r.most + 31) / 32);
+  const GroupedRates &n = kGroupedNarrow, &w = L.h16 ? kGroupedH16 : kGroupedWide;
+  auto steps = [&](double GroupedRates::*rate) {
+    return (double)(L.tiles[kNarrow] * kNarrowGroupsPerTile) * (n.*rate) + (double)(L.tiles[kWide] * kWideGroupsPerTile) * (w.*rate);
+  };
+  double alone = steps(&GroupedRates::alone) + steps(&GroupedRates::alone_row) * top;
+  if (blocks > cus || (blocks > cus / 2 && grid > 1.1 * blocks)) alone *= 1.42;
+  const double all = (steps(&GroupedRates::all) * blocks + steps(&GroupedRates::all_row) * tiles) / (2 * cus);
+  return 6.6 + std::max(alone, all) + 0.27 * std::min(alone, all) + 4.1 * blocks / (2 * cus) + 0.14e-3 * (grid - blocks);
+}
+
+// Against the 64-row kernel (565 calls: 0.90 of the time in the geometric mean with the rule, 0.89 with the better one each time; eight more than
+// 3 % slower, one by 16: mix 896 x 7041, 13 experts with up to 33 rows).
+bool block_grouped_is_better(const Layout& L, int E, const GroupedRows& r) {
+  return L.K >= 512 && block_grouped_time(L, E, r) < 0.93 * mid_grouped_time(L, E, r);
+}
+
+int launch_block_grouped(const ccq_weight* w0, const Layout& L, int E, int64_t codes_stride, int64_t scales_stride, int64_t ab_stride, const void* x,
+                         int64_t ldx, const int32_t* sorted_rows, int T, int P, const int32_t* expert_offsets, const GroupedRows& rows, void* y, int64_t ldy,
+                         void* stream) {
+  const int n_blocks = (L.N + kBlockCols - 1) / kBlockCols;
+  const int m_blocks = grouped_row_blocks(E, rows);
+  // 32-bit lane offsets reach any activation row, and the grid fits
+  if (E < 1 || E > 65535 || n_blocks > 65535 || rows.most < 1 || (int64_t)T * ldx * 2 + 4096 > (int64_t)1 << 32) return CCQ_ERR_UNSUPPORTED;
+  BlockPart p;
+  p.n_first = 0;
+  p.n_count = L.N;
+  p.mt = 4;
+  p.S = 1;
+  BlockArgs a = block_args(w0, L, x, P, ldx, y, ldy, nullptr, p);
+  a.sorted_rows = sorted_rows;
+  a.expert_offsets = expert_offsets;
+  a.codes_stride = codes_stride;
+  a.scales_stride = scales_stride;
+  a.ab_stride = ab_stride;
+  const BlockKernel kern = L.h16 ? block_grouped_h16(L.scale_mode)
+                                 : (L.tiles[kWide] == 0 ? block_grouped_narrow(L.scale_mode)
+                                                        : (L.tiles[kNarrow] == 0 ? block_grouped_wide(L.scale_mode) : block_grouped_mix(L.scale_mode)));
+  const size_t lds = kBlockLds0 + (size_t)2 * 128 * kGroup * 2;
+  hipLaunchKernelGGL(kern, dim3((unsigned)m_blocks, (unsigned)n_blocks, (unsigned)E), dim3(256), lds, static_cast<hipStream_t>(stream), a);
+  return hipGetLastError() == hipSuccess ? CCQ_OK : CCQ_ERR_HIP;
 }
 
 }  // namespace ccq

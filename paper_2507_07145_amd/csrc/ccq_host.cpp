@@ -757,17 +757,15 @@ extern "C" int ccq_grouped_gemm(const ccq_weight* w0, int32_t E, int64_t codes_s
   c.L = L;
   c.m_tile_hint = grouped_tile_rows(E, P);
   int active = E, most_rows = P;
-  int64_t row_blocks[2] = {0, 0};   // of 64 and of 128 rows
+  GroupedRows rows;
   if (expert_offsets_host) {
     active = 0;
-    most_rows = 0;
     for (int e = 0; e < E; ++e) {
-      const int rows = expert_offsets_host[e + 1] - expert_offsets_host[e];
-      active += rows > 0 ? 1 : 0;
-      most_rows = std::max(most_rows, rows);
-      row_blocks[0] += ceil_div(rows, 64);
-      row_blocks[1] += ceil_div(rows, 128);
+      const int n = expert_offsets_host[e + 1] - expert_offsets_host[e];
+      active += n > 0 ? 1 : 0;
+      rows.add(n);
     }
+    most_rows = rows.most;
   }
   if (expert_offsets_host && experts_listed(E, active)) {
     // launch over the experts that have rows only
@@ -777,11 +775,15 @@ extern "C" int ccq_grouped_gemm(const ccq_weight* w0, int32_t E, int64_t codes_s
       if (expert_offsets_host[e + 1] > expert_offsets_host[e]) c.active_ids[k++] = (uint16_t)e;
   }
   if (expert_offsets_host && most_rows > 32) {
-    // many rows per expert (a prefill-sized routing): the 64-row kernel, one grid over (row block, column block,
-    // expert); on narrow-format weights measured 2.2-2.4 times faster than 64-row passes of the per-row-tile kernel
-    // from 33 rows on, slower below
-    rc = launch_mid_grouped(w0, L, E, codes_stride, scales_stride, ab_stride, x, ldx, sorted_rows, T, P, expert_offsets_dev, most_rows, row_blocks,
-                            y, ldy, hip_stream);
+    // many rows per expert (a prefill-sized routing): one grid over (row block, column block, expert), of the prompt kernel's blocks or, where
+    // these are too few for the chip, the 64-row kernel's, which cut K inside a workgroup; the latter on narrow-format weights measured 2.2-2.4
+    // times faster than 64-row passes of the per-row-tile kernel from 33 rows on, slower below
+    rc = block_grouped_is_better(L, E, rows) ? launch_block_grouped(w0, L, E, codes_stride, scales_stride, ab_stride, x, ldx, sorted_rows, T, P,
+                                                                    expert_offsets_dev, rows, y, ldy, hip_stream)
+                                             : CCQ_ERR_UNSUPPORTED;
+    if (rc != CCQ_ERR_UNSUPPORTED) return rc;
+    rc = launch_mid_grouped(w0, L, E, codes_stride, scales_stride, ab_stride, x, ldx, sorted_rows, T, P, expert_offsets_dev, rows, y, ldy,
+                            hip_stream);
     if (rc != CCQ_ERR_UNSUPPORTED) return rc;
   }
   const int with_rows = expert_offsets_host ? active : std::min(E, P);   // experts that have rows (without the host copy: at most P)
@@ -875,6 +877,17 @@ extern "C" int ccq_prompt_plan(const ccq_weight* w, int32_t M, int32_t* out) {
     std::memcpy(out + 4 * i, v, sizeof(v));
   }
   return plan.parts;
+}
+
+// For tests, no part of the interface: whether a grouped call with these offsets takes the prompt kernel.
+extern "C" int ccq_prompt_grouped(const ccq_weight* w0, int32_t E, const int32_t* expert_offsets_host) {
+  Layout L;
+  const int rc = make_layout(w0, &L);
+  if (rc != CCQ_OK) return rc;
+  if (!expert_offsets_host) return CCQ_ERR_NULL;
+  GroupedRows rows;
+  for (int e = 0; e < E; ++e) rows.add(expert_offsets_host[e + 1] - expert_offsets_host[e]);
+  return rows.most > 32 && block_grouped_is_better(L, E, rows) ? 1 : 0;
 }
 
 // The GPU quantizer is built for every layout the multiply kernels read.

@@ -155,9 +155,26 @@ int launch_gemv16(const ccq_weight* w, const Layout& L, const void* x, int M, in
 // Kernel for a few dozen to a few hundred rows, any format mix (ccq_mid.hip): 64-row tiles, K cut into S
 // shares whose fp32 partial tiles go to `partial` ([S][M][N]) when S > 1 (then call launch_reduce_splits).
 constexpr int kMidMinM = 17;
+// Rows of a grouped call's experts: the most of one, and how many blocks of 32, 64 and 128 rows they fill.
+struct GroupedRows {
+  int most = 0;
+  int64_t tiles32 = 0, blocks64 = 0, blocks128 = 0;
+  void add(int rows) {
+    most = most < rows ? rows : most;
+    tiles32 += (rows + 31) / 32;
+    blocks64 += (rows + 63) / 64;
+    blocks128 += (rows + 127) / 128;
+  }
+};
 int launch_mid_grouped(const ccq_weight* w0, const Layout& L, int E, int64_t codes_stride, int64_t scales_stride, int64_t ab_stride, const void* x,
-                       int64_t ldx, const int32_t* sorted_rows, int T, int P, const int32_t* expert_offsets, int most_rows, const int64_t (&row_blocks)[2], void* y,
-                       int64_t ldy, void* stream);
+                       int64_t ldx, const int32_t* sorted_rows, int T, int P, const int32_t* expert_offsets, const GroupedRows& rows, void* y, int64_t ldy,
+                       void* stream);
+double mid_grouped_time(const Layout& L, int E, const GroupedRows& rows);   // estimates, microseconds
+double block_grouped_time(const Layout& L, int E, const GroupedRows& rows);
+bool block_grouped_is_better(const Layout& L, int E, const GroupedRows& rows);
+int launch_block_grouped(const ccq_weight* w0, const Layout& L, int E, int64_t codes_stride, int64_t scales_stride, int64_t ab_stride, const void* x,
+                         int64_t ldx, const int32_t* sorted_rows, int T, int P, const int32_t* expert_offsets, const GroupedRows& rows, void* y, int64_t ldy,
+                         void* stream);
 int mid_splits(const Layout& L, int M);              // the most shares across the grid (what the workspace is asked for)
 int mid_shares(const Layout& L, int M, int most);    // those that a call takes
 double mid_time(const Layout& L, int M);             // estimate of a dense call, microseconds
