@@ -449,6 +449,10 @@ __global__ void __launch_bounds__(256) ccq_encode_cluster_kernel(const EncArgs a
 // value of every block of eight candidates is tracked (best block, second best value); the eight of the best block are
 // compared in fp32 as sums of squares; both times the answer is taken only when the next best is further away than
 // rounding reaches, and the other vectors are searched in fp64.
+// Bound by vector issue, so what is not needed stays out: products in vector registers (two wavefronts per SIMD asked for at least: with more
+// registers allowed the compiler takes accumulator registers and moves every product out, 256 moves per 64 vectors), minima without
+// the quieting of their operands, a lane of the map per candidate, its levels from a table.  8192 x 8192, finish pass 425 -> 305 us, 676 ->
+// 600 vector instructions per 64 vectors by the last two (1066 at first).
 typedef __attribute__((ext_vector_type(8))) __bf16 enc_bf16x8;
 typedef __attribute__((ext_vector_type(2))) __bf16 enc_bf16x2;
 typedef __attribute__((ext_vector_type(2))) float enc_f32x2;
@@ -467,29 +471,43 @@ __device__ __forceinline__ uint32_t cluster_code(float q, float al, float bem) {
 
 struct RowMap {
   enc_u32x4 A[8];   // the candidates, 32 per tile
+  const uint32_t* states;   // of all of them, a byte each (LDS, this wavefront's)
   float al, bem, zp, lmax;
 };
 
-__device__ __forceinline__ void row_map(RowMap& m, float al, float be, float zp, int lane) {
+// A lane works out one candidate of two tiles' 64, and the halves of the wavefront exchange them.
+__device__ __forceinline__ void row_map(RowMap& m, float al, float be, float zp, uint32_t* states, int lane) {
   m.al = al;
   m.bem = be + 0x1p23f;
   m.zp = zp;
   m.lmax = fmaxf(zp, 63.f - zp);
+  m.states = states;
+  const bool upper = lane >= 32;
 #pragma unroll
-  for (int t = 0; t < 8; ++t) {
-    const uint32_t c = cluster_code((float)(32 * t + (lane & 31)), al, m.bem);
+  for (int t = 0; t < 8; t += 2) {
+    const uint32_t c = cluster_code((float)(32 * t + lane), al, m.bem);
     float lv[4], n = 0.f;
+    uint32_t all = 0;
 #pragma unroll
     for (int i = 0; i < 4; ++i) {
-      lv[i] = (float)unit_state<kEncNarrow>(c, i) - zp;
+      const uint32_t st = unit_state<kEncNarrow>(c, i);
+      lv[i] = (float)st - zp;
       n = __builtin_fmaf(lv[i], lv[i], n);
+      all |= st << (8 * i);
     }
+    states[32 * t + lane] = all;
     const uint32_t l01 = enc_pack_bf16(lv[0], lv[1]), l23 = enc_pack_bf16(lv[2], lv[3]);
     const uint32_t nh = enc_pack_bf16(n, 0.f);
     const uint32_t nn = nh | (enc_pack_bf16(n - enc_lo(nh), 0.f) << 16);
-    const bool upper = lane >= 32;
-    m.A[t] = enc_u32x4{l01, l23, upper ? nn : l01, upper ? 0u : l23};
+    // element 0: what the lower lanes hold, in both halves; 1: what the upper lanes hold
+    const auto x01 = __builtin_amdgcn_permlane32_swap(l01, l01, false, false);
+    const auto x23 = __builtin_amdgcn_permlane32_swap(l23, l23, false, false);
+    const auto xn = __builtin_amdgcn_permlane32_swap(nn, nn, false, false);
+#pragma unroll
+    for (int h = 0; h < 2; ++h) m.A[t + h] = enc_u32x4{x01[h], x23[h], upper ? xn[h] : x01[h], upper ? 0u : x23[h]};
   }
+  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+  __builtin_amdgcn_wave_barrier();
 }
 
 __device__ __forceinline__ double cluster_cost(uint32_t c, const double (&v)[4], double s, double zp) {
@@ -537,7 +555,8 @@ __device__ __forceinline__ uint32_t search_cluster(const RowMap& m, const float4
 #pragma unroll
       for (int b = 0; b < 2; ++b) {
         const float b0 = fminf(fminf(d[8 * b], d[8 * b + 1]), d[8 * b + 2]), b1 = fminf(fminf(d[8 * b + 3], d[8 * b + 4]), d[8 * b + 5]);
-        see_block(fminf(fminf(b0, b1), fminf(d[8 * b + 6], d[8 * b + 7])), 2 * k + b, best[h], second[h], at[h]);
+        const float b2 = fminf(fminf(b0, b1), d[8 * b + 6]);
+        see_block(med_(b2, d[8 * b + 7], -kFar), 2 * k + b, best[h], second[h], at[h]);
       }
     }
   }
@@ -556,19 +575,25 @@ __device__ __forceinline__ uint32_t search_cluster(const RowMap& m, const float4
   bool sure = next - first > 0x1p-18f * (4.f * m.lmax * m.lmax + 8.f * m.lmax * tmax);
   // the best block's candidates: rows 16 (blk % 2) + 4 half + {0..3, 8..11} of tile blk / 2
   const int q0 = 16 * blk + (upper ? 4 : 0);
+  const enc_u32x4 near[2] = {*reinterpret_cast<const enc_u32x4*>(m.states + q0), *reinterpret_cast<const enc_u32x4*>(m.states + q0 + 8)};
+  float u[4];   // the wanted places among the states: rounded once more than t, which every difference then carries
+#pragma unroll
+  for (int k = 0; k < 4; ++k) u[k] = t[k] + m.zp;
   Best2 in;
 #pragma unroll
   for (int i = 0; i < 8; ++i) {
-    const uint32_t c = cluster_code((float)(q0 + i + (i & 4)), m.al, m.bem);
+    const uint32_t states = near[i >> 2][i & 3];
     float T = 0.f;
 #pragma unroll
     for (int k = 0; k < 4; ++k) {
-      const float d = ((float)unit_state<kEncNarrow>(c, k) - m.zp) - t[k];
+      const float d = (float)((states >> (8 * k)) & 255u) - u[k];
       T = __builtin_fmaf(d, d, T);
     }
     in.see(T, i + (i & 4));
   }
-  sure = sure && in.gap() > search_margin(in.best, tmax) && tmax <= kSearchMaxT;
+  // (2 sum |d| 2^-24 |u| on either side, in search_margin's terms)
+  const float apart = search_margin(in.best, tmax) + 0x1p-22f * (tmax + fabsf(m.zp)) * (in.best + 1.f);
+  sure = sure && in.gap() > apart && tmax <= kSearchMaxT;
   uint32_t q = (uint32_t)(q0 + in.at) & 255u;
   unsigned long long todo = __ballot(active && !sure);
   while (todo) {   // exactly: four candidates per lane
@@ -628,14 +653,15 @@ __device__ __forceinline__ void store_bytes(const EncArgs& a, const ClusterBlock
 // reach (never worse than rounding the unconstrained code by Eq. 1, which is one of the candidates), then one more Eq. 4
 // refit with the final codes, kept when the error does not grow; its sums run one group per lane.
 template <int TILES>
-__global__ void __launch_bounds__(256) ccq_encode_finish_narrow_kernel(const EncArgs a) {
+__global__ void __launch_bounds__(256, 4) ccq_encode_finish_narrow_kernel(const EncArgs a) {
   __shared__ __attribute__((aligned(16))) float wl[16 * TILES * kEncRow];
   __shared__ __attribute__((aligned(16))) uint32_t ql[16 * TILES * 4];
+  __shared__ __attribute__((aligned(16))) uint32_t states[4 * 256];
   const int lane = threadIdx.x & 63, gj = lane >> 4;
   const ClusterBlock b = cluster_block<TILES>(a);
   if (b.n < a.N) {   // (uniform in the wavefront)
     RowMap m;
-    row_map(m, a.alpha[b.n], a.beta[b.n], (float)a.zp, lane);
+    row_map(m, a.alpha[b.n], a.beta[b.n], (float)a.zp, states + 256 * b.row, lane);
 #pragma unroll 1
     for (int t = 0; t < TILES; ++t) {
       const int p = (b.tile0 + t) * 4 + gj, slot = (t * 4 + b.row) * 4 + gj;
@@ -762,13 +788,14 @@ __global__ void __launch_bounds__(64 * LPG) ccq_encode_compress_kernel(const Enc
 // Narrow format: over the 256 codes of the row's map; the four fields of a k-tile's groups go into one 16-bit word per
 // row (group j in bits 4j..4j+3; groups that pad the last k-tile keep field 0: scale 0).
 template <int TILES>
-__global__ void __launch_bounds__(256) ccq_encode_compress_narrow_kernel(const EncArgs a) {
+__global__ void __launch_bounds__(256, 4) ccq_encode_compress_narrow_kernel(const EncArgs a) {
   __shared__ __attribute__((aligned(16))) uint32_t ql[16 * TILES * 4];
+  __shared__ __attribute__((aligned(16))) uint32_t states[4 * 256];
   const int lane = threadIdx.x & 63, gj = lane >> 4;
   const ClusterBlock b = cluster_block<TILES>(a);
   if (b.n < a.N) {   // (uniform in the wavefront)
     RowMap m;
-    row_map(m, a.alpha[b.n], a.beta[b.n], (float)a.zp, lane);
+    row_map(m, a.alpha[b.n], a.beta[b.n], (float)a.zp, states + 256 * b.row, lane);
 #pragma unroll 1
     for (int t = 0; t < TILES; ++t) {
       const int tile = b.tile0 + t, p = tile * 4 + gj;
