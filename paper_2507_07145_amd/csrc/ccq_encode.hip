@@ -345,16 +345,86 @@ __device__ __forceinline__ double refit_scale(const float* wg, const uint16_t* c
   return fp16_scale(s1);
 }
 
+// Smallest and largest (<< 16) code, narrow format, of each row's four groups under the scales sl, returned to threads 0 .. 15.  Of the second search
+// nothing else is wanted, so only vectors that can have one of the two are searched.  cl holds the first search's codes: what such a code costs
+// under the new scale is no less than what the nearest one does, so the nearest one's first state, the upper six bits of its code, is no
+// further from its weight than the root of that cost.  A vector whose least possible state is above the row's smallest greatest one cannot have
+// the row's smallest code, and so for the largest.  About one in eight is left on Gaussian weights; they are listed (in cl) and shared out
+// over the workgroup.  (8192 x 8192, first pass: 287 us with all vectors searched, 219.)
+template <int LPG>
+__device__ __forceinline__ uint32_t code_range(const float* wl, uint16_t* cl, const double* sl, double zp, bool there, bool live, int tid) {
+  constexpr int CS = kEncUnitRow<kEncNarrow>, kThreads = 64 * LPG, kMine = 16 / LPG;
+  static_assert(64 * CS >= 1024, "the list takes the place of the codes");
+  __shared__ uint32_t row_lo[16], row_hi[16], listed;
+  const int lane = tid & 63, gl = tid / LPG, sub = tid % LPG;
+  if (tid < 16) row_lo[tid] = 0xFFFFu, row_hi[tid] = 0u;
+  if (tid == 0) listed = 0;
+  __syncthreads();
+  const InvScale inv = inv_scale(live ? sl[gl] : 1.0);
+  const float zpf = (float)zp;
+  int lo[kMine], hi[kMine], least = 63, most = 0;   // a row's smallest greatest state, and its largest least one
+#pragma unroll
+  for (int i = 0; i < kMine; ++i) {
+    const int j = sub + i * LPG;
+    float v[4], T = 0.f, u0 = 0.f;
+    unit_weights<kEncNarrow>(wl + gl * kEncRow, j, v);
+    const uint32_t c = cl[gl * CS + j];
+#pragma unroll
+    for (int k = 0; k < 4; ++k) {
+      const float u = unit_scale(v[k], inv) + zpf, d = (float)unit_state<kEncNarrow>(c, k) - u;
+      T = __builtin_fmaf(d, d, T);
+      if (k == 0) u0 = u;
+    }
+    // (u and T are off by a millionth of themselves; NaN and what is far beyond the levels can be anything)
+    const bool known = T < 1e6f;
+    const float r = __builtin_fmaf(__builtin_amdgcn_sqrtf(T), 1.001f, 0.01f);
+    lo[i] = known ? (int)med_(ceilf(u0 - r), 0.f, 63.f) : 0;
+    hi[i] = known ? (int)med_(floorf(u0 + r), 0.f, 63.f) : 63;
+    if (!live) lo[i] = hi[i] = 0;   // codes of zero
+    if (there) least = min(least, hi[i]), most = max(most, lo[i]);
+  }
+#pragma unroll
+  for (int off = 2 * LPG; off >= 1; off >>= 1) {
+    least = min(least, __shfl_xor(least, off));
+    most = max(most, __shfl_xor(most, off));
+  }
+  __syncthreads();   // the codes have been read
+#pragma unroll
+  for (int i = 0; i < kMine; ++i)
+    if (there && live && (lo[i] <= least || hi[i] >= most)) cl[atomicAdd(&listed, 1u)] = (uint16_t)(gl * 16 + sub + i * LPG);
+  if (there && !live && sub == 0) atomicMin(&row_lo[gl >> 2], 0u);
+  __syncthreads();
+  const int count = (int)listed;
+  const H16Tail none = {};
+#pragma unroll 1
+  for (int i0 = 0; i0 < count; i0 += kThreads) {
+    // (with sixteen lanes per group a wavefront's exact searches, one after the other, are the time: every wavefront takes a few)
+    const int i = i0 + (LPG > 4 ? lane * LPG + (tid >> 6) : tid);
+    const bool active = i < count;
+    const int id = active ? cl[i] : 0, g = id >> 4;
+    float v[4];
+    unit_weights<kEncNarrow>(wl + g * kEncRow, id & 15, v);
+    const double s = sl[g];
+    const uint32_t c = search_unit<kEncNarrow>(v, s, inv_scale(active ? s : 1.0), zp, none, 0, active, lane) & 0xFFFFu;
+    if (active) {
+      atomicMin(&row_lo[g >> 2], c);
+      atomicMax(&row_hi[g >> 2], c);
+    }
+  }
+  __syncthreads();
+  return tid < 16 ? row_lo[tid] | (row_hi[tid] << 16) : 0u;
+}
+
 // First pass, LPG lanes per (row, group): scale = absmax / (2^(L-1) - 1), search, Eq. 4 refit (kept when the error does
 // not grow), fp16 rounding, search again with the stored scale.  An all-zero group gets scale 0 and codes 0.  Without
 // Code Cluster this is the final result and is written in device order; with it only the scales and the range of the
-// codes are wanted by the passes that follow.
+// codes are wanted by the passes that follow (code_range).
 template <int FMT, int LPG>
 __global__ void __launch_bounds__(64 * LPG) ccq_encode_groups_kernel(const EncArgs a) {
   constexpr int CS = kEncUnitRow<FMT>;
   __shared__ __attribute__((aligned(16))) float wl[64 * kEncRow];
   __shared__ uint16_t cl[64 * CS];
-  __shared__ double sl[LPG > 4 ? 64 : 1];
+  __shared__ double sl[FMT == kEncNarrow || LPG > 4 ? 64 : 1];
   const int tid = threadIdx.x, lane = tid & 63, rt = blockIdx.x / a.quads, quad = blockIdx.x % a.quads;
   load_groups<64 * LPG>(a, rt, quad, wl, tid);
   __syncthreads();
@@ -373,38 +443,30 @@ __global__ void __launch_bounds__(64 * LPG) ccq_encode_groups_kernel(const EncAr
   const bool live = amax != 0.f;
   const double s0 = (double)amax / (double)EncTraits<FMT>::QMAX;
   search_groups<FMT, LPG>(wg, cg, s0, a.zp, a.tail, live, sub, lane);
-  if constexpr (LPG > 4) {
-    if (sub == 0) sl[gl] = s0;
-  }
+  constexpr bool kOneWave = FMT == kEncNarrow || LPG > 4;
+  if (kOneWave && sub == 0) sl[gl] = s0;
   __syncthreads();
   double s = 0.0;
-  if constexpr (LPG <= 4) {   // every lane of a group runs its sums
-    if (live) s = refit_scale<FMT>(wg, cg, s0, a.zp);
-    __syncthreads();
-  } else {                    // one lane per group, all in the first wavefront: sixteen copies would share the CU's fp64 units
-    if (tid < 64) {
-      const double st = sl[tid];
-      if (st != 0.0) sl[tid] = refit_scale<FMT>(wl + tid * kEncRow, cl + tid * CS, st, a.zp);
+  if constexpr (kOneWave) {
+    // The sums, one lane per group: sixteen copies would share the CU's fp64 units.  By one wavefront of the workgroup, not the same in all of
+    // them, as a wavefront's place decides its SIMD.  (Two lanes per group, 8192 x 8192, against both running the sums: narrow 219 -> 211 us, but
+    // wide 287 -> 293, whose workgroups have more to do on either side of it.)
+    if ((tid >> 6) == (int)((blockIdx.x * 2654435761u) >> (32 - (LPG == 2 ? 1 : (LPG == 4 ? 2 : 4))))) {
+      const double st = sl[lane];
+      if (st != 0.0) sl[lane] = refit_scale<FMT>(wl + lane * kEncRow, cl + lane * CS, st, a.zp);
     }
     __syncthreads();
     s = sl[gl];
+  } else {
+    if (live) s = refit_scale<FMT>(wg, cg, s0, a.zp);
+    __syncthreads();
   }
-  search_groups<FMT, LPG>(wg, cg, s, a.zp, a.tail, live, sub, lane);
   if constexpr (FMT == kEncNarrow) {
     if (there && sub == 0) a.rowscale[(int64_t)n * a.GK + p] = fp16_bits(s);
-    uint32_t lo = 0xFFFFu, hi = 0;
-    if (there)
-      for (int j = sub; j < 16; j += LPG) {
-        lo = min(lo, (uint32_t)cg[j]);
-        hi = max(hi, (uint32_t)cg[j]);
-      }
-#pragma unroll
-    for (int off = 2 * LPG; off >= 1; off >>= 1) {
-      lo = min(lo, (uint32_t)__shfl_xor((int)lo, off));
-      hi = max(hi, (uint32_t)__shfl_xor((int)hi, off));
-    }
-    if (n < a.N && (gl & 3) == 0 && sub == 0) a.minmax[(int64_t)n * a.quads + quad] = lo | (hi << 16);
+    const uint32_t range = code_range<LPG>(wl, cl, sl, a.zp, there, live, tid);
+    if (tid < 16 && rt * kRowsPerTile + tid < a.N) a.minmax[(int64_t)(rt * kRowsPerTile + tid) * a.quads + quad] = range;
   } else {
+    search_groups<FMT, LPG>(wg, cg, s, a.zp, a.tail, live, sub, lane);
     __syncthreads();
     store_units<FMT>(a, rt, quad, cl, tid, 64 * LPG);
     if (there && sub == 0) {
