@@ -188,8 +188,12 @@ __global__ void __launch_bounds__(256 * mid_waves(FM, BM, SCHEDULE != kLean))
   }
   const uint8_t* code_wide = code_row + (int64_t)a.tiles[kNarrow] * kNarrowTileBytes;
   const uint16_t* scale_wide = scale_row + (int64_t)a.tiles[kNarrow] * kNarrowTileScaleHalfs;
-  uint32_t c43 = 0x43000000u, mask2 = kDecMask2, base2 = kDecBase2, mask_w = 0x00070000u, mask_w2 = kDecMaskW2;  // mask_w: the hybrid word's 3-bit states
-  asm volatile("" : "+v"(c43), "+s"(mask2), "+v"(base2), "+s"(mask_w), "+s"(mask_w2));
+  uint32_t c43 = 0x43000000u, mask2 = kDecMask2, base2 = kDecBase2, mask_w = 0x00070000u;  // mask_w: the hybrid word's 3-bit states
+  asm volatile("" : "+v"(c43), "+s"(mask2), "+v"(base2), "+s"(mask_w));
+  // fp16 scales: the windows stay where they lie, but for the narrow format alone (33 to 100 rows: wide 42 x 4416 x 3408 17.5 -> 17.2 us; mix
+  // 93 x 1600 x 2386 17.1 -> 16.5, with the wide ones only 16.8; narrow level, seventeen calls within 1 %)
+  constexpr bool kWindowsN = SM == 0 && HAS_W;
+  const DecWindows win_n = dec_windows<false>(), win_w = dec_windows<true>();
 
   // code entries in registers: the k-tile being decoded and the next one of the same kind
   u32x4 cn[2], cn_next[2];
@@ -270,20 +274,19 @@ __global__ void __launch_bounds__(256 * mid_waves(FM, BM, SCHEDULE != kLean))
     float s;
     if constexpr (SM == 0) s = fp16_of((j >> 1) ? sn.y : sn.x, j);
     else s = (float)((sn.x >> (4 * j)) & 0xFu) * ssup;  // (s_q >> s_shift) & s_mask times s_super: exact
-    const float c0 = -(kDecBase + a.zp[kNarrow]) * s;   // exact: 8-bit times at most 15-bit significand
+    float c0[3];   // exact: 8-bit times at most 15-bit significand (fp16 scales: 12-bit times 11-bit)
+#pragma unroll
+    for (int i = 0; i < (kWindowsN ? 3 : 1); ++i) c0[i] = -(kNarrowBases[i] + a.zp[kNarrow]) * s;
 #pragma unroll
     for (int q = 0; q < 2; ++q) {
       uint32_t o[8];
-      decode16_narrow(dword_sel(cn[q], j), al, bem, s, c0, mask2, base2, o);
+      if constexpr (kWindowsN) decode16_narrow_fp16(dword_sel(cn[q], j), al, bem, s, c0, win_n, o);
+      else decode16_narrow(dword_sel(cn[q], j), al, bem, s, c0[0], mask2, base2, o);
       bf[2 * q] = u32x4{o[0], o[1], o[2], o[3]};
       bf[2 * q + 1] = u32x4{o[4], o[5], o[6], o[7]};
     }
   };
-  // byte selectors of the wide format (low and high halfword of a dword): two neighbouring codes of entries i and i + 1 as
-  // {0, b, 0, a}, and the two codes of the single weights as {0, second, 0, first}
-  const uint32_t sel_pair[2] = {h ? 0x0C040C01u : 0x0C010C00u, h ? 0x0C060C03u : 0x0C030C02u};
-  const uint32_t sel_one[2] = {h ? 0x0C050C00u : 0x0C040C04u, h ? 0x0C070C02u : 0x0C060C06u};
-  const uint32_t one_shift = h ? 4u : 2u, funnel = h ? 0u : 16u;
+  const WideLane wlane = wide_lane(h);
   // group j of the held wide (or hybrid-word) k-tile
   auto decode_wide = [&](u32x4 (&bf)[KK], int j) {
     float s;
@@ -318,25 +321,15 @@ __global__ void __launch_bounds__(256 * mid_waves(FM, BM, SCHEDULE != kLean))
         bf[kk] = u32x4{pack_bf16_m(f0, f1), pack_bf16_m(f2, f3), pack_bf16_m(f4, f5), pack_bf16_m(f6, f6)};
       }
     } else {
-      const float c0 = -(kDecBase + a.zp[kWide]) * s;
-      float f[32];  // 0: the first single weight (32, or 31), 1..30: the whole codes, 31: the second one (63, or 30)
+      float c0[3];
 #pragma unroll
-      for (int i = 0; i < 5; ++i) {
-        float w6[6];
-        decode6_wide(__builtin_amdgcn_perm(dword_sel(cw[i + 1], j >> 1), dword_sel(cw[i], j >> 1), sel_pair[j & 1]), s, c0, mask_w2, base2, w6);
+      for (int i = 0; i < (SM == 0 ? 3 : 1); ++i) c0[i] = -(kWideBases[i] + a.zp[kWide]) * s;
+      uint32_t d[6], o[16];
 #pragma unroll
-        for (int e = 0; e < 6; ++e) f[1 + 6 * i + e] = w6[e];
-      }
-      const uint32_t pe = __builtin_amdgcn_perm(dword_sel(cw[NQ - 1], j >> 1), dword_sel(cw[0], j >> 1), sel_one[j & 1]);
-      f[0] = __builtin_fmaf((float)__builtin_bit_cast(f16x2, dec_and_or(pe << one_shift, mask_w2, base2)).x, s, c0);
-      f[31] = __builtin_fmaf((float)__builtin_bit_cast(f16x2, dec_and_or(pe, mask_w2, base2)).y, s, c0);
-      uint32_t q[16];
+      for (int i = 0; i < 6; ++i) d[i] = dword_sel(cw[min(i, NQ - 1)], j >> 1);
+      decode32_wide<SM == 0>(d, j & 1, s, c0, wlane, win_w, o);
 #pragma unroll
-      for (int i = 0; i < 16; ++i) q[i] = pack_bf16_m(f[2 * i], f[2 * i + 1]);
-#pragma unroll
-      for (int kk = 0; kk < 4; ++kk)
-#pragma unroll
-        for (int d = 0; d < 4; ++d) bf[kk][d] = __builtin_amdgcn_alignbit(q[(4 * kk + d + 1) & 15], q[4 * kk + d], funnel);
+      for (int kk = 0; kk < 4; ++kk) bf[kk] = u32x4{o[4 * kk], o[4 * kk + 1], o[4 * kk + 2], o[4 * kk + 3]};
     }
   };
 
