@@ -251,8 +251,9 @@ int launch_block_grouped(const ccq_weight* w0, const Layout& L, int E, int64_t c
                          void* stream) {
   const int n_blocks = (L.N + kBlockCols - 1) / kBlockCols;
   const int m_blocks = grouped_row_blocks(E, rows);
-  // 32-bit lane offsets reach any activation row, and the grid fits
-  if (E < 1 || E > 65535 || n_blocks > 65535 || rows.most < 1 || (int64_t)T * ldx * 2 + 4096 > (int64_t)1 << 32) return CCQ_ERR_UNSUPPORTED;
+  // 32-bit lane offsets reach any activation row and the row tiles of a wavefront, and the grid fits
+  if (E < 1 || E > 65535 || n_blocks > 65535 || rows.most < 1 || (int64_t)T * ldx * 2 + 4096 > (int64_t)1 << 32 || 4 * L.row_tile_bytes >= (int64_t)1 << 31)
+    return CCQ_ERR_UNSUPPORTED;
   BlockPart p;
   p.n_first = 0;
   p.n_count = L.N;

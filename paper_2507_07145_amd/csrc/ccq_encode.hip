@@ -511,10 +511,10 @@ __global__ void __launch_bounds__(256) ccq_encode_cluster_kernel(const EncArgs a
 // value of every block of eight candidates is tracked (best block, second best value); the eight of the best block are
 // compared in fp32 as sums of squares; both times the answer is taken only when the next best is further away than
 // rounding reaches, and the other vectors are searched in fp64.
-// Bound by vector issue, so what is not needed stays out: products in vector registers (two wavefronts per SIMD asked for at least: with more
+// Bound by vector issue, so what is not needed stays out: products in vector registers (four wavefronts per SIMD asked for: with more than 256
 // registers allowed the compiler takes accumulator registers and moves every product out, 256 moves per 64 vectors), minima without
 // the quieting of their operands, a lane of the map per candidate, its levels from a table.  8192 x 8192, finish pass 425 -> 305 us, 676 ->
-// 600 vector instructions per 64 vectors by the last two (1066 at first).
+// 613 vector instructions per 64 vectors by the last two (1066 at first).
 typedef __attribute__((ext_vector_type(8))) __bf16 enc_bf16x8;
 typedef __attribute__((ext_vector_type(2))) __bf16 enc_bf16x2;
 typedef __attribute__((ext_vector_type(2))) float enc_f32x2;

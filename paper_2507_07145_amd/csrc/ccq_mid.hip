@@ -1,8 +1,8 @@
-// Fused dequantize-and-multiply for a few dozen activation rows (about 17 to 128), any mix of the
-// narrow (L=6,N=4,S=3 + Code Cluster) and wide (L=4,N=3,S=2) formats, gfx950.
+// Fused dequantize-and-multiply for a few dozen activation rows (17 to 64; more where the product is too small for the prompt kernel's
+// blocks, ccq_block.h, to fill the chip; experts with more than 32 rows, likewise), any mix of the narrow (L=6,N=4,S=3 + Code
+// Cluster) and wide (L=4,N=3,S=2) formats, gfx950.
 //
-// With that many rows the per-row-tile kernel re-stages the activations far too often, and the
-// 256-row kernel wastes three quarters of its tile.  Here a workgroup of four wavefronts owns a 64 x 128 (or, on the
+// With that many rows the per-row-tile kernel re-stages the activations far too often, and taller blocks waste most of their tile.  Here a workgroup of four wavefronts owns a 64 x 128 (or, on the
 // narrow format, 128 x 128) tile of the output and a share of K (S shares across the grid, up to four in a workgroup; fp32 partial tiles go to
 // the workspace and are added in index order by the reduction kernel when S > 1).  K is walked one 64-weight group per
 // step; per step
@@ -193,7 +193,9 @@ __global__ void __launch_bounds__(256 * mid_waves(FM, BM, SCHEDULE != kLean))
   // fp16 scales: the windows stay where they lie, but for the narrow format alone (33 to 100 rows: wide 42 x 4416 x 3408 17.5 -> 17.2 us; mix
   // 93 x 1600 x 2386 17.1 -> 16.5, with the wide ones only 16.8; narrow level, seventeen calls within 1 %)
   constexpr bool kWindowsN = SM == 0 && HAS_W;
-  const DecWindows win_n = dec_windows<false>(), win_w = dec_windows<true>();
+  DecWindows win_n{}, win_w{};
+  if constexpr (kWindowsN) win_n = dec_windows<false>();
+  if constexpr (HAS_W && !H16) win_w = dec_windows<true>();
 
   // code entries in registers: the k-tile being decoded and the next one of the same kind
   u32x4 cn[2], cn_next[2];

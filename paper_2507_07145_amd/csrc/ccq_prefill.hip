@@ -1,7 +1,7 @@
-// Prefill (large M) fused dequantize-and-multiply for the narrow format
-// (L=6,N=4,S=3 + Code Cluster), gfx950.
+// Fused dequantize-and-multiply of many rows for the narrow format (L=6,N=4,S=3 + Code Cluster) with K below 512, gfx950: few steps
+// of K, for which the prompt kernel (ccq_block.h) takes too long to start.
 //
-// This is the one place where the work is a dense contraction: a workgroup owns
+// A workgroup owns
 // a 256 x BN tile of the output, walks K in steps of one 64-weight group, and per
 // step
 //   - copies the 256 x 64 activation tile to LDS,
