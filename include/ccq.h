@@ -170,15 +170,16 @@ int ccq_gemm(const ccq_weight *w, const void *x, int32_t M, int64_t ldx, void *y
              void *workspace, int64_t workspace_bytes, void *hip_stream);
 
 /* Workspace bytes ccq_gemm needs for exactly M rows (<= the ccq_pack_info figure for any M_max >= M);
- * -1 for an invalid descriptor.  Pure host code. */
+ * -1 for an invalid descriptor.  Pure host code.  A prompt is served with less of it too, in several passes over the rows
+ * with the same results, down to what the same call needed in 64-row blocks. */
 int64_t ccq_gemm_workspace_bytes(const ccq_weight *w, int32_t M);
 
 /* ccq_gemm for callers that cannot allocate device memory or bring a workspace: code under HIP graph capture,
  * tight serving loops, harnesses that forbid hipMalloc.  Same arguments, kernels and results as ccq_gemm (bit for
  * bit), without the workspace: the fp32 partial tiles of the K shares live in a device array that belongs to the
  * library (ccq_gemm_static_max_workspace() bytes, 8 MiB, held on every GPU the library has run on until the
- * process ends).  A call that would need more (ccq_gemm_workspace_bytes(w, M) tells) returns CCQ_ERR_WORKSPACE and
- * enqueues nothing.  No hipMalloc, hipFree or other allocating call is made.  All calls on one GPU share the
+ * process ends).  A prompt (more than 64 rows) whose ccq_gemm_workspace_bytes(w, M) is more goes through the array some rows
+ * at a time, where its rows can; any other call that needs more returns CCQ_ERR_WORKSPACE and enqueues nothing.  No hipMalloc, hipFree or other allocating call is made.  All calls on one GPU share the
  * array: calls that may overlap on one GPU (different streams, concurrent graph launches) race on it and
  * must be ordered by the caller; calls on one stream are ordered by the stream. */
 int ccq_gemm_static(const ccq_weight *w, const void *x, int32_t M, int64_t ldx, void *y, int64_t ldy, void *hip_stream);
