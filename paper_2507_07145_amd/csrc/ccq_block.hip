@@ -17,8 +17,7 @@ constexpr BlockRates kRatesH16 = {0.64, 0.08, 0.47, 0.151, 0.93, 1.70, 2.02};
 constexpr double kCallTime = 9.1, kSecondPart = 5.4;      // of the first and the second part of a call
 constexpr double kRoundTime = -3.0, kRoundTimeRow = 0.80; // more per round of blocks: start, and the outputs
 constexpr double kPartialRate = 9.9e6;                    // bytes of partial tiles, written and read, per microsecond
-// A plan's partial tiles: no more than this, and 32 rows of them fit the 8 MiB of ccq_gemm_static.
-constexpr int64_t kPartialMost = 100 << 20, kPartialRow = (8 << 20) / 32;
+constexpr int64_t kPartialRow = (8 << 20) / 32;           // 32 rows of a plan's partial tiles fit 8 MiB, that is
 
 static double part_time(const Layout& L, int M, const BlockPart& p) {
   const double qn = L.tiles[kNarrow] ? 4.0 * ((L.tiles[kNarrow] + p.S - 1) / p.S) : 0.0, qw = L.tiles[kWide] ? 4.0 * ((2 * L.tiles[kWide] + p.S - 1) / p.S) : 0.0;
@@ -64,7 +63,7 @@ static double best_part(const Layout& L, int M, int n_first, int n_count, BlockP
         // more shares only while there are CUs for them (128-row blocks: two to a CU); every share has quads of every kind
         if (blocks * S > (p.mt > 4 ? cus : 2 * cus) + 16) break;
         if ((L.tiles[kNarrow] > 0 && L.tiles[kNarrow] < S) || (L.tiles[kWide] > 0 && 2 * L.tiles[kWide] < S)) break;
-        if (part_workspace(M, p) > kPartialMost || part_workspace(1, p) > kPartialRow) break;
+        if (part_workspace(M, p) > kPromptPartialMost || part_workspace(1, p) > kPartialRow) break;
       }
       const double t = part_time(L, M, p);
       if (t < t_best) {
@@ -129,7 +128,7 @@ int64_t block_workspace(int M, const BlockPlan& plan) {
 }
 
 int64_t block_workspace_most(const Layout& L, int M_max) {
-  return M_max <= 64 || L.K < 512 ? 0 : std::min<int64_t>(kPartialMost, (int64_t)8 * M_max * L.Npad * 4);
+  return M_max <= 64 || L.K < 512 ? 0 : std::min<int64_t>(kPromptPartialMost, (int64_t)8 * M_max * L.Npad * 4);
 }
 
 static BlockArgs block_args(const ccq_weight* w, const Layout& L, const void* x, int M, int64_t ldx, void* y, int64_t ldy, float* partial, const BlockPart& p) {

@@ -1,6 +1,7 @@
 // Internal declarations shared by the host layer and the kernel launchers of
 // libccq.  Nothing here is part of the public C ABI (include/ccq.h).
 #pragma once
+#include <atomic>
 #include <cstdint>
 
 #include "ccq.h"
@@ -195,12 +196,20 @@ int gemm_dispatch(const ccq_weight* w, const void* x, int32_t M, int64_t ldx, vo
 int64_t gemm_workspace_need(const ccq_weight* w, int32_t M);
 int64_t gemm_workspace_least(const ccq_weight* w, int32_t M);   // the least that a call is served with
 
+// Device arrays of the library (ccq_static.hip, ccq_static_prompt.hip): the address on the current GPU, and those that are known already.
+constexpr int kMaxDevices = 64;
+typedef std::atomic<void*> SymbolAddresses[kMaxDevices];
+int symbol_of_current_device(const void* symbol, SymbolAddresses& known, void** out);
+int prompt_scratch_of_current_device(void** out);   // kPromptPartialMost bytes
+
 // Prompts, every format (ccq_block.h, ccq_block.hip): blocks of 32 mt x 256 outputs (mt = 4 .. 8) over one or two ranges of columns, K cut
 // into S shares whose fp32 partial tiles go through the workspace.
 struct BlockPart {
   int n_first = 0, n_count = 0;   // columns; n_first a multiple of 256
   int mt = 8, S = 1;
 };
+// Partial tiles that a plan asks for at most: with a block for each of 256 CUs and 16 more, of 256 x 256 fp32 (128-row blocks: two to a CU), it would not ask for more.
+constexpr int64_t kPromptPartialMost = (int64_t)68 << 20;
 struct BlockPlan {
   int parts = 0;                  // 0: the call is one for the other kernels
   BlockPart part[2];
