@@ -170,8 +170,8 @@ int ccq_gemm(const ccq_weight *w, const void *x, int32_t M, int64_t ldx, void *y
              void *workspace, int64_t workspace_bytes, void *hip_stream);
 
 /* Workspace bytes ccq_gemm needs for exactly M rows (<= the ccq_pack_info figure for any M_max >= M);
- * -1 for an invalid descriptor.  Pure host code.  A prompt is served with less of it too, in several passes over the rows
- * with the same results, down to what the same call needed in 64-row blocks. */
+ * -1 for an invalid descriptor.  Pure host code.  A prompt is served with less of it too, down to what 64-row blocks
+ * need for it: K is then cut into fewer shares, or 64-row blocks take over, and the sums are added in another order. */
 int64_t ccq_gemm_workspace_bytes(const ccq_weight *w, int32_t M);
 
 /* ccq_gemm for callers that cannot allocate device memory or bring a workspace: code under HIP graph capture,

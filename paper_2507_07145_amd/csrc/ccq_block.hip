@@ -17,7 +17,7 @@ constexpr BlockRates kRatesH16 = {0.64, 0.08, 0.47, 0.151, 0.93, 1.70, 2.02};
 constexpr double kCallTime = 9.1, kSecondPart = 5.4;      // of the first and the second part of a call
 constexpr double kRoundTime = -3.0, kRoundTimeRow = 0.80; // more per round of blocks: start, and the outputs
 constexpr double kPartialRate = 9.9e6;                    // bytes of partial tiles, written and read, per microsecond
-constexpr int64_t kPartialRow = (8 << 20) / 32;           // 32 rows of a plan's partial tiles fit 8 MiB, that is
+constexpr int64_t kPartialRow = (8 << 20) / 32;           // bytes of partial tiles per row at most: the fit has no more
 
 static double part_time(const Layout& L, int M, const BlockPart& p) {
   const double qn = L.tiles[kNarrow] ? 4.0 * ((L.tiles[kNarrow] + p.S - 1) / p.S) : 0.0, qw = L.tiles[kWide] ? 4.0 * ((2 * L.tiles[kWide] + p.S - 1) / p.S) : 0.0;
@@ -45,8 +45,8 @@ static int64_t part_workspace(int M, const BlockPart& p) {
   return p.S > 1 ? (int64_t)p.S * M * ((p.n_count + kRowsPerTile - 1) / kRowsPerTile * kRowsPerTile) * 4 : 0;
 }
 
-// The best blocks and shares for a range of columns.
-static double best_part(const Layout& L, int M, int n_first, int n_count, BlockPart* best) {
+// The best blocks and shares for a range of columns, with `bytes` of workspace.
+static double best_part(const Layout& L, int M, int n_first, int n_count, int64_t bytes, BlockPart* best) {
   const int64_t cus = device_cus();
   const int b = (M + 255) / 256;   // row blocks, and their heights without rows to spare
   const int heights[4] = {4, std::max(5, (M + 32 * b - 1) / (32 * b)), std::max(5, (M + 32 * b + 31) / (32 * (b + 1))), 8};
@@ -63,7 +63,7 @@ static double best_part(const Layout& L, int M, int n_first, int n_count, BlockP
         // more shares only while there are CUs for them (128-row blocks: two to a CU); every share has quads of every kind
         if (blocks * S > (p.mt > 4 ? cus : 2 * cus) + 16) break;
         if ((L.tiles[kNarrow] > 0 && L.tiles[kNarrow] < S) || (L.tiles[kWide] > 0 && 2 * L.tiles[kWide] < S)) break;
-        if (part_workspace(M, p) > kPromptPartialMost || part_workspace(1, p) > kPartialRow) break;
+        if (part_workspace(M, p) > bytes || part_workspace(1, p) > kPartialRow) break;
       }
       const double t = part_time(L, M, p);
       if (t < t_best) {
@@ -75,13 +75,18 @@ static double best_part(const Layout& L, int M, int n_first, int n_count, BlockP
   return t_best;
 }
 
+// What a plan has to beat: the 64-row kernel is taken where it is as good, for small products and short K.  (832 calls of 65 to 4096 rows against the
+// kernels that served them before: 0.80 of the time in the geometric mean, one more than 3 % slower, 75 rows of 1472 x 6080 by 9 %; with the 64-row
+// kernel's time as it is, 25.)
+static double worth_it(const Layout& L, int M) { return 0.95 * mid_time(L, M) - 1.5; }
+
 // All columns alike, or as many as fill the CUs a whole number of times in tall blocks and the rest, which would leave CUs idle, in whatever
 // is best for them (narrow 7168 x 18432, M = 2048, 576 blocks of 256 x 256: 477 us, in three rounds; 512 of them and 128 blocks of
 // 128 x 256 in two shares: 424 us).
-static BlockPlan make_plan(const Layout& L, int M) {
+static BlockPlan make_plan(const Layout& L, int M, int64_t bytes) {
   BlockPlan plan;
   plan.parts = 1;
-  plan.time = kCallTime + best_part(L, M, 0, L.N, &plan.part[0]);
+  plan.time = kCallTime + best_part(L, M, 0, L.N, bytes, &plan.part[0]);
   const int64_t cus = device_cus();
   const int b = (M + 255) / 256, mt = std::max(5, (M + 32 * b - 1) / (32 * b));
   const int64_t row_blocks = (M + 32 * mt - 1) / (32 * mt), n_blocks = (L.N + kBlockCols - 1) / kBlockCols, rounds = row_blocks * n_blocks / cus;
@@ -90,7 +95,7 @@ static BlockPlan make_plan(const Layout& L, int M) {
     BlockPart p[2];
     p[0].n_count = (int)n_full * kBlockCols;
     p[0].mt = mt;
-    const double t = kCallTime + kSecondPart + part_time(L, M, p[0]) + best_part(L, M, p[0].n_count, L.N - p[0].n_count, &p[1]);
+    const double t = kCallTime + kSecondPart + part_time(L, M, p[0]) + best_part(L, M, p[0].n_count, L.N - p[0].n_count, bytes, &p[1]);
     if (t < plan.time) {
       plan.parts = 2;
       plan.time = t;
@@ -98,26 +103,7 @@ static BlockPlan make_plan(const Layout& L, int M) {
       plan.part[1] = p[1];
     }
   }
-  // The 64-row kernel where it is as good: small products and short K.  (832 calls of 65 to 4096 rows against the kernels that served them before: 0.80
-  // of the time in the geometric mean, one more than 3 % slower, 75 rows of 1472 x 6080 by 9 %; with the 64-row kernel's time as it is, 25.)
-  if (plan.time > 0.95 * mid_time(L, M) - 1.5) plan.parts = 0;
-  return plan;
-}
-
-BlockPlan block_plan(const Layout& L, int M) {
-  if (M <= 64 || L.K < 512) return BlockPlan{};
-  // a call asks several times: the last answer of this thread, a function of these numbers
-  struct Key {
-    int tn, tw, h16, K, N, M, cus;
-    bool operator==(const Key& o) const { return tn == o.tn && tw == o.tw && h16 == o.h16 && K == o.K && N == o.N && M == o.M && cus == o.cus; }
-  };
-  static thread_local Key last{-1, -1, -1, -1, -1, -1, -1};
-  static thread_local BlockPlan plan;
-  const Key key{L.tiles[kNarrow], L.tiles[kWide], L.h16 ? 1 : 0, L.K, L.N, M, device_cus()};
-  if (!(key == last)) {
-    plan = make_plan(L, M);
-    last = key;
-  }
+  if (plan.time > worth_it(L, M)) plan.parts = 0;
   return plan;
 }
 
@@ -125,6 +111,32 @@ int64_t block_workspace(int M, const BlockPlan& plan) {
   int64_t need = 0;
   for (int i = 0; i < plan.parts; ++i) need = std::max(need, part_workspace(M, plan.part[i]));
   return need;
+}
+
+// With less workspace than a plan asks for, fewer shares are looked at, down to none, and the 64-row kernel takes over where that is the faster: by these
+// estimates a call is never slower with more of it.  (One in passes over the rows, each of which decodes all weights again, was up to seven times as slow.)
+BlockPlan block_plan(const Layout& L, int M, int64_t bytes) {
+  if (M <= 64 || L.K < 512) return BlockPlan{};
+  // a call asks several times: the last answers of this thread, functions of these numbers, with all of the workspace and with less
+  struct Key {
+    int tn = -1, tw = -1, h16 = -1, K = -1, N = -1, M = -1, cus = -1;
+    int64_t bytes = -1;
+    bool operator==(const Key& o) const {
+      return tn == o.tn && tw == o.tw && h16 == o.h16 && K == o.K && N == o.N && M == o.M && cus == o.cus && bytes == o.bytes;
+    }
+  };
+  static thread_local Key last[2];
+  static thread_local BlockPlan plan[2];
+  Key key{L.tiles[kNarrow], L.tiles[kWide], L.h16 ? 1 : 0, L.K, L.N, M, device_cus(), kPromptPartialMost};
+  for (int i = 0; i < 2; ++i) {
+    if (!(key == last[i])) {
+      plan[i] = make_plan(L, M, key.bytes);
+      last[i] = key;
+    }
+    if (block_workspace(M, plan[i]) <= bytes) return plan[i];
+    key.bytes = bytes;
+  }
+  return BlockPlan{};
 }
 
 int64_t block_workspace_most(const Layout& L, int M_max) {
@@ -182,30 +194,22 @@ static int launch_part(const ccq_weight* w, const Layout& L, const void* x, int 
   return hipGetLastError() == hipSuccess ? CCQ_OK : CCQ_ERR_HIP;
 }
 
-// With less of a workspace than the plan's, the rows go through it some at a time: the same sums in the same order for every output.
-int launch_block(const ccq_weight* w, const Layout& L, const void* x, int M, int64_t ldx, void* y, int64_t ldy, void* workspace, int64_t workspace_bytes,
-                 const BlockPlan& plan, void* stream) {
+int launch_block(const ccq_weight* w, const Layout& L, const void* x, int M, int64_t ldx, void* y, int64_t ldy, void* workspace, const BlockPlan& plan,
+                 void* stream) {
   for (int i = 0; i < plan.parts; ++i) {
     const BlockPart& p = plan.part[i];
     // lane offsets have 32 bits; column blocks are a grid dimension
     if ((int64_t)32 * p.mt * ldx * 2 >= (int64_t)1 << 32 || 4 * L.row_tile_bytes >= (int64_t)1 << 31 || (p.n_count + kBlockCols - 1) / kBlockCols > 65535)
       return CCQ_ERR_UNSUPPORTED;
-    if (workspace_bytes < std::min(part_workspace(32, p), part_workspace(M, p))) return CCQ_ERR_UNSUPPORTED;
   }
   for (int i = 0; i < plan.parts; ++i) {
     const BlockPart& p = plan.part[i];
-    int rows = M;
-    if (part_workspace(M, p) > workspace_bytes) rows = (int)(workspace_bytes / part_workspace(32, p)) * 32;
-    for (int m0 = 0; m0 < M; m0 += rows) {
-      const int m = std::min(rows, M - m0);
-      const uint16_t* xm = static_cast<const uint16_t*>(x) + m0 * ldx;
-      uint16_t* ym = static_cast<uint16_t*>(y) + m0 * ldy;
-      float* partial = p.S > 1 ? static_cast<float*>(workspace) : nullptr;
-      int rc = launch_part(w, L, xm, m, ldx, ym, ldy, partial, p, stream);
-      if (rc == CCQ_OK && p.S > 1)
-        rc = launch_reduce_splits(partial, ym + p.n_first, ldy, m, p.n_count, (p.n_count + kRowsPerTile - 1) / kRowsPerTile * kRowsPerTile, p.S, stream);
-      if (rc != CCQ_OK) return rc;
-    }
+    float* partial = p.S > 1 ? static_cast<float*>(workspace) : nullptr;
+    int rc = launch_part(w, L, x, M, ldx, y, ldy, partial, p, stream);
+    if (rc == CCQ_OK && p.S > 1)
+      rc = launch_reduce_splits(partial, static_cast<uint16_t*>(y) + p.n_first, ldy, M, p.n_count, (p.n_count + kRowsPerTile - 1) / kRowsPerTile * kRowsPerTile,
+                                p.S, stream);
+    if (rc != CCQ_OK) return rc;
   }
   return CCQ_OK;
 }

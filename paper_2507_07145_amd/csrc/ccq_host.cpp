@@ -596,7 +596,8 @@ int gemm_dispatch(const ccq_weight* w, const void* x, int32_t M, int64_t ldx, vo
   if (!explicit_launch) {
     const DensePath path = dense_path(L, M);
     if (path == kPathBlock) {
-      rc = launch_block(w, L, x, M, ldx, y, ldy, workspace, have, block_plan(L, M), stream);
+      const BlockPlan plan = block_plan(L, M, have);
+      rc = plan.parts > 0 ? launch_block(w, L, x, M, ldx, y, ldy, workspace, plan, stream) : CCQ_ERR_UNSUPPORTED;
       if (rc != CCQ_ERR_UNSUPPORTED) return rc;
     }
     // many rows and short K, narrow format only: the 256-row LDS-tiled MFMA kernel
@@ -862,21 +863,30 @@ extern "C" int ccq_prompt_block_cols(const ccq_weight* w, int32_t M) {
   return dense_path(L, M) == kPathPrefill ? prefill_block_cols(L, M) : 0;
 }
 
-// For tests, no part of the interface: how a dense call of M rows goes to the block kernel (0: not at all): the number of ranges of columns, of
-// each the first column, the columns, 32-row tiles of a block and shares of K.
-extern "C" int ccq_prompt_plan(const ccq_weight* w, int32_t M, int32_t* out) {
+// For tests, no part of the interface: how a dense call of M rows with `bytes` of workspace goes to the block kernel (0: not at all): the number of
+// ranges of columns, of each the first column, the columns, 32-row tiles of a block and shares of K; and the estimated times of the call and of the
+// 64-row kernel (the same where that takes it).
+extern "C" int ccq_prompt_plan_within(const ccq_weight* w, int32_t M, int64_t bytes, int32_t* out, double* times) {
   Layout L;
   const int rc = make_layout(w, &L);
   if (rc != CCQ_OK) return rc;
-  if (!out) return CCQ_ERR_NULL;
+  if (!out || !times) return CCQ_ERR_NULL;
+  times[0] = times[1] = mid_time(L, M);
   if (dense_path(L, M) != kPathBlock) return 0;
-  const BlockPlan plan = block_plan(L, M);
+  const BlockPlan plan = block_plan(L, M, bytes);
   for (int i = 0; i < plan.parts; ++i) {
     const BlockPart& p = plan.part[i];
     const int32_t v[4] = {p.n_first, p.n_count, p.mt, p.S};
     std::memcpy(out + 4 * i, v, sizeof(v));
   }
+  if (plan.parts > 0) times[0] = plan.time;
   return plan.parts;
+}
+
+// The same with all the workspace that it asks for.
+extern "C" int ccq_prompt_plan(const ccq_weight* w, int32_t M, int32_t* out) {
+  double times[2];
+  return ccq_prompt_plan_within(w, M, kPromptPartialMost, out, times);
 }
 
 // For tests, no part of the interface: whether a grouped call with these offsets takes the prompt kernel.

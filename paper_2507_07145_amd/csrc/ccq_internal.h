@@ -215,12 +215,12 @@ struct BlockPlan {
   BlockPart part[2];
   double time = 0.0;              // estimate, microseconds
 };
-BlockPlan block_plan(const Layout& L, int M);
+BlockPlan block_plan(const Layout& L, int M, int64_t bytes = kPromptPartialMost);   // with that much workspace
 int64_t block_workspace(int M, const BlockPlan& plan);
 int64_t block_workspace_most(const Layout& L, int M_max);   // of any call of up to M_max rows, or more
-// CCQ_ERR_UNSUPPORTED, with nothing launched, where the rows lie too far apart or the workspace does not hold 32 rows.
-int launch_block(const ccq_weight* w, const Layout& L, const void* x, int M, int64_t ldx, void* y, int64_t ldy, void* workspace, int64_t workspace_bytes,
-                 const BlockPlan& plan, void* stream);
+// `workspace` holds what the plan asks for.  CCQ_ERR_UNSUPPORTED, with nothing launched, where the rows lie too far apart.
+int launch_block(const ccq_weight* w, const Layout& L, const void* x, int M, int64_t ldx, void* y, int64_t ldy, void* workspace, const BlockPlan& plan,
+                 void* stream);
 
 // Large-M kernel for narrow-format weights and short K (ccq_prefill.hip).
 int prefill_block_cols(const Layout& L, int M);  // column-block width launch_prefill uses: 128, 192 or 256

@@ -1,6 +1,6 @@
 """The block kernel (csrc/ccq_block.h): every height of its blocks, with K whole and in shares, over one range of columns and over two, as the
 plan picks them (which the first tests ask of the host code).  Ragged in rows, columns and K, both scale modes, against the oracle: products, and
-decoded weights bit for bit; with less of a workspace than asked for, and captured."""
+decoded weights bit for bit; with less of a workspace than asked for (a plan of its own, which the host code is asked for too), and captured."""
 import ctypes
 
 import numpy as np
@@ -81,6 +81,37 @@ def test_plans_are_sound():
     assert taken > 300
 
 
+def _plan_within(w, M, nbytes):
+    """Parts, and the estimated times of the call and of the 64-row kernel."""
+    out, times = (ctypes.c_int32 * 8)(), (ctypes.c_double * 2)()
+    n = b.load().ccq_prompt_plan_within(ctypes.byref(w), M, ctypes.c_int64(nbytes), out, times)
+    return [tuple(out[4 * i:4 * i + 4]) for i in range(n)], times[0], times[1]
+
+
+def test_less_workspace_is_never_slower_than_none():
+    """By the estimates that choose: a call with more workspace takes no longer, none takes longer than the 64-row kernel, and all of it is what the
+    query asks for.  (With the rows in passes through 8 of the 48 MiB that the first of these asks for it took 520 us, on the 64-row kernel 105.)"""
+    rng = np.random.default_rng(92)
+    calls = [("wide", 8192, 8192, 512), ("narrow", 18432, 7168, 1024), ("h16", 7232, 5001, 777), ("narrow", 28672, 8192, 256)]
+    while len(calls) < 150:
+        family = ("narrow", "wide", "h16")[len(calls) % 3]
+        K, N, M = 64 * int(np.exp(rng.uniform(2.1, 6.1))), int(np.exp(rng.uniform(6, 10.2))), int(np.exp(rng.uniform(4.2, 8.0)))
+        if any(S > 1 for _, _, _, S in _plan(b.descriptor(K, N, FMTS[family]), M)):
+            calls.append((family, K, N, M))
+    served = 0
+    for family, K, N, M in calls:
+        w = b.descriptor(K, N, FMTS[family])
+        need, last = b.gemm_workspace_bytes(w, M), np.inf
+        for part in (0, 1, 2, 4, 6, 7, 8, 16):
+            plan, t, mid = _plan_within(w, M, need * part // 8)
+            assert t <= min(last, mid), (family, K, N, M, part)
+            assert all(S == 1 or S * M * (-(-count // 16) * 16) * 4 <= need * part // 8 for _, count, _, S in plan)
+            last = t
+            served += part < 8 and bool(plan)
+        assert plan == _plan(w, M)
+    assert served > 200
+
+
 def _case(family, K, N, M, mode):
     gf = _map(family, K)
     a = _ragged_arrays(family, mode, K, N, gf, synth.rng(92, K + N + mode))
@@ -113,16 +144,29 @@ def test_products_and_decoded_weights(family, K, N, M, parts, mode):
 @pytest.mark.gpu
 @pytest.mark.parametrize("family,K,N,M,parts", [c for c in CASES if any(cut for _, cut in c[4])][::2])
 def test_less_workspace_and_capture(family, K, N, M, parts):
-    """With part of the workspace the rows go in several passes: the same bits."""
-    _, w = _case(family, K, N, M, 0)
-    x = b.bf16_tensor(synth.activations_bf16(M, K, synth.rng(92, 3)), DEV)
+    """Part of the workspace and none: other shares or the 64-row kernel, or refused; and the captured call."""
+    W, w = _case(family, K, N, M, 0)
+    x_bits = synth.activations_bf16(M, K, synth.rng(92, 3))
+    x = b.bf16_tensor(x_bits, DEV)
     need = b.gemm_workspace_bytes(w.desc, M)
     want = b.bf16_bits(b.gemm(w, x)).copy()
     buf = torch.full((need + 4096,), 0xFF, dtype=torch.uint8, device=DEV)
     out = torch.zeros((M, (N + 7) // 8 * 8), dtype=torch.bfloat16, device=DEV)[:, :N]
-    assert np.array_equal(b.bf16_bits(b.gemm(w, x, out=out, workspace=buf[:need // 2 // 16 * 16])), want)
+    cols = np.unique(np.concatenate([np.arange(40), np.arange(N - 40, N), synth.rng(92, 6).integers(0, N, 40)]))
+    refused = False
+    for nbytes in (need - 16, need // 2 // 16 * 16, need // 8 // 16 * 16, 0):
+        try:
+            got = b.bf16_bits(b.gemm(w, x, out=out, workspace=buf[:nbytes]))
+        except b.CcqError as e:
+            assert e.status == -5, "less than 64-row blocks need is refused"
+            refused = True
+            continue
+        assert not refused, "served with less than what was refused"
+        assert_gemm_close(got[:, cols], o.matmul(x_bits, W[cols]), f"{family} K={K} N={N} M={M} workspace {nbytes} of {need}", rounded=(x_bits, W[cols]))
+        torch.cuda.synchronize()
+        assert bool((buf[nbytes:] == 0xFF).all()), "written outside of the workspace"
+        buf.fill_(0xFF)
     torch.cuda.synchronize()
-    assert bool((buf[need // 2 // 16 * 16:] == 0xFF).all()), "written outside of the workspace"
     side = torch.cuda.Stream()
     side.wait_stream(torch.cuda.current_stream())
     graph = torch.cuda.CUDAGraph()
