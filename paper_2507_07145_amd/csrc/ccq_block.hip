@@ -75,7 +75,7 @@ static double best_part(const Layout& L, int M, int n_first, int n_count, int64_
   return t_best;
 }
 
-// What a plan has to beat: the 64-row kernel is taken where it is as good, for small products and short K.  (832 calls of 65 to 4096 rows against the
+// What a plan's time may be: the 64-row kernel is taken where it is as good, for small products and short K.  (832 calls of 65 to 4096 rows against the
 // kernels that served them before: 0.80 of the time in the geometric mean, one more than 3 % slower, 75 rows of 1472 x 6080 by 9 %; with the 64-row
 // kernel's time as it is, 25.)
 static double worth_it(const Layout& L, int M) { return 0.95 * mid_time(L, M) - 1.5; }
@@ -103,7 +103,6 @@ static BlockPlan make_plan(const Layout& L, int M, int64_t bytes) {
       plan.part[1] = p[1];
     }
   }
-  if (plan.time > worth_it(L, M)) plan.parts = 0;
   return plan;
 }
 
@@ -131,6 +130,7 @@ BlockPlan block_plan(const Layout& L, int M, int64_t bytes) {
   for (int i = 0; i < 2; ++i) {
     if (!(key == last[i])) {
       plan[i] = make_plan(L, M, key.bytes);
+      if (plan[i].time > worth_it(L, M)) plan[i].parts = 0;
       last[i] = key;
     }
     if (block_workspace(M, plan[i]) <= bytes) return plan[i];
@@ -139,8 +139,22 @@ BlockPlan block_plan(const Layout& L, int M, int64_t bytes) {
   return BlockPlan{};
 }
 
+// Of the row counts of one 32-row tile the first one's plan has the most partial tiles per row: a plan's time grows with the rows by its partial tiles
+// alone, so those with more of them drop out as the rows grow.  For the same reason, as the 64-row kernel's time grows evenly too, a plan that is not worth it for the
+// first and the last of them is so for none.  (What column range the tiles are of moves the padding to whole row tiles by eight shares' at most.)
+// Past the rows looked at no K is cut: 128-row blocks (two to a CU), and taller ones, of a single column block fill the chip.
 int64_t block_workspace_most(const Layout& L, int M_max) {
-  return M_max <= 64 || L.K < 512 ? 0 : std::min<int64_t>(kPromptPartialMost, (int64_t)8 * M_max * L.Npad * 4);
+  if (M_max <= 64 || L.K < 512) return 0;
+  int64_t need = 0;
+  const int64_t last = std::min<int64_t>(M_max, ((int64_t)device_cus() + 16) * 128);
+  for (int64_t m = 65; m <= last; m += 32) {
+    const int first = (int)m, end = (int)std::min(m + 31, last);
+    const BlockPlan plan = make_plan(L, first, kPromptPartialMost);
+    const int64_t bytes = block_workspace(end, plan);
+    if (bytes <= need || (plan.time > worth_it(L, first) && make_plan(L, end, kPromptPartialMost).time > worth_it(L, end))) continue;
+    need = std::min(bytes + (int64_t)8 * end * (L.Npad - L.N) * 4, kPromptPartialMost);
+  }
+  return need;
 }
 
 static BlockArgs block_args(const ccq_weight* w, const Layout& L, const void* x, int M, int64_t ldx, void* y, int64_t ldy, float* partial, const BlockPart& p) {

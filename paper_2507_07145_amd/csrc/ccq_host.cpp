@@ -328,7 +328,7 @@ static int64_t dense_need(const Layout& L, int M) { return std::max(dense_least(
 // do not change (they depend on the row count through its 16-, 32-, 64- and 256-row blocks and the thresholds 1,
 // 4, 16, 32, 128), and with both fixed the need grows with the row count: only those row counts are looked at.
 // K is cut only while the row and column blocks do not fill the chip, which bounds the row counts that matter.  (The block kernel's
-// shares are not asked for row by row: a bound.)
+// plans change with every 32-row tile, and are bounded a tile at a time.)
 static int64_t dense_workspace_bytes(const Layout& L, int M_max) {
   int64_t need = 0;
   const int cap = std::min(M_max, 4096);

@@ -217,7 +217,7 @@ struct BlockPlan {
 };
 BlockPlan block_plan(const Layout& L, int M, int64_t bytes = kPromptPartialMost);   // with that much workspace
 int64_t block_workspace(int M, const BlockPlan& plan);
-int64_t block_workspace_most(const Layout& L, int M_max);   // of any call of up to M_max rows, or more
+int64_t block_workspace_most(const Layout& L, int M_max);   // of any call of up to M_max rows
 // `workspace` holds what the plan asks for.  CCQ_ERR_UNSUPPORTED, with nothing launched, where the rows lie too far apart.
 int launch_block(const ccq_weight* w, const Layout& L, const void* x, int M, int64_t ldx, void* y, int64_t ldy, void* workspace, const BlockPlan& plan,
                  void* stream);

@@ -81,6 +81,16 @@ def test_plans_are_sound():
     assert taken > 300
 
 
+@pytest.mark.parametrize("family,K,N,M_max", [("narrow", 1024, 1024, 2048), ("h16", 1024, 1024, 700), ("narrow", 4096, 11008, 2048), ("wide", 7168, 2001, 1500),
+                                              ("mixed", 8192, 5120, 1000), ("h16", 7232, 5001, 2048), ("wide", 640, 300, 3000), ("narrow", 28672, 8192, 257)])
+def test_pack_info_reports_what_calls_ask_for(family, K, N, M_max):
+    """The most that any row count asks for, with no more on top than the padding of eight shares to whole row tiles (it was 8 shares of all columns, up to
+    100 MiB: 64 MiB in the first of these, which asks for 8)."""
+    w = b.descriptor(K, N, FMTS[family], _map(family, K))
+    most = max(b.gemm_workspace_bytes(w, m) for m in range(1, M_max + 1))
+    assert most <= b.pack_info(w, M_max).workspace_bytes <= most + 8 * M_max * (-N % 16) * 4
+
+
 def _plan_within(w, M, nbytes):
     """Parts, and the estimated times of the call and of the 64-row kernel."""
     out, times = (ctypes.c_int32 * 8)(), (ctypes.c_double * 2)()
