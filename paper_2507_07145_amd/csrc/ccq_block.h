@@ -378,6 +378,12 @@ __device__ __forceinline__ void block_tile(const BlockArgs& a, int wave, int m0,
   const int col = lane_now & 31, half = lane_now >> 5, row8 = lane_now >> 3, part = lane_now & 7;
   unsigned char* put = own + col * 144 + half * (!GATHER && a.partial ? 16 : 8);
   const u32x4* get = reinterpret_cast<const u32x4*>(own + row8 * 144 + part * 16);
+  // what a lane reads others have written, and the other way round with the next piece: no instruction, LDS serves a wavefront in order
+  auto exchanged = [&]() {
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront", "local");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront", "local");
+  };
 #pragma unroll
   for (int i = 0; i < MT; ++i) {
     if constexpr (MT > 4) asm volatile("" : "+a"(acc[i][0]), "+a"(acc[i][1]));   // read from the accumulator registers row tile by row tile
@@ -389,6 +395,7 @@ __device__ __forceinline__ void block_tile(const BlockArgs& a, int wave, int m0,
           const f32x4 v = {acc[i][c][4 * g], acc[i][c][4 * g + 1], acc[i][c][4 * g + 2], acc[i][c][4 * g + 3]};
           *reinterpret_cast<f32x4*>(put + 32 * g) = v;
         }
+        exchanged();
         const int n = n0 + wave * 64 + c * 32 + part * 4;
 #pragma unroll
         for (int k = 0; k < 4; ++k) {
@@ -396,6 +403,7 @@ __device__ __forceinline__ void block_tile(const BlockArgs& a, int wave, int m0,
           const u32x4 v = get[k * (8 * 144 / 16)];
           if (m < a.M && n < a.Npad) __builtin_nontemporal_store(v, reinterpret_cast<u32x4*>(&a.partial[((int64_t)split * a.M + m) * a.Npad + n]));
         }
+        exchanged();
       }
     } else {
 #pragma unroll
@@ -404,6 +412,7 @@ __device__ __forceinline__ void block_tile(const BlockArgs& a, int wave, int m0,
         for (int g = 0; g < 4; ++g)
           *reinterpret_cast<u32x2*>(put + c * 64 + 16 * g) =
               u32x2{dec_pack_bf16(acc[i][c][4 * g], acc[i][c][4 * g + 1]), dec_pack_bf16(acc[i][c][4 * g + 2], acc[i][c][4 * g + 3])};
+      exchanged();
       const int n = n0 + wave * 64 + part * 8;
 #pragma unroll
       for (int k = 0; k < 4; ++k) {
@@ -420,6 +429,7 @@ __device__ __forceinline__ void block_tile(const BlockArgs& a, int wave, int m0,
           }
         }
       }
+      exchanged();
     }
   }
 }
