@@ -9,6 +9,7 @@ from cases import assert_gemm_close, canon_zero
 from oracle import ccq_oracle as o
 from paper_2507_07145_amd import binding as b
 from paper_2507_07145_amd import synth
+from prompt_kernels import prompt_kernel
 
 pytestmark = pytest.mark.gpu
 DEV = "cuda:0"
@@ -44,9 +45,10 @@ def _gemm_bits(w, x_bits, **kw):
                                               (["narrow"], 1024, 576, None)])
 @pytest.mark.parametrize("M", [1, 2, 8, 16, 17, 40, 70, 130, 300])
 def test_compressed_scales_every_kernel(kinds, K, N, n_wide, M):
-    """M = 1: GEMV kernel (narrow) or one-row skinny path; 2..16: skinny kernel; 17..: 64-row kernel, and the 256-row
-    kernel for narrow-only weights beyond 128 rows."""
+    """M = 1: GEMV kernel (narrow) or one-row skinny path; 2..16: skinny kernel; 17..: few-row or 64-row kernel; from 70 rows on the block kernel
+    for the mixes."""
     W, w = _case(kinds, K, N, 10 * len(kinds) + N % 13, n_wide)
+    assert M < 40 or prompt_kernel(w.desc, M) == ("block" if n_wide and M >= 70 else "64-row")
     x = synth.activations_bf16(M, K, synth.rng(6, 400 + M))
     assert_gemm_close(_gemm_bits(w, x), o.matmul(x, W), f"compressed scales {kinds} M={M}", rounded=(x, W) if M > 16 else None)
     ks = synth.rng(6, 410 + M).integers(0, K, M)

@@ -9,6 +9,7 @@ from cases import assert_gemm_close, canon_zero
 from oracle import ccq_oracle as o
 from paper_2507_07145_amd import binding as b
 from paper_2507_07145_amd import synth
+from prompt_kernels import prompt_kernel
 
 pytestmark = pytest.mark.gpu
 DEV = "cuda:0"
@@ -83,9 +84,11 @@ def test_gemm_rows(M):
 
 @pytest.mark.parametrize("K,N,M", [(4096, 144, 70), (2048, 16, 65), (8192, 272, 40), (512, 400, 257)])
 def test_tiled_kernel_shapes(K, N, M):
-    """More than 16 rows go through the 64-row LDS-tiled kernel: K cut into shares, ragged last blocks in M and N."""
+    """More than 32 rows go through the LDS-tiled kernels (the second of these through the block kernel, the others through the 64-row one): K cut
+    into shares, ragged last blocks in M and N."""
     c = random_h16(K, N, 26, stream0=N)
     w = c.device_weight()
+    assert prompt_kernel(w.desc, M) == ("block" if M == 65 else "64-row")
     x = synth.activations_bf16(M, K, synth.rng(26, 100 + M))
     assert_gemm_close(_gemm_bits(w, x), o.matmul(x, c.W()), f"K={K} N={N} M={M}", rounded=(x, c.W()))
     ks = synth.rng(26, 200 + M).integers(0, K, M)

@@ -1,5 +1,5 @@
-"""Infinite and very large activations in dense calls of 17 rows and more on the wide formats, whichever kernel takes them (a short or
-wide matrix the few-row kernel up to 32 rows, otherwise the 64-row kernel): an infinity gives an infinity of the weight's sign, NaN
+"""Infinite and very large activations in dense calls of 17 to 33 rows on the wide formats, whichever kernel takes them (a short or
+wide matrix the few-row kernel up to 32 rows, otherwise the 64-row kernel; the block kernel's are in test_prompt_plans.py): an infinity gives an infinity of the weight's sign, NaN
 against a zero weight, and other rows are as without it."""
 import numpy as np
 import pytest

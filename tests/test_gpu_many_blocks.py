@@ -1,6 +1,7 @@
 """The 64-row kernel with one share of K to a workgroup and several k-tiles in it, the last one ragged: what products large
 enough to fill the chip with blocks take (more than 256 of 64 x 128).  Wide, mixed and hybrid-word weights, both scale modes,
-dense and grouped, against the oracle: products, and decoded weights bit for bit through one-hot rows."""
+dense (64 rows, and a thousand, of which the block kernel takes the mixes and the hybrid words) and grouped, against the oracle: products,
+and decoded weights bit for bit through one-hot rows."""
 import numpy as np
 import pytest
 import torch
@@ -9,6 +10,7 @@ from cases import assert_gemm_close, canon_zero, grouped_rounded_weight_sigma
 from oracle import ccq_oracle as o
 from paper_2507_07145_amd import binding as b
 from paper_2507_07145_amd import synth
+from prompt_kernels import prompt_kernel
 
 pytestmark = pytest.mark.gpu
 DEV = "cuda:0"
@@ -17,7 +19,7 @@ SHAPES = {"wide": (1088, None), "mix": (1600, 9), "h16": (1088, None)}   # K, wi
 FMTS = {"wide": [b.WIDE], "mix": [b.NARROW, b.WIDE], "h16": b.H16}
 
 
-def _stack(fmt, mode, E):
+def _stack(fmt, mode, E, N=N):
     """E experts: device weights and the oracle's decoded weights."""
     K, n_wide = SHAPES[fmt]
     G, ofmt = K // 64, o.F275 if fmt == "wide" else (o.F2, o.F275)
@@ -51,10 +53,11 @@ def _want_bits(W, fp32_first):
 
 
 @pytest.mark.parametrize("mode", [0, 1])
-@pytest.mark.parametrize("fmt", ["wide", "mix", "h16"])
-def test_dense(fmt, mode):
-    M = 1000
-    w, (W,), K = _stack(fmt, mode, 1)
+@pytest.mark.parametrize("fmt,columns,M,kernel", [("wide", N, 1000, "64-row"), ("mix", N, 1000, "block"), ("h16", N, 1000, "block"),
+                                                  ("wide", 33000, 64, "64-row"), ("mix", 33000, 64, "64-row"), ("h16", 33000, 64, "64-row")])
+def test_dense(fmt, columns, M, kernel, mode):
+    w, (W,), K = _stack(fmt, mode, 1, columns)
+    assert prompt_kernel(w.desc, M) == kernel
     x = synth.activations_bf16(M, K, synth.rng(27, 90))
     assert_gemm_close(b.bf16_bits(b.gemm(w, b.bf16_tensor(x, DEV))), o.matmul(x, W), f"{fmt} mode {mode}", rounded=(x, W))
     ks = synth.rng(27, 91).permutation(K)[:M]

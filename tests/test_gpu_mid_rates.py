@@ -1,4 +1,4 @@
-"""The 64/128-row kernel's launch rules: calls whose work hardly differs take about the same time.  Ratios of the best of
+"""The launch rules of prompts: calls whose work hardly differs take about the same time.  Ratios of the best of
 interleaved runs, so that neither the card nor the host shows; each limit lies half way between what the rule gives and what
 it gave when it was wrong (both stated)."""
 import numpy as np
@@ -6,6 +6,7 @@ import pytest
 import torch
 
 from paper_2507_07145_amd import binding as b
+from prompt_kernels import prompt_kernel
 
 pytestmark = pytest.mark.gpu
 DEV = "cuda:0"
@@ -69,6 +70,7 @@ def test_scale_modes_alike():
     """Narrow format, 128 rows: the two scale modes do the same work.  37 us each; with the compiler after four wavefronts
     per SIMD, the one with fp16 scales waited for every LDS read by itself: 43 against 37 us."""
     K = N = 8192
+    assert prompt_kernel(b.descriptor(K, N, [b.NARROW]), 128) == "64-row"
     f, g = (_dense(_weight("narrow", K, N, mode), 128) for mode in (0, 1))
     assert _ratio(f, g) < 1.08
 
@@ -80,7 +82,15 @@ def test_uneven_shares():
 
 
 def test_a_few_rows_more_than_a_block():
-    """Narrow format, 160 rows against 128 at 144 column blocks: both are two rounds of 64-row blocks (81 and 76 us).  As
-    128-row blocks, also two rounds, the 160 rows took 106 us."""
+    """Narrow format, 160 rows against 128: the block kernel's blocks of as many rows, in three shares (51 and 44 us)."""
     w = _weight("narrow", 7168, 18432)
+    assert prompt_kernel(w.desc, 160) == prompt_kernel(w.desc, 128) == "block"
+    assert _ratio(_dense(w, 160), _dense(w, 128)) < 1.2
+
+
+def test_a_few_rows_more_than_two_blocks():
+    """Narrow format, K below 512, 160 rows against 128 at 144 column blocks on the 64-row kernel: 64-row blocks, two to a CU, against 128-row ones (11.2 and
+    12.6 us).  At K = 7168, with 128-row blocks, 288 of them, the 160 rows took 1.4 of the 128 rows' time."""
+    w = _weight("narrow", 448, 18432)
+    assert prompt_kernel(w.desc, 160) == prompt_kernel(w.desc, 128) == "64-row"
     assert _ratio(_dense(w, 160), _dense(w, 128)) < 1.2

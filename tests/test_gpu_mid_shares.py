@@ -1,6 +1,7 @@
 """The 64-row kernel (csrc/ccq_mid.hip) where its shares of K and blocks change: one to four shares in a workgroup (as many as there are
 k-tiles, some of them shorter), shares in a workgroup and across the grid at once, blocks of 64 and of 128 rows with one to four row tiles
-that hold rows, one and two workgroups per CU and more.  Weights are exact there, so decoded weights are held to the bit."""
+that hold rows, one and two workgroups per CU and more.  (Of the wide formats the block kernel takes some, which are named.)  Weights are exact
+there, so decoded weights are held to the bit."""
 import numpy as np
 import pytest
 import torch
@@ -9,6 +10,7 @@ from cases import assert_gemm_close, canon_zero
 from oracle import ccq_oracle as o
 from paper_2507_07145_amd import binding as b
 from paper_2507_07145_amd import synth
+from prompt_kernels import prompt_kernel
 from test_gpu_random_shapes import _ragged_arrays, _upload
 
 pytestmark = pytest.mark.gpu
@@ -16,14 +18,18 @@ DEV = "cuda:0"
 
 DENSE = [
     (640, 33, 33),      # three (ragged) narrow k-tiles, two wide ones: fewer than the shares that the registers allow
-    (1088, 300, 65),    # shares of unequal length
-    (2112, 200, 130),   # shares across the grid too
+    (1088, 300, 64),    # shares of unequal length
+    (1088, 300, 65),
+    (2112, 200, 64),    # shares across the grid too
+    (2112, 200, 130),
     (576, 12000, 64),   # 94 blocks
     (576, 17000, 70),   # 266 blocks of 64 rows, 133 of 128 (three row tiles of which hold rows)
+    (448, 17000, 70),
     (320, 4300, 400),   # 238 blocks of 64 rows
     (320, 9000, 500),   # more than two 64-row blocks per CU: 128-row ones, two per CU
     (128, 9000, 1300),  # more than two 128-row ones
 ]
+BLOCK = [("wide", 1088, 300, 65), ("h16", 1088, 300, 65), ("wide", 2112, 200, 130), ("h16", 2112, 200, 130), ("h16", 576, 17000, 70)]
 
 
 @pytest.mark.parametrize("K,N,M", DENSE)
@@ -35,6 +41,7 @@ def test_dense(family, mode, K, N, M):
     gf = synth.group_format_map(G, max(1, G // 3), rng) if family == "mixed" else None
     a = _ragged_arrays(family, mode, K, N, gf, rng)
     w = _upload(family, mode, K, N, gf, a)
+    assert prompt_kernel(w.desc, M) == ("block" if (family, K, N, M) in BLOCK else "64-row")
     x = synth.activations_bf16(M, K, synth.rng(71, M))
     ks = synth.rng(71, 9).integers(0, K, M)
     ks[:2] = [K - 1, 0]

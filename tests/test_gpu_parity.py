@@ -13,6 +13,7 @@ from cases import Case, assert_gemm_close, canon_zero, encoded_case, random_case
 from oracle import ccq_oracle as o
 from paper_2507_07145_amd import binding as b
 from paper_2507_07145_amd import synth
+from prompt_kernels import prompt_kernel
 
 pytestmark = pytest.mark.gpu
 DEV = "cuda:0"
@@ -85,6 +86,7 @@ def test_large_m_kernel_small_shapes(K, N, M):
     test_prompt_blocks.py; ragged last blocks in M and N, decoded weights exact and products within tolerance."""
     c = random_case(K, N, ["narrow"], 1, stream0=900 + N)
     w = c.device_weight(DEV)
+    assert prompt_kernel(w.desc, M) == ("256-row" if M == 2900 else "64-row")
     x = synth.activations_bf16(M, K, synth.rng(1, 950 + M))
     assert_gemm_close(_gemm_bits(w, x), o.matmul(x, c.W()), f"large-M K={K} N={N} M={M}", rounded=(x, c.W()))
     ks = synth.rng(1, 960 + M).integers(0, K, M)
@@ -135,11 +137,12 @@ def test_formats_decode_and_gemm(kinds, K, N, n_wide):
                                                 (["narrow"], 2048, 128, 100, None), (["narrow", "wide"], 2048, 64, 17, 8),
                                                 (["wide"], 1024, 400, 130, None)])
 def test_mid_kernel_formats(kinds, K, N, M, n_wide):
-    """17 and more rows (any format mix; beyond 128 rows unless narrow only) run the 64-row LDS-tiled kernel: K cut into
+    """These run the 64-row LDS-tiled kernel (up to 32 rows the few-row kernel): K cut into
     one or several shares, ragged row and column blocks, the group map of mixed formats.  Decoded weights exact through
     one-hot rows, products within tolerance."""
     c = random_case(K, N, kinds, 9, stream0=20 * len(kinds) + N % 11, n_wide=n_wide)
     w = c.device_weight(DEV)
+    assert M <= 32 or prompt_kernel(w.desc, M) == "64-row"
     x = synth.activations_bf16(M, K, synth.rng(9, 300 + M))
     assert_gemm_close(_gemm_bits(w, x), o.matmul(x, c.W()), f"mid {kinds} K={K} N={N} M={M}", rounded=(x, c.W()))
     ks = synth.rng(9, 310 + M).integers(0, K, M)

@@ -196,6 +196,27 @@ def test_less_workspace_and_capture(family, K, N, M, parts):
 
 
 @pytest.mark.gpu
+@pytest.mark.parametrize("mode", [0, 1])
+@pytest.mark.parametrize("family,K,N,M", [("narrow", 1792, 1158, 1605), ("wide", 1216, 947, 95), ("mixed", 2432, 919, 206), ("mixed", 512, 4534, 1812), ("h16", 1152, 962, 126)])
+def test_infinite_activations(family, K, N, M, mode):
+    """An infinity gives an infinity of the weight's sign, NaN against a zero weight (in the last group of K also against the padding beside it), and
+    other rows are as without it."""
+    W, w = _case(family, K, N, M, mode)
+    assert _plan(w.desc, M)
+    x = b.bf16_tensor(synth.activations_bf16(M, K, synth.rng(92, 7)), DEV)
+    want = b.gemm(w, x).float().cpu().numpy()
+    rows = [0, 31, 64, M - 1]
+    for m, k, sign in zip(rows, [0, 5 * 64 + 7, K // 2 + 1, K - 1], [1.0, -1.0, -1.0, 1.0]):
+        x[m, k] = sign * float("inf")
+        want[m] = np.where(W[:, k] == 0, np.nan, np.where(sign * W[:, k] > 0, np.inf, -np.inf))
+    got = b.gemm(w, x).float().cpu().numpy()
+    padded = np.isnan(got[M - 1])
+    assert padded.all() or np.array_equal(padded, np.isnan(want[M - 1]))
+    want[M - 1, padded] = np.nan
+    assert np.array_equal(got, want, equal_nan=True)
+
+
+@pytest.mark.gpu
 @pytest.mark.parametrize("family,K,N,M", [("narrow", 1472, 7330, 2182), ("wide", 1600, 9000, 2114), ("h16", 640, 7262, 2182), ("wide", 1216, 947, 95)])
 def test_static_entry(family, K, N, M):
     """The first two ask for more than the library's own array, which the 64-row kernel would do without: served, with the same bits."""
