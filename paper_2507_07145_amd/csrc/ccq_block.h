@@ -9,9 +9,10 @@
 //     decode32_wide, decode32_h16 of ccq_decode.h: the correctly rounded bf16 of the exact weight): decoded weights never see LDS,
 //   - and multiplies them with the activation tile by MFMA 32x32x16 bf16 (fp32 accumulators), weights as the first operand: a
 //     lane then holds four neighbouring outputs of one row, which leave in 16-byte stores.
-// What bounds it is the chip's power: with all CUs busy the core clock falls to 1.65 GHz (2.4 GHz with one block), while the MFMA
-// pipe is busy 80 % of the cycles.  What a step spends besides its MFMAs is therefore kept small: 0.5 LDS operand reads per MFMA,
-// 3.2 vector instructions of decode, no LDS writes by instructions.
+// What bounds it is issue at the clock that the chip's power leaves: MFMA and vector instructions do not overlap (narrow, 256-row blocks: the MFMA pipe
+// is busy 71 % of the cycles, vector instructions at four cycles each make 27 %; hybrid word 60 and 38 %), and with all CUs busy the core clock falls to
+// 1.7 to 1.8 GHz (2.4 GHz with one block).  What a step spends besides its MFMAs is therefore kept small: 0.5 LDS operand reads per MFMA,
+// 3.05 vector instructions (narrow; hybrid word 5.0), no LDS writes by instructions.
 #pragma once
 #include <hip/hip_runtime.h>
 

@@ -75,9 +75,9 @@ static double best_part(const Layout& L, int M, int n_first, int n_count, int64_
   return t_best;
 }
 
-// What a plan's time may be: the 64-row kernel is taken where it is as good, for small products and short K.  (832 calls of 65 to 4096 rows against the
-// kernels that served them before: 0.80 of the time in the geometric mean, one more than 3 % slower, 75 rows of 1472 x 6080 by 9 %; with the 64-row
-// kernel's time as it is, 25.)
+// What a plan's time may be: the 64-row kernel is taken where it is as good, for small products and short K.  (1032 calls of 65 to 4096 rows against the
+// kernels that served them before: 0.82 of the time in the geometric mean, three more than 3 % slower, the worst, hybrid word 1280 x 937, 1273 rows, 22.7 / 20.3 us;
+// with the 64-row kernel's time as it is, 25 of the 832 that the times were fitted to.)
 static double worth_it(const Layout& L, int M) { return 0.95 * mid_time(L, M) - 1.5; }
 
 // All columns alike, or as many as fill the CUs a whole number of times in tall blocks and the rest, which would leave CUs idle, in whatever

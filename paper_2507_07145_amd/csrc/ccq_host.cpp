@@ -173,9 +173,9 @@ static DensePath dense_path(const Layout& L, int M) {
     // per element are ratios between the kernels, not times: the 256-row kernel costs 1.0 with 192-column blocks, 1.3 with 128 and 1.2
     // with 256 columns; the 64-row kernel, which decodes every weight tile four times as often (twice with 128-row blocks), costs
     // 1.37 and 1.1 of a round in fixed set-up, and past two 64-row blocks per CU, where 128-row ones start a second round,
-    // at least four rounds.  Fitted to both kernels on 2325 calls of 144 to 2048 rows: 27 are more than 5 % slower than on the other
-    // one, by 12 % at most (with 2.4 and 0.42 for the 64-row kernel, from before its K shares and 128-row blocks: 219, up to 42 %;
-    // 11264 x 5020, 1500 rows, 277 against 195 us).
+    // at least four rounds.  Fitted at longer K; on 300 random calls that come here (K 64 to 448, 129 to 8000 rows) seven are more than 5 %
+    // slower than on the other kernel, the worst 128 x 2412, 5087 rows, 23.3 on the 256-row kernel against 17.1 us, and 64 x 1024, 3081 rows, 10.2 on
+    // the 64-row kernel against 8.1.
     const int64_t cus = device_cus();
     const int bn = prefill_block_cols(L, M);
     const int64_t wg_p = (int64_t)ceil_div(M, 256) * ceil_div(L.N, bn);
@@ -636,7 +636,7 @@ int gemm_dispatch(const ccq_weight* w, const void* x, int32_t M, int64_t ldx, vo
       if (rc == CCQ_OK && S > 1) rc = launch_reduce_splits(partial, y, ldy, M, L.N, L.Npad, S, stream);
       return rc;
     }
-    // a few dozen rows (or many rows on wide / mixed formats): the 64-row LDS-tiled kernel
+    // a few dozen rows, and prompts that the kernels above leave: the 64-row LDS-tiled kernel
     if (path == kPathMid || path == kPathBlock || path == kPathPrefill) {
       const int S = mid_shares(L, M, mid_splits(L, M));
       float* partial = S > 1 ? static_cast<float*>(workspace) : nullptr;
