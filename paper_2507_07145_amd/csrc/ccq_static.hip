@@ -53,11 +53,12 @@ extern "C" int ccq_gemm_static(const ccq_weight* w, const void* x, int32_t M, in
   const int64_t need = gemm_workspace_need(w, M);
   void* ws = nullptr;
   int64_t bytes = 0;
-  if (need > 0) {
-    const bool prompt = need > kStaticScratchBytes;
-    const int rc = prompt ? prompt_scratch_of_current_device(&ws) : scratch_of_current_device(&ws);
+  if (need > kStaticScratchBytes && prompt_scratch_of_current_device(&ws) == CCQ_OK) {
+    bytes = kPromptPartialMost;
+  } else if (need > 0) {   // (a GPU without room for the second array: a plan within the first one)
+    const int rc = scratch_of_current_device(&ws);
     if (rc != CCQ_OK) return rc;
-    bytes = prompt ? kPromptPartialMost : kStaticScratchBytes;
+    bytes = kStaticScratchBytes;
   }
   // The partial tiles are written in full by the multiply kernel before the reduction reads them: nothing in the
   // arrays has to start at zero, whatever the previous call left there.
