@@ -180,9 +180,10 @@ int64_t ccq_gemm_workspace_bytes(const ccq_weight *w, int32_t M);
  * library (ccq_gemm_static_max_workspace() bytes, 8 MiB, held on every GPU the library has run on until the
  * process ends).  A call whose ccq_gemm_workspace_bytes(w, M) is more returns CCQ_ERR_WORKSPACE and enqueues nothing, but for
  * a prompt (more than 64 rows) that 64-row blocks would serve with 8 MiB: the first such call on a GPU makes it hold
- * a second array, of 68 MiB, as long (without room for it the 8 MiB serve: results as of ccq_gemm with so much).  No hipMalloc, hipFree or other allocating call is made.  All calls on one GPU share the
- * arrays: calls that may overlap on one GPU (different streams, concurrent graph launches) race on them and
- * must be ordered by the caller; calls on one stream are ordered by the stream. */
+ * a second array, of 68 MiB, as long (without room for it the 8 MiB serve, with the results of ccq_gemm with so much
+ * workspace).  No hipMalloc, hipFree or other allocating call is made.  All calls on one GPU share the arrays: calls
+ * that may overlap on one GPU (different streams, concurrent graph launches) race on them and must be ordered by the
+ * caller; calls on one stream are ordered by the stream. */
 int ccq_gemm_static(const ccq_weight *w, const void *x, int32_t M, int64_t ldx, void *y, int64_t ldy, void *hip_stream);
 int64_t ccq_gemm_static_max_workspace(void);
 
